@@ -143,10 +143,17 @@ struct WsLayout {
 
 int fil_beads(const lb_params *p) { return p->n_fil > 0 && p->fil_beads > 0 ? p->n_fil * p->fil_beads : 0; }
 
+bool is_tau1(const lb_params &p) { return p.tau[0] == 1.0 && p.tau[1] == 1.0; }
+// tau = 1 without the sink needs only the streamed moments of a node: the step
+// runs as two passes (sc_step.hip)
+bool two_pass(const lb_params &p) { return p.model == LB_MODEL_SC && is_tau1(p) && !p.sink_on; }
+
 WsLayout ws_layout(const lb_params *p) {
     WsLayout w{};
     const int64_t n = nodes(p);
-    w.max_tiles = tiles_xy(p->nx, p->ny, 4);
+    // one slot per xy tile of the fused step, or per work-group of the two-pass
+    // step that touches the plane below the reservoir (at most one more)
+    w.max_tiles = tiles_xy(p->nx, p->ny, 4) + 1;
     size_t o = 0;
     w.mat = o;
     o = align256(o + size_t(n));
@@ -188,10 +195,10 @@ WsLayout ws_layout(const lb_params *p) {
     o = align256(o + nr * sizeof(int));
     w.rodargs = o;
     o = align256(o + (rods ? 2 * sizeof(RodArgs) : 0));
-    // fluid densities of the current state in compute precision, written by
-    // the fluid step for the rod passes
+    // densities of the current state in compute precision, written by the
+    // fluid step for its second pass and for the rod and filament passes
     w.rho = o;
-    const bool dens = rods || fil_beads(p) > 0;
+    const bool dens = rods || fil_beads(p) > 0 || two_pass(*p);
     o = align256(o + (dens ? 2 * size_t(lb_pop_stride(p)) * (p->prec == LB_F64 ? 8 : 4) : 0));
     // filaments: bead records, stencils, partner lists, the fixed-point
     // momentum grid [3][fs] and its claim flags [fs]
@@ -368,7 +375,6 @@ struct lb_ctx {
     double psi_host[32];
     TileCfg tile;
     int ntx, nty, nzc, zchunk;
-    int nledger;
     int nslots;    // ledger slot pairs (reservoir tiles, then sink work-groups)
     int32_t *hbuf; // [2][nz][nx*ny] sink column heights per z chunk, or null
     int max_tiles;
@@ -387,7 +393,6 @@ static void apply_tiles(lb_ctx *c, int tile_y, int rows_per_thread, int zchunk) 
     c->tile.rows_per_thread = rows_per_thread;
     c->ntx = (p->nx + 63) / 64;
     c->nty = (p->ny + tile_y - 1) / tile_y;
-    c->nledger = c->ntx * c->nty;
     int zc = zchunk;
     if (zc <= 0) {
         // about two work-groups per CU while marching at least 8 planes
@@ -541,7 +546,7 @@ int lb_init(const lb_params *p, const lb_buffers *buf, const double *rho_init_ho
     c->nbr_cnt = reinterpret_cast<int *>(ws + w.nbr_cnt);
     c->obs = ws + w.obs;
     c->rodargs_dev = reinterpret_cast<RodArgs *>(ws + w.rodargs);
-    c->rho = (p->n_rods > 0 || fil_beads(p) > 0) ? static_cast<void *>(ws + w.rho) : nullptr;
+    c->rho = (p->n_rods > 0 || fil_beads(p) > 0 || two_pass(*p)) ? static_cast<void *>(ws + w.rho) : nullptr;
     c->fil = fil_beads(p) > 0 ? reinterpret_cast<double *>(ws + w.fil) : nullptr;
     c->fil_sten = reinterpret_cast<int *>(ws + w.fil_sten);
     c->fil_nbr = reinterpret_cast<int *>(ws + w.fil_nbr);
@@ -674,8 +679,6 @@ static StepArgs step_args(const lb_ctx *c, int cur) {
     return a;
 }
 
-static bool is_tau1(const lb_params &p) { return p.tau[0] == 1.0 && p.tau[1] == 1.0; }
-
 // colour-gradient step record of a context whose current state is in buffer cur
 static CGArgs cg_args(const lb_ctx *c, int cur) {
     const lb_params &p = c->p;
@@ -725,6 +728,7 @@ int lb_step(lb_ctx *c, int32_t nsteps, hipStream_t stream) {
     const bool tau1 = is_tau1(p);
     for (int s = 0; s < nsteps; ++s) {
         hipError_t e = p.model == LB_MODEL_CG ? launch_cg_step(p.prec, cg_args(c, c->cur), stream)
+                       : two_pass(p)          ? launch_sc_split(p.prec, step_args(c, c->cur), stream)
                                               : launch_sc_step(p.prec, tau1, c->tile, step_args(c, c->cur), stream);
         if (e != hipSuccess) return hip_fail(e, "step launch");
         c->cur ^= 1;
@@ -739,7 +743,7 @@ int lb_observables(lb_ctx *c, lb_obs *out, hipStream_t stream) {
     if (!c || !out) return fail(LB_EINVAL, "null argument");
     const lb_params &p = c->p;
     HIP_TRY(launch_observables(p.prec, c->f[c->cur], c->fs, c->mat, nodes(&p), c->rref, c->ledger,
-                               p.sink_on ? c->nslots : c->nledger,
+                               c->nslots,
                                c->carry, c->partials, OBS_BLOCKS, c->result, stream),
             "observables");
     double r[OBS_FIELDS];
@@ -1594,7 +1598,7 @@ int lb_destroy(lb_ctx *c) {
 struct lb_batch {
     struct Class {
         TileCfg tile;
-        bool tau1;
+        bool split;  // two-pass step: the tile shape plays no part
         int nwork;
         int2 *work;  // device
     };
@@ -1620,20 +1624,25 @@ struct BatchLayout {
 
 bool same_tile(const TileCfg &a, const TileCfg &b) { return a.tile_y == b.tile_y && a.rows_per_thread == b.rows_per_thread; }
 
-// class of each lattice (tile shape and tau = 1 select the kernel instance)
+// work-groups of one lattice's step (of each pass of the two-pass step)
+int step_blocks(const lb_ctx *c) {
+    return two_pass(c->p) ? split_blocks(c->p.nx, c->p.ny, c->p.nz) : c->ntx * c->nty * c->nzc;
+}
+
+// class of each lattice (its step's form and tile shape select the kernel instance)
 std::vector<int> batch_classes(lb_ctx *const *ctxs, int n, std::vector<lb_batch::Class> &cls,
                                std::vector<int> &counts) {
     std::vector<int> of(n);
     for (int i = 0; i < n; ++i) {
-        const bool t1 = is_tau1(ctxs[i]->p);
         int k = 0;
-        while (k < int(cls.size()) && !(same_tile(cls[k].tile, ctxs[i]->tile) && cls[k].tau1 == t1)) ++k;
+        const bool sp = two_pass(ctxs[i]->p);
+        while (k < int(cls.size()) && !(cls[k].split == sp && (sp || same_tile(cls[k].tile, ctxs[i]->tile)))) ++k;
         if (k == int(cls.size())) {
-            cls.push_back(lb_batch::Class{ctxs[i]->tile, t1, 0, nullptr});
+            cls.push_back(lb_batch::Class{ctxs[i]->tile, sp, 0, nullptr});
             counts.push_back(0);
         }
         of[i] = k;
-        counts[k] += ctxs[i]->ntx * ctxs[i]->nty * ctxs[i]->nzc;
+        counts[k] += sp ? (step_blocks(ctxs[i]) + 7) / 8 * 8 : step_blocks(ctxs[i]);
     }
     for (int &c : counts) c = (c + 7) / 8 * 8;  // padded to whole rounds of the eight XCDs
     return of;
@@ -1683,7 +1692,8 @@ int batch_check(lb_ctx *const *ctxs, int n) {
 hipError_t batch_enqueue(lb_batch *b, int par, bool rods, hipStream_t s) {
     const int n = int(b->ctx.size());
     for (const auto &c : b->classes) {
-        hipError_t e = launch_sc_step_batch(b->prec, c.tau1, c.tile, b->steps + size_t(par) * n, c.work, c.nwork, s);
+        hipError_t e = c.split ? launch_sc_split_batch(b->prec, b->steps + size_t(par) * n, c.work, c.nwork, s)
+                               : launch_sc_step_batch(b->prec, c.tile, b->steps + size_t(par) * n, c.work, c.nwork, s);
         if (e != hipSuccess) return e;
     }
     // the rod update acts on the state the fluid step just wrote: the records
@@ -1744,7 +1754,16 @@ int lb_batch_create(lb_ctx *const *ctxs, int32_t n, void *workspace, hipStream_t
     // the round-robin dealing of work-groups gives XCD j the j-th eighth
     std::vector<std::vector<int2>> logical(b->classes.size());
     for (int i = 0; i < n; ++i) {
-        const int nb = ctxs[i]->ntx * ctxs[i]->nty * ctxs[i]->nzc;
+        const int nb = step_blocks(ctxs[i]), per = (nb + 7) / 8;
+        if (b->classes[of[i]].split) {
+            // lattice after lattice, each dealt over the XCDs like a lattice
+            // of its own
+            for (int t = 0; t < 8 * per; ++t) {
+                const int q = (t & 7) * per + (t >> 3);
+                logical[of[i]].push_back(q < nb ? make_int2(i, q) : make_int2(-1, -1));
+            }
+            continue;
+        }
         for (int t = 0; t < nb; ++t) logical[of[i]].push_back(make_int2(i, t));
     }
     hipError_t e = hipSuccess;
@@ -1753,7 +1772,8 @@ int lb_batch_create(lb_ctx *const *ctxs, int32_t n, void *workspace, hipStream_t
         const int np = counts[k];
         logical[k].resize(np, make_int2(-1, -1));
         hw[k].resize(np);
-        for (int pidx = 0; pidx < np; ++pidx) hw[k][pidx] = logical[k][(pidx & 7) * (np >> 3) + (pidx >> 3)];
+        for (int pidx = 0; pidx < np; ++pidx)
+            hw[k][pidx] = logical[k][b->classes[k].split ? pidx : (pidx & 7) * (np >> 3) + (pidx >> 3)];
         b->classes[k].nwork = np;
         b->classes[k].work = reinterpret_cast<int2 *>(ws + l.work_off[k]);
         if (e == hipSuccess)

@@ -32,7 +32,7 @@ struct StepArgs {
     const int32_t *h_read;  // [nz][nx*ny] liquid nodes per column and z chunk of the previous step
     int32_t *h_write;       // the same for this step
     double *sink_ledger;    // [ntx*nty*nzc][2] mass moved A -> B, one running pair per work-group
-    void *rho_out;          // [2][fs] fluid densities in compute precision for the rod passes, or null
+    void *rho_out;          // [2][fs] densities in compute precision (two-pass step: psi_k of every node), or null
     uint32_t sr_key;        // 16-bit storage: nonzero = stochastic rounding keyed by this step value
 };
 
@@ -162,8 +162,13 @@ hipError_t launch_fil_step(int prec, const FilArgs &a, hipStream_t s);
 hipError_t launch_sc_step(int prec, bool tau1, const TileCfg &t, const StepArgs &a, hipStream_t s);
 // all: device array of per-lattice step records; work: device list of
 // (lattice, logical tile) entries, (-1, -1) for padding
-hipError_t launch_sc_step_batch(int prec, bool tau1, const TileCfg &t, const StepArgs *all, const int2 *work, int nwork,
+hipError_t launch_sc_step_batch(int prec, const TileCfg &t, const StepArgs *all, const int2 *work, int nwork,
                                 hipStream_t s);
+// the two-pass form of the step (tau = 1, no sink): a.rho_out holds psi_k of
+// every node between the passes; work entries are (lattice, block of nodes)
+hipError_t launch_sc_split(int prec, const StepArgs &a, hipStream_t s);
+hipError_t launch_sc_split_batch(int prec, const StepArgs *all, const int2 *work, int nwork, hipStream_t s);
+int split_blocks(int nx, int ny, int nz);
 int tiles_xy(int nx, int ny, int tile_y);
 
 // auxiliary kernels (aux.hip)

@@ -1,5 +1,8 @@
-// Fused Shan-Chen D3Q19 step for gfx950: pull stream + boundaries + moments +
-// pseudopotential force + velocity shift + BGK collision + store, one pass.
+// Shan-Chen D3Q19 step for gfx950: pull stream + boundaries + moments +
+// pseudopotential force + velocity shift + BGK collision + store.  With
+// tau = 1 in both components (and no sink) the step runs as two passes of one
+// thread per node (further down); otherwise it is one fused pass, described
+// next.
 //
 // Method: lattice Boltzmann equation per component with BGK relaxation
 // (Eq. 1), second-order equilibrium (Eq. 2), moments (Eq. 3); the interfacial
@@ -179,8 +182,8 @@ __device__ __forceinline__ void sc_step_tile(const StepArgs &a, int b, int nblk,
     constexpr int NW = NT / 64;
     constexpr uint32_t E = sizeof(S);
     // software-pipelined plane loads need a second set of raw registers; that
-    // fits for tau = 1 with 4- or 2-byte storage, the other forms load and
-    // consume a plane in turn
+    // fits for tau = 1 with 4-byte storage, the other forms load and consume a
+    // plane in turn
     constexpr bool PIPE = TAU1 && sizeof(S) <= 4;
 
     __shared__ C ring[4][2][PL];
@@ -711,87 +714,490 @@ __global__ void __launch_bounds__(64 * (TY / NPT)) sc_step_kernel(StepArgs a) {
 // tile) entries over many lattices of one tile class, each with its own
 // parameter record.  The list is ordered so that the hardware's round-robin
 // dealing of work-groups to XCDs gives each XCD a contiguous range of it.
-template <class S, int TY, int NPT, bool TAU1>
-__global__ void __launch_bounds__(64 * (TY / NPT)) sc_step_batch_kernel(const StepArgs *__restrict__ all,
-                                                                         const int2 *__restrict__ work) {
+template <class S, int TY>
+__global__ void __launch_bounds__(64 * TY) sc_step_batch_kernel(const StepArgs *__restrict__ all,
+                                                                const int2 *__restrict__ work) {
     const int2 w = work[blockIdx.x];
     if (w.x < 0) return;  // padding entry, uniform per block
     const StepArgs a = all[w.x];
-    sc_step_tile<S, TY, NPT, TAU1>(a, w.y, a.ntx * a.nty * a.nzc, false);
+    sc_step_tile<S, TY, 1, false>(a, w.y, a.ntx * a.nty * a.nzc, false);
+}
+
+// ---------------------------------------------------------------------------
+// The step in two passes (tau = 1, no sink).  With tau = 1 the collision
+// forgets the streamed populations, f* = f^eq(rho_k, u_k^eq), so a node needs
+// only its moments: the stream pass pulls the 38 populations and keeps psi_k
+// (an array of its own, read with its neighbours by the second pass) and
+// j = j_A + j_B; the collide pass forms the force, the shifted velocities and
+// stores the 38 equilibria.
+//
+// Both passes are bound by HBM: 152 + 20 bytes read or written per FP32 node
+// each (the 20 come back from the caches).  The fused pass pulls the ring of
+// its tile again (1.22 x the reads), keeps two waves per SIMD (211 VGPRs) and
+// marches z in series, so a small lattice filled a few CUs only.  Measured per
+// step, fused -> two passes (stream + collide):
+//   FP32 256 x 128 x 64: 145 -> 120 us (5.3 TB/s, the rate of a large copy);
+//     with the densities of a rod lattice stored, 162 -> 134 us
+//   FP16, stochastic: 137 -> 82 us;  FP64: 299 us (5.1 TB/s)
+//   FP32 117 x 51 x 37: 61 -> 18 us;  FP64 32^3: 64 -> 10.5 us (two launches)
+// so tau = 1 always takes this form.  With tau != 1 the collision needs the
+// populations themselves, which would have to be pulled or stored once more.
+//
+// The stores of the populations are non-temporal: plain ones take 154 us per
+// FP32 step (they evict the lines of the next pull).  The blocks of the stream
+// pass in reverse order, to find the last stores in the memory-side cache:
+// 125 us.
+// ---------------------------------------------------------------------------
+constexpr int NB = 256;  // nodes per work-group of both passes, in index order
+
+// Moment q of a node between the passes, kept in the node's own elements of
+// the destination arrays (which the second pass overwrites after reading
+// them): one array per moment, or two (low and high half) in 16-bit storage.
+template <class S>
+__device__ inline void put_moment(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t fsE, int q,
+                                  typename Codec<S>::C v) {
+    if constexpr (sizeof(S) == 2) {
+        const uint32_t u = __float_as_uint(v);
+        __builtin_amdgcn_raw_buffer_store_b16(static_cast<unsigned short>(u), r, voff, (2 * q) * fsE, 0);
+        __builtin_amdgcn_raw_buffer_store_b16(static_cast<unsigned short>(u >> 16), r, voff, (2 * q + 1) * fsE, 0);
+    } else if constexpr (sizeof(S) == 4) {
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, voff, q * fsE, 0);
+    } else {
+        const unsigned long long u = __double_as_longlong(v);
+        __attribute__((ext_vector_type(2))) unsigned int w;
+        w[0] = static_cast<unsigned int>(u);
+        w[1] = static_cast<unsigned int>(u >> 32);
+        __builtin_amdgcn_raw_buffer_store_b64(w, r, voff, q * fsE, 0);
+    }
+}
+template <class S>
+__device__ inline typename Codec<S>::C get_moment(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t fsE, int q) {
+    if constexpr (sizeof(S) == 2) {
+        const uint32_t lo = __builtin_amdgcn_raw_buffer_load_b16(r, voff, (2 * q) * fsE, 0);
+        const uint32_t hi = __builtin_amdgcn_raw_buffer_load_b16(r, voff, (2 * q + 1) * fsE, 0);
+        return __uint_as_float((lo & 0xFFFFu) | (hi << 16));
+    } else {
+        return buf_load<S>(r, voff, q * fsE);
+    }
+}
+
+// A node's coordinates and the index parts of its neighbourhood (wrapped in
+// periodic directions, clamped in closed ones).
+struct NodeNbr {
+    uint32_t xs[3], ys[3], zs[3];
+    int z;
+    __device__ inline uint32_t at(int dx, int dy, int dz) const { return zs[1 + dz] + ys[1 + dy] + xs[1 + dx]; }
+};
+__device__ inline NodeNbr node_nbr(uint32_t n, const StepArgs &a) {
+    const uint32_t nx = a.nx, ny = a.ny, nxy = nx * ny;
+    const uint32_t z = n / nxy, rem = n - z * nxy, y = rem / nx, x = rem - y * nx;
+    NodeNbr o;
+    o.z = int(z);
+    o.xs[1] = x;
+    o.xs[0] = x > 0 ? x - 1 : (a.px ? nx - 1 : 0);
+    o.xs[2] = x + 1 < nx ? x + 1 : (a.px ? 0 : x);
+    o.ys[1] = y * nx;
+    o.ys[0] = y > 0 ? (y - 1) * nx : (a.py ? (ny - 1) * nx : 0);
+    o.ys[2] = y + 1 < ny ? (y + 1) * nx : (a.py ? 0 : y * nx);
+    o.zs[1] = z * nxy;
+    o.zs[0] = z > 0 ? (z - 1) * nxy : (a.pz ? (a.nz - 1) * nxy : 0);
+    o.zs[2] = int(z) + 1 < a.nz ? (z + 1) * nxy : (a.pz ? 0 : z * nxy);
+    return o;
+}
+
+// Work-groups are dealt to the eight XCDs round-robin: each XCD takes a
+// contiguous range of nodes, so that the lines two neighbouring work-groups
+// share stay in one L2.
+__device__ inline int xcd_range(int b, int nblk) { return (nblk & 7) == 0 ? (b & 7) * (nblk >> 3) + (b >> 3) : b; }
+
+template <class S>
+__device__ __forceinline__ void sc_stream_nodes(const StepArgs &a, int b) {
+    using C = typename Codec<S>::C;
+    constexpr uint32_t E = sizeof(S);
+    __shared__ double red[NB / 64][2];
+    const uint32_t nxy = static_cast<uint32_t>(a.nx) * a.ny, N = nxy * a.nz;
+    const uint32_t fsE = static_cast<uint32_t>(a.fs) * E;
+    const uint32_t n0 = static_cast<uint32_t>(b) * NB + threadIdx.x;
+    if (static_cast<uint32_t>(b) * NB >= N) return;  // uniform per block
+    const bool act = n0 < N;
+    const uint32_t n = act ? n0 : N - 1;
+    const NodeNbr nb = node_nbr(n, a);
+    const uint8_t m = gptr(a.mat)[n] & MAT_ID_MASK;
+    const bool fluid = m == MAT_FLUID;
+    const bool top = a.evap && nb.z == a.nz - 2;
+    S raw[2][Q];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const auto src = make_rsrc(static_cast<const char *>(a.fsrc) + size_t(k) * Q * fsE, Q * fsE);
+#pragma unroll
+        for (int i = 0; i < Q; ++i) raw[k][i] = buf_load<S>(src, nb.at(-cx(i), -cy(i), -cz(i)) * E, i * fsE);
+    }
+    C rho[2], dr[2], j[2][3];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const C tdev = C(a.rho_top[k] - a.rho_ref[k]);
+        C fv[Q];
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            fv[i] = Codec<S>::dec(raw[k][i]);
+            if (cz(i) == -1) fv[i] = top ? wgt<C>(i) * tdev : fv[i];
+        }
+        C s = C(0), jx = C(0), jy = C(0), jz = C(0);
+#pragma unroll
+        for (int i = 0; i < Q; ++i) s += fv[i];
+        // momentum over opposite pairs: f_i - f_opp(i) is nearly exact
+        // (the two are close), which avoids cancellation in j
+#pragma unroll
+        for (int i = 1; i < Q; i += 2) {
+            const C d = fv[i] - fv[i + 1];
+            if (cx(i) == 1) jx += d;
+            if (cx(i) == -1) jx -= d;
+            if (cy(i) == 1) jy += d;
+            if (cy(i) == -1) jy -= d;
+            if (cz(i) == 1) jz += d;
+            if (cz(i) == -1) jz -= d;
+        }
+        // Eq. 3: rho_k = sum_i f_i = rref_k + sum_i d_i (sum_i w_i = 1)
+        dr[k] = s;
+        rho[k] = C(a.rho_ref[k]) + s;
+        j[k][0] = jx;
+        j[k][1] = jy;
+        j[k][2] = jz;
+    }
+    if (act) {
+        C *psi = static_cast<C *>(a.rho_out);
+        if (!fluid) {
+            rho[0] = C(gptr(a.psi_tab)[2 * m]);
+            rho[1] = C(gptr(a.psi_tab)[2 * m + 1]);
+        }
+        gptr(psi)[n] = rho[0];
+        gptr(psi)[a.fs + n] = rho[1];
+        if (fluid) {
+            const auto dst = make_rsrc(a.fdst, Q * fsE);
+#pragma unroll
+            for (int d = 0; d < 3; ++d) put_moment<S>(dst, n * E, fsE, d, j[0][d] + j[1][d]);
+            if (a.rho_ref[0] != 0.0 || a.rho_ref[1] != 0.0) {
+                put_moment<S>(dst, n * E, fsE, 3, dr[0]);
+                put_moment<S>(dst, n * E, fsE, 4, dr[1]);
+            }
+        }
+    }
+    // ledger: this step's streaming moves the stored f*_i(t) with c_iz = +1 of
+    // the plane below the reservoir into it and pulls w_i rho_top_k out of it
+    const uint32_t b0 = a.evap ? (uint32_t(a.nz - 2) * nxy) / NB : 0;
+    if (a.evap && uint32_t(b) >= b0 && uint32_t(b) <= (uint32_t(a.nz - 1) * nxy - 1) / NB) {  // uniform
+        double led[2] = {0.0, 0.0};
+        if (act && fluid && top) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const auto src = make_rsrc(static_cast<const char *>(a.fsrc) + size_t(k) * Q * fsE, Q * fsE);
+                double outflow = 0.0, inflow = 0.0;
+#pragma unroll
+                for (int i = 0; i < Q; ++i) {
+                    if (cz(i) == 1)
+                        outflow +=
+                            double(Codec<S>::dec(buf_load<S>(src, n * E, i * fsE))) + wgt<double>(i) * a.rho_ref[k];
+                    if (cz(i) == -1) inflow += wgt<double>(i) * a.rho_top[k];
+                }
+                led[k] = outflow - inflow;
+            }
+        }
+        const double l0 = wave_sum(led[0]), l1 = wave_sum(led[1]);
+        if ((threadIdx.x & 63) == 0) {
+            red[threadIdx.x >> 6][0] = l0;
+            red[threadIdx.x >> 6][1] = l1;
+        }
+        __syncthreads();
+        if (threadIdx.x < 2) {
+            double s = 0.0;
+            for (int q = 0; q < NB / 64; ++q) s += red[q][threadIdx.x];
+            a.ledger_part[2 * (b - b0) + threadIdx.x] += s;
+        }
+    }
+}
+
+template <class S>
+__device__ __forceinline__ void sc_collide_nodes(const StepArgs &a, int b) {
+    using C = typename Codec<S>::C;
+    constexpr uint32_t E = sizeof(S);
+    const uint32_t nxy = static_cast<uint32_t>(a.nx) * a.ny, N = nxy * a.nz;
+    const uint32_t fsE = static_cast<uint32_t>(a.fs) * E;
+    const uint32_t n = static_cast<uint32_t>(b) * NB + threadIdx.x;
+    if (n >= N) return;
+    const NodeNbr nb = node_nbr(n, a);
+    const uint8_t mt = gptr(a.mat)[n];
+    const unsigned known = *a.status;  // status bits already raised before this launch
+    const C *psi = static_cast<const C *>(a.rho_out);
+    const auto pr = [&](int k) { return make_rsrc(psi + size_t(k) * a.fs, uint32_t(a.fs) * uint32_t(sizeof(C))); };
+    // sum_i w_i psi(x + c_i) c_i taken over opposite pairs as central
+    // differences w_i c_i (psi(x + c_i) - psi(x - c_i)): no cancellation
+    C sg[2][3], own[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const auto r = pr(k);
+        C v[Q];
+#pragma unroll
+        for (int i = 0; i < Q; ++i) v[i] = buf_load<C>(r, nb.at(cx(i), cy(i), cz(i)) * uint32_t(sizeof(C)), 0);
+        own[k] = v[0];
+        C sx = C(0), sy = C(0), sz = C(0);
+#pragma unroll
+        for (int i = 1; i < Q; i += 2) {
+            const C d = wgt<C>(i) * (v[i] - v[i + 1]);
+            if (cx(i) == 1) sx += d;
+            if (cx(i) == -1) sx -= d;
+            if (cy(i) == 1) sy += d;
+            if (cy(i) == -1) sy -= d;
+            if (cz(i) == 1) sz += d;
+            if (cz(i) == -1) sz -= d;
+        }
+        sg[k][0] = sx;
+        sg[k][1] = sy;
+        sg[k][2] = sz;
+    }
+    // rod nodes go through the same arithmetic (all their moments are zero,
+    // so every deviation they store is exactly zero) and store with the fluid
+    // lanes: a wave that a rod cuts through then still writes whole lines,
+    // where masked lanes would leave partial lines that HBM has to read,
+    // merge and write back.  Nothing reads these slots before the rod passes
+    // rewrite them (link) or refill them.
+    const uint8_t mid = mt & MAT_ID_MASK;
+    if (mid != MAT_FLUID && mid != MAT_ROD) return;
+    const bool fluid = mid == MAT_FLUID;
+    const auto dst0 = make_rsrc(a.fdst, Q * fsE);
+    const C rho[2] = {fluid ? own[0] : C(0), fluid ? own[1] : C(0)};
+    C j[3] = {C(0), C(0), C(0)}, dr[2] = {rho[0], rho[1]};
+    if (fluid) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) j[d] = get_moment<S>(dst0, n * E, fsE, d);
+        if (a.rho_ref[0] != 0.0 || a.rho_ref[1] != 0.0) {
+            dr[0] = get_moment<S>(dst0, n * E, fsE, 3);
+            dr[1] = get_moment<S>(dst0, n * E, fsE, 4);
+        }
+    }
+    // Shan-Chen force: F_k = -G psi_k(x) sum_i w_i psi_kbar(x + c_i) c_i + rho_k g
+    C F[2][3];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const C gp = -C(a.G) * rho[k];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) F[k][d] = gp * sg[1 - k][d] + rho[k] * C(a.g[d]);
+    }
+    // velocity shift (tau = 1): u' = sum_k j_k / sum_k rho_k; u_k^eq = u' + F_k / rho_k
+    const C rt = rho[0] + rho[1];
+    const C ir = rt > C(0) ? C(1) / rt : C(0);
+    // health check on the physical velocity (sum_k j_k + F/2) / rho
+    unsigned st = 0;
+    {
+        C usq_chk = C(0);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const C ud = (j[d] + C(0.5) * (F[0][d] + F[1][d])) * ir;
+            usq_chk += ud * ud;
+        }
+        if (fluid && !(rt > C(0))) st |= ST_RHO;
+        if (fluid && !(usq_chk <= C(0.09))) st |= (usq_chk != usq_chk) ? ST_NAN : ST_SPEED;
+    }
+    const bool near_wall = fluid && (mt & MAT_NEAR_WALL) != 0;
+    // 16-bit storage with stochastic rounding: the random bits depend on
+    // (node, array, step) only; the wall slots reuse the encoded values
+    SrStream sr{0u, 0u};
+    if constexpr (sizeof(S) == 2) {
+        if (a.sr_key) sr.state = sr_seed(a.sr_key, n);
+    }
+    auto encode = [&](C v, int arr) -> S {
+        if constexpr (sizeof(S) == 2) {
+            if (a.sr_key) return Stochastic<S>::enc(v, sr.bits(arr));
+        }
+        return Codec<S>::enc(v);
+    };
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const auto dst = make_rsrc(static_cast<char *>(a.fdst) + size_t(k) * Q * fsE, Q * fsE);
+        C ue[3];
+        const bool ok = rho[k] >= C(1e-12);
+        const C rk = ok ? C(1) / rho[k] : C(0);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) ue[d] = j[d] * ir + F[k][d] * rk;
+        const C usq = ue[0] * ue[0] + ue[1] * ue[1] + ue[2] * ue[2];
+        S sstar[Q];
+        C deq_sum = C(0);
+        // Eq. 2 as a deviation, built per opposite pair (i, opp(i)):
+        //   f^eq - w rref = w (rho - rref) + w rho [9/2 (c.u)^2 - 3/2 u^2]  +-  w rho 3 c.u
+        // The rest population is the remainder so that sum_i f_i^eq = rho holds up to
+        // one rounding: the rounded weights do not sum to one, and using them for all
+        // 19 directions would drift the mass by a fixed factor every step.
+        C deq[Q];
+        const C base = C(-1.5) * usq;
+#pragma unroll
+        for (int i = 1; i < Q; i += 2) {
+            const C cu = C(cx(i)) * ue[0] + C(cy(i)) * ue[1] + C(cz(i)) * ue[2];
+            const C wr = wgt<C>(i) * rho[k];
+            const C sym = wgt<C>(i) * dr[k] + wr * (base + C(4.5) * cu * cu);
+            const C asym = wr * (C(3) * cu);
+            deq[i] = sym + asym;
+            deq[i + 1] = sym - asym;
+            deq_sum += deq[i];
+            deq_sum += deq[i + 1];
+        }
+        deq[0] = dr[k] - deq_sum;
+        // Eq. 1 with tau = 1: f* = f^eq
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            sstar[i] = encode(deq[i], k * Q + i);
+            buf_store<S>(sstar[i], dst, n * E, i * fsE);
+        }
+        if (near_wall) {
+            // halfway bounce-back: hand f*_j(x) to the wall node x + c_j as
+            // direction opp(j) (w_j = w_opp(j), so the deviation carries over)
+#pragma unroll
+            for (int jd = 1; jd < Q; ++jd) {
+                const uint32_t q = nb.at(cx(jd), cy(jd), cz(jd));
+                if (is_static_wall(gptr(a.mat)[q] & MAT_ID_MASK)) buf_store<S>(sstar[jd], dst, q * E, opp(jd) * fsE);
+            }
+        }
+    }
+    post_status(a.status, known, st);
+}
+
+template <class S>
+__global__ void __launch_bounds__(NB) sc_stream_kernel(StepArgs a) {
+    sc_stream_nodes<S>(a, xcd_range(blockIdx.x, gridDim.x));
+}
+template <class S>
+__global__ void __launch_bounds__(NB) sc_collide_kernel(StepArgs a) {
+    sc_collide_nodes<S>(a, xcd_range(blockIdx.x, gridDim.x));
+}
+// batches: a work list of (lattice, run of BATCH_RUN node blocks) entries
+constexpr int BATCH_RUN = 1;
+template <class S>
+__global__ void __launch_bounds__(NB) sc_stream_batch_kernel(const StepArgs *__restrict__ all,
+                                                             const int2 *__restrict__ work) {
+    const int2 w = work[blockIdx.x];
+    if (w.x < 0) return;  // padding entry, uniform per block
+    const StepArgs a = all[w.x];
+    sc_stream_nodes<S>(a, w.y);
+}
+template <class S>
+__global__ void __launch_bounds__(NB) sc_collide_batch_kernel(const StepArgs *__restrict__ all,
+                                                              const int2 *__restrict__ work) {
+    const int2 w = work[blockIdx.x];
+    if (w.x < 0) return;
+    const StepArgs a = all[w.x];
+    sc_collide_nodes<S>(a, w.y);
+}
+
+int split_blocks(int nx, int ny, int nz) { return int((int64_t(nx) * ny * nz + NB - 1) / NB); }
+
+template <class S>
+static hipError_t launch_split(const StepArgs &a, hipStream_t s) {
+    const int nblk = (split_blocks(a.nx, a.ny, a.nz) + 7) & ~7;
+    hipLaunchKernelGGL((sc_stream_kernel<S>), dim3(nblk), dim3(NB), 0, s, a);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((sc_collide_kernel<S>), dim3(nblk), dim3(NB), 0, s, a);
+    return hipGetLastError();
+}
+template <class S>
+static hipError_t launch_split_batch(const StepArgs *all, const int2 *work, int nwork, hipStream_t s) {
+    hipLaunchKernelGGL((sc_stream_batch_kernel<S>), dim3(nwork), dim3(NB), 0, s, all, work);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((sc_collide_batch_kernel<S>), dim3(nwork), dim3(NB), 0, s, all, work);
+    return hipGetLastError();
+}
+
+hipError_t launch_sc_split(int prec, const StepArgs &a, hipStream_t s) {
+    switch (prec) {
+        case LB_F64:
+            return launch_split<double>(a, s);
+        case LB_F32:
+            return launch_split<float>(a, s);
+        case LB_F16DEV:
+            return launch_split<_Float16>(a, s);
+        case LB_BF16DEV:
+            return launch_split<bf16_t>(a, s);
+        default:
+            return hipErrorInvalidValue;
+    }
+}
+hipError_t launch_sc_split_batch(int prec, const StepArgs *all, const int2 *work, int nwork, hipStream_t s) {
+    switch (prec) {
+        case LB_F64:
+            return launch_split_batch<double>(all, work, nwork, s);
+        case LB_F32:
+            return launch_split_batch<float>(all, work, nwork, s);
+        case LB_F16DEV:
+            return launch_split_batch<_Float16>(all, work, nwork, s);
+        case LB_BF16DEV:
+            return launch_split_batch<bf16_t>(all, work, nwork, s);
+        default:
+            return hipErrorInvalidValue;
+    }
 }
 
 int tiles_xy(int nx, int ny, int tile_y) { return ((nx + 63) / 64) * ((ny + tile_y - 1) / tile_y); }
 
-template <class S, int TY, int NPT, bool TAU1>
+template <class S, int TY, int NPT, bool TAU1, bool SINK>
 static hipError_t launch_one(const StepArgs &a, hipStream_t s) {
     const int nblk = a.ntx * a.nty * a.nzc;
+    hipLaunchKernelGGL((sc_step_kernel<S, TY, NPT, TAU1, SINK>), dim3(nblk), dim3(64 * (TY / NPT)), 0, s, a);
+    return hipGetLastError();
+}
+
+// The fused step runs where the two-pass step does not: tau != 1 (the tiles
+// of one row per thread, whose registers hold the populations), and the sink.
+template <class S>
+static hipError_t launch_prec(bool tau1, const TileCfg &t, const StepArgs &a, hipStream_t s) {
+    const int ty = t.tile_y, rp = t.rows_per_thread;
     if (a.sink) {
         if constexpr (std::is_same_v<S, float>) {
-            hipLaunchKernelGGL((sc_step_kernel<S, TY, NPT, TAU1, true>), dim3(nblk), dim3(64 * (TY / NPT)), 0, s, a);
-            return hipGetLastError();
-        } else if constexpr (std::is_same_v<S, double> && TAU1) {
+            if (ty == 4 && rp == 1)
+                return tau1 ? launch_one<S, 4, 1, true, true>(a, s) : launch_one<S, 4, 1, false, true>(a, s);
+            if (ty == 8 && rp == 1)
+                return tau1 ? launch_one<S, 8, 1, true, true>(a, s) : launch_one<S, 8, 1, false, true>(a, s);
+            if (tau1 && ty == 8 && rp == 2) return launch_one<S, 8, 2, true, true>(a, s);
+            if (tau1 && ty == 16 && rp == 2) return launch_one<S, 16, 2, true, true>(a, s);
+        } else if constexpr (std::is_same_v<S, double>) {
             // With the sink, the FP64 instantiation of the 64 x 8 tile with
             // one row per thread gave wrong populations while the other FP64
             // tiles and all FP32 tiles match the oracle; the same tiling runs
             // with two rows per thread (identical work-groups and slots).
-            if constexpr (TY == 8 && NPT == 1) {
-                hipLaunchKernelGGL((sc_step_kernel<double, 8, 2, true, true>), dim3(nblk), dim3(64 * 4), 0, s, a);
-            } else {
-                hipLaunchKernelGGL((sc_step_kernel<S, TY, NPT, TAU1, true>), dim3(nblk), dim3(64 * (TY / NPT)), 0, s,
-                                   a);
-            }
-            return hipGetLastError();
+            if (tau1 && ty == 4 && rp == 1) return launch_one<S, 4, 1, true, true>(a, s);
+            if (tau1 && ty == 8) return launch_one<S, 8, 2, true, true>(a, s);
+            if (tau1 && ty == 16 && rp == 2) return launch_one<S, 16, 2, true, true>(a, s);
         }
         return hipErrorInvalidValue;  // the sink runs with FP32 storage, or FP64 with tau = 1
     }
-    hipLaunchKernelGGL((sc_step_kernel<S, TY, NPT, TAU1, false>), dim3(nblk), dim3(64 * (TY / NPT)), 0, s, a);
-    return hipGetLastError();
-}
-
-template <class S, bool TAU1>
-static hipError_t launch_prec(const TileCfg &t, const StepArgs &a, hipStream_t s) {
-    if (t.tile_y == 4 && t.rows_per_thread == 1) return launch_one<S, 4, 1, TAU1>(a, s);
-    if (t.tile_y == 8 && t.rows_per_thread == 1) return launch_one<S, 8, 1, TAU1>(a, s);
-    if constexpr (TAU1) {
-        // tau = 1 keeps only moments per owned node, so several rows fit
-        if (t.tile_y == 8 && t.rows_per_thread == 2) return launch_one<S, 8, 2, TAU1>(a, s);
-        if (t.tile_y == 16 && t.rows_per_thread == 2) return launch_one<S, 16, 2, TAU1>(a, s);
-    }
+    if (tau1) return hipErrorInvalidValue;  // launch_sc_split
+    if (ty == 4 && rp == 1) return launch_one<S, 4, 1, false, false>(a, s);
+    if (ty == 8 && rp == 1) return launch_one<S, 8, 1, false, false>(a, s);
     return hipErrorInvalidValue;
 }
 
-template <class S, int TY, int NPT, bool TAU1>
-static hipError_t launch_batch_one(const StepArgs *all, const int2 *work, int nwork, hipStream_t s) {
-    hipLaunchKernelGGL((sc_step_batch_kernel<S, TY, NPT, TAU1>), dim3(nwork), dim3(64 * (TY / NPT)), 0, s, all, work);
-    return hipGetLastError();
-}
-
-template <class S, bool TAU1>
+template <class S>
 static hipError_t launch_batch_prec(const TileCfg &t, const StepArgs *all, const int2 *work, int nwork, hipStream_t s) {
-    if (t.tile_y == 4 && t.rows_per_thread == 1) return launch_batch_one<S, 4, 1, TAU1>(all, work, nwork, s);
-    if (t.tile_y == 8 && t.rows_per_thread == 1) return launch_batch_one<S, 8, 1, TAU1>(all, work, nwork, s);
-    if constexpr (TAU1) {
-        if (t.tile_y == 8 && t.rows_per_thread == 2) return launch_batch_one<S, 8, 2, TAU1>(all, work, nwork, s);
-        if (t.tile_y == 16 && t.rows_per_thread == 2) return launch_batch_one<S, 16, 2, TAU1>(all, work, nwork, s);
+    if (t.rows_per_thread != 1) return hipErrorInvalidValue;
+    if (t.tile_y == 4) {
+        hipLaunchKernelGGL((sc_step_batch_kernel<S, 4>), dim3(nwork), dim3(64 * 4), 0, s, all, work);
+    } else if (t.tile_y == 8) {
+        hipLaunchKernelGGL((sc_step_batch_kernel<S, 8>), dim3(nwork), dim3(64 * 8), 0, s, all, work);
+    } else {
+        return hipErrorInvalidValue;
     }
-    return hipErrorInvalidValue;
+    return hipGetLastError();
 }
 
-hipError_t launch_sc_step_batch(int prec, bool tau1, const TileCfg &t, const StepArgs *all, const int2 *work, int nwork,
+hipError_t launch_sc_step_batch(int prec, const TileCfg &t, const StepArgs *all, const int2 *work, int nwork,
                                 hipStream_t s) {
     switch (prec) {
         case LB_F64:
-            return tau1 ? launch_batch_prec<double, true>(t, all, work, nwork, s)
-                        : launch_batch_prec<double, false>(t, all, work, nwork, s);
+            return launch_batch_prec<double>(t, all, work, nwork, s);
         case LB_F32:
-            return tau1 ? launch_batch_prec<float, true>(t, all, work, nwork, s)
-                        : launch_batch_prec<float, false>(t, all, work, nwork, s);
+            return launch_batch_prec<float>(t, all, work, nwork, s);
         case LB_F16DEV:
-            return tau1 ? launch_batch_prec<_Float16, true>(t, all, work, nwork, s)
-                        : launch_batch_prec<_Float16, false>(t, all, work, nwork, s);
+            return launch_batch_prec<_Float16>(t, all, work, nwork, s);
         case LB_BF16DEV:
-            return tau1 ? launch_batch_prec<bf16_t, true>(t, all, work, nwork, s)
-                        : launch_batch_prec<bf16_t, false>(t, all, work, nwork, s);
+            return launch_batch_prec<bf16_t>(t, all, work, nwork, s);
         default:
             return hipErrorInvalidValue;
     }
@@ -800,13 +1206,13 @@ hipError_t launch_sc_step_batch(int prec, bool tau1, const TileCfg &t, const Ste
 hipError_t launch_sc_step(int prec, bool tau1, const TileCfg &t, const StepArgs &a, hipStream_t s) {
     switch (prec) {
         case LB_F64:
-            return tau1 ? launch_prec<double, true>(t, a, s) : launch_prec<double, false>(t, a, s);
+            return launch_prec<double>(tau1, t, a, s);
         case LB_F32:
-            return tau1 ? launch_prec<float, true>(t, a, s) : launch_prec<float, false>(t, a, s);
+            return launch_prec<float>(tau1, t, a, s);
         case LB_F16DEV:
-            return tau1 ? launch_prec<_Float16, true>(t, a, s) : launch_prec<_Float16, false>(t, a, s);
+            return launch_prec<_Float16>(tau1, t, a, s);
         case LB_BF16DEV:
-            return tau1 ? launch_prec<bf16_t, true>(t, a, s) : launch_prec<bf16_t, false>(t, a, s);
+            return launch_prec<bf16_t>(tau1, t, a, s);
         default:
             return hipErrorInvalidValue;
     }
