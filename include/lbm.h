@@ -92,8 +92,8 @@ typedef struct {
     double rod_d0_wall;           /* rod-wall contact distance */
     int32_t wall_on;              /* 1: wall plane at z = wall_z repels rods */
     double wall_z;
-    /* tiling of the fused step, which runs with tau != 1 or the sink (0 =
-     * library default); see lb_autotune */
+    /* tiling of the fused step, which runs with tau != 1 (0 = library
+     * default); see lb_autotune */
     int32_t tile_y;               /* 4, 8 or 16 rows per tile */
     int32_t rows_per_thread;      /* 1 or 2 */
     int32_t zchunk;               /* planes marched by one work-group; 0 = auto */
@@ -431,7 +431,7 @@ int lb_kirchhoff_noalloc(const double *pos_dev, int32_t n, const lb_kirchhoff_sp
 int lb_rod_beads(lb_ctx *ctx, double bead_spacing, double *pos_dev, int32_t cap, int32_t *n_out, hipStream_t stream);
 
 /* Tile shape of the fused step: 64 x tile_y columns, rows_per_thread rows per
- * thread, zchunk planes marched per work-group.  With tau = 1 and no sink the
+ * thread, zchunk planes marched per work-group.  With tau = 1 the
  * step runs as two untiled passes: a shape is accepted and changes nothing. */
 typedef struct {
     int32_t tile_y, rows_per_thread, zchunk;

@@ -61,10 +61,11 @@ int64_t nodes(const lb_params *p) { return int64_t(p->nx) * p->ny * p->nz; }
 // Workspace layout (all offsets 256-byte aligned):
 //   mat      : N bytes, working material map with flag bits
 //   ledger   : max_tiles * 2 doubles, per-xy-tile reservoir ledger; with the
-//              evaporation sink max_tiles * nz more pairs, one per work-group
-//              (xy tile, z chunk) of the step
+//              evaporation sink a pair more per work-group of the step (at most
+//              one per smallest xy tile and plane)
 //   heights  : with the sink, [2][nz][ny*nx] int32 liquid-node counts per
-//              column and z chunk (read by one step, written by the other)
+//              column and z chunk (read by one step, written by the other;
+//              the two-pass step uses the first chunk only)
 //   status   : 256 bytes (status word)
 //   partials : OBS_BLOCKS * OBS_FIELDS doubles
 //   result   : 256 bytes
@@ -144,9 +145,9 @@ struct WsLayout {
 int fil_beads(const lb_params *p) { return p->n_fil > 0 && p->fil_beads > 0 ? p->n_fil * p->fil_beads : 0; }
 
 bool is_tau1(const lb_params &p) { return p.tau[0] == 1.0 && p.tau[1] == 1.0; }
-// tau = 1 without the sink needs only the streamed moments of a node: the step
-// runs as two passes (sc_step.hip)
-bool two_pass(const lb_params &p) { return p.model == LB_MODEL_SC && is_tau1(p) && !p.sink_on; }
+// tau = 1 needs only the streamed moments of a node: the step runs as two
+// passes (sc_step.hip)
+bool two_pass(const lb_params &p) { return p.model == LB_MODEL_SC && is_tau1(p); }
 
 WsLayout ws_layout(const lb_params *p) {
     WsLayout w{};
@@ -158,7 +159,7 @@ WsLayout ws_layout(const lb_params *p) {
     w.mat = o;
     o = align256(o + size_t(n));
     w.ledger = o;
-    w.nslots = w.max_tiles * (p->sink_on ? 1 + p->nz : 1);
+    w.nslots = w.max_tiles + (p->sink_on ? tiles_xy(p->nx, p->ny, 4) * p->nz : 0);
     o = align256(o + size_t(w.nslots) * 2 * sizeof(double));
     w.heights = o;
     o = align256(o + (p->sink_on ? 2 * size_t(n) * sizeof(int32_t) : 0));
@@ -725,11 +726,10 @@ int lb_step(lb_ctx *c, int32_t nsteps, hipStream_t stream) {
     if (!c) return fail(LB_EINVAL, "null ctx");
     if (nsteps < 0) return fail(LB_EINVAL, "negative step count");
     const lb_params &p = c->p;
-    const bool tau1 = is_tau1(p);
     for (int s = 0; s < nsteps; ++s) {
         hipError_t e = p.model == LB_MODEL_CG ? launch_cg_step(p.prec, cg_args(c, c->cur), stream)
                        : two_pass(p)          ? launch_sc_split(p.prec, step_args(c, c->cur), stream)
-                                              : launch_sc_step(p.prec, tau1, c->tile, step_args(c, c->cur), stream);
+                                              : launch_sc_step(p.prec, c->tile, step_args(c, c->cur), stream);
         if (e != hipSuccess) return hip_fail(e, "step launch");
         c->cur ^= 1;
         c->steps++;

@@ -159,16 +159,16 @@ struct FilArgs {
 };
 hipError_t launch_fil_step(int prec, const FilArgs &a, hipStream_t s);
 
-hipError_t launch_sc_step(int prec, bool tau1, const TileCfg &t, const StepArgs &a, hipStream_t s);
+hipError_t launch_sc_step(int prec, const TileCfg &t, const StepArgs &a, hipStream_t s);
 // all: device array of per-lattice step records; work: device list of
 // (lattice, logical tile) entries, (-1, -1) for padding
 hipError_t launch_sc_step_batch(int prec, const TileCfg &t, const StepArgs *all, const int2 *work, int nwork,
                                 hipStream_t s);
-// the two-pass form of the step (tau = 1, no sink): a.rho_out holds psi_k of
+// the two-pass form of the step (tau = 1): a.rho_out holds psi_k of
 // every node between the passes; work entries are (lattice, block of nodes)
 hipError_t launch_sc_split(int prec, const StepArgs &a, hipStream_t s);
 hipError_t launch_sc_split_batch(int prec, const StepArgs *all, const int2 *work, int nwork, hipStream_t s);
-int split_blocks(int nx, int ny, int nz);
+__host__ __device__ int split_blocks(int nx, int ny, int nz);
 int tiles_xy(int nx, int ny, int tile_y);
 
 // auxiliary kernels (aux.hip)

@@ -1,8 +1,7 @@
 // Shan-Chen D3Q19 step for gfx950: pull stream + boundaries + moments +
 // pseudopotential force + velocity shift + BGK collision + store.  With
-// tau = 1 in both components (and no sink) the step runs as two passes of one
-// thread per node (further down); otherwise it is one fused pass, described
-// next.
+// tau = 1 in both components the step runs as two passes of one thread per
+// node (further down); otherwise it is one fused pass, described next.
 //
 // Method: lattice Boltzmann equation per component with BGK relaxation
 // (Eq. 1), second-order equilibrium (Eq. 2), moments (Eq. 3); the interfacial
@@ -42,9 +41,8 @@
 //    nodes), which the rod passes read instead of summing 19 populations per
 //    surface node in the order of their lists.
 //
-// Evaporation sink (a separate instantiation; FP32 storage, or FP64 with
-// tau = 1): after the
-// collision, an interface node (liquid here, a gas fluid node at z + 1) moves
+// Evaporation sink (separate instantiations; FP32 storage, or FP64 with
+// tau = 1): after the collision, an interface node (liquid here, a gas fluid node at z + 1) moves
 // min(J0 / (K + h / h0), f*_0^A) from A's rest population to B's (Methods,
 // evaporation paragraph; Eq. 8).  h, the column's liquid nodes, comes from
 // the previous step's per-chunk counts; this step writes its own.
@@ -170,22 +168,16 @@ __device__ inline C wave_sum(C v) {
 // One work-group's tile: logical tile b of a lattice whose step runs as nblk
 // work-groups.  remap: b is a hardware dispatch index to be spread over the
 // XCDs (else b is already the logical tile).
-template <class S, int TY, int NPT, bool TAU1, bool SINK = false>
+template <class S, int TY, bool SINK>
 __device__ __forceinline__ void sc_step_tile(const StepArgs &a, int b, int nblk, bool remap) {
     using C = typename Codec<S>::C;
     constexpr int TX = 64;
-    constexpr int RY = TY / NPT;
-    constexpr int NT = TX * RY;
+    constexpr int NT = TX * TY;
     constexpr int HX = TX + 2, HY = TY + 2, PL = HX * HY;
     constexpr int NH = 2 * HX + 2 * TY;
     constexpr int NHPT = (NH + NT - 1) / NT;
     constexpr int NW = NT / 64;
     constexpr uint32_t E = sizeof(S);
-    // software-pipelined plane loads need a second set of raw registers; that
-    // fits for tau = 1 with 4-byte storage, the other forms load and consume a
-    // plane in turn
-    constexpr bool PIPE = TAU1 && sizeof(S) <= 4;
-
     __shared__ C ring[4][2][PL];
     __shared__ C psi_tab[16][2];
     __shared__ double red[NW][2];
@@ -236,17 +228,10 @@ __device__ __forceinline__ void sc_step_tile(const StepArgs &a, int b, int nblk,
     const C ta[2] = {C(a.tau[0]), C(a.tau[1])};
     const C gb[3] = {C(a.g[0]), C(a.g[1]), C(a.g[2])};
 
-    // ---- owned interior nodes and ring (halo) nodes of this thread
-    NodeXY own[NPT];
-    bool own_fin[NPT];
-    int own_ring[NPT];
-#pragma unroll
-    for (int r = 0; r < NPT; ++r) {
-        const int yy = ly + r * RY;
-        own[r] = make_node(x0 + lx, y0 + yy, a);
-        own_fin[r] = (x0 + lx < a.nx) && (y0 + yy < a.ny);
-        own_ring[r] = (yy + 1) * HX + (lx + 1);
-    }
+    // ---- owned interior node and ring (halo) nodes of this thread
+    const NodeXY own = make_node(x0 + lx, y0 + ly, a);
+    const bool own_fin = (x0 + lx < a.nx) && (y0 + ly < a.ny);
+    const int own_ring = (ly + 1) * HX + (lx + 1);
     NodeXY hal[NHPT];
     int hal_ring[NHPT];
     bool hal_on[NHPT];
@@ -277,31 +262,25 @@ __device__ __forceinline__ void sc_step_tile(const StepArgs &a, int b, int nblk,
     // evaporation sink (Eq. 8): flux of each owned column from the heights
     // the previous step counted over all z chunks, this chunk's count of
     // liquid nodes after the sink, and the mass this thread moved A -> B
-    C sink_J[NPT];
-    int sink_cnt[NPT];
+    C sink_J = C(0);
+    int sink_cnt = 0;
     double sink_mv = 0.0;
     if constexpr (SINK) {
-#pragma unroll
-        for (int r = 0; r < NPT; ++r) {
-            int h = 0;
-            if (own_fin[r])
-                for (int q = 0; q < a.nzc; ++q) h += a.h_read[size_t(q) * nxy + own[r].xy[1][1]];
-            sink_J[r] = C(a.sink_J0) / (C(a.sink_K) + C(h) / C(a.sink_h0));
-            sink_cnt[r] = 0;
-        }
+        int h = 0;
+        if (own_fin)
+            for (int q = 0; q < a.nzc; ++q) h += a.h_read[size_t(q) * nxy + own.xy[1][1]];
+        sink_J = C(a.sink_J0) / (C(a.sink_K) + C(h) / C(a.sink_h0));
     }
 
-    // moments of the owned nodes: current plane and next plane
-    C cur_rho[NPT][2], cur_drho[NPT][2], cur_j[NPT][2][3];
-    C nxt_rho[NPT][2], nxt_drho[NPT][2], nxt_j[NPT][2][3];
-    C cur_f[TAU1 ? 1 : NPT][TAU1 ? 1 : 2][TAU1 ? 1 : Q];
-    C nxt_f[TAU1 ? 1 : NPT][TAU1 ? 1 : 2][TAU1 ? 1 : Q];
-    uint8_t cur_m[NPT], nxt_m[NPT];
+    // moments and populations of the owned node: current plane and next plane
+    C cur_rho[2], cur_drho[2], cur_j[2][3], cur_f[2][Q];
+    C nxt_rho[2], nxt_drho[2], nxt_j[2][3], nxt_f[2][Q];
+    uint8_t cur_m, nxt_m;
 
     // raw pulled values of one plane, in flight between issue() and process()
-    S raw_own[NPT][2][Q];
+    S raw_own[2][Q];
     S raw_hal[NHPT][2][Q];
-    uint8_t mat_own[NPT], mat_hal[NHPT];
+    uint8_t mat_own, mat_hal[NHPT];
     bool plane_valid = false, plane_top = false;
 
     // psi of a node given its material byte and densities
@@ -327,17 +306,14 @@ __device__ __forceinline__ void sc_step_tile(const StepArgs &a, int b, int nblk,
         const int zp = a.pz ? wrap1(zz + 1, a.nz) : min(zz + 1, a.nz - 1);
         const uint32_t zoE[3] = {zm * nxy * E, zz * nxy * E, zp * nxy * E};
         plane_top = a.evap && (zz == a.nz - 2);
+        mat_own = uint8_t(__builtin_amdgcn_raw_buffer_load_b8(matr, own.xy[1][1], zz * nxy, 0));
 #pragma unroll
-        for (int r = 0; r < NPT; ++r) {
-            mat_own[r] = uint8_t(__builtin_amdgcn_raw_buffer_load_b8(matr, own[r].xy[1][1], zz * nxy, 0));
+        for (int k = 0; k < 2; ++k)
 #pragma unroll
-            for (int k = 0; k < 2; ++k)
-#pragma unroll
-                for (int i = 0; i < Q; ++i)
-                    if (!(cz(i) == -1 && plane_top))
-                        raw_own[r][k][i] =
-                            buf_load<S>(src[k], own[r].xy[1 - cy(i)][1 - cx(i)] * E, i * fsE + zoE[1 - cz(i)]);
-        }
+            for (int i = 0; i < Q; ++i)
+                if (!(cz(i) == -1 && plane_top))
+                    raw_own[k][i] =
+                        buf_load<S>(src[k], own.xy[1 - cy(i)][1 - cx(i)] * E, i * fsE + zoE[1 - cz(i)]);
 #pragma unroll
         for (int mm = 0; mm < NHPT; ++mm) {
             if (!hal_on[mm]) continue;
@@ -361,57 +337,52 @@ __device__ __forceinline__ void sc_step_tile(const StepArgs &a, int b, int nblk,
     // keep, into the owned nodes' moments for the next finish.
     auto process = [&](int z, bool keep) {
         const int slot = z & 3;
+        const bool v = plane_valid && own.valid;
+        const uint8_t m = v ? mat_own : uint8_t(MAT_ID_MASK);
+        C rho[2] = {C(0), C(0)}, drho[2] = {C(0), C(0)};
+        C j[2][3] = {{C(0), C(0), C(0)}, {C(0), C(0), C(0)}};
+        const bool fl = v && (m & MAT_ID_MASK) == MAT_FLUID;
 #pragma unroll
-        for (int r = 0; r < NPT; ++r) {
-            const bool v = plane_valid && own[r].valid;
-            const uint8_t m = v ? mat_own[r] : uint8_t(MAT_ID_MASK);
-            C rho[2] = {C(0), C(0)}, drho[2] = {C(0), C(0)};
-            C j[2][3] = {{C(0), C(0), C(0)}, {C(0), C(0), C(0)}};
-            const bool fl = v && (m & MAT_ID_MASK) == MAT_FLUID;
+        for (int k = 0; k < 2; ++k) {
+            C fv[Q];
+#pragma unroll
+            for (int i = 0; i < Q; ++i) fv[i] = devof(raw_own, k, i);
+            C s = C(0), jx = C(0), jy = C(0), jz = C(0);
+#pragma unroll
+            for (int i = 0; i < Q; ++i) s += fv[i];
+            // momentum over opposite pairs: f_i - f_opp(i) is nearly exact
+            // (the two are close), which avoids cancellation in j
+#pragma unroll
+            for (int i = 1; i < Q; i += 2) {
+                const C d = fv[i] - fv[i + 1];
+                if (cx(i) == 1) jx += d;
+                if (cx(i) == -1) jx -= d;
+                if (cy(i) == 1) jy += d;
+                if (cy(i) == -1) jy -= d;
+                if (cz(i) == 1) jz += d;
+                if (cz(i) == -1) jz -= d;
+            }
+            // Eq. 3: rho_k = sum_i f_i = rref_k + sum_i d_i (sum_i w_i = 1)
+            drho[k] = fl ? s : C(0);
+            rho[k] = fl ? rref[k] + s : C(0);
+            j[k][0] = fl ? jx : C(0);
+            j[k][1] = fl ? jy : C(0);
+            j[k][2] = fl ? jz : C(0);
+            if (keep) {
+#pragma unroll
+                for (int i = 0; i < Q; ++i) nxt_f[k][i] = fv[i];
+            }
+        }
+        ring[slot][0][own_ring] = v ? psi_of(m, 0, rho[0]) : C(0);
+        ring[slot][1][own_ring] = v ? psi_of(m, 1, rho[1]) : C(0);
+        if (keep) {
+            nxt_m = m;
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
-                C fv[Q];
+                nxt_rho[k] = rho[k];
+                nxt_drho[k] = drho[k];
 #pragma unroll
-                for (int i = 0; i < Q; ++i) fv[i] = devof(raw_own[r], k, i);
-                C s = C(0), jx = C(0), jy = C(0), jz = C(0);
-#pragma unroll
-                for (int i = 0; i < Q; ++i) s += fv[i];
-                // momentum over opposite pairs: f_i - f_opp(i) is nearly exact
-                // (the two are close), which avoids cancellation in j
-#pragma unroll
-                for (int i = 1; i < Q; i += 2) {
-                    const C d = fv[i] - fv[i + 1];
-                    if (cx(i) == 1) jx += d;
-                    if (cx(i) == -1) jx -= d;
-                    if (cy(i) == 1) jy += d;
-                    if (cy(i) == -1) jy -= d;
-                    if (cz(i) == 1) jz += d;
-                    if (cz(i) == -1) jz -= d;
-                }
-                // Eq. 3: rho_k = sum_i f_i = rref_k + sum_i d_i (sum_i w_i = 1)
-                drho[k] = fl ? s : C(0);
-                rho[k] = fl ? rref[k] + s : C(0);
-                j[k][0] = fl ? jx : C(0);
-                j[k][1] = fl ? jy : C(0);
-                j[k][2] = fl ? jz : C(0);
-                if constexpr (!TAU1) {
-                    if (keep) {
-#pragma unroll
-                        for (int i = 0; i < Q; ++i) nxt_f[r][k][i] = fv[i];
-                    }
-                }
-            }
-            ring[slot][0][own_ring[r]] = v ? psi_of(m, 0, rho[0]) : C(0);
-            ring[slot][1][own_ring[r]] = v ? psi_of(m, 1, rho[1]) : C(0);
-            if (keep) {
-                nxt_m[r] = m;
-#pragma unroll
-                for (int k = 0; k < 2; ++k) {
-                    nxt_rho[r][k] = rho[k];
-                    nxt_drho[r][k] = drho[k];
-#pragma unroll
-                    for (int d = 0; d < 3; ++d) nxt_j[r][k][d] = j[k][d];
-                }
+                for (int d = 0; d < 3; ++d) nxt_j[k][d] = j[k][d];
             }
         }
 #pragma unroll
@@ -434,46 +405,33 @@ __device__ __forceinline__ void sc_step_tile(const StepArgs &a, int b, int nblk,
     };
 
     auto shift_next = [&]() {
+        cur_m = nxt_m;
 #pragma unroll
-        for (int r = 0; r < NPT; ++r) {
-            cur_m[r] = nxt_m[r];
+        for (int k = 0; k < 2; ++k) {
+            cur_rho[k] = nxt_rho[k];
+            cur_drho[k] = nxt_drho[k];
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                cur_rho[r][k] = nxt_rho[r][k];
-                cur_drho[r][k] = nxt_drho[r][k];
+            for (int d = 0; d < 3; ++d) cur_j[k][d] = nxt_j[k][d];
 #pragma unroll
-                for (int d = 0; d < 3; ++d) cur_j[r][k][d] = nxt_j[r][k][d];
-                if constexpr (!TAU1) {
-#pragma unroll
-                    for (int i = 0; i < Q; ++i) cur_f[r][k][i] = nxt_f[r][k][i];
-                }
-            }
+            for (int i = 0; i < Q; ++i) cur_f[k][i] = nxt_f[k][i];
         }
     };
 
     // prologue: the plane behind the first one (psi only), the first plane
-    // (psi + moments), then the loads of the plane after it
+    // (psi, moments and populations)
     issue(zfirst - dir);
     process(zfirst - dir, false);
     issue(zfirst);
     process(zfirst, true);
     shift_next();
-    if constexpr (PIPE) issue(zfirst + dir);
 
     for (int it = 0; it < nplanes; ++it) {
         const int z = zfirst + it * dir;
         // the ring holds 4 planes: this iteration writes plane z + dir and
         // reads z - 1, z, z + 1; the next one writes z + 2 dir, which no
         // thread of this iteration reads, so one barrier per plane suffices
-        if constexpr (PIPE) {
-            process(z + dir, true);
-            // software pipeline: the pulls of plane z + 2 dir stay in flight
-            // across the barrier (which waits on LDS only) and the finish below
-            if (it + 1 < nplanes) issue(z + 2 * dir);
-        } else {
-            issue(z + dir);
-            process(z + dir, true);
-        }
+        issue(z + dir);
+        process(z + dir, true);
         __syncthreads();
 
         const int sm = (z - 1) & 3, s0 = z & 3, sp = (z + 1) & 3;
@@ -482,22 +440,20 @@ __device__ __forceinline__ void sc_step_tile(const StepArgs &a, int b, int nblk,
         double led[2] = {0.0, 0.0};
         unsigned st = 0;
 
-#pragma unroll
-        for (int r = 0; r < NPT; ++r) {
-            // rod nodes go through the same arithmetic (all their moments are
-            // zero, so every deviation they store is exactly zero) and store
-            // with the fluid lanes: a wave that a rod cuts through then still
-            // writes whole lines, where masked lanes would leave partial lines
-            // that HBM has to read, merge and write back.  Nothing reads these
-            // slots before the rod passes rewrite them (link) or refill them.
-            const uint8_t mid = cur_m[r] & MAT_ID_MASK;
-            if (!own_fin[r] || (mid != MAT_FLUID && mid != MAT_ROD)) continue;
+        // rod nodes go through the same arithmetic (all their moments are
+        // zero, so every deviation they store is exactly zero) and store
+        // with the fluid lanes: a wave that a rod cuts through then still
+        // writes whole lines, where masked lanes would leave partial lines
+        // that HBM has to read, merge and write back.  Nothing reads these
+        // slots before the rod passes rewrite them (link) or refill them.
+        const uint8_t mid = cur_m & MAT_ID_MASK;
+        if (own_fin && (mid == MAT_FLUID || mid == MAT_ROD)) {
             const bool fluid = mid == MAT_FLUID;
-            const int rc = own_ring[r];
-            const C rho[2] = {cur_rho[r][0], cur_rho[r][1]};
+            const int rc = own_ring;
+            const C rho[2] = {cur_rho[0], cur_rho[1]};
             if (a.rho_out) {  // lattices with rods: the densities for the rod passes
                 C *ro = static_cast<C *>(a.rho_out);
-                const int64_t nn = int64_t(z) * nxy + own[r].xy[1][1];
+                const int64_t nn = int64_t(z) * nxy + own.xy[1][1];
                 ro[nn] = rho[0];
                 ro[a.fs + nn] = rho[1];
             }
@@ -508,7 +464,7 @@ __device__ __forceinline__ void sc_step_tile(const StepArgs &a, int b, int nblk,
             if constexpr (SINK) {
                 if (rho[0] > rho[1] && (a.pz || z + 1 < a.nz) && ring[sp][0][rc] < ring[sp][1][rc]) {
                     const int za = a.pz ? wrap1(z + 1, a.nz) : z + 1;
-                    const uint8_t ma = uint8_t(__builtin_amdgcn_raw_buffer_load_b8(matr, own[r].xy[1][1], za * nxy, 0));
+                    const uint8_t ma = uint8_t(__builtin_amdgcn_raw_buffer_load_b8(matr, own.xy[1][1], za * nxy, 0));
                     sink_if = (ma & MAT_ID_MASK) == MAT_FLUID;
                 }
             }
@@ -543,7 +499,7 @@ __device__ __forceinline__ void sc_step_tile(const StepArgs &a, int b, int nblk,
             const C rden = den > C(0) ? C(1) / den : C(0);
             C up[3];
 #pragma unroll
-            for (int d = 0; d < 3; ++d) up[d] = (cur_j[r][0][d] * om[0] + cur_j[r][1][d] * om[1]) * rden;
+            for (int d = 0; d < 3; ++d) up[d] = (cur_j[0][d] * om[0] + cur_j[1][d] * om[1]) * rden;
             // health check on the physical velocity (sum_k j_k + F/2) / rho
             {
                 const C rt = rho[0] + rho[1];
@@ -551,18 +507,18 @@ __device__ __forceinline__ void sc_step_tile(const StepArgs &a, int b, int nblk,
                 C usq_chk = C(0);
 #pragma unroll
                 for (int d = 0; d < 3; ++d) {
-                    const C ud = (cur_j[r][0][d] + cur_j[r][1][d] + C(0.5) * (F[0][d] + F[1][d])) * ir;
+                    const C ud = (cur_j[0][d] + cur_j[1][d] + C(0.5) * (F[0][d] + F[1][d])) * ir;
                     usq_chk += ud * ud;
                 }
                 if (fluid && !(rt > C(0))) st |= ST_RHO;
                 if (fluid && !(usq_chk <= C(0.09))) st |= (usq_chk != usq_chk) ? ST_NAN : ST_SPEED;
             }
 
-            const uint32_t voE = own[r].xy[1][1] * E;
-            const bool near_wall = fluid && (cur_m[r] & MAT_NEAR_WALL) != 0;
+            const uint32_t voE = own.xy[1][1] * E;
+            const bool near_wall = fluid && (cur_m & MAT_NEAR_WALL) != 0;
             // 16-bit storage with stochastic rounding: the random bits depend on
             // (node, array, step) only; the wall slots reuse the encoded values
-            const int64_t gnode = int64_t(z) * nxy + own[r].xy[1][1];
+            const int64_t gnode = int64_t(z) * nxy + own.xy[1][1];
             SrStream sr{0u, 0u};
             if constexpr (sizeof(S) == 2) {
                 if (a.sr_key) sr.state = sr_seed(a.sr_key, gnode);
@@ -581,7 +537,7 @@ __device__ __forceinline__ void sc_step_tile(const StepArgs &a, int b, int nblk,
 #pragma unroll
                 for (int d = 0; d < 3; ++d) ue[d] = up[d] + F[k][d] * rk;
                 const C usq = ue[0] * ue[0] + ue[1] * ue[1] + ue[2] * ue[2];
-                const C dr = cur_drho[r][k];
+                const C dr = cur_drho[k];
                 S sstar[Q];
                 C deq_sum = C(0);
                 // Eq. 2 as a deviation, built per opposite pair (i, opp(i)):
@@ -605,17 +561,12 @@ __device__ __forceinline__ void sc_step_tile(const StepArgs &a, int b, int nblk,
                 deq[0] = dr - deq_sum;
 #pragma unroll
                 for (int i = 0; i < Q; ++i) {
-                    C ds;
-                    if constexpr (TAU1) {
-                        ds = deq[i];  // Eq. 1 with tau = 1: f* = f^eq
-                    } else {
-                        ds = fluid ? cur_f[r][k][i] - (cur_f[r][k][i] - deq[i]) * om[k] : C(0);
-                    }
+                    C ds = fluid ? cur_f[k][i] - (cur_f[k][i] - deq[i]) * om[k] : C(0);
                     if constexpr (SINK) {
                         // Eq. 8: min(J, f*_0^A), at least 0, leaves A's rest population for B's
                         if (i == 0 && sink_if) {
                             if (k == 0) {
-                                sink_d = fmax(fmin(sink_J[r], ds + wgt<C>(0) * rref[0]), C(0));
+                                sink_d = fmax(fmin(sink_J, ds + wgt<C>(0) * rref[0]), C(0));
                                 ds -= sink_d;
                             } else {
                                 ds += sink_d;
@@ -647,7 +598,7 @@ __device__ __forceinline__ void sc_step_tile(const StepArgs &a, int b, int nblk,
                         static_cast<uint32_t>(a.pz ? wrap1(z + 1, a.nz) : min(z + 1, a.nz - 1)) * nxy};
 #pragma unroll
                     for (int jd = 1; jd < Q; ++jd) {
-                        const uint32_t nxyo = own[r].xy[1 + cy(jd)][1 + cx(jd)];
+                        const uint32_t nxyo = own.xy[1 + cy(jd)][1 + cx(jd)];
                         const uint8_t nm = uint8_t(__builtin_amdgcn_raw_buffer_load_b8(matr, nxyo, zl[1 + cz(jd)], 0));
                         if (is_static_wall(nm & MAT_ID_MASK))
                             buf_store<S>(sstar[jd], dst[k], nxyo * E,
@@ -657,7 +608,7 @@ __device__ __forceinline__ void sc_step_tile(const StepArgs &a, int b, int nblk,
             }
             if constexpr (SINK) {
                 // the column height the next step reads: liquid after the sink
-                sink_cnt[r] += (rho[0] - sink_d > rho[1] + sink_d) ? 1 : 0;
+                sink_cnt += (rho[0] - sink_d > rho[1] + sink_d) ? 1 : 0;
                 sink_mv += double(sink_d);
             }
         }
@@ -688,9 +639,7 @@ __device__ __forceinline__ void sc_step_tile(const StepArgs &a, int b, int nblk,
     if constexpr (SINK) {
         // this chunk's column heights, and the work-group's moved mass into
         // its own ledger pair (A loses it, B gains it)
-#pragma unroll
-        for (int r = 0; r < NPT; ++r)
-            if (own_fin[r]) a.h_write[size_t(tz) * nxy + own[r].xy[1][1]] = sink_cnt[r];
+        if (own_fin) a.h_write[size_t(tz) * nxy + own.xy[1][1]] = sink_cnt;
         const double mv = wave_sum(sink_mv);
         __syncthreads();  // red may still be read by the last ledger plane's sum
         if (lx == 0) red[tid >> 6][0] = mv;
@@ -705,9 +654,9 @@ __device__ __forceinline__ void sc_step_tile(const StepArgs &a, int b, int nblk,
     }
 }
 
-template <class S, int TY, int NPT, bool TAU1, bool SINK>
-__global__ void __launch_bounds__(64 * (TY / NPT)) sc_step_kernel(StepArgs a) {
-    sc_step_tile<S, TY, NPT, TAU1, SINK>(a, blockIdx.x, gridDim.x, true);
+template <class S, int TY, bool SINK>
+__global__ void __launch_bounds__(64 * TY) sc_step_kernel(StepArgs a) {
+    sc_step_tile<S, TY, SINK>(a, blockIdx.x, gridDim.x, true);
 }
 
 // Batched step: one launch walks a device work list of (lattice, logical
@@ -720,11 +669,11 @@ __global__ void __launch_bounds__(64 * TY) sc_step_batch_kernel(const StepArgs *
     const int2 w = work[blockIdx.x];
     if (w.x < 0) return;  // padding entry, uniform per block
     const StepArgs a = all[w.x];
-    sc_step_tile<S, TY, 1, false>(a, w.y, a.ntx * a.nty * a.nzc, false);
+    sc_step_tile<S, TY, false>(a, w.y, a.ntx * a.nty * a.nzc, false);
 }
 
 // ---------------------------------------------------------------------------
-// The step in two passes (tau = 1, no sink).  With tau = 1 the collision
+// The step in two passes (tau = 1).  The collision with tau = 1
 // forgets the streamed populations, f* = f^eq(rho_k, u_k^eq), so a node needs
 // only its moments: the stream pass pulls the 38 populations and keeps psi_k
 // (an array of its own, read with its neighbours by the second pass) and
@@ -780,6 +729,8 @@ __device__ inline typename Codec<S>::C get_moment(__amdgpu_buffer_rsrc_t r, uint
         return buf_load<S>(r, voff, q * fsE);
     }
 }
+
+__host__ __device__ int split_blocks(int nx, int ny, int nz) { return int((int64_t(nx) * ny * nz + NB - 1) / NB); }
 
 // A node's coordinates and the index parts of its neighbourhood (wrapped in
 // periodic directions, clamped in closed ones).
@@ -882,6 +833,8 @@ __device__ __forceinline__ void sc_stream_nodes(const StepArgs &a, int b) {
             }
         }
     }
+    // the sink's column counts of this step start at zero (the collide pass adds)
+    if (a.sink && n0 < nxy) a.h_write[n0] = 0;
     // ledger: this step's streaming moves the stored f*_i(t) with c_iz = +1 of
     // the plane below the reservoir into it and pulls w_i rho_top_k out of it
     const uint32_t b0 = a.evap ? (uint32_t(a.nz - 2) * nxy) / NB : 0;
@@ -916,14 +869,16 @@ __device__ __forceinline__ void sc_stream_nodes(const StepArgs &a, int b) {
     }
 }
 
-template <class S>
-__device__ __forceinline__ void sc_collide_nodes(const StepArgs &a, int b) {
+// Collides one node per thread of block b.  Returns the mass the sink moved
+// from A to B there.
+template <class S, bool SINK = false>
+__device__ __forceinline__ double sc_collide_nodes(const StepArgs &a, int b) {
     using C = typename Codec<S>::C;
     constexpr uint32_t E = sizeof(S);
     const uint32_t nxy = static_cast<uint32_t>(a.nx) * a.ny, N = nxy * a.nz;
     const uint32_t fsE = static_cast<uint32_t>(a.fs) * E;
     const uint32_t n = static_cast<uint32_t>(b) * NB + threadIdx.x;
-    if (n >= N) return;
+    if (n >= N) return 0.0;
     const NodeNbr nb = node_nbr(n, a);
     const uint8_t mt = gptr(a.mat)[n];
     const unsigned known = *a.status;  // status bits already raised before this launch
@@ -931,7 +886,7 @@ __device__ __forceinline__ void sc_collide_nodes(const StepArgs &a, int b) {
     const auto pr = [&](int k) { return make_rsrc(psi + size_t(k) * a.fs, uint32_t(a.fs) * uint32_t(sizeof(C))); };
     // sum_i w_i psi(x + c_i) c_i taken over opposite pairs as central
     // differences w_i c_i (psi(x + c_i) - psi(x - c_i)): no cancellation
-    C sg[2][3], own[2];
+    C sg[2][3], own[2], above[2];
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
         const auto r = pr(k);
@@ -939,6 +894,7 @@ __device__ __forceinline__ void sc_collide_nodes(const StepArgs &a, int b) {
 #pragma unroll
         for (int i = 0; i < Q; ++i) v[i] = buf_load<C>(r, nb.at(cx(i), cy(i), cz(i)) * uint32_t(sizeof(C)), 0);
         own[k] = v[0];
+        above[k] = v[5];
         C sx = C(0), sy = C(0), sz = C(0);
 #pragma unroll
         for (int i = 1; i < Q; i += 2) {
@@ -961,7 +917,7 @@ __device__ __forceinline__ void sc_collide_nodes(const StepArgs &a, int b) {
     // merge and write back.  Nothing reads these slots before the rod passes
     // rewrite them (link) or refill them.
     const uint8_t mid = mt & MAT_ID_MASK;
-    if (mid != MAT_FLUID && mid != MAT_ROD) return;
+    if (mid != MAT_FLUID && mid != MAT_ROD) return 0.0;
     const bool fluid = mid == MAT_FLUID;
     const auto dst0 = make_rsrc(a.fdst, Q * fsE);
     const C rho[2] = {fluid ? own[0] : C(0), fluid ? own[1] : C(0)};
@@ -996,6 +952,16 @@ __device__ __forceinline__ void sc_collide_nodes(const StepArgs &a, int b) {
         }
         if (fluid && !(rt > C(0))) st |= ST_RHO;
         if (fluid && !(usq_chk <= C(0.09))) st |= (usq_chk != usq_chk) ? ST_NAN : ST_SPEED;
+    }
+    // sink (Eq. 8): a liquid node under a gas fluid node moves min(J, f*_0^A)
+    bool sink_if = false;
+    C sink_J = C(0), sink_d = C(0);
+    if constexpr (SINK) {
+        if (fluid && rho[0] > rho[1] && above[0] < above[1] && (a.pz || nb.z + 1 < a.nz) &&
+            (gptr(a.mat)[nb.at(0, 0, 1)] & MAT_ID_MASK) == MAT_FLUID) {
+            sink_if = true;
+            sink_J = C(a.sink_J0) / (C(a.sink_K) + C(gptr(a.h_read)[nb.at(0, 0, 0) - nb.zs[1]]) / C(a.sink_h0));
+        }
     }
     const bool near_wall = fluid && (mt & MAT_NEAR_WALL) != 0;
     // 16-bit storage with stochastic rounding: the random bits depend on
@@ -1043,7 +1009,19 @@ __device__ __forceinline__ void sc_collide_nodes(const StepArgs &a, int b) {
         // Eq. 1 with tau = 1: f* = f^eq
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
-            sstar[i] = encode(deq[i], k * Q + i);
+            C ds = deq[i];
+            if constexpr (SINK) {
+                // Eq. 8: min(J, f*_0^A), at least 0, leaves A's rest population for B's
+                if (i == 0 && sink_if) {
+                    if (k == 0) {
+                        sink_d = fmax(fmin(sink_J, ds + wgt<C>(0) * C(a.rho_ref[0])), C(0));
+                        ds -= sink_d;
+                    } else {
+                        ds += sink_d;
+                    }
+                }
+            }
+            sstar[i] = encode(ds, k * Q + i);
             buf_store<S>(sstar[i], dst, n * E, i * fsE);
         }
         if (near_wall) {
@@ -1057,15 +1035,35 @@ __device__ __forceinline__ void sc_collide_nodes(const StepArgs &a, int b) {
         }
     }
     post_status(a.status, known, st);
+    if constexpr (SINK) {
+        // the column height the next step reads: liquid after the sink (an
+        // integer count, so the order of the adds does not matter)
+        if (fluid && rho[0] - sink_d > rho[1] + sink_d) atomicAdd(a.h_write + (nb.at(0, 0, 0) - nb.zs[1]), 1);
+    }
+    return double(sink_d);
 }
 
 template <class S>
 __global__ void __launch_bounds__(NB) sc_stream_kernel(StepArgs a) {
     sc_stream_nodes<S>(a, xcd_range(blockIdx.x, gridDim.x));
 }
-template <class S>
+template <class S, bool SINK>
 __global__ void __launch_bounds__(NB) sc_collide_kernel(StepArgs a) {
-    sc_collide_nodes<S>(a, xcd_range(blockIdx.x, gridDim.x));
+    const int b = xcd_range(blockIdx.x, gridDim.x);
+    const double mv = sc_collide_nodes<S, SINK>(a, b);
+    if constexpr (SINK) {
+        // the block's moved mass into its own ledger pair (A loses it, B gains it)
+        __shared__ double red[NB / 64];
+        const double w = wave_sum(mv);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = w;
+        __syncthreads();
+        if (threadIdx.x == 0 && b < split_blocks(a.nx, a.ny, a.nz)) {
+            double sum = 0.0;
+            for (int q = 0; q < NB / 64; ++q) sum += red[q];
+            a.sink_ledger[2 * size_t(b)] += sum;
+            a.sink_ledger[2 * size_t(b) + 1] -= sum;
+        }
+    }
 }
 // batches: a work list of (lattice, run of BATCH_RUN node blocks) entries
 constexpr int BATCH_RUN = 1;
@@ -1086,15 +1084,20 @@ __global__ void __launch_bounds__(NB) sc_collide_batch_kernel(const StepArgs *__
     sc_collide_nodes<S>(a, w.y);
 }
 
-int split_blocks(int nx, int ny, int nz) { return int((int64_t(nx) * ny * nz + NB - 1) / NB); }
-
 template <class S>
 static hipError_t launch_split(const StepArgs &a, hipStream_t s) {
     const int nblk = (split_blocks(a.nx, a.ny, a.nz) + 7) & ~7;
     hipLaunchKernelGGL((sc_stream_kernel<S>), dim3(nblk), dim3(NB), 0, s, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((sc_collide_kernel<S>), dim3(nblk), dim3(NB), 0, s, a);
+    if (a.sink) {
+        if constexpr (sizeof(S) >= 4) {  // the sink runs with FP32 or FP64 storage
+            hipLaunchKernelGGL((sc_collide_kernel<S, true>), dim3(nblk), dim3(NB), 0, s, a);
+            return hipGetLastError();
+        }
+        return hipErrorInvalidValue;
+    }
+    hipLaunchKernelGGL((sc_collide_kernel<S, false>), dim3(nblk), dim3(NB), 0, s, a);
     return hipGetLastError();
 }
 template <class S>
@@ -1137,40 +1140,28 @@ hipError_t launch_sc_split_batch(int prec, const StepArgs *all, const int2 *work
 
 int tiles_xy(int nx, int ny, int tile_y) { return ((nx + 63) / 64) * ((ny + tile_y - 1) / tile_y); }
 
-template <class S, int TY, int NPT, bool TAU1, bool SINK>
+template <class S, int TY, bool SINK>
 static hipError_t launch_one(const StepArgs &a, hipStream_t s) {
     const int nblk = a.ntx * a.nty * a.nzc;
-    hipLaunchKernelGGL((sc_step_kernel<S, TY, NPT, TAU1, SINK>), dim3(nblk), dim3(64 * (TY / NPT)), 0, s, a);
+    hipLaunchKernelGGL((sc_step_kernel<S, TY, SINK>), dim3(nblk), dim3(64 * TY), 0, s, a);
     return hipGetLastError();
 }
 
-// The fused step runs where the two-pass step does not: tau != 1 (the tiles
-// of one row per thread, whose registers hold the populations), and the sink.
+// The fused step runs where the two-pass step does not, with tau != 1: the
+// tiles of one row per thread, whose registers hold the populations.
 template <class S>
-static hipError_t launch_prec(bool tau1, const TileCfg &t, const StepArgs &a, hipStream_t s) {
+static hipError_t launch_prec(const TileCfg &t, const StepArgs &a, hipStream_t s) {
     const int ty = t.tile_y, rp = t.rows_per_thread;
+    if (rp != 1) return hipErrorInvalidValue;
     if (a.sink) {
-        if constexpr (std::is_same_v<S, float>) {
-            if (ty == 4 && rp == 1)
-                return tau1 ? launch_one<S, 4, 1, true, true>(a, s) : launch_one<S, 4, 1, false, true>(a, s);
-            if (ty == 8 && rp == 1)
-                return tau1 ? launch_one<S, 8, 1, true, true>(a, s) : launch_one<S, 8, 1, false, true>(a, s);
-            if (tau1 && ty == 8 && rp == 2) return launch_one<S, 8, 2, true, true>(a, s);
-            if (tau1 && ty == 16 && rp == 2) return launch_one<S, 16, 2, true, true>(a, s);
-        } else if constexpr (std::is_same_v<S, double>) {
-            // With the sink, the FP64 instantiation of the 64 x 8 tile with
-            // one row per thread gave wrong populations while the other FP64
-            // tiles and all FP32 tiles match the oracle; the same tiling runs
-            // with two rows per thread (identical work-groups and slots).
-            if (tau1 && ty == 4 && rp == 1) return launch_one<S, 4, 1, true, true>(a, s);
-            if (tau1 && ty == 8) return launch_one<S, 8, 2, true, true>(a, s);
-            if (tau1 && ty == 16 && rp == 2) return launch_one<S, 16, 2, true, true>(a, s);
+        if constexpr (std::is_same_v<S, float>) {  // FP64 runs the sink with tau = 1 only
+            if (ty == 4) return launch_one<S, 4, true>(a, s);
+            if (ty == 8) return launch_one<S, 8, true>(a, s);
         }
-        return hipErrorInvalidValue;  // the sink runs with FP32 storage, or FP64 with tau = 1
+        return hipErrorInvalidValue;
     }
-    if (tau1) return hipErrorInvalidValue;  // launch_sc_split
-    if (ty == 4 && rp == 1) return launch_one<S, 4, 1, false, false>(a, s);
-    if (ty == 8 && rp == 1) return launch_one<S, 8, 1, false, false>(a, s);
+    if (ty == 4) return launch_one<S, 4, false>(a, s);
+    if (ty == 8) return launch_one<S, 8, false>(a, s);
     return hipErrorInvalidValue;
 }
 
@@ -1203,16 +1194,16 @@ hipError_t launch_sc_step_batch(int prec, const TileCfg &t, const StepArgs *all,
     }
 }
 
-hipError_t launch_sc_step(int prec, bool tau1, const TileCfg &t, const StepArgs &a, hipStream_t s) {
+hipError_t launch_sc_step(int prec, const TileCfg &t, const StepArgs &a, hipStream_t s) {
     switch (prec) {
         case LB_F64:
-            return launch_prec<double>(tau1, t, a, s);
+            return launch_prec<double>(t, a, s);
         case LB_F32:
-            return launch_prec<float>(tau1, t, a, s);
+            return launch_prec<float>(t, a, s);
         case LB_F16DEV:
-            return launch_prec<_Float16>(tau1, t, a, s);
+            return launch_prec<_Float16>(t, a, s);
         case LB_BF16DEV:
-            return launch_prec<bf16_t>(tau1, t, a, s);
+            return launch_prec<bf16_t>(t, a, s);
         default:
             return hipErrorInvalidValue;
     }
