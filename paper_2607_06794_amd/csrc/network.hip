@@ -5,13 +5,14 @@
 //
 // The network is small next to the lattice (a few thousand beads per
 // deposit), so the solve is latency-bound, not bandwidth-bound:
-//  * neighbours: one thread per bead scans every bead through LDS tiles in
-//    index order (a deterministic, ascending neighbour list per bead);
+//  * neighbours: one wavefront per bead scans every bead in index order (a
+//    deterministic, ascending neighbour list per bead);
 //  * Kirchhoff: a Jacobi-preconditioned conjugate-gradient solve in one
-//    work-group -- the search direction in LDS (up to NET_LDS_P beads), the
-//    other vectors in L2; each iteration costs one sparse product and two
-//    work-group reductions in a fixed order, and the loop is bounded by the
-//    caller's iteration limit.
+//    work-group; each iteration costs one sparse product and two work-group
+//    reductions in a fixed order, and the loop is bounded by the caller's
+//    iteration limit.  Up to NET_ROWS beads the rows are sorted by length and
+//    their vectors kept in registers; beyond, the vectors live in L2 and the
+//    search direction in LDS (up to NET_LDS_P beads).
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -97,41 +98,248 @@ __device__ inline void wg_sum(double (&v)[NV], double *sh) {
     }
 }
 
-// beads j != i with 0 < r_ij^2 < r_c^2, ascending j; deg may exceed
-// NET_DEG (only the first NET_DEG are stored; the host reports the excess)
+// r_ij^2 = (dx^2 + dy^2) + dz^2 without contraction: the edge decision is
+// taken exactly as stated
+__device__ inline double net_r2(const double *pos, int i, int j) {
+    const double dx = pos[3 * j] - pos[3 * i], dy = pos[3 * j + 1] - pos[3 * i + 1], dz = pos[3 * j + 2] - pos[3 * i + 2];
+    return __dadd_rn(__dadd_rn(__dmul_rn(dx, dx), __dmul_rn(dy, dy)), __dmul_rn(dz, dz));
+}
+
+// Beads j != i with 0 < r_ij^2 < r_c^2, ascending j; deg may exceed NET_DEG
+// (only the first NET_DEG are stored; the host reports the excess).  One
+// wavefront per bead, 64 candidates at a time, compacted by ballots: with one
+// thread per bead the scan was a chain of n tests on n / 256 work-groups
+// (314 us for 3 300 beads; now 12).  ROWS: the lists of the row-sorted solve,
+// as 16-bit indices (the conductances follow when the rows are laid out).
+template <bool ROWS>
 __global__ void __launch_bounds__(NET_TB) net_edges_kernel(NetArgs a) {
-    __shared__ double tile[NET_TB * 3];
-    const int i = blockIdx.x * NET_TB + int(threadIdx.x);
-    const bool own = i < a.n;
-    const double px = own ? a.pos[3 * i] : 0.0, py = own ? a.pos[3 * i + 1] : 0.0, pz = own ? a.pos[3 * i + 2] : 0.0;
+    const int i = blockIdx.x * (NET_TB / 64) + int(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (i >= a.n) return;  // uniform per wavefront
     int k = 0;
-    for (int j0 = 0; j0 < a.n; j0 += NET_TB) {
-        const int j = j0 + int(threadIdx.x);
-        __syncthreads();
-        if (j < a.n) {
-            tile[3 * threadIdx.x] = a.pos[3 * j];
-            tile[3 * threadIdx.x + 1] = a.pos[3 * j + 1];
-            tile[3 * threadIdx.x + 2] = a.pos[3 * j + 2];
-        }
-        __syncthreads();
-        const int m = min(NET_TB, a.n - j0);
-        if (own) {
-            for (int q = 0; q < m; ++q) {
-                const double dx = tile[3 * q] - px, dy = tile[3 * q + 1] - py, dz = tile[3 * q + 2] - pz;
-                // (dx^2 + dy^2) + dz^2 without contraction: the edge decision
-                // is taken exactly as stated
-                const double r2 = __dadd_rn(__dadd_rn(__dmul_rn(dx, dx), __dmul_rn(dy, dy)), __dmul_rn(dz, dz));
-                if (r2 > 0.0 && r2 < a.rc2) {
-                    if (k < NET_DEG) {
-                        a.nbr[size_t(i) * NET_DEG + k] = j0 + q;
-                        a.g[size_t(i) * NET_DEG + k] = 1.0 / sqrt(r2);
-                    }
-                    ++k;
-                }
+    for (int j0 = 0; j0 < a.n; j0 += 64) {
+        const int j = min(j0 + lane, a.n - 1);
+        const double r2 = net_r2(a.pos, i, j);
+        const bool hit = j0 + lane < a.n && r2 > 0.0 && r2 < a.rc2;
+        const uint64_t m = __ballot(hit);
+        const int at = k + __popcll(m & ((uint64_t(1) << lane) - 1));
+        if (hit && at < NET_DEG) {
+            if constexpr (ROWS) {
+                reinterpret_cast<uint16_t *>(a.nbr)[size_t(i) * NET_DEG + at] = uint16_t(j);
+            } else {
+                a.nbr[size_t(i) * NET_DEG + at] = j;
+                a.g[size_t(i) * NET_DEG + at] = 1.0 / sqrt(r2);
             }
         }
+        k += __popcll(m);
     }
-    if (own) a.deg[i] = k;
+    if (lane == 0) a.deg[i] = k;
+}
+
+// ---------------------------------------------------------------------------
+// Networks of up to NET_ROWS beads: the rows sorted by degree (ties in bead
+// order), so that the 64 rows of a wavefront have nearly equal lengths, and
+// laid out edge-major: conductance k of the row of rank q at g[k n + q], eight
+// times its neighbour's bead index (the byte offset of a vector element) the
+// 16-bit half k & 1 of cols[(k / 2) n + q].  A wavefront then reads 64 rows'
+// next edges from consecutive addresses.  Past its end a row is filled with
+// edges of no conductance to bead 0, so the product needs no bounds.
+// ---------------------------------------------------------------------------
+constexpr int NET_ROWS = 8192;
+
+__device__ inline uint32_t *net_cols(const NetArgs &a) {
+    // the second half of the neighbour array; the 16-bit lists are its first
+    return reinterpret_cast<uint32_t *>(a.nbr) + size_t(a.n) * (NET_DEG / 2);
+}
+
+// one wavefront per bead: its rank, then its row
+__global__ void __launch_bounds__(NET_TB) net_rows_kernel(NetArgs a) {
+    const int i = blockIdx.x * (NET_TB / 64) + int(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (i >= a.n) return;  // uniform per wavefront
+    const int di = min(a.deg[i], NET_DEG);
+    int before = 0;
+    for (int j0 = 0; j0 < a.n; j0 += 64) {
+        const int j = j0 + lane, dj = j < a.n ? min(a.deg[j], NET_DEG) : -1;
+        before += __popcll(__ballot(dj > di || (dj == di && j < i)));
+    }
+    if (lane == 0) a.cls[before] = i;  // the bead of each rank
+    const int j = lane < di ? reinterpret_cast<const uint16_t *>(a.nbr)[size_t(i) * NET_DEG + lane] : 0;
+    a.g[size_t(lane) * a.n + before] = lane < di ? 1.0 / sqrt(net_r2(a.pos, i, j)) : 0.0;
+    reinterpret_cast<uint16_t *>(net_cols(a))[(size_t(lane >> 1) * a.n + before) * 2 + (lane & 1)] = uint16_t(8 * j);
+}
+
+// v plus its neighbour N lanes on within each row of 16 (rotated); over N = 8,
+// 4, 2, 1 every lane gets the same sum of its row
+template <int N>
+__device__ inline double row_add(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x120 + N, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x120 + N, 0xF, 0xF, true);
+    return v + __hiloint2double(hi, lo);
+}
+__device__ inline double row_sum(double v) { return row_add<1>(row_add<2>(row_add<4>(row_add<8>(v)))); }
+__device__ inline double lane_value(double v, int lane) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                            __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
+// Work-group sums of v[q] over 16 wavefronts in a fixed order, the same in
+// every thread.  One barrier: sh (64 doubles per value) must not be the array
+// of the previous sum, whose readers may still be at it.
+template <int NV>
+__device__ inline void group_sum(double (&v)[NV], double *sh) {
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+        v[q] = row_sum(v[q]);
+        if ((l & 15) == 0) sh[q * 64 + w * 4 + (l >> 4)] = v[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+        const double t = row_sum(sh[q * 64 + l]);
+        v[q] = (lane_value(t, 0) + lane_value(t, 16)) + (lane_value(t, 32) + lane_value(t, 48));
+    }
+}
+
+// Potentials, node currents and the current leaving the source, as
+// net_solve_kernel below, in one work-group whose thread t owns the rows of
+// rank t, t + 1024, ...: their vectors stay in registers (the potentials and
+// the search direction, which every neighbour reads, in LDS) and the matrix
+// streams from L2 coalesced.  Bound by one CU's throughput on that stream and
+// on the LDS gather: per wavefront and edge about 10 + 12 cycles, 0.55 MB and
+// 860 gathers per iteration for 3 300 beads with 55 000 directed edges.  There
+// a call takes 2.8 ms (9.8 us per iteration) against 7.5 ms with the vectors
+// in L2 and rows of unequal length side by side; 8 140 beads 11.6 against
+// 27.4 ms.
+template <int R>
+__global__ void __launch_bounds__(NET_CG) net_rows_solve_kernel(NetArgs a) {
+    __shared__ double sh[3][128];
+    extern __shared__ double P[];
+    const int n = a.n, t = threadIdx.x;
+    double *X = P + n;  // the potentials by rank, each touched by its owner only
+    const uint32_t *cols = net_cols(a);
+    if (t < 4) a.cnt[t] = 0;
+    int row[R], bead[R], dk[R];
+    bool fr[R];
+    double r[R], p[R], dg[R], q[R];
+    double s0[2] = {0.0, 0.0};  // r.z, r.r
+    int maxdeg = 0, nsrc = 0, nsnk = 0, dsum = 0;
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < R; ++s) {
+        const int rk = t + s * NET_CG;
+        const bool have = rk < n;
+        row[s] = min(rk, n - 1);
+        bead[s] = a.cls[row[s]];
+        const int d = have ? a.deg[bead[s]] : 0;
+        dk[s] = min(d, NET_DEG);
+        const int ci = net_class(a.pos[3 * bead[s]], a);
+        fr[s] = have && ci == 0;
+        double b = 0.0;
+        dg[s] = 0.0;
+        for (int k = 0; k < dk[s]; ++k) {
+            const uint32_t c = cols[size_t(k >> 1) * n + row[s]];
+            const int j = (k & 1 ? int(c >> 16) : int(c & 0xFFFFu)) >> 3;
+            const double gk = a.g[size_t(k) * n + row[s]];
+            dg[s] += gk;
+            if (net_class(a.pos[3 * j], a) == 1) b += gk * a.dV;
+        }
+        if (have) X[row[s]] = ci == 1 ? a.dV : 0.0;
+        r[s] = fr[s] ? b : 0.0;
+        p[s] = fr[s] && dg[s] > 0.0 ? r[s] / dg[s] : 0.0;
+        if (have) P[bead[s]] = p[s];
+        s0[0] += r[s] * p[s];
+        s0[1] += r[s] * r[s];
+        maxdeg = max(maxdeg, d);
+        nsrc += have && ci == 1;
+        nsnk += have && ci == 2;
+        dsum += dk[s];  // the stored edges (a degree above NET_DEG is rejected)
+    }
+    atomicMax(&a.cnt[0], maxdeg);
+    atomicAdd(&a.cnt[1], nsrc);
+    atomicAdd(&a.cnt[2], nsnk);
+    atomicAdd(&a.cnt[3], dsum);
+    group_sum(s0, sh[0]);  // its barrier also publishes P
+    double rz = s0[0], rr = s0[1];
+    const double bb = s0[1], stop2 = a.tol * a.tol * bb;
+    int it = 0;
+    while (it < a.max_iter && rr > stop2) {
+        double pq[1] = {0.0};
+#pragma unroll
+        for (int s = 0; s < R; ++s) {
+            double off = 0.0;
+            const int width = __builtin_amdgcn_readfirstlane(dk[s]);  // the first lane's row is the longest
+            for (int k = 0; k < width; k += 4) {  // (eight at a time: 3.05 ms, the rows' ends cost more)
+                uint32_t c[2];
+                double g[4];
+#pragma unroll
+                for (int e = 0; e < 2; ++e) c[e] = cols[size_t((k >> 1) + e) * n + row[s]];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) g[e] = a.g[size_t(k + e) * n + row[s]];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const uint32_t at = e & 1 ? c[e >> 1] >> 16 : c[e >> 1] & 0xFFFFu;
+                    off += g[e] * *reinterpret_cast<const double *>(reinterpret_cast<const char *>(P) + at);
+                }
+            }
+            q[s] = fr[s] ? dg[s] * p[s] - off : 0.0;
+            pq[0] += p[s] * q[s];
+        }
+        group_sum(pq, sh[1]);
+        if (!(pq[0] > 0.0)) break;  // same value in every thread
+        const double alpha = rz / pq[0];
+        double s1[2] = {0.0, 0.0};
+#pragma unroll
+        for (int s = 0; s < R; ++s) {
+            if (!fr[s]) continue;
+            r[s] -= alpha * q[s];
+            X[row[s]] += alpha * p[s];
+            q[s] = dg[s] > 0.0 ? r[s] / dg[s] : 0.0;  // z
+            s1[0] += r[s] * q[s];
+            s1[1] += r[s] * r[s];
+        }
+        group_sum(s1, sh[2]);
+        const double beta = rz > 0.0 ? s1[0] / rz : 0.0;
+        rz = s1[0];
+        rr = s1[1];
+#pragma unroll
+        for (int s = 0; s < R; ++s)
+            if (fr[s]) {
+                p[s] = q[s] + beta * p[s];
+                P[bead[s]] = p[s];
+            }
+        __syncthreads();  // the next product reads every bead's p
+        ++it;
+    }
+    __syncthreads();
+    // Eq. 15 and the current leaving the source electrode
+#pragma unroll
+    for (int s = 0; s < R; ++s)
+        if (t + s * NET_CG < n) {
+            P[bead[s]] = X[row[s]];
+            a.V[bead[s]] = X[row[s]];
+        }
+    __syncthreads();
+    double st[1] = {0.0};
+#pragma unroll
+    for (int s = 0; s < R; ++s) {
+        const bool src = t + s * NET_CG < n && net_class(a.pos[3 * bead[s]], a) == 1;
+        const double xs = X[row[s]];
+        double sum = 0.0;
+        for (int k = 0; k < dk[s]; ++k) {
+            const uint32_t c = cols[size_t(k >> 1) * n + row[s]];
+            const int j = (k & 1 ? int(c >> 16) : int(c & 0xFFFFu)) >> 3;
+            const double e = a.g[size_t(k) * n + row[s]] * (xs - P[j]);
+            sum += fabs(e);
+            if (src && net_class(a.pos[3 * j], a) != 1) st[0] += e;
+        }
+        if (t + s * NET_CG < n) a.I[bead[s]] = 0.5 * sum;
+    }
+    group_sum(st, sh[0]);
+    if (t == 0) {
+        a.out[0] = st[0];
+        a.out[1] = bb > 0.0 ? sqrt(rr / bb) : 0.0;
+        a.out[2] = double(it);
+    }
 }
 
 // Networks of up to NET_LDS_P beads keep the search direction p in LDS for
@@ -280,14 +488,31 @@ __global__ void rod_beads_kernel(const double *rods, int n_rods, int nb, double 
 
 hipError_t launch_net_edges(const NetArgs &a, hipStream_t s) {
     if (a.n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(net_edges_kernel, dim3((a.n + NET_TB - 1) / NET_TB), dim3(NET_TB), 0, s, a);
+    const int nblk = (a.n + NET_TB / 64 - 1) / (NET_TB / 64);
+    if (a.n <= NET_ROWS) {
+        hipLaunchKernelGGL(net_edges_kernel<true>, dim3(nblk), dim3(NET_TB), 0, s, a);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(net_rows_kernel, dim3(nblk), dim3(NET_TB), 0, s, a);
+    } else {
+        hipLaunchKernelGGL(net_edges_kernel<false>, dim3(nblk), dim3(NET_TB), 0, s, a);
+    }
     return hipGetLastError();
 }
 
 hipError_t launch_net_solve(const NetArgs &a, hipStream_t s) {
     if (a.n <= 0) return hipSuccess;
-    if (a.n <= NET_LDS_P)
-        hipLaunchKernelGGL(net_solve_kernel<true>, dim3(1), dim3(NET_CG), size_t(a.n) * sizeof(double), s, a);
+    const size_t lds = size_t(a.n) * sizeof(double), lds2 = 2 * lds;
+    if (a.n <= NET_CG)
+        hipLaunchKernelGGL(net_rows_solve_kernel<1>, dim3(1), dim3(NET_CG), lds2, s, a);
+    else if (a.n <= 2 * NET_CG)
+        hipLaunchKernelGGL(net_rows_solve_kernel<2>, dim3(1), dim3(NET_CG), lds2, s, a);
+    else if (a.n <= 4 * NET_CG)
+        hipLaunchKernelGGL(net_rows_solve_kernel<4>, dim3(1), dim3(NET_CG), lds2, s, a);
+    else if (a.n <= NET_ROWS)
+        hipLaunchKernelGGL(net_rows_solve_kernel<8>, dim3(1), dim3(NET_CG), lds2, s, a);
+    else if (a.n <= NET_LDS_P)
+        hipLaunchKernelGGL(net_solve_kernel<true>, dim3(1), dim3(NET_CG), lds, s, a);
     else
         hipLaunchKernelGGL(net_solve_kernel<false>, dim3(1), dim3(NET_CG), 0, s, a);
     return hipGetLastError();
