@@ -93,7 +93,7 @@ static int rod_nblk(const lb_params &p) { return rod_shell_cap(p) / 256; }
 
 // Observable scratch: droplet column scan, then deposit binning and graph.
 struct ObsLayout {
-    size_t col_h, col_wet, line_x, line_y, out, bins, sval, dep_out, ens_acc, ens_out, labels, graph, map, probe_xyz,
+    size_t col_h, col_wet, line_x, line_y, out, adj, dep_out, ens_acc, ens_out, labels, graph, map, probe_xyz,
         probe_p, total;
 };
 static ObsLayout obs_layout(const lb_params *p) {
@@ -110,10 +110,8 @@ static ObsLayout obs_layout(const lb_params *p) {
     o = align256(o + size_t(p->ny) * sizeof(double));
     l.out = o;
     o = align256(o + 16 * sizeof(double));
-    l.bins = o;
-    o = align256(o + nr * 4 * DEP_NB * sizeof(int16_t));
-    l.sval = o;
-    o = align256(o + nr * sizeof(double));
+    l.adj = o;
+    o = align256(o + nr * (LB_MAX_RODS / 64) * sizeof(unsigned long long));
     l.dep_out = o;
     o = align256(o + 6 * DEP_MAXBIN * sizeof(double));
     l.ens_acc = o;
@@ -875,8 +873,7 @@ static int deposit_args(lb_ctx *c, const lb_deposit_spec *s, DepArgs &d) {
     d.r_contact = s->r_contact;
     d.x_src = s->x_src;
     d.x_snk = s->x_snk;
-    d.bins = reinterpret_cast<int16_t *>(c->obs + l.bins);
-    d.sval = reinterpret_cast<double *>(c->obs + l.sval);
+    d.adj = reinterpret_cast<unsigned long long *>(c->obs + l.adj);
     d.out = reinterpret_cast<double *>(c->obs + l.dep_out);
     d.labels = reinterpret_cast<int32_t *>(c->obs + l.labels);
     d.graph = reinterpret_cast<int32_t *>(c->obs + l.graph);

@@ -196,8 +196,8 @@ struct ObsArgs {
     int64_t fs;
     int nx, ny, nz, ix, iy;
     double rho_ref[2];
-    double *col_h;   // [ny][nx] column heights
-    int *col_wet;    // [ny][nx] wet nodes per column
+    double *col_h;   // largest column height per work-group of the scan
+    int *col_wet;    // wet nodes per work-group of the scan
     double *line_x;  // [nx] colour on plane z = 1 along row iy
     double *line_y;  // [ny] colour on plane z = 1 along column ix
     double *out;     // h, r_x, r_y, theta_x, theta_y, wet nodes
@@ -209,8 +209,7 @@ struct DepArgs {
     int n_rods, nb, nbx, nby;
     int nx, ny, nz, px, py, pz;
     double half, xc, yc, strip_x, strip_y, r_contact, x_src, x_snk;
-    int16_t *bins;   // [n_rods][4][DEP_NB]: bead bin x, bead bin y, segment bin x, segment bin y (-1 outside)
-    double *sval;    // [n_rods] 2 e_x^2 - 1
+    unsigned long long *adj;  // [n_rods][LB_MAX_RODS / 64] contact bitmap
     double *out;     // axial: count, S, segments [3][DEP_MAXBIN]; then transverse, same
     int32_t *labels; // [n_rods] cluster label (smallest rod index of the cluster)
     int32_t *graph;  // n_rods, edges, largest cluster, spanning
@@ -307,7 +306,7 @@ struct SurLattice {
     int64_t fs;
     double rref[2], tau[2], G, g[3];
     const double *psi_tab;  // [16][2] ghost pseudo-densities per material id (device)
-    double *psi;            // [2][nx ny nz] scratch
+    double *psi;            // scratch: psi_k [2][nx ny nz], a restriction's momenta in rows 2..4
 };
 hipError_t launch_restrict(int prec, const void *f, const SurLattice &L, int D, int H, int W, float *outf,
                            uint16_t *outb, hipStream_t s);

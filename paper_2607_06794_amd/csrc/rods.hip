@@ -1022,17 +1022,20 @@ __global__ void __launch_bounds__(RB) rod_update_kernel(RodBatch bt, int init) {
     block_sums(acc, sh, part_slot(a.part_upd, a, r, blockIdx.x), init != 0);
 }
 
-// totals over rods in a fixed order: solid ledger [2], rod momentum M V [3]
-__global__ void rod_sums_kernel(RodArgs a, double *out) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// totals over rods in a fixed order (one wavefront: strided over its lanes,
+// then a butterfly): solid ledger [2], rod momentum M V [3]
+__global__ void __launch_bounds__(64) rod_sums_kernel(RodArgs a, double *out) {
     double s[5] = {0, 0, 0, 0, 0};
-    for (int r = 0; r < a.n_rods; ++r) {
+    for (int r = threadIdx.x; r < a.n_rods; r += 64) {
         const double *rod = a.rods + r * ROD_STRIDE;
         s[0] += rod[ROD_SOLID];
         s[1] += rod[ROD_SOLID + 1];
         for (int q = 0; q < 3; ++q) s[2 + q] += a.mass * rod[ROD_V + q];
     }
-    for (int q = 0; q < 5; ++q) out[q] = s[q];
+    for (int q = 0; q < 5; ++q) {
+        s[q] = wave_sum_d(s[q]);
+        if (threadIdx.x == 0) out[q] = s[q];
+    }
 }
 
 // ---------------------------------------------------------------------------
