@@ -9,7 +9,7 @@
 //   dgrad    dx[q, c] = sum_{t, o} g[q - o_t, o] w[t, c, o],  g = dy (y > 0)
 //            M = positions, N = input channels, K = 27 x output channels
 //   wgrad    dw[t, c, o] += sum_p x[p + o_t, c] g[p, o]
-//            M = 27 x input channels, N = output channels, K = positions
+//            M = input channels, N = output channels of one tap, K = positions
 // A work-group of four wavefronts computes a 256 x 32, 128 x 64 or 128 x 128
 // tile (chosen by N), each wavefront 64 x 32 or 64 x 64; K advances in steps
 // of 32 through two LDS buffers.
@@ -446,196 +446,155 @@ __global__ void relu_grad_kernel(const float *dy, const uint16_t *y, int64_t n, 
 }
 
 
-// Weight gradient as one GEMM over all taps: C[(t, c)][o] = sum_p x[p + o_t][c]
-// g[p][o], M = 27 cin rows in dw's own (tap-major) order, N = cout, K = the
-// positions of one chunk; chunks add their partial sums with FP32 atomics.
-// Operands are staged K-contiguous ([row][position]): each thread loads 8
-// channels of one position (16 bytes) and scatters them down a column.  A
-// g tile serves every tap of the row tile.
-template <int BM, int BN, int WM, int WN>
-__global__ void __launch_bounds__(256) conv_wgrad_kernel(ConvArgs a, const uint16_t *g, float *dw, int chunk) {
-    constexpr int MB = BM / WM / 32, NB = BN / WN / 32;
-    static_assert(WM * WN == 4 && MB * WM * 32 == BM && NB * WN * 32 == BN, "tile shape");
-    constexpr int XL = BM / 64, GL = BN / 64;  // loads per thread (0: the first 4 BM or 4 BN threads)
-    constexpr int XLT = XL > 0 ? XL : 1, GLT = GL > 0 ? GL : 1;
-    __shared__ __attribute__((aligned(16))) uint16_t Xs[2][BM * LDK];
-    __shared__ __attribute__((aligned(16))) uint16_t Gs[2][BN * LDK];
-    const int tid = threadIdx.x, wv = tid >> 6, l = tid & 63;
-    const int P = a.D * a.H * a.W, HW = a.H * a.W;
-    const int cin = a.c1 + a.c2;
-    const int M = 27 * cin;
-    const int m0 = blockIdx.y * BM, n0 = blockIdx.z * BN;
-    const int wm = (wv / WN) * MB * 32, wn = (wv % WN) * NB * 32;
-    const int pbeg = blockIdx.x * chunk, pend = min(P, pbeg + chunk);
-    const int pl = tid & 31;
-    const int H2 = a.H >> 1, W2 = a.W >> 1;
-
-    // x loads: rows m0 + 8 rg .. + 7 (tap t, channels c .. c + 7), position pl
-    int xc[XLT], xr[XLT], xdz[XLT], xdy[XLT], xdx[XLT];
-    bool xon[XLT];
-#pragma unroll
-    for (int j = 0; j < XLT; ++j) {
-        const int rg = (tid >> 5) + 8 * j;
-        xr[j] = 8 * rg;
-        const int r = m0 + xr[j];
-        xon[j] = (XL > 0 || tid < 4 * BM) && r < M;
-        const int t = xon[j] ? r / cin : 13;
-        xc[j] = r % cin;
-        xdz[j] = t / 9 - 1;
-        xdy[j] = (t / 3) % 3 - 1;
-        xdx[j] = t % 3 - 1;
-    }
-    int go[GLT];
-    bool gon[GLT];
-#pragma unroll
-    for (int j = 0; j < GLT; ++j) {
-        go[j] = 8 * ((tid >> 5) + 8 * j);
-        gon[j] = (GL > 0 || tid < 4 * BN) && n0 + go[j] < a.cout;
-    }
-    // this thread's position, advanced by BK per stage
-    int cp = pbeg + pl, cw = cp % a.W, chh = (cp / a.W) % a.H, cd = cp / HW;
-
-    uint4 rx[XLT], rg[GLT];
-    bool xok[XLT], gok[GLT];
-    auto load = [&]() {
-        const bool valid = cp < pend;
-#pragma unroll
-        for (int j = 0; j < XLT; ++j) {
-            const int qd = cd + xdz[j], qh = chh + xdy[j], qw = cw + xdx[j];
-            const bool ok = valid && xon[j] && unsigned(qd) < unsigned(a.D) && unsigned(qh) < unsigned(a.H) &&
-                            unsigned(qw) < unsigned(a.W);
-            const int c = xc[j];
-            const uint16_t *src;
-            if (c < a.c1)
-                src = a.up1 ? a.x1 + (((qd >> 1) * H2 + (qh >> 1)) * W2 + (qw >> 1)) * a.c1 + c
-                            : a.x1 + ((qd * a.H + qh) * a.W + qw) * a.c1 + c;
-            else
-                src = a.x2 + ((qd * a.H + qh) * a.W + qw) * a.c2 + (c - a.c1);
-            rx[j] = *reinterpret_cast<const uint4 *>(ok ? src : a.x1);
-            xok[j] = ok;
-        }
-#pragma unroll
-        for (int j = 0; j < GLT; ++j) {
-            const bool ok = valid && gon[j];
-            rg[j] = *reinterpret_cast<const uint4 *>(ok ? g + cp * a.cout + n0 + go[j] : g);
-            gok[j] = ok;
-        }
-    };
-    auto advance = [&]() {
-        cp += BK;
-        cw += BK;
-        while (cw >= a.W) {
-            cw -= a.W;
-            if (++chh >= a.H) {
-                chh = 0;
-                ++cd;
-            }
-        }
-    };
-    auto store = [&](int buf) {
-#pragma unroll
-        for (int j = 0; j < XLT; ++j) {
-            if (!(XL > 0 || tid < 4 * BM)) continue;
-            const uint4 w = xok[j] ? rx[j] : make_uint4(0, 0, 0, 0);
-            const uint16_t *v = reinterpret_cast<const uint16_t *>(&w);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) Xs[buf][(xr[j] + e) * LDK + pl] = v[e];
-        }
-#pragma unroll
-        for (int j = 0; j < GLT; ++j) {
-            if (!(GL > 0 || tid < 4 * BN)) continue;
-            const uint4 w = gok[j] ? rg[j] : make_uint4(0, 0, 0, 0);
-            const uint16_t *v = reinterpret_cast<const uint16_t *>(&w);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) Gs[buf][(go[j] + e) * LDK + pl] = v[e];
-        }
-    };
-
-    v16f acc[MB][NB];
-#pragma unroll
-    for (int i = 0; i < MB; ++i)
-#pragma unroll
-        for (int j = 0; j < NB; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-
-    const int nst = (pend - pbeg + BK - 1) / BK;
-    load();
-    store(0);
-    __syncthreads();
-    for (int st = 0; st < nst; ++st) {
-        const int cur = st & 1;
-        if (st + 1 < nst) {
-            advance();
-            load();
-        }
-#pragma unroll
-        for (int kk = 0; kk < BK; kk += 16) {
-            v8bf fa[MB], fb[NB];
-#pragma unroll
-            for (int i = 0; i < MB; ++i)
-                fa[i] = *reinterpret_cast<const v8bf *>(&Xs[cur][(wm + 32 * i + (l & 31)) * LDK + kk + 8 * (l >> 5)]);
-#pragma unroll
-            for (int j = 0; j < NB; ++j)
-                fb[j] = *reinterpret_cast<const v8bf *>(&Gs[cur][(wn + 32 * j + (l & 31)) * LDK + kk + 8 * (l >> 5)]);
-#pragma unroll
-            for (int i = 0; i < MB; ++i)
-#pragma unroll
-                for (int j = 0; j < NB; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
-        }
-        if (st + 1 < nst) store(cur ^ 1);
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < MB; ++i)
-#pragma unroll
-        for (int j = 0; j < NB; ++j) {
-            const int col = n0 + wn + 32 * j + (l & 31);
-            if (col >= a.cout) continue;
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int row = m0 + wm + 32 * i + 8 * (e >> 2) + 4 * (l >> 5) + (e & 3);
-                if (row < M) atomicAdd(dw + int64_t(row) * a.cout + col, acc[i][j][e]);
-            }
-        }
+// Weight gradient dw[t, c, o] += sum_p x[p + o_t, c] g[p, o]: a work-group owns
+// 32 input channels, 32 output channels, the nine taps of one dz and a share of
+// the volume's bricks of 4 x 8 x 8 positions; each wavefront takes one plane of
+// a brick and keeps the nine taps' 32 x 32 sums in registers.  Per brick the
+// input halo of the four shifted planes and g are staged in LDS once, position
+// by position as they lie in memory; the MFMA operands need eight positions of
+// one channel per lane, which the transposing LDS read delivers
+// (ds_read_b64_tr_b16: lane i of 16 gets element i % 4 of lanes i / 4 + 4 q,
+// q = 0..3, so four positions of its channel).
+//
+// Bound by the LDS reads (one KB per tap and 16 positions against one MFMA)
+// and by the FP32 atomics into dw: 200 G/s with every work-group adding to the
+// same addresses, which is why a work-group holds nine taps and not all 27
+// (three times the sums for the same number of work-groups). The 15
+// layers of the 128 x 64 x 32 canvas take 0.41 ms (0.34 without the atomics)
+// against 1.02 ms for a GEMM over (tap, channel) rows that staged x again for
+// each row tile, transposed it with 2-byte LDS writes and summed the bias in a
+// pass of its own; the 64 + 32 -> 32 layer 65 us (660 TFLOP/s) against 194.
+//
+typedef short v4s __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ v8bf read_tr(const char *p, int step) {
+    typedef __attribute__((address_space(3))) v4s lds_v4s;
+    const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s *)(p));
+    const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s *)(p + step));
+    return __builtin_bit_cast(v8bf, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-// bias gradient: db[o] += sum_p g[p, o] over a chunk of positions.  Each
-// thread reads 8 channels (16 bytes) of one position per iteration, 256 /
-// (channel groups) positions side by side; the sums are combined in LDS and
-// added with one FP32 atomic per channel and chunk (one thread per channel).
-__global__ void conv_bgrad_kernel(int P, int cout, int chunk, const uint16_t *g, float *db) {
-    __shared__ float part[256][9];
-    const int ng = cout >> 3;  // groups of 8 channels (cout is a multiple of 8)
-    const int pbeg = blockIdx.x * chunk, pend = min(P, pbeg + chunk);
-    const int t = threadIdx.x;
-    for (int g0 = 0; g0 < ng; g0 += 256) {
-        const int gw = min(ng - g0, 256), rows = 256 / gw;
-        const int gi = g0 + t % gw, r = t / gw;
-        float acc[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-        if (r < rows)
-#pragma unroll 8
-            for (int p = pbeg + r; p < pend; p += rows) {
-                const uint4 v = *reinterpret_cast<const uint4 *>(g + int64_t(p) * cout + 8 * gi);
-                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+__global__ void __launch_bounds__(256, 2) conv_wgrad_kernel(ConvArgs a, const uint16_t *g, float *dw, float *db) {
+    constexpr int PS = LDK * 2;  // bytes per position in LDS
+    constexpr int NX = 4 * HLY * HLX, XL = (NX * 4 + 255) / 256, GL = 4;
+    __shared__ __attribute__((aligned(16))) char Xs[(NX + 256) * PS];
+    char *Gs = Xs + NX * PS;
+    const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
+    const int cin = a.c1 + a.c2, c0 = int(blockIdx.y / 3) * 32, dz = int(blockIdx.y % 3) - 1, o0 = blockIdx.z * 32;
+    const int nbx = (a.W + BRX - 1) / BRX, nby = (a.H + BRY - 1) / BRY, nb = nbx * nby * ((a.D + 3) / 4);
+    // this lane's operand address: position row (l % 16) / 4 of its k-group's
+    // four, channels 16 (l / 16 % 2) + 4 (l % 4) .. + 3; k-group l / 32 is the
+    // brick row below
+    const int kr = (l >> 2) & 3, kg = l >> 5, cb = ((l >> 4) & 1) * 32 + (l & 3) * 8;
+    const char *xl = Xs + ((wv * HLY + kg) * HLX + kr) * PS + cb;
+    const char *gl = Gs + ((wv * BRY + kg) * BRX + kr) * PS + cb;
+    v16f acc[9];
+#pragma unroll
+    for (int j = 0; j < 9; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[j][e] = 0.0f;
+    float bsum[8] = {0, 0, 0, 0, 0, 0, 0, 0};  // g over this thread's positions, channels 8 (tid % 4) ..
+    const bool bias = db && blockIdx.y == 0;
+
+    // a thread loads the same eight channels of x and of g everywhere; a
+    // position outside the volume reads the nearest one inside and becomes zero
+    const int cx8 = c0 + 8 * (tid & 3), co8 = o0 + 8 * (tid & 3);
+    const bool skip = cx8 >= a.c1;
+    const int up = !skip && a.up1 ? 1 : 0, cs = skip ? a.c2 : a.c1;
+    const bool con = cx8 < cin, oon = co8 < a.cout;
+    const uint16_t *xs = con ? (skip ? a.x2 + cx8 - a.c1 : a.x1 + cx8) : a.x1, *gs = oon ? g + co8 : g;
+    const int Hs = a.H >> up, Ws = a.W >> up, css = con ? cs : 0, cgs = oon ? a.cout : 0;
+    uint4 hv[XL], gv[GL];
+    unsigned inside = 0;  // bit per load
+    auto fetch = [&](int b) {
+        const int x0 = (b % nbx) * BRX, y0 = (b / nbx % nby) * BRY, z0 = (b / (nbx * nby)) * 4;
+        bool ok[XL + GL];
+#pragma unroll
+        for (int j = 0; j < XL; ++j) {
+            const int hp = min((tid >> 2) + 64 * j, NX - 1);
+            const int z = z0 + hp / (HLY * HLX) + dz, y = y0 + hp / HLX % HLY - 1, x = x0 + hp % HLX - 1;
+            const int zc = min(max(z, 0), a.D - 1), yc = min(max(y, 0), a.H - 1), xc = min(max(x, 0), a.W - 1);
+            ok[j] = con && z == zc && y == yc && x == xc;
+            hv[j] = *reinterpret_cast<const uint4 *>(xs + (((zc >> up) * Hs + (yc >> up)) * Ws + (xc >> up)) * css);
+        }
+#pragma unroll
+        for (int j = 0; j < GL; ++j) {
+            const int z = z0 + j, y = y0 + (tid >> 5), x = x0 + (tid >> 2 & 7);
+            const int zc = min(z, a.D - 1), yc = min(y, a.H - 1), xc = min(x, a.W - 1);
+            ok[XL + j] = oon && z == zc && y == yc && x == xc;
+            gv[j] = *reinterpret_cast<const uint4 *>(gs + ((zc * a.H + yc) * a.W + xc) * cgs);
+        }
+        inside = 0;
+#pragma unroll
+        for (int j = 0; j < XL + GL; ++j) inside |= ok[j] ? 1u << j : 0u;
+    };
+    // this work-group's bricks: a contiguous range
+    const int nw = gridDim.x, b0 = int(int64_t(nb) * blockIdx.x / nw), b1 = int(int64_t(nb) * (blockIdx.x + 1) / nw);
+    fetch(b0);
+    for (int b = b0; b < b1; ++b) {
+        __syncthreads();  // the previous brick's reads are done
+#pragma unroll
+        for (int j = 0; j < XL; ++j) {
+            const int e = tid + 256 * j;
+            if (e < NX * 4)
+                *reinterpret_cast<uint4 *>(Xs + (e >> 2) * PS + 16 * (e & 3)) = keep4(inside >> j & 1u, hv[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < GL; ++j) {
+            gv[j] = keep4(inside >> (XL + j) & 1u, gv[j]);
+            *reinterpret_cast<uint4 *>(Gs + ((tid >> 2) + 64 * j) * PS + 16 * (tid & 3)) = gv[j];
+            if (bias) {
+                const uint32_t w[4] = {gv[j].x, gv[j].y, gv[j].z, gv[j].w};
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    acc[2 * q] += __uint_as_float(w[q] << 16);
-                    acc[2 * q + 1] += __uint_as_float(w[q] & 0xFFFF0000u);
+                    bsum[2 * q] += __uint_as_float(w[q] << 16);
+                    bsum[2 * q + 1] += __uint_as_float(w[q] & 0xFFFF0000u);
                 }
             }
-#pragma unroll
-        for (int q = 0; q < 8; ++q) part[t][q] = acc[q];
-        __syncthreads();
-        // one channel per thread, so one atomic instruction covers the block's channels
-        if (t < 8 * gw) {
-            const int gt = t >> 3, q = t & 7;
-            float tot = 0.0f;
-            for (int rr = 0; rr < rows; ++rr) tot += part[rr * gw + gt][q];
-            atomicAdd(db + 8 * g0 + t, tot);
         }
         __syncthreads();
+        if (b + 1 < b1) fetch(b + 1);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {  // 16 positions: two rows of the wavefront's plane
+            const v8bf fb = read_tr(gl + ks * 16 * PS, 4 * PS);
+#pragma unroll
+            for (int j = 0; j < 9; ++j) {
+                const v8bf fa = read_tr(xl + ((2 * ks + j / 3) * HLX + j % 3) * PS, 4 * PS);
+                acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, fb, acc[j], 0, 0, 0);
+            }
+        }
+    }
+    // the four wavefronts' sums meet in LDS, three taps at a time ([wavefront]
+    // [tap][channel][32]), and go out (LDS float atomics instead took 40 us);
+    // D element e of lane l: row (channel) 8 (e / 4) + 4 (l / 32) + e % 4, column l % 32
+    float *sum = reinterpret_cast<float *>(Xs);
+    float *own = sum + wv * 3072 + 4 * (l >> 5) * 32 + (l & 31);
+#pragma unroll
+    for (int j0 = 0; j0 < 9; j0 += 3) {
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) own[(j * 32 + 8 * (e >> 2) + (e & 3)) * 32] = acc[j0 + j][e];
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 12; ++q) {
+            const int e = tid + 256 * q, row = e >> 5 & 31, col = e & 31;
+            const float v = (sum[e] + sum[3072 + e]) + (sum[6144 + e] + sum[9216 + e]);
+            if (c0 + row < cin && o0 + col < a.cout)
+                atomicAdd(dw + (int64_t(9 * (dz + 1) + j0 + (e >> 10)) * cin + c0 + row) * a.cout + o0 + col, v);
+        }
+    }
+    if (bias) {  // uniform; one atomic instruction per work-group: all add to the same line
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+#pragma unroll
+            for (int o = 4; o < 64; o <<= 1) bsum[q] += __shfl_xor(bsum[q], o, 64);
+            if (l < 4) sum[32 * wv + 8 * l + q] = bsum[q];
+        }
+        __syncthreads();
+        if (tid < 32 && o0 + tid < a.cout)
+            atomicAdd(db + o0 + tid, (sum[tid] + sum[32 + tid]) + (sum[64 + tid] + sum[96 + tid]));
     }
 }
 
@@ -1253,31 +1212,16 @@ hipError_t launch_conv_dgrad(const ConvArgs &a, const uint16_t *g, float *dx, hi
 }
 
 hipError_t launch_conv_wgrad(const ConvArgs &a, const uint16_t *g, float *dw, float *db, hipStream_t s) {
-    const int P = a.D * a.H * a.W;
-    const int M = 27 * (a.c1 + a.c2);
-    // position chunks: the longest (256 to 16384 positions) that still give
-    // about 1024 work-groups for the 256-row tiles (the full-resolution
-    // layers need the occupancy) and about 256 for the others (there the
-    // FP32 atomics of each work-group's tile into dw weigh more)
-    auto launch = [&](auto kern, int BM, int BN) {
-        const unsigned tm = unsigned((M + BM - 1) / BM), tn = unsigned((a.cout + BN - 1) / BN);
-        const int64_t target = BM == 256 ? 1024 : 256;
-        int chunk = 16384;
-        while (chunk > 256 && int64_t((P + chunk - 1) / chunk) * tm * tn < target) chunk /= 2;
-        hipLaunchKernelGGL(kern, dim3(unsigned((P + chunk - 1) / chunk), tm, tn), dim3(256), 0, s, a, g, dw, chunk);
-    };
-    if (a.cout <= 32)
-        launch(conv_wgrad_kernel<256, 32, 4, 1>, 256, 32);
-    else if (a.cout <= 64)
-        launch(conv_wgrad_kernel<128, 64, 2, 2>, 128, 64);
-    else
-        launch(conv_wgrad_kernel<128, 128, 2, 2>, 128, 128);
-    if (db) {
-        // about 512 chunks (at least 128 positions each)
-        const int chunk = std::max(128, (P + 511) / 512);
-        hipLaunchKernelGGL(conv_bgrad_kernel, dim3(unsigned((P + chunk - 1) / chunk)), dim3(256), 0, s, P, a.cout, chunk,
-                           g, db);
-    }
+    const int nb = ((a.W + BRX - 1) / BRX) * ((a.H + BRY - 1) / BRY) * ((a.D + 3) / 4);
+    const int ncb = (a.c1 + a.c2 + 31) / 32, nob = (a.cout + 31) / 32;
+    // the bricks shared out over about WG_TARGET work-groups (two fit a CU):
+    // fewer leave CUs idle, more add their sums into dw more often (the 15
+    // layers of the 128 x 64 x 32 canvas: 413 us with 384, 417 with 512, 595
+    // with 256, 607 with 768)
+    constexpr int WG_TARGET = 448;
+    const int share = std::max(1, std::min(nb, WG_TARGET / (3 * ncb * nob)));
+    hipLaunchKernelGGL(conv_wgrad_kernel, dim3(unsigned(share), unsigned(3 * ncb), unsigned(nob)), dim3(256), 0, s, a, g,
+                       dw, db);
     return hipGetLastError();
 }
 
