@@ -540,10 +540,8 @@ int lb_sur_drift_rods(lb_ctx *ctx, const double *x_prev, double factor, hipStrea
  * [27][c1 + c2][cout], tap t = 9 (dz + 1) + 3 (dy + 1) + (dx + 1); wt: the
  * same weights packed [cout][27][c1 + c2] (lb_conv_pack_weights), read by the
  * forward only; b: FP32 [cout] or null; outputs y (BF16) and/or yf (FP32)
- * [D][H][W][cout]; acc: nullable FP32 scratch [D][H][W][cout] (forward
- * only; with it a layer of few output tiles splits its K range over more
- * work-groups, adding partial sums with atomics, so the summation order
- * varies).  c1, c2, cout: multiples of 8; D, H, W even when up1;
+ * [D][H][W][cout]; acc: not used (may be null; the sums have a fixed
+ * order).  c1, c2, cout: multiples of 8; D, H, W even when up1;
  * D H W max(c1 + c2, cout) < 2^31.  Asynchronous; LB_EINVAL on bad shapes or
  * null pointers.
  */
@@ -568,8 +566,7 @@ int lb_conv_pack_weights(const void *w, int32_t cin, int32_t cout, void *wt, hip
  * passes below. */
 int lb_relu_grad(const float *dy, const void *y, int64_t n, int32_t relu, void *g, hipStream_t stream);
 /* dx [D][H][W][c1 + c2] FP32 (overwritten) = the input gradient for the
- * pre-activation gradient g [D][H][W][cout] BF16 (lb_relu_grad).  Layers of
- * few output tiles split K and add into dx with atomics (order varies). */
+ * pre-activation gradient g [D][H][W][cout] BF16 (lb_relu_grad). */
 int lb_conv3d_backward_data(const lb_conv *conv, const void *g, float *dx, hipStream_t stream);
 /* dw [27][c1 + c2][cout] and db [cout] (nullable) FP32 += the parameter
  * gradients for g (accumulated with atomics, so the summation order varies). */
@@ -609,8 +606,7 @@ int lb_fill_f32(float *p, int64_t n, float value, hipStream_t stream);        /*
  *            cin, 2 ch[nlev-1]) and P_l x max(ch) elements;
  *   gcat     FP32 per level l < nlev - 1, P_l x (ch[l] + ch[l+1]) elements;
  *   gm       BF16 scratch of the largest layer output, P_l x cout;
- *   acc      FP32 split-K scratch of the coarse levels (largest layer output
- *            of levels >= 1).
+ *   acc      not used (non-null).
  * cin and the channel counts are multiples of 8; D, H, W divisible by
  * 2^(nlev-1).  lb_sur_forward(x) writes act, pooled and out for the BF16
  * input x [P_0][cin]; lb_sur_backward(x, gout) adds to g the parameter

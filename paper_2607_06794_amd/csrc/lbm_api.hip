@@ -1108,7 +1108,7 @@ static ConvArgs conv_args(const lb_conv *a) {
 int lb_conv3d_forward(const lb_conv *a, hipStream_t stream) {
     int rc = conv_check(a, true);
     if (rc) return rc;
-    HIP_TRY(launch_conv_fwd(conv_args(a), a->acc, stream), "conv forward");
+    HIP_TRY(launch_conv_fwd(conv_args(a), stream), "conv forward");
     return LB_OK;
 }
 

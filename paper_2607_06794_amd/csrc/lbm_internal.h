@@ -274,7 +274,7 @@ struct ConvArgs {
     float *yf;           // [P][cout] FP32 output (or null)
     int D, H, W, cout, relu;
 };
-hipError_t launch_conv_fwd(const ConvArgs &a, float *acc, hipStream_t s);
+hipError_t launch_conv_fwd(const ConvArgs &a, hipStream_t s);
 hipError_t launch_conv_dgrad(const ConvArgs &a, const uint16_t *g, float *dx, hipStream_t s);
 hipError_t launch_conv_wgrad(const ConvArgs &a, const uint16_t *g, float *dw, float *db, hipStream_t s);
 hipError_t launch_pack_weights(const uint16_t *w, int cin, int cout, uint16_t *wt, hipStream_t s);

@@ -10,9 +10,9 @@
 //            M = positions, N = input channels, K = 27 x output channels
 //   wgrad    dw[t, c, o] += sum_p x[p + o_t, c] g[p, o]
 //            M = input channels, N = output channels of one tap, K = positions
-// A work-group of four wavefronts computes a 256 x 32, 128 x 64 or 128 x 128
-// tile (chosen by N), each wavefront 64 x 32 or 64 x 64; K advances in steps
-// of 32 through two LDS buffers.
+// The kernel is chosen by the volume and N (launch_conv): a GEMM over tiles of
+// consecutive positions, bricks of positions that share their input halo in
+// LDS, or small bricks whose K is split over the wavefronts.
 // The decoder's inputs are read in place: channels [0, c1) from the coarser
 // level through nearest-neighbour upsampling, [c1, c1 + c2) from the skip.
 #include <math.h>
@@ -69,7 +69,7 @@ __device__ inline unsigned tap_mask(int d, int h, int w, int D, int H, int W) {
 }
 
 template <int BM, int BN, int WM, int WN, bool DGRAD>
-__global__ void __launch_bounds__(256) conv_gemm_kernel(ConvArgs a, const uint16_t *g, float *dx, float *acc_out) {
+__global__ void __launch_bounds__(256) conv_gemm_kernel(ConvArgs a, const uint16_t *g, float *dx) {
     static_assert(WM * WN == 4, "four wavefronts");
     constexpr int MB = BM / WM / 32, NB = BN / WN / 32;
     static_assert(MB >= 1 && NB >= 1 && MB * WM * 32 == BM && NB * WN * 32 == BN, "tile shape");
@@ -98,17 +98,11 @@ __global__ void __launch_bounds__(256) conv_gemm_kernel(ConvArgs a, const uint16
     const bool prow = p < P;
     const int pw = p % a.W, ph = (p / a.W) % a.H, pd = p / HW;
     unsigned tmask = prow ? tap_mask(pd, ph, pw, a.D, a.H, a.W) : 0u;
-    // split-K: work-group z of gridDim.z takes stages [s0, s1) and adds its
-    // partial sums (no bias or ReLU) into acc_out (forward) or dx (dgrad)
-    const int nst_all = (Kd + BK - 1) / BK;
-    const int s0 = int(int64_t(nst_all) * blockIdx.z / gridDim.z);
-    const int s1 = int(int64_t(nst_all) * (blockIdx.z + 1) / gridDim.z);
-    const bool split = gridDim.z > 1;
     int gt[GPT], gc[GPT];  // tap and channel of each k-group at the current stage
 #pragma unroll
     for (int j = 0; j < GPT; ++j) {
-        gt[j] = (s0 * BK + 8 * (ag0 + j)) / kc;
-        gc[j] = (s0 * BK + 8 * (ag0 + j)) % kc;
+        gt[j] = 8 * (ag0 + j) / kc;
+        gc[j] = 8 * (ag0 + j) % kc;
     }
     const int H2 = a.H >> 1, W2 = a.W >> 1;
 
@@ -121,8 +115,8 @@ __global__ void __launch_bounds__(256) conv_gemm_kernel(ConvArgs a, const uint16
         bn[j] = idx >> 2;
         bgi[j] = idx & 3;
         bon[j] = idx < BLD && n0 + bn[j] < N;
-        bt[j] = (s0 * BK + 8 * bgi[j]) / kc;
-        bc[j] = (s0 * BK + 8 * bgi[j]) % kc;
+        bt[j] = 8 * bgi[j] / kc;
+        bc[j] = 8 * bgi[j] % kc;
     }
 
     // Loads are unconditional (an invalid one reads a safe address) and the
@@ -199,15 +193,15 @@ __global__ void __launch_bounds__(256) conv_gemm_kernel(ConvArgs a, const uint16
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
 
-    const int nst = s1 - s0;
-    load(s0 * BK);
+    const int nst = (Kd + BK - 1) / BK;
+    load(0);
     store(0);
     __syncthreads();
     for (int st = 0; st < nst; ++st) {
         const int cur = st & 1;
         if (st + 1 < nst) {
             advance();
-            load((s0 + st + 1) * BK);
+            load((st + 1) * BK);
         }
 #pragma unroll
         for (int kk = 0; kk < BK; kk += 16) {
@@ -240,9 +234,7 @@ __global__ void __launch_bounds__(256) conv_gemm_kernel(ConvArgs a, const uint16
             for (int e = 0; e < 16; ++e) {
                 const int row = m0 + wm + 32 * i + 8 * (e >> 2) + 4 * (l >> 5) + (e & 3);
                 if (row >= P) continue;
-                if (split) {
-                    atomicAdd((DGRAD ? dx + row * cin : acc_out + row * a.cout) + col, acc[i][j][e]);
-                } else if (DGRAD) {
+                if (DGRAD) {
                     dx[row * cin + col] = acc[i][j][e];
                 } else {
                     float v = acc[i][j][e] + bias;
@@ -428,6 +420,142 @@ __global__ void __launch_bounds__(256, 2) conv_brick_kernel(ConvArgs a, const ui
         }
 }
 
+// Layers of few positions (the coarse levels).  A work-group of eight
+// wavefronts computes a brick of 2 x 4 x 4 positions x 16 NT columns, each
+// wavefront an eighth of K for the whole tile: step s = (tap, 32 channels) goes
+// to wavefront s % 8.  The brick's input halo is staged in LDS, 128 channels
+// at a time; the weights' operands (16 columns x 32 consecutive channels of one
+// tap) are loaded straight from memory into the MFMA registers, the next
+// step's in flight; the wavefronts' sums meet in LDS in a fixed order, so no
+// second pass and no atomics.  Bound by the weights' way through L1 (one line
+// per column and step).  4 096 positions,
+// 128 -> 128 channels: 16 us (220 TFLOP/s); 512 positions: 6.4 us.
+//
+typedef float v4f __attribute__((ext_vector_type(4)));
+constexpr int SBZ = 2, SBY = 4, SBX = 4, SHY = SBY + 2, SHX = SBX + 2, SNH = (SBZ + 2) * SHY * SHX;
+constexpr int SCH = 128, SLD = SCH + 8;  // channels per stage, halo row length
+
+template <int NT, bool DG>
+__global__ void __launch_bounds__(512, 4) conv_small_kernel(ConvArgs a, const uint16_t *g, float *dx) {
+    constexpr int HLB = SNH * SLD * 2, RDB = 8 * 512 * NT * 4;
+    __shared__ __attribute__((aligned(16))) char lds[HLB > RDB ? HLB : RDB];
+    uint16_t *Hs = reinterpret_cast<uint16_t *>(lds);
+    const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
+    const int cin = a.c1 + a.c2, N = DG ? cin : a.cout, kc = DG ? a.cout : cin;
+    const int nbx = (a.W + SBX - 1) / SBX, nby = (a.H + SBY - 1) / SBY, b = blockIdx.x;
+    const int x0 = (b % nbx) * SBX, y0 = b / nbx % nby * SBY, z0 = b / (nbx * nby) * SBZ, n0 = blockIdx.y * 16 * NT;
+    // operand rows of this lane: position l % 16 of each plane (halo row, the
+    // tap's offset is added), column l % 16; its channels 8 (l / 16) .. + 7
+    const int k8 = 8 * (l >> 4), hrow = ((l >> 2) & 3) * SHX + (l & 3);
+    const uint16_t *wb[NT];
+#pragma unroll
+    for (int q = 0; q < NT; ++q) {
+        const int n = min(n0 + 16 * q + (l & 15), N - 1);
+        wb[q] = DG ? a.w + int64_t(n) * a.cout : a.wt + int64_t(n) * 27 * cin;
+    }
+    const int tstride = DG ? cin * a.cout : cin;  // elements between a column's taps
+    v4f acc[2][NT];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int q = 0; q < NT; ++q) acc[i][q] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+
+    for (int c0 = 0; c0 < kc; c0 += SCH) {
+        const int cw = min(SCH, kc - c0), ncc = (cw + 31) / 32, nst = 27 * ncc;
+        __syncthreads();  // the previous stage's reads are done
+        // halo of channels c0 .. c0 + 127; outside the volume and past the channels: zero
+        constexpr int HL = (SNH * (SCH / 8) + 511) / 512;
+        uint4 hv[HL];
+        bool ok[HL];
+#pragma unroll
+        for (int j = 0; j < HL; ++j) {
+            const int e = tid + 512 * j, hp = min(e / (SCH / 8), SNH - 1), c = c0 + 8 * (e % (SCH / 8));
+            const int z = z0 + hp / (SHY * SHX) - 1, y = y0 + hp / SHX % SHY - 1, x = x0 + hp % SHX - 1;
+            const int zc = min(max(z, 0), a.D - 1), yc = min(max(y, 0), a.H - 1), xc = min(max(x, 0), a.W - 1);
+            ok[j] = c < kc && z == zc && y == yc && x == xc;
+            const int cc = min(c, kc - 8);
+            const uint16_t *src;
+            if constexpr (DG) {
+                src = g + ((zc * a.H + yc) * a.W + xc) * a.cout + cc;
+            } else {
+                const bool skip = cc >= a.c1;
+                const int u = !skip && a.up1 ? 1 : 0;
+                src = (skip ? a.x2 + cc - a.c1 : a.x1 + cc) +
+                      (((zc >> u) * (a.H >> u) + (yc >> u)) * (a.W >> u) + (xc >> u)) * (skip ? a.c2 : a.c1);
+            }
+            hv[j] = *reinterpret_cast<const uint4 *>(src);
+        }
+        // the first step's weights
+        int st = wv, t = wv / ncc, cc = wv % ncc;
+        uint4 wn[NT];
+        auto fetch = [&]() {
+            // past the channels the last eight of them (read in bounds, then zeroed)
+            const int64_t off = int64_t(t) * tstride + c0 + min(32 * cc + k8, cw - 8);
+#pragma unroll
+            for (int q = 0; q < NT; ++q) wn[q] = *reinterpret_cast<const uint4 *>(wb[q] + off);
+        };
+        fetch();
+#pragma unroll
+        for (int j = 0; j < HL; ++j) {
+            const int e = tid + 512 * j;
+            if (e < SNH * (SCH / 8))
+                *reinterpret_cast<uint4 *>(Hs + e / (SCH / 8) * SLD + 8 * (e % (SCH / 8))) = keep4(ok[j], hv[j]);
+        }
+        __syncthreads();
+        while (st < nst) {
+            const int tt = DG ? 26 - t : t, off = (tt / 9 * SHY + tt / 3 % 3) * SHX + tt % 3, c = 32 * cc + k8;
+            uint4 w[NT];
+#pragma unroll
+            for (int q = 0; q < NT; ++q) w[q] = keep4(c < cw, wn[q]);
+            st += 8;
+            cc += 8;
+            while (cc >= ncc) {
+                cc -= ncc;
+                ++t;
+            }
+            if (st < nst) fetch();
+            const uint16_t *hp = Hs + (hrow + off) * SLD + c;
+            const v8bf fa0 = *reinterpret_cast<const v8bf *>(hp);
+            const v8bf fa1 = *reinterpret_cast<const v8bf *>(hp + SHY * SHX * SLD);
+#pragma unroll
+            for (int q = 0; q < NT; ++q) {
+                const v8bf fb = __builtin_bit_cast(v8bf, w[q]);
+                acc[0][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa0, fb, acc[0][q], 0, 0, 0);
+                acc[1][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa1, fb, acc[1][q], 0, 0, 0);
+            }
+        }
+    }
+    // D element e of lane l: row 4 (l / 16) + e, column l % 16; [wavefront][row][column]
+    __syncthreads();
+    float *sum = reinterpret_cast<float *>(lds);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int q = 0; q < NT; ++q)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                sum[wv * 512 * NT + (16 * i + 4 * (l >> 4) + e) * 16 * NT + 16 * q + (l & 15)] = acc[i][q][e];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        const int e = tid + 512 * j, m = e / (16 * NT), col = n0 + e % (16 * NT);
+        const int z = z0 + (m >> 4), y = y0 + (m >> 2 & 3), x = x0 + (m & 3);
+        float v = 0.0f;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) v += sum[w * 512 * NT + e];
+        if (z >= a.D || y >= a.H || x >= a.W || col >= N) continue;
+        const int p = (z * a.H + y) * a.W + x;
+        if (DG) {
+            dx[p * cin + col] = v;
+        } else {
+            v += a.b ? a.b[col] : 0.0f;
+            if (a.relu) v = fmaxf(v, 0.0f);
+            if (a.y) a.y[p * a.cout + col] = f2bf(v);
+            if (a.yf) a.yf[p * a.cout + col] = v;
+        }
+    }
+}
+
 // packed forward weights: wt[o][t][c] = w[t][c][o]
 __global__ void pack_weights_kernel(const uint16_t *w, int cin, int cout, uint16_t *wt) {
     const int n = 27 * cin * cout;
@@ -595,17 +723,6 @@ __global__ void __launch_bounds__(256, 2) conv_wgrad_kernel(ConvArgs a, const ui
         __syncthreads();
         if (tid < 32 && o0 + tid < a.cout)
             atomicAdd(db + o0 + tid, (sum[tid] + sum[32 + tid]) + (sum[64 + tid] + sum[96 + tid]));
-    }
-}
-
-// split-K forward epilogue: y = ReLU(acc + b) in BF16 and/or FP32
-__global__ void conv_finalize_kernel(ConvArgs a, const float *acc) {
-    const int64_t n = int64_t(a.D) * a.H * a.W * a.cout;
-    for (int64_t e = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; e < n; e += int64_t(gridDim.x) * blockDim.x) {
-        float v = acc[e] + (a.b ? a.b[e % a.cout] : 0.0f);
-        if (a.relu) v = fmaxf(v, 0.0f);
-        if (a.y) a.y[e] = f2bf(v);
-        if (a.yf) a.yf[e] = v;
     }
 }
 
@@ -1131,84 +1248,60 @@ int grid_for(int64_t n) {
 
 }  // namespace
 
-template <bool DGRAD>
-static hipError_t launch_gemm(const ConvArgs &a, const uint16_t *g, float *dx, float *acc, hipStream_t s) {
-    const int P = a.D * a.H * a.W;
-    const int N = DGRAD ? a.c1 + a.c2 : a.cout;
-    const int kc = DGRAD ? a.cout : a.c1 + a.c2;
-    const int nst = (27 * kc + BK - 1) / BK;
-    // 256-row tiles while they give at least ~2 work-groups per CU, else 128;
-    // layers with fewer tiles than that split K over up to 512 work-groups
-    // (at least 8 stages each) when there is somewhere to add the partials
+// Which kernel a forward (DG = false) or input-gradient layer runs on:
+//  * up to SMALL_P positions, or where the GEMM's tiles would not fill the chip:
+//    conv_small (4 096 positions, 128 -> 128: 16 us against 36 for the GEMM
+//    with its K split over work-groups; 512 positions 6.4 against 18; 32 768
+//    positions, 64 -> 64: 31 against 23 for the bricks);
+//  * up to 64 columns on volumes of whole bricks: conv_brick;
+//  * otherwise the GEMM (262 144 positions, 32 -> 96: 104 us, conv_small 190).
+constexpr int SMALL_P = 8192;
+template <bool DG>
+static hipError_t launch_conv(const ConvArgs &a, const uint16_t *g, float *dx, hipStream_t s) {
+    const int P = a.D * a.H * a.W, N = DG ? a.c1 + a.c2 : a.cout;
+    if (P > SMALL_P && a.H % BRY == 0 && a.W % BRX == 0) {
+        const int nxy = (a.H / BRY) * (a.W / BRX);
+        if (N <= 32 && a.D % 4 == 0) {
+            hipLaunchKernelGGL((conv_brick_kernel<4, 1, DG>), dim3(unsigned(nxy * (a.D / 4))), dim3(256), 0, s, a, g, dx);
+            return hipGetLastError();
+        }
+        if (N <= 64 && a.D % 2 == 0) {
+            hipLaunchKernelGGL((conv_brick_kernel<2, 2, DG>), dim3(unsigned(nxy * (a.D / 2))), dim3(256), 0, s, a, g, dx);
+            return hipGetLastError();
+        }
+    }
+    // 256-row tiles while they give at least ~2 work-groups per CU, else 128
     const int bn = N <= 32 ? 32 : (N <= 64 ? 64 : 128);
     const unsigned ny = unsigned((N + bn - 1) / bn);
     const bool big = int64_t((P + 255) / 256) * ny >= 512;
     const unsigned gx = unsigned(big ? (P + 255) / 256 : (P + 127) / 128);
-    unsigned gz = 1;
-    if ((DGRAD || acc) && gx * ny < 256) gz = unsigned(std::max(1, std::min(nst / 8, int(512 / (gx * ny)))));
-    if (gz > 1) {
-        float *dst = DGRAD ? dx : acc;
-        const int64_t n = int64_t(P) * N;
-        hipLaunchKernelGGL(fill_f32_kernel, dim3(grid_for(n)), dim3(256), 0, s, dst, n, 0.0f);
+    if (P <= SMALL_P || gx * ny < 256) {
+        const int nb = ((a.W + SBX - 1) / SBX) * ((a.H + SBY - 1) / SBY) * ((a.D + SBZ - 1) / SBZ);
+        // four column tiles per work-group share the halo and each LDS operand;
+        // one where that leaves CUs idle
+        if (nb * ((N + 63) / 64) >= 192)
+            hipLaunchKernelGGL((conv_small_kernel<4, DG>), dim3(unsigned(nb), unsigned((N + 63) / 64)), dim3(512), 0, s, a,
+                               g, dx);
+        else
+            hipLaunchKernelGGL((conv_small_kernel<1, DG>), dim3(unsigned(nb), unsigned((N + 15) / 16)), dim3(512), 0, s, a,
+                               g, dx);
+        return hipGetLastError();
     }
-    const dim3 grid(gx, ny, gz);
-    if (N <= 32) {
-        if (big)
-            hipLaunchKernelGGL((conv_gemm_kernel<256, 32, 4, 1, DGRAD>), grid, dim3(256), 0, s, a, g, dx, acc);
-        else
-            hipLaunchKernelGGL((conv_gemm_kernel<128, 32, 4, 1, DGRAD>), grid, dim3(256), 0, s, a, g, dx, acc);
-    } else if (N <= 64) {
-        if (big)
-            hipLaunchKernelGGL((conv_gemm_kernel<256, 64, 4, 1, DGRAD>), grid, dim3(256), 0, s, a, g, dx, acc);
-        else
-            hipLaunchKernelGGL((conv_gemm_kernel<128, 64, 2, 2, DGRAD>), grid, dim3(256), 0, s, a, g, dx, acc);
-    } else {
-        if (big)
-            hipLaunchKernelGGL((conv_gemm_kernel<256, 128, 2, 2, DGRAD>), grid, dim3(256), 0, s, a, g, dx, acc);
-        else
-            hipLaunchKernelGGL((conv_gemm_kernel<128, 128, 2, 2, DGRAD>), grid, dim3(256), 0, s, a, g, dx, acc);
-    }
-    if (!DGRAD && gz > 1)
-        hipLaunchKernelGGL(conv_finalize_kernel, dim3(grid_for(int64_t(P) * N)), dim3(256), 0, s, a, acc);
+    const dim3 grid(gx, ny);
+    auto gemm = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, a, g, dx); };
+    if (N <= 32)
+        big ? gemm(conv_gemm_kernel<256, 32, 4, 1, DG>) : gemm(conv_gemm_kernel<128, 32, 4, 1, DG>);
+    else if (N <= 64)
+        big ? gemm(conv_gemm_kernel<256, 64, 4, 1, DG>) : gemm(conv_gemm_kernel<128, 64, 2, 2, DG>);
+    else
+        big ? gemm(conv_gemm_kernel<256, 128, 2, 2, DG>) : gemm(conv_gemm_kernel<128, 128, 2, 2, DG>);
     return hipGetLastError();
 }
 
-hipError_t launch_conv_fwd(const ConvArgs &a, float *acc, hipStream_t s) {
-    // volumes of whole bricks: the halo-staged kernel (4 x 8 x 8 bricks for up
-    // to 32 output channels, 2 x 8 x 8 for up to 64)
-    if (a.H % BRY == 0 && a.W % BRX == 0) {
-        const int nxy = (a.H / BRY) * (a.W / BRX);
-        if (a.cout <= 32 && a.D % 4 == 0) {
-            hipLaunchKernelGGL((conv_brick_kernel<4, 1, false>), dim3(unsigned(nxy * (a.D / 4))), dim3(256), 0, s, a,
-                               nullptr, nullptr);
-            return hipGetLastError();
-        }
-        if (a.cout <= 64 && a.D % 2 == 0) {
-            hipLaunchKernelGGL((conv_brick_kernel<2, 2, false>), dim3(unsigned(nxy * (a.D / 2))), dim3(256), 0, s, a,
-                               nullptr, nullptr);
-            return hipGetLastError();
-        }
-    }
-    return launch_gemm<false>(a, nullptr, nullptr, acc, s);
-}
+hipError_t launch_conv_fwd(const ConvArgs &a, hipStream_t s) { return launch_conv<false>(a, nullptr, nullptr, s); }
 
 hipError_t launch_conv_dgrad(const ConvArgs &a, const uint16_t *g, float *dx, hipStream_t s) {
-    // volumes of whole bricks: the halo-staged kernel over g with mirrored taps
-    const int cin = a.c1 + a.c2;
-    if (a.H % BRY == 0 && a.W % BRX == 0) {
-        const int nxy = (a.H / BRY) * (a.W / BRX);
-        if (cin <= 32 && a.D % 4 == 0) {
-            hipLaunchKernelGGL((conv_brick_kernel<4, 1, true>), dim3(unsigned(nxy * (a.D / 4))), dim3(256), 0, s, a, g,
-                               dx);
-            return hipGetLastError();
-        }
-        if (cin <= 64 && a.D % 2 == 0) {
-            hipLaunchKernelGGL((conv_brick_kernel<2, 2, true>), dim3(unsigned(nxy * (a.D / 2))), dim3(256), 0, s, a, g,
-                               dx);
-            return hipGetLastError();
-        }
-    }
-    return launch_gemm<true>(a, g, dx, nullptr, s);
+    return launch_conv<true>(a, g, dx, s);
 }
 
 hipError_t launch_conv_wgrad(const ConvArgs &a, const uint16_t *g, float *dw, float *db, hipStream_t s) {
