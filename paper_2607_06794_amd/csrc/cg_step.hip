@@ -7,148 +7,156 @@
 // a ghost colour in the solid layer and wall normals from the voxel geometry,
 // the interface normal turned to the wall's contact angle.
 //
-// The curvature needs the colour two nodes out, so the step runs as three
-// passes over SoA arrays (thread per node, x fastest, coalesced):
-//   1. colour:  pull the 38 populations of each fluid node, C into an array;
-//               then each static wall node's ghost colour, the w-weighted
-//               mean C of its fluid neighbours, into the same array;
-//   2. normal:  grad C from the neighbours' C (ghost colours on walls),
-//               unit normal with the contact-angle correction next to walls,
-//               n and |grad C| into four arrays;
-//   3. collide: pull again, moments, curvature from the neighbours' normals,
+// The curvature needs the colour two nodes out, so the step runs as passes
+// over SoA arrays (thread per node, x fastest, coalesced):
+//   1. stream:  pull the 38 populations of each fluid node, C into an array;
+//               with tau = 1 also rho_k and j, since the collision then needs
+//               nothing else of them (f* = f^eq plus the force);
+//   2. ghost:   each static wall node's ghost colour, the w-weighted mean C
+//               of its fluid neighbours, into the same array, 0 elsewhere;
+//   3. normal:  grad C from the neighbours' C, unit normal with the
+//               contact-angle correction next to walls, n and |grad C| into
+//               four arrays;
+//   4. collide: the moments (tau != 1: pulled and summed again), curvature
+//               from the neighbours' normals where the node has a normal,
 //               CSF force, Guo-forced BGK per component, recolouring, store,
 //               and hand the bounce-back values to the wall nodes.
-// Passes 2 and 3 read their stencils from L2 (each value is used by 19
-// threads of neighbouring rows).  HBM traffic per fluid node: the populations
-// read twice and written once plus the colour and normal arrays.
+// Bound by HBM: with tau = 1 the populations are read once and written once
+// (pulled twice with tau != 1).  All stencil loads are unconditional (the
+// arrays hold neutral values where a neighbour does not count), so that they
+// are in flight together.  Per FP32 step of 256 x 128 x 64, before -> now:
+//   tau = 1: colour 79, ghost 11, normal 48, collide 168 us -> stream 65,
+//   ghost 6.4, normal 12, collide 58 us (4.9 and 5.5 TB/s in the two passes
+//   over the populations, a large copy 5.3), 309 -> 141 us with the launches;
+//   tau != 1: 309 -> 195 us; FP64: 536 -> 313 and 534 -> 393 us.
 #include "lbm_device.h"
 #include "lbm_internal.h"
+#include "node_access.h"
 
 namespace lbm {
 
 namespace {
 
-__device__ inline int wrapc(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
-
-// neighbour x + d of a node along one axis: wrapped in a periodic direction;
-// in a closed one, false when outside the lattice
-__device__ inline bool step_axis(int &v, int d, int n, int per) {
-    v += d;
-    if (per) {
-        v = wrapc(v, n);
-        return true;
-    }
-    return v >= 0 && v < n;
-}
-
-template <class S>
-__device__ inline typename Codec<S>::C load_pop(const CGArgs &a, const S *f, int k, int i, int64_t node) {
-    using C = typename Codec<S>::C;
-    return Codec<S>::dec(f[(int64_t(k) * Q + i) * a.fs + node]) + wgt<C>(i) * C(a.rho_ref[k]);
-}
-
-// the 38 post-streaming populations of fluid node (x, y, z): f_i(x) =
+// the 38 post-streaming deviations of node neighbourhood nb: f_i(x) =
 // f*_i(x - c_i); wall nodes hold the bounce-back values handed to them
 template <class S>
-__device__ inline void pull(const CGArgs &a, int x, int y, int z, typename Codec<S>::C (&fv)[2][Q]) {
-    const S *f = static_cast<const S *>(a.fsrc);
+__device__ inline void pull(const CGArgs &a, const NodeNbr &nb, typename Codec<S>::C (&fv)[2][Q]) {
+    constexpr uint32_t E = sizeof(S);
+    const uint32_t fsE = static_cast<uint32_t>(a.fs) * E;
 #pragma unroll
-    for (int i = 0; i < Q; ++i) {
-        // fluid nodes never sit on a closed end plane, so x - c_i is inside
-        const int xs = a.px ? wrapc(x - cx(i), a.nx) : x - cx(i);
-        const int ys = a.py ? wrapc(y - cy(i), a.ny) : y - cy(i);
-        const int zs = a.pz ? wrapc(z - cz(i), a.nz) : z - cz(i);
-        const int64_t src = (int64_t(zs) * a.ny + ys) * a.nx + xs;
+    for (int k = 0; k < 2; ++k) {
+        const auto src = make_rsrc(static_cast<const char *>(a.fsrc) + size_t(k) * Q * fsE, Q * fsE);
 #pragma unroll
-        for (int k = 0; k < 2; ++k) fv[k][i] = load_pop<S>(a, f, k, i, src);
+        for (int i = 0; i < Q; ++i)
+            fv[k][i] = Codec<S>::dec(buf_load<S>(src, nb.at(-cx(i), -cy(i), -cz(i)) * E, i * fsE));
     }
 }
 
-__device__ inline void decode(int64_t n, const CGArgs &a, int &x, int &y, int &z) {
-    x = int(n % a.nx);
-    const int64_t r = n / a.nx;
-    y = int(r % a.ny);
-    z = int(r / a.ny);
-}
-
-// ---- pass 1: colour of every fluid node -----------------------------------
-template <class S>
-__global__ void __launch_bounds__(256) cg_colour_kernel(CGArgs a) {
-    using C = typename Codec<S>::C;
-    const int64_t n = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (n >= a.nodes) return;
-    if ((a.mat[n] & MAT_ID_MASK) != MAT_FLUID) return;
-    int x, y, z;
-    decode(n, a, x, y, z);
-    C fv[2][Q];
-    pull<S>(a, x, y, z, fv);
-    C r0 = C(0), r1 = C(0);
-#pragma unroll
-    for (int i = 0; i < Q; ++i) {
-        r0 += fv[0][i];
-        r1 += fv[1][i];
-    }
-    const C rt = r0 + r1;
-    static_cast<C *>(a.colour)[n] = rt > C(0) ? (r0 - r1) / rt : C(0);
-}
-
-// ---- pass 1b: ghost colour of the static wall nodes: the w-weighted mean C
-// of each wall node's fluid neighbours (0 without any), stored in the colour
-// array so that the normal pass reads one value per neighbour
+// Eq. 3: rho_k = rref_k + sum_i d_i and j over opposite pairs
 template <class C>
-__global__ void __launch_bounds__(256) cg_ghost_kernel(CGArgs a) {
-    const int64_t n = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+__device__ inline void moments(const CGArgs &a, const C (&fv)[2][Q], C (&rho)[2], C (&j)[3]) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) j[d] = C(0);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        C s = C(0);
+#pragma unroll
+        for (int i = 0; i < Q; ++i) s += fv[k][i];
+        rho[k] = C(a.rho_ref[k]) + s;
+#pragma unroll
+        for (int i = 1; i < Q; i += 2) {
+            const C d = fv[k][i] - fv[k][i + 1];
+            if (cx(i)) j[0] += cx(i) * d;
+            if (cy(i)) j[1] += cy(i) * d;
+            if (cz(i)) j[2] += cz(i) * d;
+        }
+    }
+}
+
+// ---- pass 1: colour (and, MOM, moments) of every fluid node ----------------
+template <class S, bool MOM>
+__global__ void __launch_bounds__(NB) cg_stream_kernel(CGArgs a) {
+    using C = typename Codec<S>::C;
+    const uint32_t n = static_cast<uint32_t>(xcd_range(blockIdx.x, gridDim.x)) * NB + threadIdx.x;
     if (n >= a.nodes) return;
-    if (!is_static_wall(a.mat[n] & MAT_ID_MASK)) return;
-    int x, y, z;
-    decode(n, a, x, y, z);
-    C *col = static_cast<C *>(a.colour);
+    const bool fluid = (gptr(a.mat)[n] & MAT_ID_MASK) == MAT_FLUID;
+    C fv[2][Q], rho[2], j[3];
+    pull<S>(a, node_nbr(n, a), fv);
+    moments(a, fv, rho, j);
+    if (!fluid) return;
+    const C rt = rho[0] + rho[1];
+    gptr(static_cast<C *>(a.colour))[n] = rt > C(0) ? (rho[0] - rho[1]) / rt : C(0);
+    if constexpr (MOM) {
+        const uint32_t fsE = static_cast<uint32_t>(a.fs) * sizeof(S);
+        const auto dst = make_rsrc(a.fdst, Q * fsE);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) put_moment<S>(dst, n * sizeof(S), fsE, d, j[d]);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) put_moment<S>(dst, n * sizeof(S), fsE, 3 + k, rho[k]);
+    }
+}
+
+// ---- pass 2: ghost colour of the static wall nodes: the w-weighted mean C
+// of each wall node's fluid neighbours (0 without any); 0 on other solid nodes.
+// So the normal pass reads one value per neighbour and no material.
+template <class C>
+__global__ void __launch_bounds__(NB) cg_ghost_kernel(CGArgs a) {
+    const uint32_t n = static_cast<uint32_t>(xcd_range(blockIdx.x, gridDim.x)) * NB + threadIdx.x;
+    if (n >= a.nodes) return;
+    const uint8_t m = gptr(a.mat)[n] & MAT_ID_MASK;
+    if (m == MAT_FLUID) return;
+    auto col = gptr(static_cast<C *>(a.colour));
+    if (!is_static_wall(m)) {
+        col[n] = C(0);
+        return;
+    }
+    const NodeNbr nb = node_nbr(n, a);
+    const int x = int(nb.xs[1]), y = int(nb.ys[1] / uint32_t(a.nx));
+    const bool in[3][2] = {{a.px || x > 0, a.px || x + 1 < a.nx},
+                           {a.py || y > 0, a.py || y + 1 < a.ny},
+                           {a.pz || nb.z > 0, a.pz || nb.z + 1 < a.nz}};
+    uint8_t mq[Q];
+    C cq[Q];
+#pragma unroll
+    for (int i = 1; i < Q; ++i) {
+        const uint32_t q = nb.at(cx(i), cy(i), cz(i));
+        mq[i] = gptr(a.mat)[q];
+        cq[i] = col[q];
+    }
     C num = C(0), den = C(0);
 #pragma unroll
-    for (int j = 1; j < Q; ++j) {
-        int vx = x, vy = y, vz = z;
-        if (!step_axis(vx, cx(j), a.nx, a.px) || !step_axis(vy, cy(j), a.ny, a.py) || !step_axis(vz, cz(j), a.nz, a.pz))
-            continue;
-        const int64_t v = (int64_t(vz) * a.ny + vy) * a.nx + vx;
-        if ((a.mat[v] & MAT_ID_MASK) == MAT_FLUID) {
-            num += wgt<C>(j) * col[v];
-            den += wgt<C>(j);
-        }
+    for (int i = 1; i < Q; ++i) {
+        bool f = (mq[i] & MAT_ID_MASK) == MAT_FLUID;
+        if (cx(i)) f = f && in[0][cx(i) > 0];
+        if (cy(i)) f = f && in[1][cy(i) > 0];
+        if (cz(i)) f = f && in[2][cz(i) > 0];
+        num += f ? wgt<C>(i) * cq[i] : C(0);
+        den += f ? wgt<C>(i) : C(0);
     }
     col[n] = den > C(0) ? num / den : C(0);
 }
 
-// colour seen at node q: C on fluid nodes, the ghost colour on static wall
-// nodes, 0 elsewhere
+// ---- pass 3: interface normal ---------------------------------------------
 template <class C>
-__device__ inline C colour_at(const CGArgs &a, int qx, int qy, int qz) {
-    const int64_t q = (int64_t(qz) * a.ny + qy) * a.nx + qx;
-    const uint8_t m = a.mat[q] & MAT_ID_MASK;
-    return (m == MAT_FLUID || is_static_wall(m)) ? static_cast<const C *>(a.colour)[q] : C(0);
-}
-
-// ---- pass 2: interface normal ---------------------------------------------
-template <class C>
-__global__ void __launch_bounds__(256) cg_normal_kernel(CGArgs a) {
-    const int64_t n = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+__global__ void __launch_bounds__(NB) cg_normal_kernel(CGArgs a) {
+    const uint32_t n = static_cast<uint32_t>(xcd_range(blockIdx.x, gridDim.x)) * NB + threadIdx.x;
     if (n >= a.nodes) return;
-    C *nrm = static_cast<C *>(a.normal);
-    const uint8_t mb = a.mat[n];
+    const uint8_t mb = gptr(a.mat)[n];
+    const NodeNbr nb = node_nbr(n, a);
+    const auto col = make_rsrc(a.colour, uint32_t(a.fs) * uint32_t(sizeof(C)));
+    // grad C = (1 / c_s^2) sum_i w_i C(x + c_i) c_i, over opposite pairs
+    C v[Q];
+#pragma unroll
+    for (int i = 1; i < Q; ++i) v[i] = buf_load<C>(col, nb.at(cx(i), cy(i), cz(i)) * uint32_t(sizeof(C)), 0);
     C nv[3] = {C(0), C(0), C(0)}, mag = C(0);
     if ((mb & MAT_ID_MASK) == MAT_FLUID) {
-        int x, y, z;
-        decode(n, a, x, y, z);
-        // grad C = (1 / c_s^2) sum_i w_i C(x + c_i) c_i
         C g[3] = {C(0), C(0), C(0)};
 #pragma unroll
-        for (int i = 1; i < Q; ++i) {
-            const int qx = a.px ? wrapc(x + cx(i), a.nx) : x + cx(i);
-            const int qy = a.py ? wrapc(y + cy(i), a.ny) : y + cy(i);
-            const int qz = a.pz ? wrapc(z + cz(i), a.nz) : z + cz(i);
-            const C v = wgt<C>(i) * colour_at<C>(a, qx, qy, qz);
-            if (cx(i)) g[0] += cx(i) * v;
-            if (cy(i)) g[1] += cy(i) * v;
-            if (cz(i)) g[2] += cz(i) * v;
+        for (int i = 1; i < Q; i += 2) {
+            const C d = wgt<C>(i) * (v[i] - v[i + 1]);
+            if (cx(i)) g[0] += cx(i) * d;
+            if (cy(i)) g[1] += cy(i) * d;
+            if (cz(i)) g[2] += cz(i) * d;
         }
 #pragma unroll
         for (int d = 0; d < 3; ++d) g[d] *= C(3);
@@ -159,20 +167,19 @@ __global__ void __launch_bounds__(256) cg_normal_kernel(CGArgs a) {
             if (mb & MAT_NEAR_WALL) {
                 // wall normal from the solid neighbours (into the fluid) and
                 // their w-weighted mean cos(theta)
+                uint8_t mq[Q];
+#pragma unroll
+                for (int i = 1; i < Q; ++i) mq[i] = gptr(a.mat)[nb.at(cx(i), cy(i), cz(i))] & MAT_ID_MASK;
                 C s[3] = {C(0), C(0), C(0)}, ws = C(0), cts = C(0);
 #pragma unroll
                 for (int i = 1; i < Q; ++i) {
-                    const int qx = a.px ? wrapc(x + cx(i), a.nx) : x + cx(i);
-                    const int qy = a.py ? wrapc(y + cy(i), a.ny) : y + cy(i);
-                    const int qz = a.pz ? wrapc(z + cz(i), a.nz) : z + cz(i);
-                    const uint8_t mq = a.mat[(int64_t(qz) * a.ny + qy) * a.nx + qx] & MAT_ID_MASK;
-                    if (is_static_wall(mq)) {
+                    if (is_static_wall(mq[i])) {
                         const C w = wgt<C>(i);
                         s[0] += w * C(cx(i));
                         s[1] += w * C(cy(i));
                         s[2] += w * C(cz(i));
                         ws += w;
-                        cts += w * C(a.cos_theta[mq]);
+                        cts += w * C(a.cos_theta[mq[i]]);
                     }
                 }
                 const C sn = sqrt(s[0] * s[0] + s[1] * s[1] + s[2] * s[2]);
@@ -191,64 +198,77 @@ __global__ void __launch_bounds__(256) cg_normal_kernel(CGArgs a) {
             }
         }
     }
-#pragma unroll
-    for (int d = 0; d < 3; ++d) nrm[d * a.fs + n] = nv[d];
+    auto nrm = gptr(static_cast<C *>(a.normal));
     nrm[3 * a.fs + n] = mag;
+    // read only where |grad C| is above the threshold; whole wavefronts store
+    if (__any(mag > C(a.grad_eps))) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) nrm[d * a.fs + n] = nv[d];
+    }
 }
 
-// ---- pass 3: force, collision, recolouring ---------------------------------
-template <class S>
-__global__ void __launch_bounds__(256) cg_collide_kernel(CGArgs a) {
+// ---- pass 4: force, collision, recolouring ---------------------------------
+template <class S, bool MOM>
+__global__ void __launch_bounds__(NB) cg_collide_kernel(CGArgs a) {
     using C = typename Codec<S>::C;
-    const int64_t n = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    constexpr uint32_t E = sizeof(S);
+    const uint32_t n = static_cast<uint32_t>(xcd_range(blockIdx.x, gridDim.x)) * NB + threadIdx.x;
     if (n >= a.nodes) return;
-    const uint8_t mb = a.mat[n];
+    const uint8_t mb = gptr(a.mat)[n];
     if ((mb & MAT_ID_MASK) != MAT_FLUID) return;
     const unsigned known = *a.status;  // status bits already raised before this launch
-    int x, y, z;
-    decode(n, a, x, y, z);
-    C fv[2][Q];
-    pull<S>(a, x, y, z, fv);
-    // moments (Eq. 3)
-    C rho[2], j[3] = {C(0), C(0), C(0)};
+    const NodeNbr nb = node_nbr(n, a);
+    const uint32_t fsE = static_cast<uint32_t>(a.fs) * E;
+    const auto dst0 = make_rsrc(a.fdst, Q * fsE);
+    const auto nrm = make_rsrc(a.normal, 4 * static_cast<uint32_t>(a.fs) * uint32_t(sizeof(C)));
+    const uint32_t fsC = static_cast<uint32_t>(a.fs) * uint32_t(sizeof(C));
+    auto normal_at = [&](uint32_t q, int d) { return buf_load<C>(nrm, q * uint32_t(sizeof(C)), d * fsC); };
+    C fv[2][Q], rho[2], j[3];
+    if constexpr (MOM) {
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        C s = C(0);
+        for (int d = 0; d < 3; ++d) j[d] = get_moment<S>(dst0, n * E, fsE, d);
 #pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            s += fv[k][i];
-            if (cx(i)) j[0] += cx(i) * fv[k][i];
-            if (cy(i)) j[1] += cy(i) * fv[k][i];
-            if (cz(i)) j[2] += cz(i) * fv[k][i];
-        }
-        rho[k] = s;
+        for (int k = 0; k < 2; ++k) rho[k] = get_moment<S>(dst0, n * E, fsE, 3 + k);
+    } else {
+        pull<S>(a, nb, fv);
+        moments(a, fv, rho, j);
     }
+    const C mag = normal_at(n, 3), eps = C(a.grad_eps);
     const C rt = rho[0] + rho[1];
     const C irt = rt > C(0) ? C(1) / rt : C(1);
-    // curvature kappa = -div n; a neighbour without a normal of its own (not
-    // fluid, or |grad C| at or below the threshold) enters with this node's
-    const C *nrm = static_cast<const C *>(a.normal);
-    const C n0[3] = {nrm[n], nrm[a.fs + n], nrm[2 * a.fs + n]};
-    const C mag = nrm[3 * a.fs + n];
-    C div = C(0);
+    // CSF force F = (sigma / 2) kappa |grad C| n plus the body force; without a
+    // normal (|grad C| at or below the threshold) n is zero and kappa not needed
+    C n0[3] = {C(0), C(0), C(0)}, F[3] = {C(0), C(0), C(0)};
+    if (!(mag <= eps)) {
+        C v[Q][3], mq[Q];
 #pragma unroll
-    for (int i = 1; i < Q; ++i) {
-        const int qx = a.px ? wrapc(x + cx(i), a.nx) : x + cx(i);
-        const int qy = a.py ? wrapc(y + cy(i), a.ny) : y + cy(i);
-        const int qz = a.pz ? wrapc(z + cz(i), a.nz) : z + cz(i);
-        const int64_t q = (int64_t(qz) * a.ny + qy) * a.nx + qx;
-        const bool def = (a.mat[q] & MAT_ID_MASK) == MAT_FLUID && nrm[3 * a.fs + q] > C(a.grad_eps);
-        C d = C(0);
-        if (cx(i)) d += cx(i) * (def ? nrm[q] : n0[0]);
-        if (cy(i)) d += cy(i) * (def ? nrm[a.fs + q] : n0[1]);
-        if (cz(i)) d += cz(i) * (def ? nrm[2 * a.fs + q] : n0[2]);
-        div += wgt<C>(i) * d;
+        for (int i = 0; i < Q; ++i) {
+            const uint32_t q = nb.at(cx(i), cy(i), cz(i));
+            mq[i] = i ? normal_at(q, 3) : mag;
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+                if (i == 0 || (d == 0 ? cx(i) : d == 1 ? cy(i) : cz(i))) v[i][d] = normal_at(q, d);
+        }
+#pragma unroll
+        for (int d = 0; d < 3; ++d) n0[d] = mag > eps ? v[0][d] : C(0);
+        // curvature kappa = -div n; a neighbour without a normal of its own (not
+        // fluid, or |grad C| at or below the threshold) enters with this node's
+        C div = C(0);
+#pragma unroll
+        for (int i = 1; i < Q; ++i) {
+            const bool def = mq[i] > eps;
+            C d = C(0);
+            if (cx(i)) d += cx(i) * (def ? v[i][0] : n0[0]);
+            if (cy(i)) d += cy(i) * (def ? v[i][1] : n0[1]);
+            if (cz(i)) d += cz(i) * (def ? v[i][2] : n0[2]);
+            div += wgt<C>(i) * d;
+        }
+        const C kappa = C(-3) * div;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) F[d] = C(0.5) * C(a.sigma) * kappa * mag * n0[d];
     }
-    const C kappa = C(-3) * div;
-    // CSF force F = (sigma / 2) kappa |grad C| n plus the body force
-    C F[3];
 #pragma unroll
-    for (int d = 0; d < 3; ++d) F[d] = C(0.5) * C(a.sigma) * kappa * mag * n0[d] + rt * C(a.g[d]);
+    for (int d = 0; d < 3; ++d) F[d] += rt * C(a.g[d]);
     // common velocity with the half-force shift
     C u[3];
 #pragma unroll
@@ -262,76 +282,87 @@ __global__ void __launch_bounds__(256) cg_collide_kernel(CGArgs a) {
     }
     const C uF = u[0] * F[0] + u[1] * F[1] + u[2] * F[2];
     // colour-blind post-collision populations: per component BGK towards
-    // f^eq(rho_k, u) plus Guo's source with F_k = (rho_k / rho) F, summed
-    C tot[Q];
+    // f^eq(rho_k, u) plus Guo's source with F_k = (rho_k / rho) F, summed:
+    //   tot_i = sum_k (1 - om_k) f_ki + ef w_i shape_i + es src_i
+    C ef = rt, es = C(0.5) * (rt * irt);
+    C keep[2] = {C(0), C(0)};
+    if constexpr (!MOM) {
+        const C om[2] = {C(a.omega[0]), C(a.omega[1])};
+        ef = om[0] * rho[0] + om[1] * rho[1];
+        es = ((C(1) - C(0.5) * om[0]) * rho[0] + (C(1) - C(0.5) * om[1]) * rho[1]) * irt;
 #pragma unroll
-    for (int i = 0; i < Q; ++i) {
+        for (int k = 0; k < 2; ++k) keep[k] = C(1) - om[k];
+    }
+    C tot[Q];
+    const C sym0 = ef * (C(1) - C(1.5) * usq) - es * C(3) * uF;
+    tot[0] = wgt<C>(0) * sym0;
+#pragma unroll
+    for (int i = 1; i < Q; i += 2) {
         const C cu = C(cx(i)) * u[0] + C(cy(i)) * u[1] + C(cz(i)) * u[2];
         const C cF = C(cx(i)) * F[0] + C(cy(i)) * F[1] + C(cz(i)) * F[2];
-        const C w = wgt<C>(i);
-        const C shape = C(1) + C(3) * cu + C(4.5) * cu * cu - C(1.5) * usq;
-        const C src = w * (C(3) * (cF - uF) + C(9) * cu * cF);
-        C sum = C(0);
+        const C sym = wgt<C>(i) * (sym0 + cu * (C(4.5) * ef * cu + C(9) * es * cF));
+        const C asym = wgt<C>(i) * (C(3) * (ef * cu + es * cF));
+        tot[i] = sym + asym;
+        tot[i + 1] = sym - asym;
+    }
+    if constexpr (!MOM) {
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const C om = C(a.omega[k]);
-            const C feq = w * rho[k] * shape;
-            sum += fv[k][i] - (fv[k][i] - feq) * om + (C(1) - C(0.5) * om) * (rho[k] * irt) * src;
-        }
-        tot[i] = sum;
+        for (int i = 0; i < Q; ++i)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) tot[i] += keep[k] * (fv[k][i] + wgt<C>(i) * C(a.rho_ref[k]));
     }
     // recolouring: proportional share plus +- beta (rho_1 rho_2 / rho) w_i cos phi_i
     const C seg = C(a.beta) * rho[0] * rho[1] * irt;
-    const C fr0 = rho[0] * irt, fr1 = rho[1] * irt;
-    S *dst = static_cast<S *>(a.fdst);
-    const bool near_wall = (mb & MAT_NEAR_WALL) != 0;
+    const C fr[2] = {rho[0] * irt, rho[1] * irt};
+    C sc[Q];
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
-        C cphi = C(0);
-        if (i > 0) {
-            const C cn = C(cx(i)) * n0[0] + C(cy(i)) * n0[1] + C(cz(i)) * n0[2];
-            cphi = i <= 6 ? cn : cn * C(0.70710678118654752440);
+        const C cn = C(cx(i)) * n0[0] + C(cy(i)) * n0[1] + C(cz(i)) * n0[2];
+        sc[i] = i == 0 ? C(0) : seg * wgt<C>(i) * (i <= 6 ? cn : cn * C(0.70710678118654752440));
+    }
+    const bool near_wall = (mb & MAT_NEAR_WALL) != 0;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const auto dst = make_rsrc(static_cast<char *>(a.fdst) + size_t(k) * Q * fsE, Q * fsE);
+        S e[Q];
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            const C o = k == 0 ? fr[0] * tot[i] + sc[i] : fr[1] * tot[i] - sc[i];
+            e[i] = Codec<S>::enc(o - wgt<C>(i) * C(a.rho_ref[k]));
+            buf_store<S>(e[i], dst, n * E, i * fsE);
         }
-        const C w = wgt<C>(i);
-        const C o0 = fr0 * tot[i] + seg * w * cphi;
-        const C o1 = fr1 * tot[i] - seg * w * cphi;
-        const S e0 = Codec<S>::enc(o0 - w * C(a.rho_ref[0]));
-        const S e1 = Codec<S>::enc(o1 - w * C(a.rho_ref[1]));
-        dst[int64_t(i) * a.fs + n] = e0;
-        dst[(int64_t(Q) + i) * a.fs + n] = e1;
-        if (near_wall && i > 0) {
+        if (near_wall) {
             // halfway bounce-back: the wall node x + c_i holds f*_i(x) as
             // direction opp(i) for the next pull
-            int qx = x, qy = y, qz = z;
-            if (step_axis(qx, cx(i), a.nx, a.px) && step_axis(qy, cy(i), a.ny, a.py) &&
-                step_axis(qz, cz(i), a.nz, a.pz)) {
-                const int64_t q = (int64_t(qz) * a.ny + qy) * a.nx + qx;
-                if (is_static_wall(a.mat[q] & MAT_ID_MASK)) {
-                    dst[int64_t(opp(i)) * a.fs + q] = e0;
-                    dst[(int64_t(Q) + opp(i)) * a.fs + q] = e1;
-                }
+#pragma unroll
+            for (int i = 1; i < Q; ++i) {
+                const uint32_t q = nb.at(cx(i), cy(i), cz(i));
+                if (is_static_wall(gptr(a.mat)[q] & MAT_ID_MASK)) buf_store<S>(e[i], dst, q * E, opp(i) * fsE);
             }
         }
     }
 }
 
+template <class S, bool MOM>
+static hipError_t launch_cg(const CGArgs &a, hipStream_t s) {
+    const dim3 grid(unsigned((a.nodes + NB - 1) / NB + 7) & ~7u), block(NB);
+    hipLaunchKernelGGL((cg_stream_kernel<S, MOM>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((cg_ghost_kernel<S>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((cg_normal_kernel<S>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((cg_collide_kernel<S, MOM>), grid, block, 0, s, a);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_cg_step(int prec, const CGArgs &a, hipStream_t s) {
-    const dim3 grid(unsigned((a.nodes + 255) / 256)), block(256);
+    // with tau = 1 the collision forgets the streamed populations
+    const bool mom = a.omega[0] == 1.0 && a.omega[1] == 1.0;
     switch (prec) {
         case LB_F64:
-            hipLaunchKernelGGL(cg_colour_kernel<double>, grid, block, 0, s, a);
-            hipLaunchKernelGGL(cg_ghost_kernel<double>, grid, block, 0, s, a);
-            hipLaunchKernelGGL(cg_normal_kernel<double>, grid, block, 0, s, a);
-            hipLaunchKernelGGL(cg_collide_kernel<double>, grid, block, 0, s, a);
-            return hipGetLastError();
+            return mom ? launch_cg<double, true>(a, s) : launch_cg<double, false>(a, s);
         case LB_F32:
-            hipLaunchKernelGGL(cg_colour_kernel<float>, grid, block, 0, s, a);
-            hipLaunchKernelGGL(cg_ghost_kernel<float>, grid, block, 0, s, a);
-            hipLaunchKernelGGL(cg_normal_kernel<float>, grid, block, 0, s, a);
-            hipLaunchKernelGGL(cg_collide_kernel<float>, grid, block, 0, s, a);
-            return hipGetLastError();
+            return mom ? launch_cg<float, true>(a, s) : launch_cg<float, false>(a, s);
         default:
             return hipErrorInvalidValue;
     }
