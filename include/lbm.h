@@ -244,6 +244,9 @@ int lb_init(const lb_params *p, const lb_buffers *buf, const double *rho_init_ho
  * rod-wall forces, re-mask with cover/uncover, and the moving bounce-back of
  * the next step.  A no-op without rods.  Asynchronous. */
 int lb_rods_step(lb_ctx *ctx, hipStream_t stream);
+/* nsteps coupled steps: lb_step(1) followed by lb_rods_step or lb_fil_step,
+ * nsteps times, with the same results.  Asynchronous. */
+int lb_coupled_step(lb_ctx *ctx, int32_t nsteps, hipStream_t stream);
 
 /* Copy the rod states to out_host [n_rods][13] (layout as in lb_init).
  * Synchronises. */

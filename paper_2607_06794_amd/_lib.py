@@ -35,6 +35,7 @@ EXPORTS = (
     "lb_set_tiles",
     "lb_autotune",
     "lb_rods_step",
+    "lb_coupled_step",
     "lb_rods_get",
     "lb_fil_set",
     "lb_fil_step",
@@ -319,6 +320,8 @@ def load(path: str = LIB_PATH):
     lib.lb_last_error.restype = ct.c_char_p
     lib.lb_rods_step.argtypes = [ct.c_void_p, ct.c_void_p]
     lib.lb_rods_step.restype = ct.c_int
+    lib.lb_coupled_step.argtypes = [ct.c_void_p, ct.c_int32, ct.c_void_p]
+    lib.lb_coupled_step.restype = ct.c_int
     lib.lb_rods_get.argtypes = [ct.c_void_p, ct.c_void_p, ct.c_void_p]
     lib.lb_rods_get.restype = ct.c_int
     lib.lb_fil_set.argtypes = [ct.c_void_p, ct.c_void_p, ct.c_void_p]

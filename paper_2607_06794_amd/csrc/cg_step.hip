@@ -111,7 +111,7 @@ __global__ void __launch_bounds__(NB) cg_ghost_kernel(CGArgs a) {
         return;
     }
     const NodeNbr nb = node_nbr(n, a);
-    const int x = int(nb.xs[1]), y = int(nb.ys[1] / uint32_t(a.nx));
+    const int x = int(nb.xs[1]), y = int(a.by_nx(nb.ys[1]));
     const bool in[3][2] = {{a.px || x > 0, a.px || x + 1 < a.nx},
                            {a.py || y > 0, a.py || y + 1 < a.ny},
                            {a.pz || nb.z > 0, a.pz || nb.z + 1 < a.nz}};

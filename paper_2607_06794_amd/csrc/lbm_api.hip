@@ -409,6 +409,7 @@ static RodArgs rod_args(lb_ctx *c) {
     const lb_params &p = c->p;
     RodArgs a{};
     a.f = c->f[c->cur];
+    a.f2 = c->f[c->cur ^ 1];
     a.rho = c->rho;
     a.rods = c->rods;
     a.shell_cap = p.n_rods > 0 ? rod_shell_cap(p) : 0;
@@ -605,6 +606,7 @@ int lb_init(const lb_params *p, const lb_buffers *buf, const double *rho_init_ho
         for (int q = 0; q < 2; ++q) {
             c->rodargs_host[q] = rod_args(c);
             c->rodargs_host[q].f = c->f[q];
+            c->rodargs_host[q].f2 = c->f[q ^ 1];
         }
         if ((e = hipMemcpyAsync(c->rodargs_dev, c->rodargs_host, sizeof(c->rodargs_host), hipMemcpyHostToDevice,
                                 stream)) != hipSuccess)
@@ -644,6 +646,8 @@ static StepArgs step_args(const lb_ctx *c, int cur) {
     a.nx = p.nx;
     a.ny = p.ny;
     a.nz = p.nz;
+    a.by_nx = Divider(p.nx);
+    a.by_ny = Divider(p.ny);
     a.px = p.periodic[0];
     a.py = p.periodic[1];
     a.pz = p.periodic[2];
@@ -673,8 +677,36 @@ static StepArgs step_args(const lb_ctx *c, int cur) {
         a.sink_ledger = c->ledger + 2 * size_t(c->max_tiles);
     }
     a.rho_out = c->rho;
+    a.jm = a.fdst;
     if (p.round_stochastic && (p.prec == LB_F16DEV || p.prec == LB_BF16DEV))
         a.sr_key = (uint32_t(c->steps + 1) * 0x9E3779B1u ^ p.sr_seed) | 1u;  // never 0 (0 = nearest)
+    return a;
+}
+
+// Steps of one call can pass the state on as moments (the collision with tau = 1
+// leaves nothing else): FP32 and FP64, which keep them as they were computed.
+// Small lattices live in the caches, where the pass over populations is the
+// shorter one: without rods and reservoir, us per step populations / moments,
+// FP32 32^3 9.8 / 11.2, 64^3 (40 MB) 18.9 / 20.1, 80^3 (78 MB) 33.8 / 26.8; FP64
+// 32^3 11.6 / 13.2, 56^3 (53 MB) 25.0 / 26.4, 64^3 (80 MB) 34.1 / 27.6: the line
+// lies at 64 MiB of populations.  A reservoir's booking ends the pass over
+// populations (it opens the other one), so that moments are even or ahead from
+// the smallest lattice on (32^3 12.8 / 11.6, 128 x 64 x 32 19.0 / 19.6), and the
+// rods' link pass reads 8 values of a node instead of up to 36 (39 / 23 us).
+static bool moment_chain(const lb_params &p) {
+    if (!two_pass(p) || p.sink_on || (p.prec != LB_F32 && p.prec != LB_F64)) return false;
+    return p.n_rods > 0 || p.evap_on || 2 * Q * nodes(&p) * elem_bytes(p.prec) > (int64_t(64) << 20);
+}
+// Step record of such a call: the populations in buffer src at its start, in
+// buffer dst at its end.  In between, the buffer that does not hold the
+// populations has j (arrays 0 .. 4) and the moments (arrays 5 .. 14), and the
+// other one the slots of the rod nodes.
+static StepArgs chain_args(const lb_ctx *c, int src, int dst) {
+    StepArgs a = step_args(c, src);
+    char *o = static_cast<char *>(c->f[src ^ 1]);
+    a.jm = o;
+    a.mom = o + 5 * size_t(c->fs) * (c->p.prec == LB_F64 ? 8 : 4);
+    a.fdst = c->f[dst];
     return a;
 }
 
@@ -694,6 +726,8 @@ static CGArgs cg_args(const lb_ctx *c, int cur) {
     a.pz = p.periodic[2];
     a.fs = c->fs;
     a.nodes = nodes(&p);
+    a.by_nx = Divider(p.nx);
+    a.by_ny = Divider(p.ny);
     for (int k = 0; k < 2; ++k) {
         a.omega[k] = 1.0 / p.tau[k];
         a.rho_ref[k] = c->rref[k];
@@ -718,15 +752,36 @@ static hipError_t sink_heights(lb_ctx *c, hipStream_t s) {
                                c->hbuf + size_t(c->cur) * slab, s);
 }
 
+// nsteps >= 2 steps from populations to populations with moments in between,
+// each followed by the rod update if there are rods
+static int run_chain(lb_ctx *c, int32_t nsteps, hipStream_t stream) {
+    const lb_params &p = c->p;
+    const int src = c->cur, dst = (src + nsteps) & 1;
+    const StepArgs a = chain_args(c, src, dst);
+    for (int s = 0; s < nsteps; ++s) {
+        const bool last = s + 1 == nsteps;
+        hipError_t e = launch_sc_split(p.prec, a, s > 0, !last, stream);
+        if (e == hipSuccess && p.n_rods > 0)
+            e = launch_rods_step(p.prec, RodBatch{c->rodargs_dev + (last ? dst : src), nullptr, 1}, 1, p.n_rods,
+                                 rod_nblk(p), p.n_rods, !last, stream);
+        if (e != hipSuccess) return hip_fail(e, "step launch");
+    }
+    c->cur = dst;
+    c->steps += nsteps;
+    c->rho_fresh = 1;
+    return LB_OK;
+}
+
 extern "C" {
 
 int lb_step(lb_ctx *c, int32_t nsteps, hipStream_t stream) {
     if (!c) return fail(LB_EINVAL, "null ctx");
     if (nsteps < 0) return fail(LB_EINVAL, "negative step count");
     const lb_params &p = c->p;
+    if (nsteps >= 2 && p.n_rods == 0 && moment_chain(p)) return run_chain(c, nsteps, stream);
     for (int s = 0; s < nsteps; ++s) {
         hipError_t e = p.model == LB_MODEL_CG ? launch_cg_step(p.prec, cg_args(c, c->cur), stream)
-                       : two_pass(p)          ? launch_sc_split(p.prec, step_args(c, c->cur), stream)
+                       : two_pass(p)          ? launch_sc_split(p.prec, step_args(c, c->cur), false, false, stream)
                                               : launch_sc_step(p.prec, c->tile, step_args(c, c->cur), stream);
         if (e != hipSuccess) return hip_fail(e, "step launch");
         c->cur ^= 1;
@@ -1407,8 +1462,21 @@ int lb_rods_step(lb_ctx *c, hipStream_t stream) {
     // current state (the update keeps them so for the nodes it refills), else
     // they sum the populations themselves
     HIP_TRY(launch_rods_step(c->p.prec, RodBatch{c->rodargs_dev + c->cur, nullptr, c->rho_fresh}, 1, c->p.n_rods,
-                             rod_nblk(c->p), c->p.n_rods, stream),
+                             rod_nblk(c->p), c->p.n_rods, false, stream),
             "rods step");
+    return LB_OK;
+}
+
+int lb_coupled_step(lb_ctx *c, int32_t nsteps, hipStream_t stream) {
+    if (!c) return fail(LB_EINVAL, "null ctx");
+    if (nsteps < 0) return fail(LB_EINVAL, "negative step count");
+    if (nsteps >= 2 && c->p.n_rods > 0 && moment_chain(c->p)) return run_chain(c, nsteps, stream);
+    if (fil_beads(&c->p) == 0 && c->p.n_rods == 0) return lb_step(c, nsteps, stream);
+    for (int s = 0; s < nsteps; ++s) {
+        int rc = lb_step(c, 1, stream);
+        if (rc == LB_OK) rc = fil_beads(&c->p) > 0 ? lb_fil_step(c, stream) : lb_rods_step(c, stream);
+        if (rc != LB_OK) return rc;
+    }
     return LB_OK;
 }
 
@@ -1697,7 +1765,7 @@ hipError_t batch_enqueue(lb_batch *b, int par, bool rods, hipStream_t s) {
     // of the next parity
     if (rods && b->total_rods > 0)
         return launch_rods_step(b->prec, RodBatch{b->rods + size_t(par ^ 1) * n, b->rodmap, 1}, n, b->total_rods,
-                                b->nblk_max, b->max_rods, s);
+                                b->nblk_max, b->max_rods, false, s);
     return hipSuccess;
 }
 
@@ -1738,6 +1806,7 @@ int lb_batch_create(lb_ctx *const *ctxs, int32_t n, void *workspace, hipStream_t
             sa[size_t(q) * n + i] = step_args(c, c->cur ^ q);
             ra[size_t(q) * n + i] = rod_args(c);
             ra[size_t(q) * n + i].f = c->f[c->cur ^ q];
+            ra[size_t(q) * n + i].f2 = c->f[c->cur ^ q ^ 1];
         }
         for (int r = 0; r < c->p.n_rods; ++r) rmap.push_back(make_int2(i, r));
         if (c->p.n_rods > 0) {

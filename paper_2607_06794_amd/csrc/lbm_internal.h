@@ -9,6 +9,21 @@
 namespace lbm {
 
 // Arguments of the fused step kernel (passed by value as kernel arguments).
+// n / d for n < 2^31 by a divisor known at the launch: a product and a shift
+// (m = floor(2^(31 + s) / d) + 1 with 2^s >= d makes the quotient exact)
+struct Divider {
+    uint32_t m = 0;
+    int s = 0;
+    Divider() = default;
+    explicit Divider(uint32_t d) {
+        while ((uint64_t(1) << s) < d) ++s;
+        m = static_cast<uint32_t>((uint64_t(1) << (31 + s)) / d + 1);
+    }
+    __host__ __device__ uint32_t operator()(uint32_t n) const {
+        return static_cast<uint32_t>((uint64_t(n) * m) >> 31 >> s);
+    }
+};
+
 struct StepArgs {
     const void *fsrc;
     void *fdst;
@@ -33,6 +48,9 @@ struct StepArgs {
     int32_t *h_write;       // the same for this step
     double *sink_ledger;    // [ntx*nty*nzc][2] mass moved A -> B, one running pair per work-group
     void *rho_out;          // [2][fs] densities in compute precision (two-pass step: psi_k of every node), or null
+    Divider by_nx, by_ny;
+    void *jm;               // two-pass step: 5 arrays for j and the deviations between the passes
+    void *mom;              // two-pass step: the state as moments, 10 fs elements (see node_access.h)
     uint32_t sr_key;        // 16-bit storage: nonzero = stochastic rounding keyed by this step value
 };
 
@@ -46,6 +64,7 @@ struct CGArgs {
     int px, py, pz;
     int64_t fs;     // elements between population arrays
     int64_t nodes;  // nx * ny * nz
+    Divider by_nx, by_ny;
     double omega[2];
     double sigma, beta, grad_eps;
     double g[3];
@@ -77,6 +96,7 @@ constexpr int ROD_NBR = 64;                                  // neighbour-list e
 
 struct RodArgs {
     void *f;    // current populations (post-collision state)
+    void *f2;   // the other population buffer
     void *rho;  // [2][fs] fluid densities of the current state (compute precision)
     double *rods;
     double *part_adh, *part_upd, *part_link;  // [n_rods][nblk][ROD_PART] partial sums
@@ -108,9 +128,10 @@ struct RodBatch {
 // a: host copy of the single lattice's record (sizes, newid), bt its device copy
 hipError_t launch_rods_place(int prec, const RodArgs &a, const RodBatch &bt, hipStream_t s);
 // one rod update for every lattice of bt: n_lat lattices, total_rods rods,
-// nblk_max surface-list work-groups per rod and max_rods rods per lattice at most
+// nblk_max surface-list work-groups per rod and max_rods rods per lattice at most.
+// mom: the state is kept as moments in f2, the slots of the rod nodes in f
 hipError_t launch_rods_step(int prec, const RodBatch &bt, int n_lat, int total_rods, int nblk_max, int max_rods,
-                            hipStream_t s);
+                            bool mom, hipStream_t s);
 hipError_t launch_rods_sums(const RodArgs &a, double *out, hipStream_t s);
 // surrogate jump of one lattice's rods: centres advected by `steps` times the
 // mean of the coarse velocities of canvases c0 and c1 ([D][H][W][8]); then all
@@ -166,7 +187,9 @@ hipError_t launch_sc_step_batch(int prec, const TileCfg &t, const StepArgs *all,
                                 hipStream_t s);
 // the two-pass form of the step (tau = 1): a.rho_out holds psi_k of
 // every node between the passes; work entries are (lattice, block of nodes)
-hipError_t launch_sc_split(int prec, const StepArgs &a, hipStream_t s);
+// src, dst: the state before and after the step is kept as moments in a.mom
+// (FP32 or FP64 storage, no sink; see node_access.h), else as populations
+hipError_t launch_sc_split(int prec, const StepArgs &a, bool src, bool dst, hipStream_t s);
 hipError_t launch_sc_split_batch(int prec, const StepArgs *all, const int2 *work, int nwork, hipStream_t s);
 __host__ __device__ int split_blocks(int nx, int ny, int nz);
 int tiles_xy(int nx, int ny, int tile_y);

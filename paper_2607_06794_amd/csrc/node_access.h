@@ -101,6 +101,100 @@ __device__ inline typename Codec<S>::C get_moment(__amdgpu_buffer_rsrc_t r, uint
     }
 }
 
+// f^eq of one component at a node (Eq. 2) as deviations from w_i rref, in the form
+// that every pass shares: with R = rho / 18, A = (rho - rref) / 18 - 3/2 R u^2,
+//   f^eq_i - w_i rref = A + R c.u (3 + 9/2 c.u)    (half of it for the diagonals),
+// evaluated with the roundings written here and no others, so that a population
+// computed again from the same (rho, u) is the same number.  The rest population
+// is the remainder, dr - sum of the others, so that sum_i f_i^eq = rho holds up to
+// one rounding: the rounded weights do not sum to one, and using them for all 19
+// directions would drift the mass by a fixed factor every step.
+__device__ inline float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ inline double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+template <class C>
+struct Eq {
+    C A, R, u[3];
+};
+template <class C>
+__device__ inline Eq<C> make_eq(C dr, C rho, C ux, C uy, C uz) {
+#pragma clang fp contract(off)
+    Eq<C> e;
+    const C usq = fma_(uz, uz, fma_(uy, uy, ux * ux));
+    e.R = wgt<C>(1) * rho;
+    e.A = fma_(e.R, C(-1.5) * usq, wgt<C>(1) * dr);
+    e.u[0] = ux;
+    e.u[1] = uy;
+    e.u[2] = uz;
+    return e;
+}
+// direction i > 0; u(d): component d of the velocity
+template <class C, class F>
+__device__ inline C eq_pop(int i, C A, C R, F u) {
+#pragma clang fp contract(off)
+    C cu = C(0);
+    if (cx(i)) cu = cx(i) > 0 ? u(0) : -u(0);
+    if (cy(i)) cu = cx(i) ? (cy(i) > 0 ? cu + u(1) : cu - u(1)) : (cy(i) > 0 ? u(1) : -u(1));
+    if (cz(i)) cu = cx(i) || cy(i) ? (cz(i) > 0 ? cu + u(2) : cu - u(2)) : (cz(i) > 0 ? u(2) : -u(2));
+    const C f = fma_(R, cu * fma_(C(4.5), cu, C(3)), A);
+    return i <= 6 ? f : C(0.5) * f;
+}
+template <class C>
+__device__ inline C eq_pop(int i, const Eq<C> &e) {
+    return eq_pop(i, e.A, e.R, [&](int d) { return e.u[d]; });
+}
+
+// Between the steps of one call with tau = 1 a node is its moments per component
+// k: (rho_k - rref_k, u_k^eq) as one vector, element n at 4 (k fs + n), and the
+// rest population at (8 + k) fs + n; the others are f^eq_i(rho_k, u_k^eq).
+template <class S>
+__device__ inline void load_state(__amdgpu_buffer_rsrc_t r, uint32_t n, uint32_t fsE, int k, S (&m)[4]) {
+    const uint32_t voff = n * uint32_t(4 * sizeof(S)), soff = uint32_t(4 * k) * fsE;
+#pragma unroll
+    for (int h = 0; h < int(sizeof(S)) / 4; ++h) {
+        const auto v = __builtin_amdgcn_raw_buffer_load_b128(r, voff + 16 * h, soff, 0);
+        if constexpr (sizeof(S) == 4) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) m[q] = __uint_as_float(v[q]);
+        } else {
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                m[2 * h + q] = __hiloint2double(static_cast<int>(v[2 * q + 1]), static_cast<int>(v[2 * q]));
+        }
+    }
+}
+// The store's whole offset is in the lane register: with an SGPR offset the
+// compiler lets the next instruction overwrite the data registers of a 16-byte
+// store, and lanes were seen to store what it wrote (it keeps the wait state that
+// such a store needs only where the offset is a constant).
+template <class S>
+__device__ inline void store_state(__amdgpu_buffer_rsrc_t r, uint32_t n, uint32_t fsE, int k, const S (&m)[4]) {
+    const uint32_t voff = n * uint32_t(4 * sizeof(S)) + uint32_t(4 * k) * fsE;
+#pragma unroll
+    for (int h = 0; h < int(sizeof(S)) / 4; ++h) {
+        __attribute__((ext_vector_type(4))) unsigned int v;
+        if constexpr (sizeof(S) == 4) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] = __float_as_uint(m[q]);
+        } else {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const unsigned long long u = __double_as_longlong(m[2 * h + q]);
+                v[2 * q] = static_cast<unsigned int>(u);
+                v[2 * q + 1] = static_cast<unsigned int>(u >> 32);
+            }
+        }
+        __builtin_amdgcn_raw_buffer_store_b128(v, r, voff + 16 * h, 0, 0);
+    }
+}
+// The entry of a node whose populations are elements of the other population
+// buffer (rod nodes: the slots that the link pass wrote; nodes that the update
+// pass refilled): a quiet NaN of its own payload, which no arithmetic here
+// makes, in place of rho_A - rref_A.
+__device__ inline float pop_mark(float) { return __uint_as_float(0x7FC0B0D5u); }
+__device__ inline double pop_mark(double) { return __longlong_as_double(0x7FF80B0D50000000ll); }
+__device__ inline bool is_pop_mark(float v) { return __float_as_uint(v) == 0x7FC0B0D5u; }
+__device__ inline bool is_pop_mark(double v) { return __double_as_longlong(v) == 0x7FF80B0D50000000ll; }
+
 // A node's coordinates and the index parts of its neighbourhood (wrapped in
 // periodic directions, clamped in closed ones).
 struct NodeNbr {
@@ -109,21 +203,25 @@ struct NodeNbr {
     __device__ inline uint32_t at(int dx, int dy, int dz) const { return zs[1 + dz] + ys[1 + dy] + xs[1 + dx]; }
 };
 template <class Args>
-__device__ inline NodeNbr node_nbr(uint32_t n, const Args &a) {
-    const uint32_t nx = a.nx, ny = a.ny, nxy = nx * ny;
-    const uint32_t z = n / nxy, rem = n - z * nxy, y = rem / nx, x = rem - y * nx;
+__device__ inline NodeNbr node_nbr(uint32_t x, uint32_t y, uint32_t z, const Args &a) {
+    const uint32_t nx = a.nx, ny = a.ny, nz = a.nz, nxy = nx * ny;
     NodeNbr o;
     o.z = int(z);
     o.xs[1] = x;
     o.xs[0] = x > 0 ? x - 1 : (a.px ? nx - 1 : 0);
     o.xs[2] = x + 1 < nx ? x + 1 : (a.px ? 0 : x);
     o.ys[1] = y * nx;
-    o.ys[0] = y > 0 ? (y - 1) * nx : (a.py ? (ny - 1) * nx : 0);
-    o.ys[2] = y + 1 < ny ? (y + 1) * nx : (a.py ? 0 : y * nx);
+    o.ys[0] = y > 0 ? o.ys[1] - nx : (a.py ? (ny - 1) * nx : 0);
+    o.ys[2] = y + 1 < ny ? o.ys[1] + nx : (a.py ? 0 : o.ys[1]);
     o.zs[1] = z * nxy;
-    o.zs[0] = z > 0 ? (z - 1) * nxy : (a.pz ? (a.nz - 1) * nxy : 0);
-    o.zs[2] = int(z) + 1 < a.nz ? (z + 1) * nxy : (a.pz ? 0 : z * nxy);
+    o.zs[0] = z > 0 ? o.zs[1] - nxy : (a.pz ? (nz - 1) * nxy : 0);
+    o.zs[2] = z + 1 < nz ? o.zs[1] + nxy : (a.pz ? 0 : o.zs[1]);
     return o;
+}
+template <class Args>
+__device__ inline NodeNbr node_nbr(uint32_t n, const Args &a) {
+    const uint32_t row = a.by_nx(n), z = a.by_ny(row);
+    return node_nbr(n - row * a.nx, row - z * a.ny, z, a);
 }
 
 // Work-groups are dealt to the eight XCDs round-robin: each XCD takes a

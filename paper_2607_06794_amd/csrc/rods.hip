@@ -21,6 +21,7 @@
 
 #include "lbm_device.h"
 #include "lbm_internal.h"
+#include "node_access.h"
 
 namespace lbm {
 
@@ -299,6 +300,25 @@ __device__ inline void stored_densities(const RodArgs &a, int64_t n, double rho[
     const auto *ro = gptr(static_cast<const typename Codec<S>::C *>(a.rho));
     rho[0] = double(ro[n]);
     rho[1] = double(ro[a.fs + n]);
+}
+
+// The state of node n as moments (see node_access.h): component k's vector, which
+// lies behind the five arrays that the step keeps between its passes in the
+// buffer other than a.f.
+template <class S>
+__device__ inline S *state_at(const RodArgs &a, int64_t n, int k) {
+    return static_cast<S *>(a.f2) + 5 * a.fs + 4 * (k * a.fs + n);
+}
+template <class S>
+__device__ inline S *rest_at(const RodArgs &a, int64_t n, int k) {
+    return static_cast<S *>(a.f2) + (13 + k) * a.fs + n;
+}
+template <class S>
+__device__ inline void state_of(const RodArgs &a, int64_t n, S (&m)[2][4]) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) m[k][q] = gptr(state_at<S>(a, n, k))[q];
 }
 
 // listed node of this thread: false if the entry is past the end of the list
@@ -871,7 +891,7 @@ __global__ void fill_i32_kernel(int *p, int64_t n, int v) {
 //    wavefront each (two lanes per neighbour gather the neighbour densities);
 //    the finding thread then adds the transfer to its own sums.
 // ---------------------------------------------------------------------------
-template <class S>
+template <class S, bool MOM>
 __global__ void __launch_bounds__(RB) rod_update_kernel(RodBatch bt, int init) {
     __shared__ double sh[RB / 64 * 8];
     __shared__ int wcount[RB / 64];
@@ -897,13 +917,29 @@ __global__ void __launch_bounds__(RB) rod_update_kernel(RodBatch bt, int init) {
             if (!init) {
                 const d3 arm = min_image(mk(x, y, z) - X, a);
                 d3 mom = mk(0, 0, 0);
+                // post-collision populations, from the moments where those hold the state
+                Eq<typename Codec<S>::C> eq[2];
+                double rest[2] = {0.0, 0.0};
+                if constexpr (MOM) {
+                    S m[2][4];
+                    state_of<S>(a, n, m);
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        eq[k] = make_eq(m[k][0], S(a.rho_ref[k]) + m[k][0], m[k][1], m[k][2], m[k][3]);
+                        rest[k] = double(gptr(rest_at<S>(a, n, k))[0]);
+                    }
+                    gptr(state_at<S>(a, n, 0))[0] = pop_mark(S(0));
+                }
 #pragma unroll
                 for (int k = 0; k < 2; ++k) {
                     double s = 0.0;
                     d3 jk = mk(0, 0, 0);
 #pragma unroll
                     for (int i = 0; i < Q; ++i) {
-                        const double v = decf(f, (k * Q + i) * a.fs + n) + wgt<double>(i) * a.rho_ref[k];
+                        double d;
+                        if constexpr (MOM) d = i ? double(eq_pop(i, eq[k])) : rest[k];
+                        else d = decf(f, (k * Q + i) * a.fs + n);
+                        const double v = d + wgt<double>(i) * a.rho_ref[k];
                         s += v;
                         jk = jk + v * mk(cx(i), cy(i), cz(i));
                     }
@@ -989,12 +1025,20 @@ __global__ void __launch_bounds__(RB) rod_update_kernel(RodBatch bt, int init) {
         const d3 pu = mk(ux, uy, uz);
         const d3 ub = velocity_at(rod, pu, a);
         const double usq = dot(ub, ub);
+        // (with the state as moments the node keeps its mark: these are read instead)
         if (lane < 2 * Q) {
             const int kk = lane / Q, ii = lane % Q;
             const double cu = cx(ii) * ub.x + cy(ii) * ub.y + cz(ii) * ub.z;
             const double feq = wgt<double>(ii) * (kk ? rb[1] : rb[0]) * (1.0 + 3.0 * cu + 4.5 * cu * cu - 1.5 * usq);
-            f[(kk * Q + ii) * a.fs + un] =
-                Codec<S>::enc(typename Codec<S>::C(feq - wgt<double>(ii) * (kk ? a.rho_ref[1] : a.rho_ref[0])));
+            const S v = Codec<S>::enc(typename Codec<S>::C(feq - wgt<double>(ii) * (kk ? a.rho_ref[1] : a.rho_ref[0])));
+            f[(kk * Q + ii) * a.fs + un] = v;
+            // halfway bounce-back of the next pull, as the collision writes it
+            int xx = ux + cx(ii), yy = uy + cy(ii), zz = uz + cz(ii);
+            const bool okx = wrap_coord(xx, a.nx, a.px), oky = wrap_coord(yy, a.ny, a.py);
+            if (near_wall && okx && oky && wrap_coord(zz, a.nz, a.pz)) {
+                const int64_t q = (int64_t(zz) * a.ny + yy) * a.nx + xx;
+                if (is_static_wall(a.mat[q] & MAT_ID_MASK)) f[(kk * Q + opp(ii)) * a.fs + q] = v;
+            }
         }
         // the refilled node's densities (those of f^eq) keep the density
         // array valid for the passes after this one
@@ -1047,7 +1091,7 @@ __global__ void __launch_bounds__(64) rod_sums_kernel(RodArgs a, double *out) {
 //    momentum they carry.  Without COMMIT (the occupancy is current, as after
 //    a lift): the slots only.
 // ---------------------------------------------------------------------------
-template <class S, bool COMMIT>
+template <class S, bool COMMIT, bool MOM>
 __global__ void __launch_bounds__(RB) rod_link_kernel(RodBatch bt, int init) {
     using C = typename Codec<S>::C;
     __shared__ double sh[RB / 64 * 8];
@@ -1111,11 +1155,26 @@ __global__ void __launch_bounds__(RB) rod_link_kernel(RodBatch bt, int init) {
             // population instead (a line the wave reads anyway), so that no
             // load sits behind a branch that would wait for it
             S fo[Q][2];
+            bool stored = true;
+            if constexpr (MOM) {
+                S m[2][4];
+                state_of<S>(a, n, m);
+                stored = is_pop_mark(m[0][0]);
+                // the populations as the node would store them
 #pragma unroll
-            for (int i = 1; i < Q; ++i) {
-                const bool l = (links >> i) & 1u;
+                for (int k = 0; k < 2; ++k) {
+                    const auto eq = make_eq(m[k][0], S(a.rho_ref[k]) + m[k][0], m[k][1], m[k][2], m[k][3]);
 #pragma unroll
-                for (int k = 0; k < 2; ++k) fo[i][k] = gload(f + (l ? (k * Q + opp(i)) * a.fs : 0) + n);
+                    for (int i = 1; i < Q; ++i) fo[i][k] = eq_pop(opp(i), eq);
+                }
+            }
+            if (stored) {
+#pragma unroll
+                for (int i = 1; i < Q; ++i) {
+                    const bool l = (links >> i) & 1u;
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) fo[i][k] = gload(f + (l ? (k * Q + opp(i)) * a.fs : 0) + n);
+                }
             }
             const d3 dx0 = min_image(mk(x, y, z) - X, a);
             // wall velocity at the link midpoint x - c_i / 2: V + Omega x (dx0 -
@@ -1340,8 +1399,8 @@ hipError_t launch_rods_place(int prec, const RodArgs &a, const RodBatch &bt, hip
     hipLaunchKernelGGL(rod_mask_kernel, dim3(2 * a.n_rods), dim3(MB), 0, s, bt);
     return rods_by_prec(prec, [&](auto *tag) {
         using S = std::remove_pointer_t<decltype(tag)>;
-        hipLaunchKernelGGL(rod_update_kernel<S>, grid, dim3(RB), 0, s, bt, 1);
-        hipLaunchKernelGGL((rod_link_kernel<S, true>), grid, dim3(RB), 0, s, bt, 1);
+        hipLaunchKernelGGL((rod_update_kernel<S, false>), grid, dim3(RB), 0, s, bt, 1);
+        hipLaunchKernelGGL((rod_link_kernel<S, true, false>), grid, dim3(RB), 0, s, bt, 1);
         return hipGetLastError();
     });
 }
@@ -1370,7 +1429,7 @@ hipError_t launch_rods_link(int prec, const RodArgs &a, const RodBatch &bt, hipS
     const dim3 grid(a.nblk, a.n_rods);
     return rods_by_prec(prec, [&](auto *tag) {
         using S = std::remove_pointer_t<decltype(tag)>;
-        hipLaunchKernelGGL((rod_link_kernel<S, false>), grid, dim3(RB), 0, s, bt, 0);
+        hipLaunchKernelGGL((rod_link_kernel<S, false, false>), grid, dim3(RB), 0, s, bt, 0);
         return hipGetLastError();
     });
 }
@@ -1381,7 +1440,7 @@ hipError_t launch_rods_sums(const RodArgs &a, double *out, hipStream_t s) {
 }
 
 hipError_t launch_rods_step(int prec, const RodBatch &bt, int n_lat, int total_rods, int nblk_max, int max_rods,
-                            hipStream_t s) {
+                            bool mom, hipStream_t s) {
     if (total_rods == 0) return hipSuccess;
     const dim3 grid(nblk_max, total_rods);
     return rods_by_prec(prec, [&](auto *tag) {
@@ -1391,8 +1450,16 @@ hipError_t launch_rods_step(int prec, const RodBatch &bt, int n_lat, int total_r
                            s, bt);
         // the re-mask, with one work-group per rod more for the neighbour lists
         hipLaunchKernelGGL(rod_mask_kernel, dim3(2 * total_rods), dim3(MB), 0, s, bt);
-        hipLaunchKernelGGL(rod_update_kernel<S>, grid, dim3(RB), 0, s, bt, 0);
-        hipLaunchKernelGGL((rod_link_kernel<S, true>), grid, dim3(RB), 0, s, bt, 0);
+        if constexpr (sizeof(S) >= 4) {
+            if (mom) {
+                hipLaunchKernelGGL((rod_update_kernel<S, true>), grid, dim3(RB), 0, s, bt, 0);
+                hipLaunchKernelGGL((rod_link_kernel<S, true, true>), grid, dim3(RB), 0, s, bt, 0);
+                return hipGetLastError();
+            }
+        }
+        if (mom) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((rod_update_kernel<S, false>), grid, dim3(RB), 0, s, bt, 0);
+        hipLaunchKernelGGL((rod_link_kernel<S, true, false>), grid, dim3(RB), 0, s, bt, 0);
         return hipGetLastError();
     });
 }

@@ -640,6 +640,97 @@ __global__ void __launch_bounds__(64 * TY) sc_step_batch_kernel(const StepArgs *
 // ---------------------------------------------------------------------------
 __host__ __device__ int split_blocks(int nx, int ny, int nz) { return int((int64_t(nx) * ny * nz + NB - 1) / NB); }
 
+// Books one streaming's exchange with the reservoir into the slot of block b:
+// out(k, i) = f*_i - w_i rref_k of a node below it (here), for c_iz = +1.
+template <class F>
+__device__ __forceinline__ void book_top(const StepArgs &a, int b, bool here, double (&red)[NB / 64][2], F out) {
+    const uint32_t nxy = static_cast<uint32_t>(a.nx) * a.ny;
+    const uint32_t b0 = a.evap ? (uint32_t(a.nz - 2) * nxy) / NB : 0;
+    if (!(a.evap && uint32_t(b) >= b0 && uint32_t(b) <= (uint32_t(a.nz - 1) * nxy - 1) / NB)) return;  // uniform
+    double led[2] = {0.0, 0.0};
+    if (here) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            double outflow = 0.0, inflow = 0.0;
+#pragma unroll
+            for (int i = 0; i < Q; ++i) {
+                if (cz(i) == 1) outflow += double(out(k, i)) + wgt<double>(i) * a.rho_ref[k];
+                if (cz(i) == -1) inflow += wgt<double>(i) * a.rho_top[k];
+            }
+            led[k] = outflow - inflow;
+        }
+    }
+    const double l0 = wave_sum(led[0]), l1 = wave_sum(led[1]);
+    if ((threadIdx.x & 63) == 0) {
+        red[threadIdx.x >> 6][0] = l0;
+        red[threadIdx.x >> 6][1] = l1;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        double s = 0.0;
+        for (int q = 0; q < NB / 64; ++q) s += red[q][threadIdx.x];
+        a.ledger_part[2 * (b - b0) + threadIdx.x] += s;
+    }
+}
+
+// Sums of component k's streamed deviations fv (Eq. 3): rho_k - rref_k and j_k.
+// top: the plane below the reservoir, which sends w_i rho_top_k.
+template <class C>
+__device__ __forceinline__ void stream_moments(const StepArgs &a, int k, bool top, C (&fv)[Q], C &dr, C (&j)[3]) {
+    const C tdev = C(a.rho_top[k] - a.rho_ref[k]);
+#pragma unroll
+    for (int i = 0; i < Q; ++i)
+        if (cz(i) == -1) fv[i] = top ? wgt<C>(i) * tdev : fv[i];
+    C s = C(0), jx = C(0), jy = C(0), jz = C(0);
+#pragma unroll
+    for (int i = 0; i < Q; ++i) s += fv[i];
+    // momentum over opposite pairs: f_i - f_opp(i) is nearly exact
+    // (the two are close), which avoids cancellation in j
+#pragma unroll
+    for (int i = 1; i < Q; i += 2) {
+        const C d = fv[i] - fv[i + 1];
+        if (cx(i) == 1) jx += d;
+        if (cx(i) == -1) jx -= d;
+        if (cy(i) == 1) jy += d;
+        if (cy(i) == -1) jy -= d;
+        if (cz(i) == 1) jz += d;
+        if (cz(i) == -1) jz -= d;
+    }
+    dr = s;
+    j[0] = jx;
+    j[1] = jy;
+    j[2] = jz;
+}
+
+// Node n after streaming: psi_k into a.rho_out, j (and, with a storage
+// reference, the deviations) into a.jm.
+template <class S>
+__device__ __forceinline__ void stream_store(const StepArgs &a, uint32_t n, uint8_t m, const typename Codec<S>::C (&dr)[2],
+                                             const typename Codec<S>::C (&j)[2][3]) {
+    using C = typename Codec<S>::C;
+    constexpr uint32_t E = sizeof(S);
+    const uint32_t fsE = static_cast<uint32_t>(a.fs) * E;
+    const bool fluid = m == MAT_FLUID;
+    // sum_i f_i = rref_k + sum_i d_i (sum_i w_i = 1)
+    C rho[2] = {C(a.rho_ref[0]) + dr[0], C(a.rho_ref[1]) + dr[1]};
+    C *psi = static_cast<C *>(a.rho_out);
+    if (!fluid) {
+        rho[0] = C(gptr(a.psi_tab)[2 * m]);
+        rho[1] = C(gptr(a.psi_tab)[2 * m + 1]);
+    }
+    gptr(psi)[n] = rho[0];
+    gptr(psi)[a.fs + n] = rho[1];
+    if (fluid) {
+        const auto dst = make_rsrc(a.jm, Q * fsE);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) put_moment<S>(dst, n * E, fsE, d, j[0][d] + j[1][d]);
+        if (a.rho_ref[0] != 0.0 || a.rho_ref[1] != 0.0) {
+            put_moment<S>(dst, n * E, fsE, 3, dr[0]);
+            put_moment<S>(dst, n * E, fsE, 4, dr[1]);
+        }
+    }
+}
+
 template <class S>
 __device__ __forceinline__ void sc_stream_nodes(const StepArgs &a, int b) {
     using C = typename Codec<S>::C;
@@ -662,95 +753,29 @@ __device__ __forceinline__ void sc_stream_nodes(const StepArgs &a, int b) {
 #pragma unroll
         for (int i = 0; i < Q; ++i) raw[k][i] = buf_load<S>(src, nb.at(-cx(i), -cy(i), -cz(i)) * E, i * fsE);
     }
-    C rho[2], dr[2], j[2][3];
+    C dr[2], j[2][3];
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-        const C tdev = C(a.rho_top[k] - a.rho_ref[k]);
         C fv[Q];
 #pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            fv[i] = Codec<S>::dec(raw[k][i]);
-            if (cz(i) == -1) fv[i] = top ? wgt<C>(i) * tdev : fv[i];
-        }
-        C s = C(0), jx = C(0), jy = C(0), jz = C(0);
-#pragma unroll
-        for (int i = 0; i < Q; ++i) s += fv[i];
-        // momentum over opposite pairs: f_i - f_opp(i) is nearly exact
-        // (the two are close), which avoids cancellation in j
-#pragma unroll
-        for (int i = 1; i < Q; i += 2) {
-            const C d = fv[i] - fv[i + 1];
-            if (cx(i) == 1) jx += d;
-            if (cx(i) == -1) jx -= d;
-            if (cy(i) == 1) jy += d;
-            if (cy(i) == -1) jy -= d;
-            if (cz(i) == 1) jz += d;
-            if (cz(i) == -1) jz -= d;
-        }
-        // Eq. 3: rho_k = sum_i f_i = rref_k + sum_i d_i (sum_i w_i = 1)
-        dr[k] = s;
-        rho[k] = C(a.rho_ref[k]) + s;
-        j[k][0] = jx;
-        j[k][1] = jy;
-        j[k][2] = jz;
+        for (int i = 0; i < Q; ++i) fv[i] = Codec<S>::dec(raw[k][i]);
+        stream_moments(a, k, top, fv, dr[k], j[k]);
     }
-    if (act) {
-        C *psi = static_cast<C *>(a.rho_out);
-        if (!fluid) {
-            rho[0] = C(gptr(a.psi_tab)[2 * m]);
-            rho[1] = C(gptr(a.psi_tab)[2 * m + 1]);
-        }
-        gptr(psi)[n] = rho[0];
-        gptr(psi)[a.fs + n] = rho[1];
-        if (fluid) {
-            const auto dst = make_rsrc(a.fdst, Q * fsE);
-#pragma unroll
-            for (int d = 0; d < 3; ++d) put_moment<S>(dst, n * E, fsE, d, j[0][d] + j[1][d]);
-            if (a.rho_ref[0] != 0.0 || a.rho_ref[1] != 0.0) {
-                put_moment<S>(dst, n * E, fsE, 3, dr[0]);
-                put_moment<S>(dst, n * E, fsE, 4, dr[1]);
-            }
-        }
-    }
+    if (act) stream_store<S>(a, n, m, dr, j);
     // the sink's column counts of this step start at zero (the collide pass adds)
     if (a.sink && n0 < nxy) a.h_write[n0] = 0;
     // ledger: this step's streaming moves the stored f*_i(t) with c_iz = +1 of
     // the plane below the reservoir into it and pulls w_i rho_top_k out of it
-    const uint32_t b0 = a.evap ? (uint32_t(a.nz - 2) * nxy) / NB : 0;
-    if (a.evap && uint32_t(b) >= b0 && uint32_t(b) <= (uint32_t(a.nz - 1) * nxy - 1) / NB) {  // uniform
-        double led[2] = {0.0, 0.0};
-        if (act && fluid && top) {
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const auto src = make_rsrc(static_cast<const char *>(a.fsrc) + size_t(k) * Q * fsE, Q * fsE);
-                double outflow = 0.0, inflow = 0.0;
-#pragma unroll
-                for (int i = 0; i < Q; ++i) {
-                    if (cz(i) == 1)
-                        outflow +=
-                            double(Codec<S>::dec(buf_load<S>(src, n * E, i * fsE))) + wgt<double>(i) * a.rho_ref[k];
-                    if (cz(i) == -1) inflow += wgt<double>(i) * a.rho_top[k];
-                }
-                led[k] = outflow - inflow;
-            }
-        }
-        const double l0 = wave_sum(led[0]), l1 = wave_sum(led[1]);
-        if ((threadIdx.x & 63) == 0) {
-            red[threadIdx.x >> 6][0] = l0;
-            red[threadIdx.x >> 6][1] = l1;
-        }
-        __syncthreads();
-        if (threadIdx.x < 2) {
-            double s = 0.0;
-            for (int q = 0; q < NB / 64; ++q) s += red[q][threadIdx.x];
-            a.ledger_part[2 * (b - b0) + threadIdx.x] += s;
-        }
-    }
+    book_top(a, b, act && fluid && top, red, [&](int k, int i) {
+        const auto src = make_rsrc(static_cast<const char *>(a.fsrc) + size_t(k) * Q * fsE, Q * fsE);
+        return Codec<S>::dec(buf_load<S>(src, n * E, i * fsE));
+    });
 }
 
 // Collides one node per thread of block b.  Returns the mass the sink moved
 // from A to B there.
-template <class S, bool SINK = false>
+// DST: the new state is kept as moments (a.mom), else as populations (a.fdst).
+template <class S, bool SINK = false, bool DST = false>
 __device__ __forceinline__ double sc_collide_nodes(const StepArgs &a, int b) {
     using C = typename Codec<S>::C;
     constexpr uint32_t E = sizeof(S);
@@ -798,7 +823,7 @@ __device__ __forceinline__ double sc_collide_nodes(const StepArgs &a, int b) {
     const uint8_t mid = mt & MAT_ID_MASK;
     if (mid != MAT_FLUID && mid != MAT_ROD) return 0.0;
     const bool fluid = mid == MAT_FLUID;
-    const auto dst0 = make_rsrc(a.fdst, Q * fsE);
+    const auto dst0 = make_rsrc(a.jm, Q * fsE);
     const C rho[2] = {fluid ? own[0] : C(0), fluid ? own[1] : C(0)};
     C j[3] = {C(0), C(0), C(0)}, dr[2] = {rho[0], rho[1]};
     if (fluid) {
@@ -863,29 +888,23 @@ __device__ __forceinline__ double sc_collide_nodes(const StepArgs &a, int b) {
         const C rk = ok ? C(1) / rho[k] : C(0);
 #pragma unroll
         for (int d = 0; d < 3; ++d) ue[d] = j[d] * ir + F[k][d] * rk;
-        const C usq = ue[0] * ue[0] + ue[1] * ue[1] + ue[2] * ue[2];
-        S sstar[Q];
-        C deq_sum = C(0);
-        // Eq. 2 as a deviation, built per opposite pair (i, opp(i)):
-        //   f^eq - w rref = w (rho - rref) + w rho [9/2 (c.u)^2 - 3/2 u^2]  +-  w rho 3 c.u
-        // The rest population is the remainder so that sum_i f_i^eq = rho holds up to
-        // one rounding: the rounded weights do not sum to one, and using them for all
-        // 19 directions would drift the mass by a fixed factor every step.
-        C deq[Q];
-        const C base = C(-1.5) * usq;
+        // Eq. 2 with tau = 1: f* = f^eq
+        const Eq<C> eq = make_eq(dr[k], rho[k], ue[0], ue[1], ue[2]);
+        C deq[Q], deq_sum = C(0);
 #pragma unroll
-        for (int i = 1; i < Q; i += 2) {
-            const C cu = C(cx(i)) * ue[0] + C(cy(i)) * ue[1] + C(cz(i)) * ue[2];
-            const C wr = wgt<C>(i) * rho[k];
-            const C sym = wgt<C>(i) * dr[k] + wr * (base + C(4.5) * cu * cu);
-            const C asym = wr * (C(3) * cu);
-            deq[i] = sym + asym;
-            deq[i + 1] = sym - asym;
+        for (int i = 1; i < Q; ++i) {
+            deq[i] = eq_pop(i, eq);
             deq_sum += deq[i];
-            deq_sum += deq[i + 1];
         }
         deq[0] = dr[k] - deq_sum;
-        // Eq. 1 with tau = 1: f* = f^eq
+        if constexpr (DST) {
+            const C v[4] = {fluid ? dr[k] : pop_mark(C(0)), ue[0], ue[1], ue[2]};
+            const auto st = make_rsrc(a.mom, 10 * fsE);
+            store_state<S>(st, n, fsE, k, v);
+            put_moment<S>(st, n * E, fsE, 8 + k, deq[0]);
+            continue;
+        }
+        S sstar[Q];
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
             C ds = deq[i];
@@ -926,10 +945,175 @@ template <class S>
 __global__ void __launch_bounds__(NB) sc_stream_kernel(StepArgs a) {
     sc_stream_nodes<S>(a, xcd_range(blockIdx.x, gridDim.x));
 }
-template <class S, bool SINK>
+// The stream pass from moments.  A work-group takes a brick of XB x YB x ZB
+// nodes; the moments of the brick and its ring go to LDS once, as what the
+// populations need of a node (A, R and u, see node_access.h), so that the 18 x 2
+// evaluations per node read 3 or 4 values each.  The work-groups past the
+// bricks book the streaming's exchange with the reservoir.
+//
+// Against the pass over populations it reads 40 bytes per FP32 node instead of
+// 152, and the collision behind it stores 40 instead of 152; what bounds it is
+// the evaluation (about 450 vector and 140 LDS instructions per node).  Per step
+// in a call of many, populations -> moments:
+//   FP32 256 x 128 x 64: 124 -> 66 us (48 + 27 in the profiler's clocks);
+//     128 x 64 x 64: 33 -> 26; 117 x 51 x 37: 18.3 -> 17.4
+//   FP64 256 x 128 x 64: 304 -> 138 us; 128 x 64 x 64: 64 -> 43; 32^3: 14.5 -> 13
+// (128 x 64 x 32 alone is even in FP32, 18.8 -> 19.5), so every call of two steps
+// or more takes it.  Bricks of 32 x 4 x 4 are as fast on large lattices and
+// 8 percent slower on the ragged one; reading the neighbours' moments through L1
+// instead of LDS: 61 us for the pass, before the rest population had its array.
+constexpr int XB = 32, YB = 4, ZB = 2, BT = XB * YB * ZB;
+constexpr int XH = XB + 2, YH = YB + 2, ZH = ZB + 2, BH = XH * YH * ZH;
+static_assert(BT == NB, "the booking work-groups take blocks of NB nodes");
+__host__ __device__ int state_bricks(int nx, int ny, int nz) {
+    return ((nx + XB - 1) / XB) * ((ny + YB - 1) / YB) * ((nz + ZB - 1) / ZB);
+}
+
+template <class S>
+__device__ __forceinline__ void sc_stream_state(const StepArgs &a, int b) {
+    using C = S;  // FP32 and FP64 storage only
+    constexpr uint32_t E = sizeof(S);
+    extern __shared__ char lds_raw[];
+    __shared__ int wmark[BT / 64];
+    __shared__ double led[NB / 64][2];
+    C *sh = reinterpret_cast<C *>(lds_raw);  // [2][A, R, ux, uy, uz][BH]
+    auto val = [&](int k, int q, int h) -> C & { return sh[(5 * k + q) * BH + h]; };
+    const int nbx = (a.nx + XB - 1) / XB, nby = (a.ny + YB - 1) / YB, nbr = state_bricks(a.nx, a.ny, a.nz);
+    const uint32_t nxy = static_cast<uint32_t>(a.nx) * a.ny, fsE = static_cast<uint32_t>(a.fs) * E;
+    const C rref[2] = {C(a.rho_ref[0]), C(a.rho_ref[1])};
+    const auto st = make_rsrc(a.mom, 10 * fsE);
+    const auto src = [&](int k) { return make_rsrc(static_cast<const char *>(a.fsrc) + size_t(k) * Q * fsE, Q * fsE); };
+    if (b >= nbr) {  // uniform per block
+        const int bb = b - nbr + int(uint32_t(a.nz - 2) * nxy / NB);
+        const uint32_t n = static_cast<uint32_t>(bb) * NB + threadIdx.x;
+        const bool here = n / nxy + 2 == static_cast<uint32_t>(a.nz) &&
+                          (gptr(a.mat)[n] & MAT_ID_MASK) == MAT_FLUID;
+        book_top(a, bb, here, led, [&](int k, int i) {
+            C v[4], v0[4];
+            load_state<S>(st, n, fsE, k, v);
+            load_state<S>(st, n, fsE, 0, v0);
+            const C f = buf_load<S>(src(k), n * E, i * fsE);
+            return is_pop_mark(v0[0]) ? f : eq_pop(i, make_eq(v[0], rref[k] + v[0], v[1], v[2], v[3]));
+        });
+        return;
+    }
+    // z fastest: an XCD's range is whole columns, so that rods lying on the
+    // substrate are shared out (in z slabs they would be one XCD's)
+    const int nbz = nbr / (nbx * nby), col = b / nbz;
+    const int x0 = col % nbx * XB, y0 = col / nbx * YB, z0 = (b - col * nbz) * ZB;
+    // coordinate of the ring: wrapped, or clamped where nothing reads it
+    auto at = [](int v, int n, int per) {
+        const int lo = per ? n - 1 : 0, hi = per ? 0 : n - 1;
+        return v < 0 ? lo : (v >= n ? hi : v);
+    };
+    constexpr int HL = (BH + BT - 1) / BT;
+    C v[HL][2][4];
+#pragma unroll
+    for (int l = 0; l < HL; ++l) {
+        const int h = min(int(threadIdx.x) + BT * l, BH - 1);
+        const int x = min(x0 - 1 + h % XH, a.nx), y = min(y0 - 1 + h / XH % YH, a.ny), z = min(z0 - 1 + h / (XH * YH), a.nz);
+        const uint32_t n = uint32_t(at(z, a.nz, a.pz)) * nxy + uint32_t(at(y, a.ny, a.py)) * a.nx + at(x, a.nx, a.px);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) load_state<S>(st, n, fsE, k, v[l][k]);
+    }
+    const int tx = threadIdx.x % XB, ty = threadIdx.x / XB % YB, tz = threadIdx.x / (XB * YB);
+    const int x = x0 + tx, y = y0 + ty, z = z0 + tz;
+    const bool act = x < a.nx && y < a.ny && z < a.nz;
+    const uint32_t n = act ? uint32_t(z) * nxy + uint32_t(y) * a.nx + x : 0;
+    const uint8_t mt = gptr(a.mat)[n], m = mt & MAT_ID_MASK;
+    const C rest[2] = {get_moment<S>(st, n * E, fsE, 8), get_moment<S>(st, n * E, fsE, 9)};
+    bool mark = false;
+#pragma unroll
+    for (int l = 0; l < HL; ++l) {
+        const int h = threadIdx.x + BT * l;
+        if (h >= BH) continue;
+        mark |= is_pop_mark(v[l][0][0]);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const C *w = v[l][k];
+            const Eq<C> e = make_eq(w[0], rref[k] + w[0], w[1], w[2], w[3]);
+            val(k, 0, h) = is_pop_mark(w[0]) ? w[0] : e.A;
+            val(k, 1, h) = e.R;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) val(k, 2 + d, h) = e.u[d];
+        }
+    }
+    const bool any = __any(mark);
+    if ((threadIdx.x & 63) == 0) wmark[threadIdx.x >> 6] = any;
+    __syncthreads();
+    bool marks = false;  // the brick or its ring holds a marked node
+#pragma unroll
+    for (int q = 0; q < BT / 64; ++q) marks |= wmark[q] != 0;
+    if (!act) return;
+    const int hc = ((tz + 1) * YH + ty + 1) * XH + tx + 1;
+    const bool fluid = m == MAT_FLUID, top = a.evap && z == a.nz - 2;
+    const auto ring = [&](int i) { return hc - ((cz(i) * YH + cy(i)) * XH + cx(i)); };
+    const NodeNbr nb = node_nbr(x, y, z, a);
+    const auto nbr_at = [&](int i) { return nb.at(-cx(i), -cy(i), -cz(i)); };
+    // directions that come from a static wall, and from a marked node (bit 0: this one)
+    unsigned walls = 0, slots = 0;
+    if (fluid && (mt & MAT_NEAR_WALL)) {
+        uint8_t mq[Q];
+#pragma unroll
+        for (int i = 1; i < Q; ++i) mq[i] = gptr(a.mat)[nbr_at(i)] & MAT_ID_MASK;
+#pragma unroll
+        for (int i = 1; i < Q; ++i) walls |= is_static_wall(mq[i]) ? 1u << i : 0u;
+    }
+    if (marks && fluid) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) slots |= is_pop_mark(val(0, 0, ring(i))) ? 1u << i : 0u;
+    }
+    C dr[2], j[2][3];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        C fv[Q];
+        fv[0] = rest[k];
+#pragma unroll
+        for (int i = 1; i < Q; ++i) {
+            const int h = ring(i);
+            fv[i] = eq_pop(i, val(k, 0, h), val(k, 1, h), [&](int d) { return val(k, 2 + d, h); });
+        }
+        // halfway bounce-back: from a static wall comes the node's own f*_opp(i)
+        if (walls) {
+            const Eq<C> e{val(k, 0, hc), val(k, 1, hc), {val(k, 2, hc), val(k, 3, hc), val(k, 4, hc)}};
+#pragma unroll
+            for (int i = 1; i < Q; ++i) fv[i] = (walls >> i) & 1u ? eq_pop(opp(i), e) : fv[i];
+        }
+        // from a marked node the element of its population; directions without one
+        // read the node's first element again, so that all loads are in flight
+        // together and cost no lines of their own
+        if (slots) {
+            // a marked node's own populations are what its walls return
+            const unsigned far = slots & ~walls, self = slots & 1u ? walls : 0u;
+            S slot[Q];
+#pragma unroll
+            for (int i = 0; i < Q; ++i) {
+                uint32_t v = n * E;
+                v = far >> i & 1u ? nbr_at(i) * E + i * fsE : v;
+                v = self >> i & 1u ? n * E + opp(i) * fsE : v;
+                slot[i] = buf_load<S>(src(k), v, 0);
+            }
+#pragma unroll
+            for (int i = 0; i < Q; ++i) fv[i] = (far | self) >> i & 1u ? Codec<S>::dec(slot[i]) : fv[i];
+        }
+        stream_moments(a, k, top, fv, dr[k], j[k]);
+    }
+    stream_store<S>(a, n, m, dr, j);
+}
+
+template <class S>
+__global__ void __launch_bounds__(BT, sizeof(S) == 4 ? 5 : 2) sc_stream_state_kernel(StepArgs a) {
+    // the booking work-groups first (they are a few long chains), then the bricks
+    // in XCD order
+    const int nbr = state_bricks(a.nx, a.ny, a.nz), n8 = (nbr + 7) & ~7, nbk = gridDim.x - n8, g = blockIdx.x;
+    const int b = g < nbk ? nbr + g : xcd_range(g - nbk, n8);
+    if (g >= nbk && b >= nbr) return;
+    sc_stream_state<S>(a, b);
+}
+template <class S, bool SINK, bool DST>
 __global__ void __launch_bounds__(NB) sc_collide_kernel(StepArgs a) {
     const int b = xcd_range(blockIdx.x, gridDim.x);
-    const double mv = sc_collide_nodes<S, SINK>(a, b);
+    const double mv = sc_collide_nodes<S, SINK, DST>(a, b);
     if constexpr (SINK) {
         // the block's moved mass into its own ledger pair (A loses it, B gains it)
         __shared__ double red[NB / 64];
@@ -963,21 +1147,35 @@ __global__ void __launch_bounds__(NB) sc_collide_batch_kernel(const StepArgs *__
     sc_collide_nodes<S>(a, w.y);
 }
 
+// work-groups that book the plane below the reservoir: blocks of NB nodes
+static int book_blocks(const StepArgs &a) {
+    const int64_t nxy = int64_t(a.nx) * a.ny;
+    return a.evap ? int(((a.nz - 1) * nxy - 1) / NB - (a.nz - 2) * nxy / NB) + 1 : 0;
+}
 template <class S>
-static hipError_t launch_split(const StepArgs &a, hipStream_t s) {
-    const int nblk = (split_blocks(a.nx, a.ny, a.nz) + 7) & ~7;
-    hipLaunchKernelGGL((sc_stream_kernel<S>), dim3(nblk), dim3(NB), 0, s, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (a.sink) {
-        if constexpr (sizeof(S) >= 4) {  // the sink runs with FP32 or FP64 storage
-            hipLaunchKernelGGL((sc_collide_kernel<S, true>), dim3(nblk), dim3(NB), 0, s, a);
-            return hipGetLastError();
+static hipError_t launch_split(const StepArgs &a, bool src, bool dst, hipStream_t s) {
+    const dim3 grid((split_blocks(a.nx, a.ny, a.nz) + 7) & ~7), block(NB);
+    if ((a.sink || src || dst) && sizeof(S) < 4) return hipErrorInvalidValue;
+    if (a.sink && (src || dst)) return hipErrorInvalidValue;
+    auto collide = [&](auto kern) {
+        hipLaunchKernelGGL(kern, grid, block, 0, s, a);
+        return hipGetLastError();
+    };
+    if constexpr (sizeof(S) >= 4) {
+        if (src) {
+            const int nbr = (state_bricks(a.nx, a.ny, a.nz) + 7) & ~7;
+            hipLaunchKernelGGL((sc_stream_state_kernel<S>), dim3(nbr + book_blocks(a)), dim3(BT),
+                               10 * BH * sizeof(S), s, a);
         }
-        return hipErrorInvalidValue;
     }
-    hipLaunchKernelGGL((sc_collide_kernel<S, false>), dim3(nblk), dim3(NB), 0, s, a);
-    return hipGetLastError();
+    if (!src) hipLaunchKernelGGL((sc_stream_kernel<S>), grid, block, 0, s, a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if constexpr (sizeof(S) >= 4) {  // the sink and the state as moments: FP32 or FP64 storage
+        if (a.sink) return collide(sc_collide_kernel<S, true, false>);
+        if (dst) return collide(sc_collide_kernel<S, false, true>);
+    }
+    return collide(sc_collide_kernel<S, false, false>);
 }
 template <class S>
 static hipError_t launch_split_batch(const StepArgs *all, const int2 *work, int nwork, hipStream_t s) {
@@ -988,16 +1186,16 @@ static hipError_t launch_split_batch(const StepArgs *all, const int2 *work, int 
     return hipGetLastError();
 }
 
-hipError_t launch_sc_split(int prec, const StepArgs &a, hipStream_t s) {
+hipError_t launch_sc_split(int prec, const StepArgs &a, bool src, bool dst, hipStream_t s) {
     switch (prec) {
         case LB_F64:
-            return launch_split<double>(a, s);
+            return launch_split<double>(a, src, dst, s);
         case LB_F32:
-            return launch_split<float>(a, s);
+            return launch_split<float>(a, src, dst, s);
         case LB_F16DEV:
-            return launch_split<_Float16>(a, s);
+            return launch_split<_Float16>(a, src, dst, s);
         case LB_BF16DEV:
-            return launch_split<bf16_t>(a, s);
+            return launch_split<bf16_t>(a, src, dst, s);
         default:
             return hipErrorInvalidValue;
     }

@@ -204,12 +204,7 @@ class Lattice:
 
     def coupled_step(self, n: int = 1):
         """n coupled steps: one fluid step then one rod or filament update each."""
-        for _ in range(int(n)):
-            self.step(1)
-            if self.n_beads:
-                self.filament_step()
-            else:
-                self.rods_step()
+        _lib.check(self.lib.lb_coupled_step(self._ctx, max(int(n), 0), _stream_ptr(self.stream)))
         return self
 
     def beads(self) -> np.ndarray:
