@@ -1671,19 +1671,27 @@ struct lb_batch {
     std::vector<int> cur0;  // each lattice's current buffer when the batch was made
     std::vector<Class> classes;
     int prec = 0;
-    StepArgs *steps = nullptr;  // device [2][n]: records for batch parity 0 and 1
+    // device [4][n]: records for batch parity 0 and 1, then the same with the
+    // result in the buffer that the step read (the last of an even number of
+    // steps with moments in between)
+    StepArgs *steps = nullptr;
     RodArgs *rods = nullptr;    // device [2][n]
     int2 *rodmap = nullptr;     // device [total_rods]
     int total_rods = 0, nblk_max = 0, max_rods = 0;
     int par = 0;  // steps taken since creation, mod 2
     hipStream_t cap = nullptr;
-    hipGraphExec_t graph[2] = {nullptr, nullptr};  // two steps from parity 0, without / with rods
+    // two steps from parity 0, without / with rods; with rods two steps from
+    // moments to moments, of parity 0 / 1
+    hipGraphExec_t graph[4] = {nullptr, nullptr, nullptr, nullptr};
+    bool chain = false;     // calls of several steps pass the state on as moments
+    int2 *swork = nullptr;  // device: work list of the stream pass from moments
+    int nswork = 0;
 };
 
 namespace {
 
 struct BatchLayout {
-    size_t steps, rods, rodmap, work, total;
+    size_t steps, rods, rodmap, work, swork, total;
     std::vector<size_t> work_off;
 };
 
@@ -1713,6 +1721,36 @@ std::vector<int> batch_classes(lb_ctx *const *ctxs, int n, std::vector<lb_batch:
     return of;
 }
 
+// Whether the lattices' calls of several steps pass the state on as moments:
+// what each does alone (moment_chain), for all of them together.
+bool batch_chain(lb_ctx *const *ctxs, int n) {
+    for (int i = 0; i < n; ++i)
+        if (!moment_chain(ctxs[i]->p)) return false;
+    return true;
+}
+
+// work list of the stream pass from moments: the booking blocks first (long
+// chains), then lattice after lattice, each dealt over the XCDs like a lattice
+// of its own
+std::vector<int2> state_work(lb_ctx *const *ctxs, int n) {
+    std::vector<int2> w;
+    for (int i = 0; i < n; ++i) {
+        const lb_params &p = ctxs[i]->p;
+        const int nb = state_bricks(p.nx, p.ny, p.nz), bk = book_blocks(p.nx, p.ny, p.nz, p.evap_on);
+        for (int t = 0; t < bk; ++t) w.push_back(make_int2(i, nb + t));
+    }
+    while (w.size() & 7) w.push_back(make_int2(-1, -1));
+    for (int i = 0; i < n; ++i) {
+        const lb_params &p = ctxs[i]->p;
+        const int nb = state_bricks(p.nx, p.ny, p.nz), per = (nb + 7) / 8;
+        for (int t = 0; t < 8 * per; ++t) {
+            const int q = (t & 7) * per + (t >> 3);
+            w.push_back(q < nb ? make_int2(i, q) : make_int2(-1, -1));
+        }
+    }
+    return w;
+}
+
 BatchLayout batch_layout(lb_ctx *const *ctxs, int n) {
     BatchLayout l{};
     std::vector<lb_batch::Class> cls;
@@ -1722,7 +1760,7 @@ BatchLayout batch_layout(lb_ctx *const *ctxs, int n) {
     for (int i = 0; i < n; ++i) total_rods += ctxs[i]->p.n_rods;
     size_t o = 0;
     l.steps = o;
-    o = align256(o + 2 * size_t(n) * sizeof(StepArgs));
+    o = align256(o + 4 * size_t(n) * sizeof(StepArgs));
     l.rods = o;
     o = align256(o + 2 * size_t(n) * sizeof(RodArgs));
     l.rodmap = o;
@@ -1732,6 +1770,8 @@ BatchLayout batch_layout(lb_ctx *const *ctxs, int n) {
         l.work_off.push_back(o);
         o = align256(o + size_t(c) * sizeof(int2));
     }
+    l.swork = o;
+    if (batch_chain(ctxs, n)) o = align256(o + state_work(ctxs, n).size() * sizeof(int2));
     l.total = o;
     return l;
 }
@@ -1754,19 +1794,45 @@ int batch_check(lb_ctx *const *ctxs, int n) {
     return LB_OK;
 }
 
-hipError_t batch_enqueue(lb_batch *b, int par, bool rods, hipStream_t s) {
+// one step from parity par.  src, dst: the state before / after it is kept as
+// moments, and par is the parity of the populations that the call began with
+// (set 2 + par: a last step whose result goes to that buffer)
+hipError_t batch_enqueue(lb_batch *b, int par, bool rods, hipStream_t s, bool src = false, bool dst = false,
+                         bool even = false) {
     const int n = int(b->ctx.size());
+    const StepArgs *rec = b->steps + size_t(even ? 2 + par : par) * n;
     for (const auto &c : b->classes) {
-        hipError_t e = c.split ? launch_sc_split_batch(b->prec, b->steps + size_t(par) * n, c.work, c.nwork, s)
-                               : launch_sc_step_batch(b->prec, c.tile, b->steps + size_t(par) * n, c.work, c.nwork, s);
+        hipError_t e = c.split ? launch_sc_split_batch(b->prec, rec, c.work, c.nwork, b->swork, b->nswork, src, dst, s)
+                               : launch_sc_step_batch(b->prec, c.tile, rec, c.work, c.nwork, s);
         if (e != hipSuccess) return e;
     }
     // the rod update acts on the state the fluid step just wrote: the records
-    // of the next parity
+    // of the next parity; with moments those of the buffer that has the slots
+    const int rp = dst || even ? par : par ^ 1;
     if (rods && b->total_rods > 0)
-        return launch_rods_step(b->prec, RodBatch{b->rods + size_t(par ^ 1) * n, b->rodmap, 1}, n, b->total_rods,
-                                b->nblk_max, b->max_rods, false, s);
+        return launch_rods_step(b->prec, RodBatch{b->rods + size_t(rp) * n, b->rodmap, 1}, n, b->total_rods,
+                                b->nblk_max, b->max_rods, dst, s);
     return hipSuccess;
+}
+
+// the graph of two such steps (from parity 0 then 1, or twice from moments to
+// moments), captured once
+int batch_graph(lb_batch *b, hipGraphExec_t &g, bool rods, bool mom) {
+    if (g) return LB_OK;
+    hipGraph_t gr = nullptr;
+    HIP_TRY(hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal), "begin capture");
+    hipError_t e1 = batch_enqueue(b, mom ? b->par : 0, rods, b->cap, mom, mom);
+    hipError_t e2 = e1 == hipSuccess ? batch_enqueue(b, mom ? b->par : 1, rods, b->cap, mom, mom) : e1;
+    hipError_t e3 = hipStreamEndCapture(b->cap, &gr);
+    if (e2 != hipSuccess) return hip_fail(e2, "capture batch step");
+    if (e3 != hipSuccess) return hip_fail(e3, "end capture");
+    hipError_t e4 = hipGraphInstantiate(&g, gr, nullptr, nullptr, 0);
+    (void)hipGraphDestroy(gr);
+    if (e4 != hipSuccess) {
+        g = nullptr;
+        return hip_fail(e4, "instantiate batch graph");
+    }
+    return LB_OK;
 }
 
 }  // namespace
@@ -1796,14 +1862,15 @@ int lb_batch_create(lb_ctx *const *ctxs, int32_t n, void *workspace, hipStream_t
     b->rods = reinterpret_cast<RodArgs *>(ws + l.rods);
     b->rodmap = reinterpret_cast<int2 *>(ws + l.rodmap);
     // per-parity records
-    std::vector<StepArgs> sa(2 * size_t(n));
+    std::vector<StepArgs> sa(4 * size_t(n));
     std::vector<RodArgs> ra(2 * size_t(n));
     std::vector<int2> rmap;
     for (int i = 0; i < n; ++i) {
         lb_ctx *c = ctxs[i];
         b->cur0.push_back(c->cur);
         for (int q = 0; q < 2; ++q) {
-            sa[size_t(q) * n + i] = step_args(c, c->cur ^ q);
+            sa[size_t(q) * n + i] = chain_args(c, c->cur ^ q, c->cur ^ q ^ 1);
+            sa[size_t(2 + q) * n + i] = chain_args(c, c->cur ^ q, c->cur ^ q);
             ra[size_t(q) * n + i] = rod_args(c);
             ra[size_t(q) * n + i].f = c->f[c->cur ^ q];
             ra[size_t(q) * n + i].f2 = c->f[c->cur ^ q ^ 1];
@@ -1845,6 +1912,12 @@ int lb_batch_create(lb_ctx *const *ctxs, int32_t n, void *workspace, hipStream_t
         if (e == hipSuccess)
             e = hipMemcpyAsync(b->classes[k].work, hw[k].data(), np * sizeof(int2), hipMemcpyHostToDevice, stream);
     }
+    const std::vector<int2> sw = batch_chain(ctxs, n) ? state_work(ctxs, n) : std::vector<int2>();
+    b->chain = !sw.empty();
+    b->nswork = int(sw.size());
+    b->swork = reinterpret_cast<int2 *>(ws + l.swork);
+    if (e == hipSuccess && b->chain)
+        e = hipMemcpyAsync(b->swork, sw.data(), sw.size() * sizeof(int2), hipMemcpyHostToDevice, stream);
     if (e == hipSuccess) e = hipMemcpyAsync(b->steps, sa.data(), sa.size() * sizeof(StepArgs), hipMemcpyHostToDevice, stream);
     if (e == hipSuccess) e = hipMemcpyAsync(b->rods, ra.data(), ra.size() * sizeof(RodArgs), hipMemcpyHostToDevice, stream);
     if (e == hipSuccess && !rmap.empty())
@@ -1867,26 +1940,29 @@ int lb_batch_step(lb_batch *b, int32_t nsteps, int32_t with_rods, int32_t use_gr
             return fail(LB_EINVAL, "lattice %d was stepped outside its batch", i);
     const bool rods = with_rods != 0;
     int left = nsteps;
+    if (b->chain && nsteps >= 2 && (rods || b->total_rods == 0)) {
+        const int par = b->par;
+        HIP_TRY(batch_enqueue(b, par, rods, stream, false, true), "batch step");
+        for (left = nsteps - 2; left > 0;) {
+            if (use_graph && left >= 2) {
+                hipGraphExec_t &g = b->graph[2 + par];
+                const int rc = batch_graph(b, g, rods, true);
+                if (rc) return rc;
+                HIP_TRY(hipGraphLaunch(g, stream), "launch batch graph");
+                left -= 2;
+            } else {
+                HIP_TRY(batch_enqueue(b, par, rods, stream, true, true), "batch step");
+                left -= 1;
+            }
+        }
+        HIP_TRY(batch_enqueue(b, par, rods, stream, true, false, (nsteps & 1) == 0), "batch step");
+        b->par ^= nsteps & 1;
+    }
     while (left > 0) {
         if (use_graph && left >= 2 && b->par == 0) {
             hipGraphExec_t &g = b->graph[rods ? 1 : 0];
-            if (!g) {
-                // capture two steps (parity 0 then 1) once; replays leave every
-                // lattice's buffer parity unchanged
-                hipGraph_t gr = nullptr;
-                HIP_TRY(hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal), "begin capture");
-                hipError_t e1 = batch_enqueue(b, 0, rods, b->cap);
-                hipError_t e2 = e1 == hipSuccess ? batch_enqueue(b, 1, rods, b->cap) : e1;
-                hipError_t e3 = hipStreamEndCapture(b->cap, &gr);
-                if (e2 != hipSuccess) return hip_fail(e2, "capture batch step");
-                if (e3 != hipSuccess) return hip_fail(e3, "end capture");
-                hipError_t e4 = hipGraphInstantiate(&g, gr, nullptr, nullptr, 0);
-                (void)hipGraphDestroy(gr);
-                if (e4 != hipSuccess) {
-                    g = nullptr;
-                    return hip_fail(e4, "instantiate batch graph");
-                }
-            }
+            const int rc = batch_graph(b, g, rods, false);
+            if (rc) return rc;
             HIP_TRY(hipGraphLaunch(g, stream), "launch batch graph");
             left -= 2;
         } else {

@@ -190,7 +190,12 @@ hipError_t launch_sc_step_batch(int prec, const TileCfg &t, const StepArgs *all,
 // src, dst: the state before and after the step is kept as moments in a.mom
 // (FP32 or FP64 storage, no sink; see node_access.h), else as populations
 hipError_t launch_sc_split(int prec, const StepArgs &a, bool src, bool dst, hipStream_t s);
-hipError_t launch_sc_split_batch(int prec, const StepArgs *all, const int2 *work, int nwork, hipStream_t s);
+// swork: the same for the stream pass from moments, whose entries are (lattice,
+// brick) and (lattice, bricks + booking block)
+hipError_t launch_sc_split_batch(int prec, const StepArgs *all, const int2 *work, int nwork, const int2 *swork,
+                                 int nswork, bool src, bool dst, hipStream_t s);
+__host__ __device__ int state_bricks(int nx, int ny, int nz);
+int book_blocks(int nx, int ny, int nz, int evap);
 __host__ __device__ int split_blocks(int nx, int ny, int nz);
 int tiles_xy(int nx, int ny, int tile_y);
 

@@ -1138,19 +1138,29 @@ __global__ void __launch_bounds__(NB) sc_stream_batch_kernel(const StepArgs *__r
     const StepArgs a = all[w.x];
     sc_stream_nodes<S>(a, w.y);
 }
-template <class S>
+template <class S, bool DST>
 __global__ void __launch_bounds__(NB) sc_collide_batch_kernel(const StepArgs *__restrict__ all,
                                                               const int2 *__restrict__ work) {
     const int2 w = work[blockIdx.x];
     if (w.x < 0) return;
     const StepArgs a = all[w.x];
-    sc_collide_nodes<S>(a, w.y);
+    sc_collide_nodes<S, false, DST>(a, w.y);
+}
+// the stream pass from moments: entries (lattice, brick), and past the bricks
+// (lattice, bricks + booking block)
+template <class S>
+__global__ void __launch_bounds__(BT, sizeof(S) == 4 ? 5 : 2)
+    sc_stream_state_batch_kernel(const StepArgs *__restrict__ all, const int2 *__restrict__ work) {
+    const int2 w = work[blockIdx.x];
+    if (w.x < 0) return;
+    const StepArgs a = all[w.x];
+    sc_stream_state<S>(a, w.y);
 }
 
 // work-groups that book the plane below the reservoir: blocks of NB nodes
-static int book_blocks(const StepArgs &a) {
-    const int64_t nxy = int64_t(a.nx) * a.ny;
-    return a.evap ? int(((a.nz - 1) * nxy - 1) / NB - (a.nz - 2) * nxy / NB) + 1 : 0;
+int book_blocks(int nx, int ny, int nz, int evap) {
+    const int64_t nxy = int64_t(nx) * ny;
+    return evap ? int(((nz - 1) * nxy - 1) / NB - (nz - 2) * nxy / NB) + 1 : 0;
 }
 template <class S>
 static hipError_t launch_split(const StepArgs &a, bool src, bool dst, hipStream_t s) {
@@ -1164,7 +1174,7 @@ static hipError_t launch_split(const StepArgs &a, bool src, bool dst, hipStream_
     if constexpr (sizeof(S) >= 4) {
         if (src) {
             const int nbr = (state_bricks(a.nx, a.ny, a.nz) + 7) & ~7;
-            hipLaunchKernelGGL((sc_stream_state_kernel<S>), dim3(nbr + book_blocks(a)), dim3(BT),
+            hipLaunchKernelGGL((sc_stream_state_kernel<S>), dim3(nbr + book_blocks(a.nx, a.ny, a.nz, a.evap)), dim3(BT),
                                10 * BH * sizeof(S), s, a);
         }
     }
@@ -1178,11 +1188,24 @@ static hipError_t launch_split(const StepArgs &a, bool src, bool dst, hipStream_
     return collide(sc_collide_kernel<S, false, false>);
 }
 template <class S>
-static hipError_t launch_split_batch(const StepArgs *all, const int2 *work, int nwork, hipStream_t s) {
-    hipLaunchKernelGGL((sc_stream_batch_kernel<S>), dim3(nwork), dim3(NB), 0, s, all, work);
+static hipError_t launch_split_batch(const StepArgs *all, const int2 *work, int nwork, const int2 *swork, int nswork,
+                                     bool src, bool dst, hipStream_t s) {
+    if ((src || dst) && sizeof(S) < 4) return hipErrorInvalidValue;
+    if constexpr (sizeof(S) >= 4) {
+        if (src)
+            hipLaunchKernelGGL((sc_stream_state_batch_kernel<S>), dim3(nswork), dim3(BT), 10 * BH * sizeof(S), s, all,
+                               swork);
+    }
+    if (!src) hipLaunchKernelGGL((sc_stream_batch_kernel<S>), dim3(nwork), dim3(NB), 0, s, all, work);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((sc_collide_batch_kernel<S>), dim3(nwork), dim3(NB), 0, s, all, work);
+    if constexpr (sizeof(S) >= 4) {
+        if (dst) {
+            hipLaunchKernelGGL((sc_collide_batch_kernel<S, true>), dim3(nwork), dim3(NB), 0, s, all, work);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((sc_collide_batch_kernel<S, false>), dim3(nwork), dim3(NB), 0, s, all, work);
     return hipGetLastError();
 }
 
@@ -1200,16 +1223,17 @@ hipError_t launch_sc_split(int prec, const StepArgs &a, bool src, bool dst, hipS
             return hipErrorInvalidValue;
     }
 }
-hipError_t launch_sc_split_batch(int prec, const StepArgs *all, const int2 *work, int nwork, hipStream_t s) {
+hipError_t launch_sc_split_batch(int prec, const StepArgs *all, const int2 *work, int nwork,
+                                 const int2 *swork, int nswork, bool src, bool dst, hipStream_t s) {
     switch (prec) {
         case LB_F64:
-            return launch_split_batch<double>(all, work, nwork, s);
+            return launch_split_batch<double>(all, work, nwork, swork, nswork, src, dst, s);
         case LB_F32:
-            return launch_split_batch<float>(all, work, nwork, s);
+            return launch_split_batch<float>(all, work, nwork, swork, nswork, src, dst, s);
         case LB_F16DEV:
-            return launch_split_batch<_Float16>(all, work, nwork, s);
+            return launch_split_batch<_Float16>(all, work, nwork, swork, nswork, src, dst, s);
         case LB_BF16DEV:
-            return launch_split_batch<bf16_t>(all, work, nwork, s);
+            return launch_split_batch<bf16_t>(all, work, nwork, swork, nswork, src, dst, s);
         default:
             return hipErrorInvalidValue;
     }

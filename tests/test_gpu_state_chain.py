@@ -125,3 +125,41 @@ def test_coupled_call_is_many(prec):
     for f, s, o in out[1:]:
         assert np.array_equal(f, out[0][0]) and np.array_equal(s, out[0][1])
         assert np.array_equal(o["ledger"], out[0][2]["ledger"]) and np.array_equal(o["solid"], out[0][2]["solid"])
+
+
+@pytest.mark.parametrize("graph", [True, False])
+def test_batch_call_is_many(graph):
+    """Lattices of a batch that all keep moments: calls of 2 to 7 steps (from
+    either buffer, replayed graphs with work between them) against each alone."""
+    from paper_2607_06794_amd.sim import Batch
+    from tests import test_gpu_batch as TB
+    from tests import test_gpu_rods as TR
+
+    def lattices():
+        a, b = TR.cap_rods_case(), TR.periodic_case()
+        a.update(tau=(1.0, 1.0), tile={}, eps_att=2e-4)
+        b.update(tau=(1.0, 1.0), tile={}, eps_att=1e-4)
+        c = make((6, 17, 31), False)
+        c.update(rods=None, wall=None, tile={})
+        return [TB._make(s) for s in (a, b, c)]
+
+    calls = [7, 2, 3, 1, 6, 5]
+    print(f"[gpu] batch of moment lattices, graph={graph}", flush=True)
+    solo = lattices()
+    for lat in solo:
+        for _ in range(sum(calls)):
+            lat.step(1)
+            lat.rods_step()
+    want = [TB._state(lat) for lat in solo]
+    lats = lattices()
+    batch = Batch(lats)
+    for n in calls:
+        batch.step(n, rods=True, graph=graph)
+        lats[0].observables(allow_unstable=True)
+    got = [TB._state(lat) for lat in lats]
+    batch.close()
+    for lat in solo + lats:
+        lat.close()
+    for (fw, rw, ow), (fg, rg, og) in zip(want, got):
+        assert np.array_equal(fw, fg) and np.array_equal(rw, rg)
+        assert np.array_equal(ow["ledger"], og["ledger"]) and np.array_equal(ow["solid"], og["solid"])
