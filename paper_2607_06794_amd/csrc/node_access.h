@@ -127,20 +127,24 @@ __device__ inline Eq<C> make_eq(C dr, C rho, C ux, C uy, C uz) {
     e.u[2] = uz;
     return e;
 }
-// direction i > 0; u(d): component d of the velocity
+// direction i > 0, without the diagonals' half; u(d): component d of the velocity
 template <class C, class F>
-__device__ inline C eq_pop(int i, C A, C R, F u) {
+__device__ inline C eq_pop_full(int i, C A, C R, F u) {
 #pragma clang fp contract(off)
     C cu = C(0);
     if (cx(i)) cu = cx(i) > 0 ? u(0) : -u(0);
     if (cy(i)) cu = cx(i) ? (cy(i) > 0 ? cu + u(1) : cu - u(1)) : (cy(i) > 0 ? u(1) : -u(1));
     if (cz(i)) cu = cx(i) || cy(i) ? (cz(i) > 0 ? cu + u(2) : cu - u(2)) : (cz(i) > 0 ? u(2) : -u(2));
-    const C f = fma_(R, cu * fma_(C(4.5), cu, C(3)), A);
-    return i <= 6 ? f : C(0.5) * f;
+    return fma_(R, cu * fma_(C(4.5), cu, C(3)), A);
+}
+template <class C>
+__device__ inline C eq_pop_full(int i, const Eq<C> &e) {
+    return eq_pop_full(i, e.A, e.R, [&](int d) { return e.u[d]; });
 }
 template <class C>
 __device__ inline C eq_pop(int i, const Eq<C> &e) {
-    return eq_pop(i, e.A, e.R, [&](int d) { return e.u[d]; });
+    const C f = eq_pop_full(i, e);
+    return i <= 6 ? f : C(0.5) * f;
 }
 
 // Between the steps of one call with tau = 1 a node is its moments per component

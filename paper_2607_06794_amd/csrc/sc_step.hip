@@ -674,27 +674,26 @@ __device__ __forceinline__ void book_top(const StepArgs &a, int b, bool here, do
 }
 
 // Sums of component k's streamed deviations fv (Eq. 3): rho_k - rref_k and j_k.
-// top: the plane below the reservoir, which sends w_i rho_top_k.
-template <class C>
+// top: the plane below the reservoir, which sends w_i rho_top_k.  FULL: fv holds
+// twice the diagonals' deviations; halving is exact, so the sums are the same.
+template <bool FULL = false, class C>
 __device__ __forceinline__ void stream_moments(const StepArgs &a, int k, bool top, C (&fv)[Q], C &dr, C (&j)[3]) {
     const C tdev = C(a.rho_top[k] - a.rho_ref[k]);
 #pragma unroll
     for (int i = 0; i < Q; ++i)
-        if (cz(i) == -1) fv[i] = top ? wgt<C>(i) * tdev : fv[i];
+        if (cz(i) == -1) fv[i] = top ? wgt<C>(FULL ? 1 : i) * tdev : fv[i];
+    auto add = [](C s, C v, int i) { return FULL && i > 6 ? fma_(C(0.5), v, s) : s + v; };
     C s = C(0), jx = C(0), jy = C(0), jz = C(0);
 #pragma unroll
-    for (int i = 0; i < Q; ++i) s += fv[i];
+    for (int i = 0; i < Q; ++i) s = add(s, fv[i], i);
     // momentum over opposite pairs: f_i - f_opp(i) is nearly exact
     // (the two are close), which avoids cancellation in j
 #pragma unroll
     for (int i = 1; i < Q; i += 2) {
         const C d = fv[i] - fv[i + 1];
-        if (cx(i) == 1) jx += d;
-        if (cx(i) == -1) jx -= d;
-        if (cy(i) == 1) jy += d;
-        if (cy(i) == -1) jy -= d;
-        if (cz(i) == 1) jz += d;
-        if (cz(i) == -1) jz -= d;
+        if (cx(i)) jx = add(jx, cx(i) > 0 ? d : -d, i);
+        if (cy(i)) jy = add(jy, cy(i) > 0 ? d : -d, i);
+        if (cz(i)) jz = add(jz, cz(i) > 0 ? d : -d, i);
     }
     dr = s;
     j[0] = jx;
@@ -1006,38 +1005,53 @@ __device__ __forceinline__ void sc_stream_state(const StepArgs &a, int b) {
         const int lo = per ? n - 1 : 0, hi = per ? 0 : n - 1;
         return v < 0 ? lo : (v >= n ? hi : v);
     };
-    constexpr int HL = (BH + BT - 1) / BT;
-    C v[HL][2][4];
+    // the brick and its ring by rows of XH nodes: XB of a row by XB threads, then
+    // the rows' two ends by the first threads
+    static_assert(YH * ZH % (BT / XB) == 0 && 2 * YH * ZH <= BT, "rows dealt evenly, their ends in one go");
+    constexpr int RL = YH * ZH / (BT / XB);
+    const int tx = threadIdx.x % XB, tr = threadIdx.x / XB;
+    const auto row = [&](int r) {
+        return uint32_t(at(min(z0 - 1 + r / YH, a.nz), a.nz, a.pz)) * nxy +
+               uint32_t(at(min(y0 - 1 + r % YH, a.ny), a.ny, a.py)) * a.nx;
+    };
+    const uint32_t xm = at(min(x0 + tx, a.nx), a.nx, a.px);
+    const bool ends = threadIdx.x < 2 * YH * ZH;
+    const int er = threadIdx.x >> 1, eh = er * XH + (threadIdx.x & 1 ? XB + 1 : 0);
+    C v[RL][2][4], ve[2][4];
 #pragma unroll
-    for (int l = 0; l < HL; ++l) {
-        const int h = min(int(threadIdx.x) + BT * l, BH - 1);
-        const int x = min(x0 - 1 + h % XH, a.nx), y = min(y0 - 1 + h / XH % YH, a.ny), z = min(z0 - 1 + h / (XH * YH), a.nz);
-        const uint32_t n = uint32_t(at(z, a.nz, a.pz)) * nxy + uint32_t(at(y, a.ny, a.py)) * a.nx + at(x, a.nx, a.px);
+    for (int l = 0; l < RL; ++l) {
+        const uint32_t q = row(tr + l * (BT / XB)) + xm;
 #pragma unroll
-        for (int k = 0; k < 2; ++k) load_state<S>(st, n, fsE, k, v[l][k]);
+        for (int k = 0; k < 2; ++k) load_state<S>(st, q, fsE, k, v[l][k]);
     }
-    const int tx = threadIdx.x % XB, ty = threadIdx.x / XB % YB, tz = threadIdx.x / (XB * YB);
+    if (ends) {
+        const uint32_t q = row(er) + at(min(x0 + (threadIdx.x & 1 ? XB : -1), a.nx), a.nx, a.px);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) load_state<S>(st, q, fsE, k, ve[k]);
+    }
+    const int ty = tr % YB, tz = tr / YB;
     const int x = x0 + tx, y = y0 + ty, z = z0 + tz;
     const bool act = x < a.nx && y < a.ny && z < a.nz;
     const uint32_t n = act ? uint32_t(z) * nxy + uint32_t(y) * a.nx + x : 0;
     const uint8_t mt = gptr(a.mat)[n], m = mt & MAT_ID_MASK;
     const C rest[2] = {get_moment<S>(st, n * E, fsE, 8), get_moment<S>(st, n * E, fsE, 9)};
     bool mark = false;
-#pragma unroll
-    for (int l = 0; l < HL; ++l) {
-        const int h = threadIdx.x + BT * l;
-        if (h >= BH) continue;
-        mark |= is_pop_mark(v[l][0][0]);
+    const auto put = [&](int h, const C(&w2)[2][4]) {
+        const bool mk = is_pop_mark(w2[0][0]);
+        mark |= mk;
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
-            const C *w = v[l][k];
+            const C *w = w2[k];
             const Eq<C> e = make_eq(w[0], rref[k] + w[0], w[1], w[2], w[3]);
-            val(k, 0, h) = is_pop_mark(w[0]) ? w[0] : e.A;
+            val(k, 0, h) = k == 0 && mk ? w[0] : e.A;
             val(k, 1, h) = e.R;
 #pragma unroll
             for (int d = 0; d < 3; ++d) val(k, 2 + d, h) = e.u[d];
         }
-    }
+    };
+#pragma unroll
+    for (int l = 0; l < RL; ++l) put((tr + l * (BT / XB)) * XH + 1 + tx, v[l]);
+    if (ends) put(eh, ve);
     const bool any = __any(mark);
     if ((threadIdx.x & 63) == 0) wmark[threadIdx.x >> 6] = any;
     __syncthreads();
@@ -1071,13 +1085,13 @@ __device__ __forceinline__ void sc_stream_state(const StepArgs &a, int b) {
 #pragma unroll
         for (int i = 1; i < Q; ++i) {
             const int h = ring(i);
-            fv[i] = eq_pop(i, val(k, 0, h), val(k, 1, h), [&](int d) { return val(k, 2 + d, h); });
+            fv[i] = eq_pop_full(i, val(k, 0, h), val(k, 1, h), [&](int d) { return val(k, 2 + d, h); });
         }
         // halfway bounce-back: from a static wall comes the node's own f*_opp(i)
         if (walls) {
             const Eq<C> e{val(k, 0, hc), val(k, 1, hc), {val(k, 2, hc), val(k, 3, hc), val(k, 4, hc)}};
 #pragma unroll
-            for (int i = 1; i < Q; ++i) fv[i] = (walls >> i) & 1u ? eq_pop(opp(i), e) : fv[i];
+            for (int i = 1; i < Q; ++i) fv[i] = (walls >> i) & 1u ? eq_pop_full(opp(i), e) : fv[i];
         }
         // from a marked node the element of its population; directions without one
         // read the node's first element again, so that all loads are in flight
@@ -1094,9 +1108,10 @@ __device__ __forceinline__ void sc_stream_state(const StepArgs &a, int b) {
                 slot[i] = buf_load<S>(src(k), v, 0);
             }
 #pragma unroll
-            for (int i = 0; i < Q; ++i) fv[i] = (far | self) >> i & 1u ? Codec<S>::dec(slot[i]) : fv[i];
+            for (int i = 0; i < Q; ++i)
+                fv[i] = (far | self) >> i & 1u ? (i > 6 ? C(2) : C(1)) * Codec<S>::dec(slot[i]) : fv[i];
         }
-        stream_moments(a, k, top, fv, dr[k], j[k]);
+        stream_moments<true>(a, k, top, fv, dr[k], j[k]);
     }
     stream_store<S>(a, n, m, dr, j);
 }
