@@ -104,17 +104,18 @@ def rod_params(lp, length=24.0):
 
 def time_step(case, prec, steps, warmup, tile, autotune, rods=None, segment=0, rho_ref=(0.0, 0.0),
               rounding="nearest"):
-    """Time `steps` coupled steps (fused fluid step + rod update).
+    """Time `steps` coupled steps (fluid step + rod update).
 
     With rods, the steps run in segments of at most `segment` steps, each
     from a freshly initialised lattice (untimed set-up and `warmup` steps
     before the first segment only): rods placed anywhere in the fluid (the
     stress placement) cross the liquid-vapour interface and the coupled state
     degrades after a few hundred steps, and timing a degraded state would time
-    less rod work.  Returns (ms per whole step, ms per fused-step launch,
-    fluid nodes, observables of the last segment, chosen tile, segments).
-    The fused step's own duration comes from a pair of HIP events around each
-    of its launches on the launch stream.
+    less rod work.  A segment is one call of that many steps.  Returns (ms per
+    whole step, ms per fluid step on its own, fluid nodes, observables of the
+    last segment, chosen tile, segments).  The fluid step's own duration comes
+    from a pair of HIP events around each of up to 100 single steps on a fresh
+    lattice, after the timed segments.
     """
     import torch
 
@@ -145,26 +146,32 @@ def time_step(case, prec, steps, warmup, tile, autotune, rods=None, segment=0, r
         n = min(seg, steps - done)
         torch.cuda.synchronize()
         stream = torch.cuda.current_stream()
-        ev = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for _ in range(n)]
         e0 = torch.cuda.Event(enable_timing=True)
         e1 = torch.cuda.Event(enable_timing=True)
         e0.record(stream)
-        for a, b in ev:
-            a.record(stream)
-            lat.step(1)
-            b.record(stream)
-            lat.rods_step()
+        lat.coupled_step(n)
         e1.record(stream)
         torch.cuda.synchronize()
         total_ms += e0.elapsed_time(e1)
-        fused_ms += sum(a.elapsed_time(b) for a, b in ev)
         obs = lat.observables(allow_unstable=True)
         worst |= int(obs["status"])
         lat.close()
         done += n
         nseg += 1
     obs["status"] = worst
-    return total_ms / steps, fused_ms / steps, n_fluid, obs, chosen, nseg
+    single = min(steps, 100)
+    lat = Lattice(lp, case["rho"], case["mat"], rods=rods)
+    lat.coupled_step(min(warmup, 10))
+    ev = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for _ in range(single)]
+    for a, b in ev:
+        a.record(stream)
+        lat.step(1)
+        b.record(stream)
+        lat.rods_step()
+    torch.cuda.synchronize()
+    fused_ms = sum(a.elapsed_time(b) for a, b in ev)
+    lat.close()
+    return total_ms / steps, fused_ms / single, n_fluid, obs, chosen, nseg
 
 
 def batched_form(steps, warmup, n_lattices=64):

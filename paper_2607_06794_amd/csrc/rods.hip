@@ -55,7 +55,12 @@ __device__ inline d3 quat_axis(const double *q) {
     return {2.0 * (x * z + w * y), 2.0 * (y * z - w * x), 1.0 - 2.0 * (x * x + y * y)};
 }
 
-__device__ inline double min_img(double d, double box, int per) { return per ? d - box * rint(d / box) : d; }
+// d - box rint(d / box); nothing to divide (some 30 instructions) while |d| is at
+// most half the box, where rint gives 0
+__device__ inline double min_img(double d, double box, int per) {
+    if (per && !(fabs(d) <= 0.5 * box)) d -= box * rint(d / box);
+    return d;
+}
 __device__ inline d3 min_image(d3 d, const RodArgs &a) {
     return {min_img(d.x, a.nx, a.px), min_img(d.y, a.ny, a.py), min_img(d.z, a.nz, a.pz)};
 }
@@ -132,6 +137,12 @@ __device__ inline double decf(const S *f, int64_t idx) {
     return static_cast<double>(Codec<S>::dec(gload(f + idx)));
 }
 
+// v - n floor(v / n) in a periodic direction, which is v while it lies in the box
+__device__ inline double into_box(double v, int n, int per) {
+    if (per && !(v >= 0.0 && v < n)) v -= n * floor(v / n);
+    return v;
+}
+
 // integer bounding box of the capsule (plus margin) in lattice coordinates
 struct Box {
     int lo[3], hi[3];
@@ -172,9 +183,8 @@ __device__ inline bool wrap_coord(int &v, int n, int per) {
 }
 
 // squared distance from lattice point p (unwrapped, near the rod) to the axis segment
-__device__ inline double axis_dist2(const double *rod, d3 p, const RodArgs &a) {
-    const d3 d = min_image(p - ld3(rod + ROD_X), a);
-    const d3 e = quat_axis(rod + ROD_Q);
+__device__ inline double axis_dist2(d3 X, d3 e, d3 p, const RodArgs &a) {
+    const d3 d = min_image(p - X, a);
     const double t = fmin(fmax(dot(d, e), -a.half), a.half);
     const d3 c = d - t * e;
     return dot(c, c);
@@ -688,9 +698,7 @@ __global__ void __launch_bounds__(LB_MAX_RODS) rod_integrate_kernel(RodBatch bt)
 #pragma unroll
                 for (int c = 0; c < 4; ++c) rm[RS_Q + c] = qn[c] / nq;
             }
-            if (a.px) X.x = X.x - a.nx * floor(X.x / a.nx);
-            if (a.py) X.y = X.y - a.ny * floor(X.y / a.ny);
-            if (a.pz) X.z = X.z - a.nz * floor(X.z / a.nz);
+            X = mk(into_box(X.x, a.nx, a.px), into_box(X.y, a.ny, a.py), into_box(X.z, a.nz, a.pz));
             st3(rm + RS_X, X);
             // every point of the rod stays within 0.9 of where it started the
             // step (the re-mask and the neighbour list rely on it): checked at
@@ -846,7 +854,7 @@ __global__ void __launch_bounds__(MB) rod_mask_kernel(RodBatch bt) {
                 y = b.lo[1] + my;
                 z = b.lo[2] + mz;
             }
-            const double d2 = axis_dist2(rod, mk(x, y, z), a);
+            const double d2 = axis_dist2(X, e, mk(x, y, z), a);
             const bool in_box = wrap_coord(x, a.nx, a.px) && wrap_coord(y, a.ny, a.py) && wrap_coord(z, a.nz, a.pz);
             if (d2 <= r2in && !in_box) atomicOr(a.status, ST_ROD_WALL);  // a rod left the lattice
             if (d2 <= r2sh && in_box) {
