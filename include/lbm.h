@@ -633,6 +633,8 @@ typedef struct {
     float *acc;
 } lb_unet;
 int lb_sur_forward(const lb_unet *net, const void *x, hipStream_t stream);
+/* pt from pb for every layer (what lb_conv_pack_weights does for one), one launch. */
+int lb_sur_pack_weights(const lb_unet *net, hipStream_t stream);
 int lb_sur_backward(const lb_unet *net, const void *x, const float *gout, hipStream_t stream);
 int lb_to_bf16(const float *x, int64_t n, void *y, hipStream_t stream);       /* round to nearest even */
 /* Network input from an FP32 canvas of P cells: y[:, c] = BF16((x[:, c] -

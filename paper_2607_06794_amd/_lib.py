@@ -46,6 +46,7 @@ EXPORTS = (
     "lb_kirchhoff",
     "lb_deposit_ensemble",
     "lb_sur_forward",
+    "lb_sur_pack_weights",
     "lb_sur_backward",
     "lb_kirchhoff_workspace_bytes",
     "lb_kirchhoff_noalloc",
@@ -342,6 +343,8 @@ def load(path: str = LIB_PATH):
     lib.lb_deposit_ensemble.restype = ct.c_int
     lib.lb_sur_forward.argtypes = [P(LbUnet), ct.c_void_p, ct.c_void_p]
     lib.lb_sur_forward.restype = ct.c_int
+    lib.lb_sur_pack_weights.argtypes = [P(LbUnet), ct.c_void_p]
+    lib.lb_sur_pack_weights.restype = ct.c_int
     lib.lb_sur_backward.argtypes = [P(LbUnet), ct.c_void_p, ct.c_void_p, ct.c_void_p]
     lib.lb_sur_backward.restype = ct.c_int
     lib.lb_rod_map.argtypes = [ct.c_void_p, ct.c_void_p, ct.c_void_p]

@@ -1186,7 +1186,10 @@ int lb_conv3d_backward_weights(const lb_conv *a, const void *g, float *dw, float
 int lb_conv_pack_weights(const void *w, int32_t cin, int32_t cout, void *wt, hipStream_t stream) {
     if (!w || !wt || cin <= 0 || cout <= 0 || int64_t(27) * cin * cout >= (1 << 30))
         return fail(LB_EINVAL, "bad weight packing");
-    HIP_TRY(launch_pack_weights(static_cast<const uint16_t *>(w), cin, cout, static_cast<uint16_t *>(wt), stream),
+    PackList ls{};
+    ls.n = 1;
+    ls.at[0] = PackLayer{static_cast<const uint16_t *>(w), static_cast<uint16_t *>(wt), 27 * cin, cout, 0};
+    HIP_TRY(launch_pack_weights(ls, stream),
             "pack weights");
     return LB_OK;
 }
@@ -1210,7 +1213,7 @@ int lb_pool2_backward(const float *gc, const float *skip, int32_t skip_stride, i
     if (!gc || !g || D < 2 || H < 2 || W < 2 || D % 2 || H % 2 || W % 2 || C < 1 ||
         (skip && (skip_off < 0 || skip_stride < skip_off + C)))
         return fail(LB_EINVAL, "bad pooling gradient");
-    HIP_TRY(launch_pool2_back(gc, skip, skip_stride, skip_off, D, H, W, C, g, stream), "pool backward");
+    HIP_TRY(launch_pool2_back(gc, skip, skip_stride, skip_off, D, H, W, C, nullptr, g, nullptr, stream), "pool backward");
     return LB_OK;
 }
 
@@ -1218,7 +1221,7 @@ int lb_up2_backward(const float *g, int32_t stride, int32_t C, int32_t D, int32_
                     hipStream_t stream) {
     if (!g || !gc || C < 1 || stride < C || D < 2 || H < 2 || W < 2 || D % 2 || H % 2 || W % 2)
         return fail(LB_EINVAL, "bad upsampling gradient");
-    HIP_TRY(launch_up2_back(g, stride, C, D, H, W, gc, stream), "upsample backward");
+    HIP_TRY(launch_up2_back(g, stride, C, D, H, W, nullptr, gc, nullptr, stream), "upsample backward");
     return LB_OK;
 }
 
@@ -1315,17 +1318,21 @@ int lb_sur_forward(const lb_unet *n, const void *x, hipStream_t stream) {
     return lb_conv3d_forward(&c, stream);
 }
 
-// gradient of one layer: pre-activation gradient of dy (through the ReLU
-// mask of its output y), weight and bias gradients, input gradient into dx
-static int unet_layer_grad(const lb_unet *n, int L, const void *x1, const void *x2, const void *y, const float *dy,
-                           float *dx, hipStream_t stream) {
-    const int relu = L == 4 * n->nlev - 2 ? 0 : 1;
-    const lb_conv c = unet_conv(n, L, x1, x2, const_cast<void *>(y), nullptr, relu);
-    const int64_t cnt = int64_t(c.D) * c.H * c.W * c.cout;
+// gradient of one layer from its pre-activation gradient gm (BF16): weight and
+// bias gradients, and the input gradient: FP32 into dx, or with mg the
+// pre-activation gradient of the layer whose output x1 is
+static int unet_layer_grad(const lb_unet *n, int L, const void *x1, const void *x2, const void *gm, float *dx, void *mg,
+                           hipStream_t stream) {
+    const lb_conv c = unet_conv(n, L, x1, x2, nullptr, nullptr, 0);
     int rc;
-    if ((rc = lb_relu_grad(dy, y, cnt, relu, n->gm, stream))) return rc;
-    if ((rc = lb_conv3d_backward_weights(&c, n->gm, n->g + n->off_w[L], n->g + n->off_b[L], stream))) return rc;
-    if (dx) return lb_conv3d_backward_data(&c, n->gm, dx, stream);
+    if ((rc = lb_conv3d_backward_weights(&c, gm, n->g + n->off_w[L], n->g + n->off_b[L], stream))) return rc;
+    if (dx) return lb_conv3d_backward_data(&c, gm, dx, stream);
+    if (!mg) return LB_OK;
+    if ((rc = conv_check(&c, false))) return rc;
+    ConvArgs a = conv_args(&c);
+    a.my = static_cast<const uint16_t *>(x1);
+    a.mg = static_cast<uint16_t *>(mg);
+    HIP_TRY(launch_conv_dgrad(a, static_cast<const uint16_t *>(gm), nullptr, stream), "conv backward data");
     return LB_OK;
 }
 
@@ -1334,42 +1341,59 @@ int lb_sur_backward(const lb_unet *n, const void *x, const float *gout, hipStrea
     if (rc) return rc;
     if (!gout) return fail(LB_EINVAL, "null output gradient");
     const int nl = n->nlev;
-    float *g = n->gB[0];
-    if ((rc = unet_layer_grad(n, 4 * nl - 2, n->act[unet_dec(n, 0, 1)], nullptr, nullptr, gout, g, stream))) return rc;
+    // gA and gB hold pre-activation gradients (BF16), and FP32 gradients of pooled inputs
+    const int64_t cnt = int64_t(n->D) * n->H * n->W * n->cout;
+    void *g = n->gB[0];
+    if ((rc = lb_relu_grad(gout, nullptr, cnt, 0, n->gm, stream))) return rc;
+    if ((rc = unet_layer_grad(n, 4 * nl - 2, n->act[unet_dec(n, 0, 1)], nullptr, n->gm, nullptr, g, stream))) return rc;
     // decoder, finest level first: dec{l}b, then dec{l}a whose input is (up(coarse), skip)
     for (int lvl = 0; lvl < nl - 1; ++lvl) {
-        float *ga = n->gA[lvl];
+        void *ga = n->gA[lvl];
         const int La = unet_dec(n, lvl, 0), Lb = unet_dec(n, lvl, 1);
-        if ((rc = unet_layer_grad(n, Lb, n->act[La], nullptr, n->act[Lb], g, ga, stream))) return rc;
+        if ((rc = unet_layer_grad(n, Lb, n->act[La], nullptr, g, nullptr, ga, stream))) return rc;
         const void *coarse = lvl + 1 < nl - 1 ? n->act[unet_dec(n, lvl + 1, 1)] : n->act[unet_enc(nl - 1, 1)];
         const int cup = lvl + 1 < nl - 1 ? n->ch[lvl + 1] : n->ch[nl - 1];
-        if ((rc = unet_layer_grad(n, La, coarse, n->act[unet_enc(lvl, 1)], n->act[La], ga, n->gcat[lvl], stream)))
-            return rc;
+        if ((rc = unet_layer_grad(n, La, coarse, n->act[unet_enc(lvl, 1)], ga, n->gcat[lvl], nullptr, stream))) return rc;
         g = n->gB[lvl + 1];
-        if ((rc = lb_up2_backward(n->gcat[lvl], cup + n->ch[lvl], cup, n->D >> lvl, n->H >> lvl, n->W >> lvl, g,
-                                  stream)))
-            return rc;
+        HIP_TRY(launch_up2_back(n->gcat[lvl], cup + n->ch[lvl], cup, n->D >> lvl, n->H >> lvl, n->W >> lvl,
+                                static_cast<const uint16_t *>(coarse), nullptr, static_cast<uint16_t *>(g), stream),
+                "upsample backward");
     }
     // encoder, coarsest level first
     for (int lvl = nl - 1; lvl >= 0; --lvl) {
+        const int La = unet_enc(lvl, 0), Lb = unet_enc(lvl, 1);
         if (lvl < nl - 1) {
             // gradient of enc{lvl}b's output: through the pooling plus the skip
             const int cup = lvl + 1 < nl - 1 ? n->ch[lvl + 1] : n->ch[nl - 1];
-            float *gn = n->gA[lvl];
-            if ((rc = lb_pool2_backward(g, n->gcat[lvl], cup + n->ch[lvl], cup, n->D >> lvl, n->H >> lvl, n->W >> lvl,
-                                        n->ch[lvl], gn, stream)))
-                return rc;
+            void *gn = n->gA[lvl];
+            HIP_TRY(launch_pool2_back(static_cast<const float *>(g), n->gcat[lvl], cup + n->ch[lvl], cup, n->D >> lvl,
+                                      n->H >> lvl, n->W >> lvl, n->ch[lvl], static_cast<const uint16_t *>(n->act[Lb]),
+                                      nullptr, static_cast<uint16_t *>(gn), stream),
+                    "pool backward");
             g = gn;
         }
-        float *ga = g != n->gB[lvl] ? n->gB[lvl] : n->gA[lvl];
-        const int La = unet_enc(lvl, 0), Lb = unet_enc(lvl, 1);
-        if ((rc = unet_layer_grad(n, Lb, n->act[La], nullptr, n->act[Lb], g, ga, stream))) return rc;
+        void *ga = g != n->gB[lvl] ? n->gB[lvl] : n->gA[lvl];
+        if ((rc = unet_layer_grad(n, Lb, n->act[La], nullptr, g, nullptr, ga, stream))) return rc;
         const void *xin = lvl == 0 ? x : n->pooled[lvl - 1];
         float *gb = nullptr;
         if (lvl > 0) gb = ga != n->gB[lvl] ? n->gB[lvl] : n->gA[lvl];
-        if ((rc = unet_layer_grad(n, La, xin, nullptr, n->act[La], ga, gb, stream))) return rc;
+        if ((rc = unet_layer_grad(n, La, xin, nullptr, ga, gb, nullptr, stream))) return rc;
         if (lvl > 0) g = gb;
     }
+    return LB_OK;
+}
+
+int lb_sur_pack_weights(const lb_unet *n, hipStream_t stream) {
+    if (!n || !n->pb || !n->pt) return fail(LB_EINVAL, "null network or weights");
+    if (n->nlev < 2 || n->nlev > LB_UNET_MAXLEV) return fail(LB_EINVAL, "nlev must be in [2, %d]", LB_UNET_MAXLEV);
+    PackList ls{};
+    ls.n = 4 * n->nlev - 1;
+    for (int L = 0; L < ls.n; ++L) {
+        const UnetLayer l = unet_layer(n, L);
+        ls.at[L] = PackLayer{static_cast<const uint16_t *>(n->pb) + n->off_w[L],
+                             static_cast<uint16_t *>(const_cast<void *>(n->pt)) + n->off_w[L], 27 * (l.c1 + l.c2), l.cout, 0};
+    }
+    HIP_TRY(launch_pack_weights(ls, stream), "pack weights");
     return LB_OK;
 }
 
@@ -1426,7 +1450,7 @@ int lb_sur_loss(const float *out, const float *xin, const float *tgt, int64_t P,
     int rc = chan_scale(scale, sc);
     if (rc) return rc;
     double *part = static_cast<double *>(scratch);
-    double *res = part + 256 * 7;
+    double *res = part + 256 * 7;  // LOSS_RESULT of the Python binding
     HIP_TRY(launch_loss(out, xin, tgt, P, sc, lam, part, res, grad, stream), "loss");
     if (result_host) {
         HIP_TRY(hipMemcpyAsync(result_host, res, 4 * sizeof(double), hipMemcpyDeviceToHost, stream), "copy loss");
@@ -1438,7 +1462,7 @@ int lb_sur_loss(const float *out, const float *xin, const float *tgt, int64_t P,
 int lb_sur_moments(const float *x, const float *y, int64_t P, void *scratch, double *result_host, hipStream_t stream) {
     if (!x || !y || !scratch || !result_host || P < 1) return fail(LB_EINVAL, "bad moments arguments");
     double *part = static_cast<double *>(scratch);
-    double *res = part + 256 * 7;
+    double *res = part + 256 * 7;  // LOSS_RESULT of the Python binding
     HIP_TRY(launch_moments(x, y, P, part, res, stream), "moments");
     HIP_TRY(hipMemcpyAsync(result_host, res, 7 * sizeof(double), hipMemcpyDeviceToHost, stream), "copy moments");
     HIP_TRY(hipStreamSynchronize(stream), "moments sync");

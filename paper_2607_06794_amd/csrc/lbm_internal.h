@@ -301,16 +301,32 @@ struct ConvArgs {
     uint16_t *y;         // [P][cout] BF16 output (or null)
     float *yf;           // [P][cout] FP32 output (or null)
     int D, H, W, cout, relu;
+    // input gradient: with mg, BF16(dx (my > 0)) goes there instead of dx (my: the
+    // input, a ReLU layer's output of c1 channels)
+    const uint16_t *my;
+    uint16_t *mg;
 };
 hipError_t launch_conv_fwd(const ConvArgs &a, hipStream_t s);
 hipError_t launch_conv_dgrad(const ConvArgs &a, const uint16_t *g, float *dx, hipStream_t s);
 hipError_t launch_conv_wgrad(const ConvArgs &a, const uint16_t *g, float *dw, float *db, hipStream_t s);
-hipError_t launch_pack_weights(const uint16_t *w, int cin, int cout, uint16_t *wt, hipStream_t s);
+// layers whose weights [K][cout] are packed [cout][K] in one launch
+struct PackLayer {
+    const uint16_t *w;
+    uint16_t *wt;
+    int K, cout, tile0;
+};
+struct PackList {
+    PackLayer at[4 * LB_UNET_MAXLEV - 1];
+    int n;
+};
+hipError_t launch_pack_weights(PackList ls, hipStream_t s);
 hipError_t launch_relu_grad(const float *dy, const uint16_t *y, int64_t n, int relu, uint16_t *g, hipStream_t s);
 hipError_t launch_pool2(const uint16_t *x, int D, int H, int W, int C, uint16_t *y, hipStream_t s);
+// with my: BF16 of the gradient where my > 0 into gb, instead of FP32 into g / gc
 hipError_t launch_pool2_back(const float *gc, const float *skip, int skip_stride, int skip_off, int D, int H, int W,
-                             int C, float *g, hipStream_t s);
-hipError_t launch_up2_back(const float *g, int stride, int C, int D, int H, int W, float *gc, hipStream_t s);
+                             int C, const uint16_t *my, float *g, uint16_t *gb, hipStream_t s);
+hipError_t launch_up2_back(const float *g, int stride, int C, int D, int H, int W, const uint16_t *my, float *gc,
+                           uint16_t *gb, hipStream_t s);
 hipError_t launch_fill_f32(float *p, int64_t n, float v, hipStream_t s);
 hipError_t launch_to_bf16(const float *x, int64_t n, uint16_t *y, hipStream_t s);
 struct ChanScale {

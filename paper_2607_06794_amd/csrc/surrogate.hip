@@ -19,6 +19,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <initializer_list>
 #include <type_traits>
 
 #include "lbm_device.h"
@@ -37,6 +38,27 @@ __device__ inline uint16_t f2bf(float x) {
 }
 __device__ inline float bf2f(uint16_t b) { return __uint_as_float(uint32_t(b) << 16); }
 
+
+// n elements of the input gradient (i < 0: none): FP32, or where the input is a
+// ReLU layer's output my, that layer's pre-activation gradient BF16(v (my > 0)) at
+// once (instead of FP32 and a pass over it: 9 us per layer of 262 144 x 32).  One
+// branch for all of them, and the mask's loads before its first use: a test per
+// element cost the GEMM of 262 144 x 96 70 us.
+template <int n, class I>
+__device__ __forceinline__ void put_grads(const ConvArgs &a, float *dx, const I (&i)[n], const float (&v)[n]) {
+    if (a.mg) {
+        float m[n];
+#pragma unroll
+        for (int q = 0; q < n; ++q) m[q] = bf2f(a.my[i[q] < 0 ? I(0) : i[q]]);
+#pragma unroll
+        for (int q = 0; q < n; ++q)
+            if (i[q] >= 0) a.mg[i[q]] = f2bf(m[q] > 0.0f ? v[q] : 0.0f);
+    } else {
+#pragma unroll
+        for (int q = 0; q < n; ++q)
+            if (i[q] >= 0) dx[i[q]] = v[q];
+    }
+}
 
 // ---------------------------------------------------------------------------
 // forward and input gradient: one implicit GEMM, C[M][N] = sum_k A[M][k] B[k][N]
@@ -229,19 +251,26 @@ __global__ void __launch_bounds__(256) conv_gemm_kernel(ConvArgs a, const uint16
         for (int j = 0; j < NB; ++j) {
             const int col = n0 + wn + 32 * j + (l & 31);
             if (col >= N) continue;
-            const float bias = (!DGRAD && a.b) ? a.b[col] : 0.0f;
+            const auto row = [&](int e) { return m0 + wm + 32 * i + 8 * (e >> 2) + 4 * (l >> 5) + (e & 3); };
+            if constexpr (DGRAD) {
+                int at[16];
+                float v[16];
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    at[e] = row(e) < P ? row(e) * cin + col : -1;
+                    v[e] = acc[i][j][e];
+                }
+                put_grads(a, dx, at, v);
+                continue;
+            }
+            const float bias = a.b ? a.b[col] : 0.0f;
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-                const int row = m0 + wm + 32 * i + 8 * (e >> 2) + 4 * (l >> 5) + (e & 3);
-                if (row >= P) continue;
-                if (DGRAD) {
-                    dx[row * cin + col] = acc[i][j][e];
-                } else {
-                    float v = acc[i][j][e] + bias;
-                    if (a.relu) v = fmaxf(v, 0.0f);
-                    if (a.y) a.y[row * a.cout + col] = f2bf(v);
-                    if (a.yf) a.yf[row * a.cout + col] = v;
-                }
+                if (row(e) >= P) continue;
+                float v = acc[i][j][e] + bias;
+                if (a.relu) v = fmaxf(v, 0.0f);
+                if (a.y) a.y[row(e) * a.cout + col] = f2bf(v);
+                if (a.yf) a.yf[row(e) * a.cout + col] = v;
             }
         }
 }
@@ -403,16 +432,29 @@ __global__ void __launch_bounds__(256, 2) conv_brick_kernel(ConvArgs a, const ui
     const int col = wn + (l & 31);
     if (col >= ncol) return;
     const float bias = (!DG && a.b) ? a.b[col] : 0.0f;
+    const auto at = [&](int i, int e) {
+        const int m = wm + 32 * i + 8 * (e >> 2) + 4 * (l >> 5) + (e & 3);
+        return (int64_t(z0 + (m >> 6)) * a.H + (y0 + ((m >> 3) & 7))) * a.W + (x0 + (m & 7));
+    };
+    if constexpr (DG) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            int64_t q[16];
+            float v[16];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                q[e] = at(i, e) * ncol + col;
+                v[e] = acc[i][e];
+            }
+            put_grads(a, dx, q, v);
+        }
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-            const int m = wm + 32 * i + 8 * (e >> 2) + 4 * (l >> 5) + (e & 3);
-            const int64_t p = (int64_t(z0 + (m >> 6)) * a.H + (y0 + ((m >> 3) & 7))) * a.W + (x0 + (m & 7));
-            if (DG) {
-                dx[p * ncol + col] = acc[i][e];
-                continue;
-            }
+            const int64_t p = at(i, e);
             float v = acc[i][e] + bias;
             if (a.relu) v = fmaxf(v, 0.0f);
             if (a.y) a.y[p * a.cout + col] = f2bf(v);
@@ -536,43 +578,122 @@ __global__ void __launch_bounds__(512, 4) conv_small_kernel(ConvArgs a, const ui
             for (int e = 0; e < 4; ++e)
                 sum[wv * 512 * NT + (16 * i + 4 * (l >> 4) + e) * 16 * NT + 16 * q + (l & 15)] = acc[i][q][e];
     __syncthreads();
+    int at[NT];  // the element of [P][N], -1 outside
+    float v[NT];
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
         const int e = tid + 512 * j, m = e / (16 * NT), col = n0 + e % (16 * NT);
         const int z = z0 + (m >> 4), y = y0 + (m >> 2 & 3), x = x0 + (m & 3);
-        float v = 0.0f;
+        v[j] = 0.0f;
 #pragma unroll
-        for (int w = 0; w < 8; ++w) v += sum[w * 512 * NT + e];
-        if (z >= a.D || y >= a.H || x >= a.W || col >= N) continue;
-        const int p = (z * a.H + y) * a.W + x;
-        if (DG) {
-            dx[p * cin + col] = v;
-        } else {
-            v += a.b ? a.b[col] : 0.0f;
-            if (a.relu) v = fmaxf(v, 0.0f);
-            if (a.y) a.y[p * a.cout + col] = f2bf(v);
-            if (a.yf) a.yf[p * a.cout + col] = v;
-        }
+        for (int w = 0; w < 8; ++w) v[j] += sum[w * 512 * NT + e];
+        at[j] = z < a.D && y < a.H && x < a.W && col < N ? ((z * a.H + y) * a.W + x) * N + col : -1;
+    }
+    if constexpr (DG) {
+        put_grads(a, dx, at, v);
+        return;
+    }
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        if (at[j] < 0) continue;
+        float r = v[j] + (a.b ? a.b[n0 + (tid + 512 * j) % (16 * NT)] : 0.0f);
+        if (a.relu) r = fmaxf(r, 0.0f);
+        if (a.y) a.y[at[j]] = f2bf(r);
+        if (a.yf) a.yf[at[j]] = r;
     }
 }
 
-// packed forward weights: wt[o][t][c] = w[t][c][o]
-__global__ void pack_weights_kernel(const uint16_t *w, int cin, int cout, uint16_t *wt) {
-    const int n = 27 * cin * cout;
-    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < n; e += gridDim.x * blockDim.x) {
-        const int o = e / (27 * cin), k = e % (27 * cin);
-        wt[e] = w[k * cout + o];
+// packed forward weights: wt[o][k] = w[k][o], k = (tap, input channel), of every layer of the list: one
+// work-group per 64 x 64 tile, turned in LDS so that both sides go by lines
+// (15 layers, 3.6 M weights: 15 launches of a strided gather 68 us, this one
+// launch 11.5)
+__global__ void __launch_bounds__(256) pack_weights_kernel(PackList ls) {
+    __shared__ uint16_t tile[64][66];
+    int L = 0;
+    while (L + 1 < ls.n && int(blockIdx.x) >= ls.at[L + 1].tile0) ++L;  // uniform
+    const PackLayer p = ls.at[L];
+    const int to = (p.cout + 63) / 64, t = blockIdx.x - p.tile0, k0 = t / to * 64, o0 = t % to * 64;
+    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int k = k0 + ty + 4 * r, o = o0 + tx;
+        if (k < p.K && o < p.cout) tile[ty + 4 * r][tx] = p.w[int64_t(k) * p.cout + o];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int k = k0 + tx, o = o0 + ty + 4 * r;
+        if (k < p.K && o < p.cout) p.wt[int64_t(o) * p.K + k] = tile[tx][ty + 4 * r];
+    }
+}
+
+// Elementwise passes take V = 8 neighbouring channels (or elements) per thread
+// where the channel counts allow and every pointer is 16-byte aligned, else one.
+template <int V>
+__device__ inline void load_f(const float *p, float (&v)[V]) {
+    if constexpr (V == 8) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const float4 q = reinterpret_cast<const float4 *>(p)[h];
+            v[4 * h] = q.x;
+            v[4 * h + 1] = q.y;
+            v[4 * h + 2] = q.z;
+            v[4 * h + 3] = q.w;
+        }
+    } else {
+        v[0] = p[0];
+    }
+}
+template <int V>
+__device__ inline void store_f(float *p, const float (&v)[V]) {
+    if constexpr (V == 8) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            reinterpret_cast<float4 *>(p)[h] = make_float4(v[4 * h], v[4 * h + 1], v[4 * h + 2], v[4 * h + 3]);
+    } else {
+        p[0] = v[0];
+    }
+}
+template <int V>
+__device__ inline void load_b(const uint16_t *p, float (&v)[V]) {
+    if constexpr (V == 8) {
+        const uint4 q = *reinterpret_cast<const uint4 *>(p);
+        const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            v[2 * h] = __uint_as_float(w[h] << 16);
+            v[2 * h + 1] = __uint_as_float(w[h] & 0xFFFF0000u);
+        }
+    } else {
+        v[0] = bf2f(p[0]);
+    }
+}
+template <int V>
+__device__ inline void store_b(uint16_t *p, const float (&v)[V]) {
+    if constexpr (V == 8) {
+        uint32_t w[4];
+#pragma unroll
+        for (int h = 0; h < 4; ++h) w[h] = f2bf(v[2 * h]) | uint32_t(f2bf(v[2 * h + 1])) << 16;
+        *reinterpret_cast<uint4 *>(p) = make_uint4(w[0], w[1], w[2], w[3]);
+    } else {
+        p[0] = f2bf(v[0]);
     }
 }
 
 // g = BF16(dy (y > 0)) (or BF16(dy) without the ReLU)
+template <int V>
 __global__ void relu_grad_kernel(const float *dy, const uint16_t *y, int64_t n, int relu, uint16_t *g) {
-    for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < n; i += int64_t(gridDim.x) * blockDim.x) {
-        const float v = (relu && !(bf2f(y[i]) > 0.0f)) ? 0.0f : dy[i];
-        g[i] = f2bf(v);
+    for (int64_t i = (blockIdx.x * int64_t(blockDim.x) + threadIdx.x) * V; i < n; i += int64_t(gridDim.x) * blockDim.x * V) {
+        float v[V], m[V];
+        load_f<V>(dy + i, v);
+        if (relu) {
+            load_b<V>(y + i, m);
+#pragma unroll
+            for (int q = 0; q < V; ++q) v[q] = m[q] > 0.0f ? v[q] : 0.0f;
+        }
+        store_b<V>(g + i, v);
     }
 }
-
 
 // Weight gradient dw[t, c, o] += sum_p x[p + o_t, c] g[p, o]: a work-group owns
 // 32 input channels, 32 output channels, the nine taps of one dz and a share of
@@ -729,50 +850,105 @@ __global__ void __launch_bounds__(256, 2) conv_wgrad_kernel(ConvArgs a, const ui
 // ---------------------------------------------------------------------------
 // pooling and the gradient plumbing of the U-Net
 // ---------------------------------------------------------------------------
+// a volume's extents for the passes below: element e = (position, channel group)
+struct Vol {
+    int D, H, W, C;  // the coarser volume, channels
+    int64_t n;       // elements
+    int w, h;        // extents of the volume that is run over
+    Divider by_c, by_w, by_h;
+    // coordinates of element e (the dividers hold up to 2^31 of them)
+    template <int V>
+    __device__ void at(int64_t e, int64_t &q, int &x, int &y, int &z, int &c) const {
+        if (n < (int64_t(1) << 31)) {
+            const uint32_t q32 = by_c(uint32_t(e)), r = by_w(q32);
+            q = q32;
+            z = by_h(r);
+            x = q32 - r * w;
+            y = r - uint32_t(z) * h;
+        } else {
+            q = e / (C / V);
+            x = int(q % w);
+            y = int(q / w % h);
+            z = int(q / w / h);
+        }
+        c = V * int(e - q * (C / V));
+    }
+};
 // y[q, c] = mean of the 8 children of q (BF16 in, BF16 out)
-__global__ void pool2_kernel(const uint16_t *x, int D, int H, int W, int C, uint16_t *y) {
-    const int64_t Pc = int64_t(D / 2) * (H / 2) * (W / 2);
-    for (int64_t e = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; e < Pc * C; e += int64_t(gridDim.x) * blockDim.x) {
-        const int c = int(e % C);
-        const int64_t q = e / C;
-        const int qw = int(q % (W / 2)), qh = int((q / (W / 2)) % (H / 2)), qd = int(q / (int64_t(W / 2) * (H / 2)));
-        float s = 0.0f;
+template <int V>
+__global__ void pool2_kernel(const uint16_t *x, Vol vol, uint16_t *y) {
+    const int W = 2 * vol.W, H = 2 * vol.H;
+    for (int64_t e = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; e < vol.n; e += int64_t(gridDim.x) * blockDim.x) {
+        int64_t q;
+        int qw, qh, qd, c;
+        vol.at<V>(e, q, qw, qh, qd, c);
+        float s[V], v[8][V];
+#pragma unroll
         for (int j = 0; j < 8; ++j) {
             const int64_t p = (int64_t(2 * qd + (j >> 2)) * H + 2 * qh + ((j >> 1) & 1)) * W + 2 * qw + (j & 1);
-            s += bf2f(x[p * C + c]);
+            load_b<V>(x + p * vol.C + c, v[j]);
         }
-        y[e] = f2bf(s * 0.125f);
+#pragma unroll
+        for (int u = 0; u < V; ++u) {
+            s[u] = 0.0f;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) s[u] += v[j][u];
+            s[u] *= 0.125f;
+        }
+        store_b<V>(y + e * V, s);
     }
 }
 
-// g[p, c] = gc[parent(p), c] / 8 (+ skip[p, off + c] when skip is given)
-__global__ void pool2_back_kernel(const float *gc, const float *skip, int skip_stride, int skip_off, int D, int H,
-                                  int W, int C, float *g) {
-    const int64_t P = int64_t(D) * H * W;
-    for (int64_t e = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; e < P * C; e += int64_t(gridDim.x) * blockDim.x) {
-        const int c = int(e % C);
-        const int64_t p = e / C;
-        const int pw = int(p % W), ph = int((p / W) % H), pd = int(p / (int64_t(W) * H));
-        const int64_t q = (int64_t(pd >> 1) * (H >> 1) + (ph >> 1)) * (W >> 1) + (pw >> 1);
-        float v = gc[q * C + c] * 0.125f;
-        if (skip) v += skip[p * skip_stride + skip_off + c];
-        g[e] = v;
+// g[p, c] = gc[parent(p), c] / 8 (+ skip[p, off + c] when skip is given); with my,
+// BF16(g (my > 0)) into gb instead (the gradient of the ReLU layer below)
+template <int V>
+__global__ void pool2_back_kernel(const float *gc, const float *skip, int skip_stride, int skip_off, Vol vol,
+                                  const uint16_t *my, float *g, uint16_t *gb) {
+    for (int64_t e = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; e < vol.n; e += int64_t(gridDim.x) * blockDim.x) {
+        int64_t p;
+        int pw, ph, pd, c;
+        vol.at<V>(e, p, pw, ph, pd, c);
+        const int64_t q = (int64_t(pd >> 1) * vol.H + (ph >> 1)) * vol.W + (pw >> 1);
+        float v[V], k[V], m[V];
+        load_f<V>(gc + q * vol.C + c, v);
+        if (skip) load_f<V>(skip + p * skip_stride + skip_off + c, k);
+        if (my) load_b<V>(my + e * V, m);
+#pragma unroll
+        for (int u = 0; u < V; ++u) {
+            v[u] *= 0.125f;
+            if (skip) v[u] += k[u];
+            if (my) v[u] = m[u] > 0.0f ? v[u] : 0.0f;
+        }
+        if (my) store_b<V>(gb + e * V, v);
+        else store_f<V>(g + e * V, v);
     }
 }
 
-// gc[q, c] = sum over the 8 children p of q of g[p, c] (g row stride `stride`)
-__global__ void up2_back_kernel(const float *g, int stride, int C, int D, int H, int W, float *gc) {
-    const int64_t Pc = int64_t(D / 2) * (H / 2) * (W / 2);
-    for (int64_t e = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; e < Pc * C; e += int64_t(gridDim.x) * blockDim.x) {
-        const int c = int(e % C);
-        const int64_t q = e / C;
-        const int qw = int(q % (W / 2)), qh = int((q / (W / 2)) % (H / 2)), qd = int(q / (int64_t(W / 2) * (H / 2)));
-        float s = 0.0f;
+// gc[q, c] = sum over the 8 children p of q of g[p, c] (g row stride `stride`);
+// with my, BF16(gc (my > 0)) into gb instead
+template <int V>
+__global__ void up2_back_kernel(const float *g, int stride, Vol vol, const uint16_t *my, float *gc, uint16_t *gb) {
+    const int W = 2 * vol.W, H = 2 * vol.H;
+    for (int64_t e = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; e < vol.n; e += int64_t(gridDim.x) * blockDim.x) {
+        int64_t q;
+        int qw, qh, qd, c;
+        vol.at<V>(e, q, qw, qh, qd, c);
+        float s[V], v[8][V], m[V];
+#pragma unroll
         for (int j = 0; j < 8; ++j) {
             const int64_t p = (int64_t(2 * qd + (j >> 2)) * H + 2 * qh + ((j >> 1) & 1)) * W + 2 * qw + (j & 1);
-            s += g[p * stride + c];
+            load_f<V>(g + p * stride + c, v[j]);
         }
-        gc[e] = s;
+        if (my) load_b<V>(my + e * V, m);
+#pragma unroll
+        for (int u = 0; u < V; ++u) {
+            s[u] = 0.0f;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) s[u] += v[j][u];
+            if (my) s[u] = m[u] > 0.0f ? s[u] : 0.0f;
+        }
+        if (my) store_b<V>(gb + e * V, s);
+        else store_f<V>(gc + e * V, s);
     }
 }
 
@@ -816,12 +992,15 @@ __global__ void __launch_bounds__(256) loss_partial_kernel(const float *out, con
                                                             sh[2][threadIdx.x] + sh[3][threadIdx.x];
 }
 
-// totals in a fixed order; res = sum mask, sum mask tgt_A, mass error, loss
-__global__ void loss_total_kernel(const double *part, int nb, double lam, double *res) {
-    if (threadIdx.x != 0) return;
+// totals in a fixed order (one wavefront: strided over its lanes, then a
+// butterfly; one thread took 26 us); res = sum mask, sum mask tgt_A, mass error, loss
+__global__ void __launch_bounds__(64) loss_total_kernel(const double *part, int nb, double lam, double *res) {
     double s[4] = {0, 0, 0, 0};
-    for (int b = 0; b < nb; ++b)
+    for (int b = threadIdx.x; b < nb; b += 64)
         for (int q = 0; q < 4; ++q) s[q] += part[b * 4 + q];
+    for (int q = 0; q < 4; ++q)
+        for (int o = 32; o > 0; o >>= 1) s[q] += __shfl_xor(s[q], o, 64);
+    if (threadIdx.x != 0) return;
     const double me = s[1] != 0.0 ? s[2] / s[1] : 0.0;
     res[0] = s[0];
     res[1] = s[1];
@@ -1318,32 +1497,75 @@ hipError_t launch_conv_wgrad(const ConvArgs &a, const uint16_t *g, float *dw, fl
     return hipGetLastError();
 }
 
-hipError_t launch_pack_weights(const uint16_t *w, int cin, int cout, uint16_t *wt, hipStream_t s) {
-    hipLaunchKernelGGL(pack_weights_kernel, dim3(grid_for(int64_t(27) * cin * cout)), dim3(256), 0, s, w, cin, cout, wt);
+hipError_t launch_pack_weights(PackList ls, hipStream_t s) {
+    int tiles = 0;
+    for (int L = 0; L < ls.n; ++L) {
+        ls.at[L].tile0 = tiles;
+        tiles += ((ls.at[L].K + 63) / 64) * ((ls.at[L].cout + 63) / 64);
+    }
+    hipLaunchKernelGGL(pack_weights_kernel, dim3(unsigned(tiles)), dim3(256), 0, s, ls);
     return hipGetLastError();
+}
+
+static bool aligned16(std::initializer_list<const void *> ps) {
+    for (const void *p : ps)
+        if (reinterpret_cast<uintptr_t>(p) & 15) return false;
+    return true;
 }
 
 hipError_t launch_relu_grad(const float *dy, const uint16_t *y, int64_t n, int relu, uint16_t *g, hipStream_t s) {
-    hipLaunchKernelGGL(relu_grad_kernel, dim3(grid_for(n)), dim3(256), 0, s, dy, y, n, relu, g);
+    if (n % 8 == 0 && aligned16({dy, relu ? y : nullptr, g}))
+        hipLaunchKernelGGL(relu_grad_kernel<8>, dim3(grid_for(n / 8)), dim3(256), 0, s, dy, y, n, relu, g);
+    else
+        hipLaunchKernelGGL(relu_grad_kernel<1>, dim3(grid_for(n)), dim3(256), 0, s, dy, y, n, relu, g);
     return hipGetLastError();
 }
 
+// the volume whose elements a pass of V channels per thread runs over: the
+// coarser one (fine: the finer one) of D x H x W
+static Vol vol_of(int D, int H, int W, int C, int V, bool fine) {
+    Vol v;
+    v.D = D / 2;
+    v.H = H / 2;
+    v.W = W / 2;
+    v.C = C;
+    v.n = (fine ? int64_t(D) * H * W : int64_t(v.D) * v.H * v.W) * (C / V);
+    v.w = fine ? W : v.W;
+    v.h = fine ? H : v.H;
+    v.by_c = Divider(C / V);
+    v.by_w = Divider(v.w);
+    v.by_h = Divider(v.h);
+    return v;
+}
+
 hipError_t launch_pool2(const uint16_t *x, int D, int H, int W, int C, uint16_t *y, hipStream_t s) {
-    hipLaunchKernelGGL(pool2_kernel, dim3(grid_for(int64_t(D / 2) * (H / 2) * (W / 2) * C)), dim3(256), 0, s, x, D, H, W,
-                       C, y);
+    const int V = C % 8 == 0 && aligned16({x, y}) ? 8 : 1;
+    const Vol v = vol_of(D, H, W, C, V, false);
+    const dim3 grid(grid_for(v.n)), block(256);
+    if (V == 8) hipLaunchKernelGGL(pool2_kernel<8>, grid, block, 0, s, x, v, y);
+    else hipLaunchKernelGGL(pool2_kernel<1>, grid, block, 0, s, x, v, y);
     return hipGetLastError();
 }
 
 hipError_t launch_pool2_back(const float *gc, const float *skip, int skip_stride, int skip_off, int D, int H, int W,
-                             int C, float *g, hipStream_t s) {
-    hipLaunchKernelGGL(pool2_back_kernel, dim3(grid_for(int64_t(D) * H * W * C)), dim3(256), 0, s, gc, skip, skip_stride,
-                       skip_off, D, H, W, C, g);
+                             int C, const uint16_t *my, float *g, uint16_t *gb, hipStream_t s) {
+    const bool wide = C % 8 == 0 && skip_stride % 4 == 0 && skip_off % 4 == 0 && aligned16({gc, skip, my, g, gb});
+    const Vol v = vol_of(D, H, W, C, wide ? 8 : 1, true);
+    const dim3 grid(grid_for(v.n)), block(256);
+    auto run = [&](auto k) { hipLaunchKernelGGL(k, grid, block, 0, s, gc, skip, skip_stride, skip_off, v, my, g, gb); };
+    if (wide) run(pool2_back_kernel<8>);
+    else run(pool2_back_kernel<1>);
     return hipGetLastError();
 }
 
-hipError_t launch_up2_back(const float *g, int stride, int C, int D, int H, int W, float *gc, hipStream_t s) {
-    hipLaunchKernelGGL(up2_back_kernel, dim3(grid_for(int64_t(D / 2) * (H / 2) * (W / 2) * C)), dim3(256), 0, s, g, stride,
-                       C, D, H, W, gc);
+hipError_t launch_up2_back(const float *g, int stride, int C, int D, int H, int W, const uint16_t *my, float *gc,
+                           uint16_t *gb, hipStream_t s) {
+    const bool wide = C % 8 == 0 && stride % 4 == 0 && aligned16({g, my, gc, gb});
+    const Vol v = vol_of(D, H, W, C, wide ? 8 : 1, false);
+    const dim3 grid(grid_for(v.n)), block(256);
+    auto run = [&](auto k) { hipLaunchKernelGGL(k, grid, block, 0, s, g, stride, v, my, gc, gb); };
+    if (wide) run(up2_back_kernel<8>);
+    else run(up2_back_kernel<1>);
     return hipGetLastError();
 }
 

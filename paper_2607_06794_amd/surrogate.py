@@ -26,6 +26,7 @@ from . import _lib
 
 CH = (32, 64, 128, 128)
 CIN, COUT = 8, 8  # padded input / output channel counts (7 and 6 used)
+LOSS_RESULT = 256 * 7  # doubles of partial sums before the results in the loss scratch
 
 
 def layer_shapes(ch=CH):
@@ -159,10 +160,7 @@ class UNet:
 
     def _pack(self):
         """Forward copies of the BF16 weights, [cout][27][cin] per layer."""
-        for name, c1, c2, co, _, _ in self.layers:
-            o = self.off[name][0]
-            _lib.check(self.lib.lb_conv_pack_weights(ct.c_void_p(self.pb.data_ptr() + 2 * o), c1 + c2, co,
-                                                     ct.c_void_p(self.pt.data_ptr() + 2 * o), self._s()))
+        _lib.check(self.lib.lb_sur_pack_weights(ct.byref(self.desc), self._s()))
 
     def set_layer(self, name, w, b):
         """w [27][cin_used][cout_used] and b [cout_used] (host arrays), zero padded."""
@@ -240,10 +238,12 @@ class UNet:
             self._gout = self.torch.zeros(self.P[0] * COUT, dtype=self.torch.float32, device=self.device)
         self.zero_grad()
         self.forward(x_bf16 if x_bf16 is not None else self.prepare(xin_f32))
-        out = self.loss(xin_f32, tgt_f32, lam, grad=self._gout)
+        self.loss(xin_f32, tgt_f32, lam, grad=self._gout, sync=False)
         self.backward(self._gout)
         self.adam(lr)
-        return out
+        # read once the step is queued, so that the GPU does not wait for the host
+        res = self.loss_scratch.view(self.torch.float64)[LOSS_RESULT:LOSS_RESULT + 4].tolist()
+        return res[3], res[2]
 
 
 # ---------------------------------------------------------------------------
