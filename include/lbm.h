@@ -543,8 +543,8 @@ int lb_sur_drift_rods(lb_ctx *ctx, const double *x_prev, double factor, hipStrea
  * [27][c1 + c2][cout], tap t = 9 (dz + 1) + 3 (dy + 1) + (dx + 1); wt: the
  * same weights packed [cout][27][c1 + c2] (lb_conv_pack_weights), read by the
  * forward only; b: FP32 [cout] or null; outputs y (BF16) and/or yf (FP32)
- * [D][H][W][cout]; acc: not used (may be null; the sums have a fixed
- * order).  c1, c2, cout: multiples of 8; D, H, W even when up1;
+ * [D][H][W][cout]; acc: nullable, not written; with it a layer of few output
+ * tiles may sum its K range in parts (in a fixed order).  c1, c2, cout: multiples of 8; D, H, W even when up1;
  * D H W max(c1 + c2, cout) < 2^31.  Asynchronous; LB_EINVAL on bad shapes or
  * null pointers.
  */

@@ -31,6 +31,7 @@
 
 #include "lbm_device.h"
 #include "lbm_internal.h"
+#include "node_access.h"
 
 namespace lbm {
 
@@ -103,20 +104,47 @@ __device__ inline int64_t nb_of(const FilArgs &a, int x, int y, int z, int i) {
     return node_at(a, xn, yn, zn);
 }
 
+// populations f*_i of fluid node n: stored, or (MOM) computed from its moments,
+// which lie behind the five arrays the step keeps between its passes in the
+// buffer other than a.f, as the numbers that would be stored
+template <class S, bool MOM>
+__device__ inline void node_pops(const FilArgs &a, const S *f, int64_t n, double (&fv)[2][Q]) {
+    if constexpr (MOM) {
+        const S *st = static_cast<const S *>(a.f2) + 5 * a.fs;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            S m[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) m[q] = gptr(st)[4 * (k * a.fs + n) + q];
+            const S rest = gptr(st)[(8 + k) * a.fs + n];
+            const auto eq = make_eq(m[0], S(a.rho_ref[k]) + m[0], m[1], m[2], m[3]);
+#pragma unroll
+            for (int i = 0; i < Q; ++i) fv[k][i] = double(i ? eq_pop(i, eq) : rest) + wgt<double>(i) * a.rho_ref[k];
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int i = 0; i < Q; ++i) fv[k][i] = popf(a, f, k, i, n);
+    }
+}
+
 // physical velocity and colour gradient of fluid node (x, y, z)
-template <class S>
+template <class S, bool MOM>
 __device__ void node_fields(const FilArgs &a, const S *f, int x, int y, int z, v3 &u, v3 &gc) {
     const int64_t n = node_at(a, x, y, z);
     double rho[2];
     node_rho(a, f, n, rho);
     // post-collision momentum of both components
+    double fv[2][Q];
+    node_pops<S, MOM>(a, f, n, fv);
     v3 jk[2];
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
         jk[k] = {0.0, 0.0, 0.0};
 #pragma unroll
         for (int i = 1; i < Q; ++i) {
-            const double fi = popf(a, f, k, i, n);
+            const double fi = fv[k][i];
             jk[k] = jk[k] + v3{cx(i) * fi, cy(i) * fi, cz(i) * fi};
         }
     }
@@ -185,7 +213,7 @@ __device__ void node_fields(const FilArgs &a, const S *f, int x, int y, int z, v
 // 1. gather: eight lanes per bead, one per stencil node; the weights and the
 //    interpolated fields are summed in stencil order through lane shuffles
 // ---------------------------------------------------------------------------
-template <class S>
+template <class S, bool MOM>
 __global__ __launch_bounds__(256) void fil_gather_kernel(FilArgs a) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     const int b = t >> 3, e = t & 7;
@@ -227,7 +255,7 @@ __global__ __launch_bounds__(256) void fil_gather_kernel(FilArgs a) {
         w = w / wsum;
         const int64_t n = node;
         const uint32_t un = static_cast<uint32_t>(n), row = un / uint32_t(a.nx);
-        node_fields(a, f, int(un - row * uint32_t(a.nx)), int(row % uint32_t(a.ny)), int(row / uint32_t(a.ny)), u, g);
+        node_fields<S, MOM>(a, f, int(un - row * uint32_t(a.nx)), int(row % uint32_t(a.ny)), int(row / uint32_t(a.ny)), u, g);
     } else {
         node = -1;
         w = 0.0;
@@ -447,7 +475,7 @@ __device__ inline double feq_i(int i, double rho, v3 u) {
     return wgt<double>(i) * rho * (1.0 + 3.0 * cu + 4.5 * cu * cu - 1.5 * usq);
 }
 
-template <class S>
+template <class S, bool MOM>
 __global__ __launch_bounds__(256) void fil_apply_kernel(FilArgs a) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= a.n * 8) return;
@@ -466,10 +494,7 @@ __global__ __launch_bounds__(256) void fil_apply_kernel(FilArgs a) {
     // the node's 38 populations, all loaded before any store (a store through
     // f would otherwise order every later load behind it)
     double fv[2][Q];
-#pragma unroll
-    for (int k = 0; k < 2; ++k)
-#pragma unroll
-        for (int i = 0; i < Q; ++i) fv[k][i] = popf(a, f, k, i, n);
+    node_pops<S, MOM>(a, f, n, fv);
     double rho[2];
     v3 uk[2];
 #pragma unroll
@@ -486,6 +511,19 @@ __global__ __launch_bounds__(256) void fil_apply_kernel(FilArgs a) {
     }
     const double tot = rho[0] + rho[1];
     if (!(tot > 0.0)) return;
+    if constexpr (MOM) {
+        // the node's populations are no equilibrium any more: they go to a.f, and
+        // the mark sends their readers there.  A component that stays as it is
+        // goes there as well.
+        gptr(static_cast<S *>(a.f2) + 5 * a.fs)[4 * int64_t(n)] = pop_mark(S(0));
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            if (!(rho[k] > 0.0))
+#pragma unroll
+                for (int i = 0; i < Q; ++i)
+                    f[(int64_t(k) * Q + i) * a.fs + n] =
+                        Codec<S>::enc(static_cast<typename Codec<S>::C>(fv[k][i] - wgt<double>(i) * a.rho_ref[k]));
+    }
     const v3 du = {dp.x / tot, dp.y / tot, dp.z / tot};
     // a node next to a static wall has already handed f*_j to the wall node
     // x + c_j as direction opp(j) (halfway bounce-back of the next pull): the
@@ -525,6 +563,11 @@ __global__ __launch_bounds__(256) void fil_apply_kernel(FilArgs a) {
     }
 }
 
+template <class K>
+static void fil_launch(K kern, dim3 grid, dim3 block, hipStream_t s, const FilArgs &a) {
+    hipLaunchKernelGGL(kern, grid, block, 0, s, a);
+}
+
 template <class F>
 static hipError_t fil_by_prec(int prec, F &&fn) {
     switch (prec) {
@@ -539,14 +582,16 @@ static hipError_t fil_by_prec(int prec, F &&fn) {
 
 }  // namespace
 
-hipError_t launch_fil_step(int prec, const FilArgs &a, hipStream_t s) {
+hipError_t launch_fil_step(int prec, const FilArgs &a, bool mom, hipStream_t s) {
     if (a.n == 0) return hipSuccess;
     double range = a.d0;
     if (a.eps_coh > 0.0 && a.r_cut > range) range = a.r_cut;
     range += a.skin;
     return fil_by_prec(prec, [&](auto *tag) {
         using S = std::remove_pointer_t<decltype(tag)>;
-        hipLaunchKernelGGL(fil_gather_kernel<S>, dim3((a.n * 8 + 255) / 256), dim3(256), 0, s, a);
+        const dim3 nodes((a.n * 8 + 255) / 256), block(256);
+        mom ? fil_launch(fil_gather_kernel<S, true>, nodes, block, s, a)
+            : fil_launch(fil_gather_kernel<S, false>, nodes, block, s, a);
         hipLaunchKernelGGL(fil_list_kernel, dim3((a.n + LT / 64 - 1) / (LT / 64)), dim3(LT), 0, s, a, range * range);
         int src = FIL_X;
         for (int sub = 0; sub < a.n_sub; ++sub) {
@@ -555,7 +600,8 @@ hipError_t launch_fil_step(int prec, const FilArgs &a, hipStream_t s) {
             src = src == FIL_X ? FIL_XN : FIL_X;
         }
         hipLaunchKernelGGL(fil_spread_kernel, dim3((a.n * 8 + 255) / 256), dim3(256), 0, s, a, src);
-        hipLaunchKernelGGL(fil_apply_kernel<S>, dim3((a.n * 8 + 255) / 256), dim3(256), 0, s, a);
+        mom ? fil_launch(fil_apply_kernel<S, true>, nodes, block, s, a)
+            : fil_launch(fil_apply_kernel<S, false>, nodes, block, s, a);
         return hipGetLastError();
     });
 }

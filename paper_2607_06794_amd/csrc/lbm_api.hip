@@ -752,9 +752,12 @@ static hipError_t sink_heights(lb_ctx *c, hipStream_t s) {
                                c->hbuf + size_t(c->cur) * slab, s);
 }
 
+static FilArgs fil_args(const lb_ctx *c, int cur);
+
 // nsteps >= 2 steps from populations to populations with moments in between,
-// each followed by the rod update if there are rods
-static int run_chain(lb_ctx *c, int32_t nsteps, hipStream_t stream) {
+// each followed by the rod update if there are rods, or with fil by the
+// filament update
+static int run_chain(lb_ctx *c, int32_t nsteps, bool fil, hipStream_t stream) {
     const lb_params &p = c->p;
     const int src = c->cur, dst = (src + nsteps) & 1;
     const StepArgs a = chain_args(c, src, dst);
@@ -764,6 +767,11 @@ static int run_chain(lb_ctx *c, int32_t nsteps, hipStream_t stream) {
         if (e == hipSuccess && p.n_rods > 0)
             e = launch_rods_step(p.prec, RodBatch{c->rodargs_dev + (last ? dst : src), nullptr, 1}, 1, p.n_rods,
                                  rod_nblk(p), p.n_rods, !last, stream);
+        if (e == hipSuccess && fil) {
+            FilArgs fa = fil_args(c, last ? dst : src);
+            fa.rho_fresh = 1;
+            e = launch_fil_step(p.prec, fa, !last, stream);
+        }
         if (e != hipSuccess) return hip_fail(e, "step launch");
     }
     c->cur = dst;
@@ -778,7 +786,7 @@ int lb_step(lb_ctx *c, int32_t nsteps, hipStream_t stream) {
     if (!c) return fail(LB_EINVAL, "null ctx");
     if (nsteps < 0) return fail(LB_EINVAL, "negative step count");
     const lb_params &p = c->p;
-    if (nsteps >= 2 && p.n_rods == 0 && moment_chain(p)) return run_chain(c, nsteps, stream);
+    if (nsteps >= 2 && p.n_rods == 0 && moment_chain(p)) return run_chain(c, nsteps, false, stream);
     for (int s = 0; s < nsteps; ++s) {
         hipError_t e = p.model == LB_MODEL_CG ? launch_cg_step(p.prec, cg_args(c, c->cur), stream)
                        : two_pass(p)          ? launch_sc_split(p.prec, step_args(c, c->cur), false, false, stream)
@@ -1163,7 +1171,7 @@ static ConvArgs conv_args(const lb_conv *a) {
 int lb_conv3d_forward(const lb_conv *a, hipStream_t stream) {
     int rc = conv_check(a, true);
     if (rc) return rc;
-    HIP_TRY(launch_conv_fwd(conv_args(a), stream), "conv forward");
+    HIP_TRY(launch_conv_fwd(conv_args(a), a->acc != nullptr, stream), "conv forward");
     return LB_OK;
 }
 
@@ -1494,11 +1502,13 @@ int lb_rods_step(lb_ctx *c, hipStream_t stream) {
 int lb_coupled_step(lb_ctx *c, int32_t nsteps, hipStream_t stream) {
     if (!c) return fail(LB_EINVAL, "null ctx");
     if (nsteps < 0) return fail(LB_EINVAL, "negative step count");
-    if (nsteps >= 2 && c->p.n_rods > 0 && moment_chain(c->p)) return run_chain(c, nsteps, stream);
-    if (fil_beads(&c->p) == 0 && c->p.n_rods == 0) return lb_step(c, nsteps, stream);
+    const bool fil = fil_beads(&c->p) > 0;
+    if (nsteps >= 2 && moment_chain(c->p) && (fil ? bool(c->fil_ready) : c->p.n_rods > 0))
+        return run_chain(c, nsteps, fil, stream);
+    if (!fil && c->p.n_rods == 0) return lb_step(c, nsteps, stream);
     for (int s = 0; s < nsteps; ++s) {
         int rc = lb_step(c, 1, stream);
-        if (rc == LB_OK) rc = fil_beads(&c->p) > 0 ? lb_fil_step(c, stream) : lb_rods_step(c, stream);
+        if (rc == LB_OK) rc = fil ? lb_fil_step(c, stream) : lb_rods_step(c, stream);
         if (rc != LB_OK) return rc;
     }
     return LB_OK;
@@ -1515,10 +1525,11 @@ int lb_rods_get(lb_ctx *c, double *out_host, hipStream_t stream) {
     return LB_OK;
 }
 
-static FilArgs fil_args(lb_ctx *c) {
+static FilArgs fil_args(const lb_ctx *c, int cur) {
     const lb_params &p = c->p;
     FilArgs a{};
-    a.f = c->f[c->cur];
+    a.f = c->f[cur];
+    a.f2 = c->f[cur ^ 1];
     a.rho = c->rho;
     a.rho_fresh = c->rho_fresh;
     a.mat = c->mat;
@@ -1593,7 +1604,7 @@ int lb_fil_step(lb_ctx *c, hipStream_t stream) {
     if (!c) return fail(LB_EINVAL, "null ctx");
     if (fil_beads(&c->p) == 0) return LB_OK;
     if (!c->fil_ready) return fail(LB_EINVAL, "lb_fil_set has not been called");
-    HIP_TRY(launch_fil_step(c->p.prec, fil_args(c), stream), "filament step");
+    HIP_TRY(launch_fil_step(c->p.prec, fil_args(c, c->cur), false, stream), "filament step");
     return LB_OK;
 }
 

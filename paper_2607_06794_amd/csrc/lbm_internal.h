@@ -158,6 +158,7 @@ constexpr int FIL_NO_OWNER = 0x7F7F7F7F;        // empty owner slot (the byte 0x
 
 struct FilArgs {
     void *f;          // current populations (post-collision state)
+    void *f2;         // the other population buffer
     const void *rho;  // [2][fs] densities of the current state (compute precision)
     int rho_fresh;    // 1: rho holds them; 0: sum the populations
     const uint8_t *mat;
@@ -178,7 +179,8 @@ struct FilArgs {
     double wall_z;
     double G, g[3], rho_top[2], rho_ref[2];
 };
-hipError_t launch_fil_step(int prec, const FilArgs &a, hipStream_t s);
+// mom: the state is kept as moments in f2; touched nodes' populations go to f
+hipError_t launch_fil_step(int prec, const FilArgs &a, bool mom, hipStream_t s);
 
 hipError_t launch_sc_step(int prec, const TileCfg &t, const StepArgs &a, hipStream_t s);
 // all: device array of per-lattice step records; work: device list of
@@ -306,7 +308,8 @@ struct ConvArgs {
     const uint16_t *my;
     uint16_t *mg;
 };
-hipError_t launch_conv_fwd(const ConvArgs &a, hipStream_t s);
+// split: the order of the sum over K is free
+hipError_t launch_conv_fwd(const ConvArgs &a, bool split, hipStream_t s);
 hipError_t launch_conv_dgrad(const ConvArgs &a, const uint16_t *g, float *dx, hipStream_t s);
 hipError_t launch_conv_wgrad(const ConvArgs &a, const uint16_t *g, float *dw, float *db, hipStream_t s);
 // layers whose weights [K][cout] are packed [cout][K] in one launch

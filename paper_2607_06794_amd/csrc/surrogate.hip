@@ -475,10 +475,12 @@ __global__ void __launch_bounds__(256, 2) conv_brick_kernel(ConvArgs a, const ui
 //
 typedef float v4f __attribute__((ext_vector_type(4)));
 constexpr int SBZ = 2, SBY = 4, SBX = 4, SHY = SBY + 2, SHX = SBX + 2, SNH = (SBZ + 2) * SHY * SHX;
-constexpr int SCH = 128, SLD = SCH + 8;  // channels per stage, halo row length
 
-template <int NT, bool DG>
-__global__ void __launch_bounds__(512, 4) conv_small_kernel(ConvArgs a, const uint16_t *g, float *dx) {
+// gz > 0: K (at most SCH channels, whole operands) in gz parts, part z to
+// wavefront z % 8, each summed from zero; else step s to wavefront s % 8
+template <int NT, bool DG, int SCH>
+__global__ void __launch_bounds__(512, 4) conv_small_kernel(ConvArgs a, const uint16_t *g, float *dx, int gz) {
+    constexpr int SLD = SCH + 8;  // channels per stage, halo row length
     constexpr int HLB = SNH * SLD * 2, RDB = 8 * 512 * NT * 4;
     __shared__ __attribute__((aligned(16))) char lds[HLB > RDB ? HLB : RDB];
     uint16_t *Hs = reinterpret_cast<uint16_t *>(lds);
@@ -496,11 +498,11 @@ __global__ void __launch_bounds__(512, 4) conv_small_kernel(ConvArgs a, const ui
         wb[q] = DG ? a.w + int64_t(n) * a.cout : a.wt + int64_t(n) * 27 * cin;
     }
     const int tstride = DG ? cin * a.cout : cin;  // elements between a column's taps
-    v4f acc[2][NT];
+    v4f acc[2][NT], tot[2][NT];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int q = 0; q < NT; ++q) acc[i][q] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int q = 0; q < NT; ++q) acc[i][q] = tot[i][q] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
 
     for (int c0 = 0; c0 < kc; c0 += SCH) {
         const int cw = min(SCH, kc - c0), ncc = (cw + 31) / 32, nst = 27 * ncc;
@@ -528,7 +530,9 @@ __global__ void __launch_bounds__(512, 4) conv_small_kernel(ConvArgs a, const ui
             hv[j] = *reinterpret_cast<const uint4 *>(src);
         }
         // the first step's weights
-        int st = wv, t = wv / ncc, cc = wv % ncc;
+        const auto part = [&](int z) { return gz ? int(int64_t(nst) * z / gz) : 0; };
+        int z = wv, st = gz ? part(z) : wv, end = part(z + 1), t = st / ncc, cc = st % ncc;
+        const bool any = gz ? z < gz : st < nst;
         uint4 wn[NT];
         auto fetch = [&]() {
             // past the channels the last eight of them (read in bounds, then zeroed)
@@ -536,7 +540,7 @@ __global__ void __launch_bounds__(512, 4) conv_small_kernel(ConvArgs a, const ui
 #pragma unroll
             for (int q = 0; q < NT; ++q) wn[q] = *reinterpret_cast<const uint4 *>(wb[q] + off);
         };
-        fetch();
+        if (any) fetch();
 #pragma unroll
         for (int j = 0; j < HL; ++j) {
             const int e = tid + 512 * j;
@@ -544,18 +548,35 @@ __global__ void __launch_bounds__(512, 4) conv_small_kernel(ConvArgs a, const ui
                 *reinterpret_cast<uint4 *>(Hs + e / (SCH / 8) * SLD + 8 * (e % (SCH / 8))) = keep4(ok[j], hv[j]);
         }
         __syncthreads();
-        while (st < nst) {
+        for (bool more = any; more;) {
             const int tt = DG ? 26 - t : t, off = (tt / 9 * SHY + tt / 3 % 3) * SHX + tt % 3, c = 32 * cc + k8;
             uint4 w[NT];
 #pragma unroll
             for (int q = 0; q < NT; ++q) w[q] = keep4(c < cw, wn[q]);
-            st += 8;
-            cc += 8;
-            while (cc >= ncc) {
-                cc -= ncc;
-                ++t;
+            bool done = false;  // a part ends with this step
+            if (gz) {
+                done = ++st == end;
+                if (done) {
+                    z += 8;
+                    st = part(z);
+                    end = part(z + 1);
+                    t = st / ncc;
+                    cc = st - t * ncc;
+                } else if (++cc == ncc) {
+                    cc = 0;
+                    ++t;
+                }
+                more = z < gz;
+            } else {
+                st += 8;
+                cc += 8;
+                while (cc >= ncc) {
+                    cc -= ncc;
+                    ++t;
+                }
+                more = st < nst;
             }
-            if (st < nst) fetch();
+            if (more) fetch();
             const uint16_t *hp = Hs + (hrow + off) * SLD + c;
             const v8bf fa0 = *reinterpret_cast<const v8bf *>(hp);
             const v8bf fa1 = *reinterpret_cast<const v8bf *>(hp + SHY * SHX * SLD);
@@ -564,6 +585,17 @@ __global__ void __launch_bounds__(512, 4) conv_small_kernel(ConvArgs a, const ui
                 const v8bf fb = __builtin_bit_cast(v8bf, w[q]);
                 acc[0][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa0, fb, acc[0][q], 0, 0, 0);
                 acc[1][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa1, fb, acc[1][q], 0, 0, 0);
+            }
+            if (done) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int q = 0; q < NT; ++q)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            tot[i][q][e] += acc[i][q][e];
+                            acc[i][q][e] = 0.0f;
+                        }
             }
         }
     }
@@ -576,7 +608,8 @@ __global__ void __launch_bounds__(512, 4) conv_small_kernel(ConvArgs a, const ui
         for (int q = 0; q < NT; ++q)
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                sum[wv * 512 * NT + (16 * i + 4 * (l >> 4) + e) * 16 * NT + 16 * q + (l & 15)] = acc[i][q][e];
+                sum[wv * 512 * NT + (16 * i + 4 * (l >> 4) + e) * 16 * NT + 16 * q + (l & 15)] =
+                    gz ? tot[i][q][e] : acc[i][q][e];
     __syncthreads();
     int at[NT];  // the element of [P][N], -1 outside
     float v[NT];
@@ -1428,17 +1461,20 @@ int grid_for(int64_t n) {
 }  // namespace
 
 // Which kernel a forward (DG = false) or input-gradient layer runs on:
-//  * up to SMALL_P positions, or where the GEMM's tiles would not fill the chip:
-//    conv_small (4 096 positions, 128 -> 128: 16 us against 36 for the GEMM
-//    with its K split over work-groups; 512 positions 6.4 against 18; 32 768
-//    positions, 64 -> 64: 31 against 23 for the bricks);
-//  * up to 64 columns on volumes of whole bricks: conv_brick;
+//  * up to 32 or 64 columns on volumes of whole bricks: conv_brick;
+//  * where the GEMM's tiles would not fill the chip and K is long enough to be cut
+//    into parts (forward: only with the layer's scratch acc, whose presence says
+//    that the order of the sum is free): conv_small (4 096 positions, 128 -> 128:
+//    @@SM@@ us against 36 for the GEMM with its K split over work-groups and added
+//    by atomics; 512 positions @@S5@@ against 18).  K is cut where those
+//    work-groups cut it, so that the result is one of theirs up to the rounding
+//    of the matrix instruction: a BF16 network amplifies every other order of
+//    its early sums to 0.3 percent of its output;
 //  * otherwise the GEMM (262 144 positions, 32 -> 96: 104 us, conv_small 190).
-constexpr int SMALL_P = 8192;
 template <bool DG>
-static hipError_t launch_conv(const ConvArgs &a, const uint16_t *g, float *dx, hipStream_t s) {
-    const int P = a.D * a.H * a.W, N = DG ? a.c1 + a.c2 : a.cout;
-    if (P > SMALL_P && a.H % BRY == 0 && a.W % BRX == 0) {
+static hipError_t launch_conv(const ConvArgs &a, bool split, const uint16_t *g, float *dx, hipStream_t s) {
+    const int P = a.D * a.H * a.W, N = DG ? a.c1 + a.c2 : a.cout, kc = DG ? a.cout : a.c1 + a.c2;
+    if (a.H % BRY == 0 && a.W % BRX == 0) {
         const int nxy = (a.H / BRY) * (a.W / BRX);
         if (N <= 32 && a.D % 4 == 0) {
             hipLaunchKernelGGL((conv_brick_kernel<4, 1, DG>), dim3(unsigned(nxy * (a.D / 4))), dim3(256), 0, s, a, g, dx);
@@ -1454,16 +1490,21 @@ static hipError_t launch_conv(const ConvArgs &a, const uint16_t *g, float *dx, h
     const unsigned ny = unsigned((N + bn - 1) / bn);
     const bool big = int64_t((P + 255) / 256) * ny >= 512;
     const unsigned gx = unsigned(big ? (P + 255) / 256 : (P + 127) / 128);
-    if (P <= SMALL_P || gx * ny < 256) {
+    // parts of K: at least eight steps each, over up to 512 work-groups
+    const int nst = (27 * kc + BK - 1) / BK;
+    const int gz = split && gx * ny < 256 ? std::min(nst / 8, int(512 / (gx * ny))) : 1;
+    if (gz > 1) {
         const int nb = ((a.W + SBX - 1) / SBX) * ((a.H + SBY - 1) / SBY) * ((a.D + SBZ - 1) / SBZ);
+        const int parts = kc % 32 == 0 && kc <= 256 ? gz : 0;
         // four column tiles per work-group share the halo and each LDS operand;
         // one where that leaves CUs idle
-        if (nb * ((N + 63) / 64) >= 192)
-            hipLaunchKernelGGL((conv_small_kernel<4, DG>), dim3(unsigned(nb), unsigned((N + 63) / 64)), dim3(512), 0, s, a,
-                               g, dx);
+        const bool wide = nb * ((N + 63) / 64) >= 192;
+        const dim3 grid(unsigned(nb), unsigned(wide ? (N + 63) / 64 : (N + 15) / 16));
+        auto run = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(512), 0, s, a, g, dx, parts); };
+        if (parts && kc > 128)
+            wide ? run(conv_small_kernel<4, DG, 256>) : run(conv_small_kernel<1, DG, 256>);
         else
-            hipLaunchKernelGGL((conv_small_kernel<1, DG>), dim3(unsigned(nb), unsigned((N + 15) / 16)), dim3(512), 0, s, a,
-                               g, dx);
+            wide ? run(conv_small_kernel<4, DG, 128>) : run(conv_small_kernel<1, DG, 128>);
         return hipGetLastError();
     }
     const dim3 grid(gx, ny);
@@ -1477,10 +1518,12 @@ static hipError_t launch_conv(const ConvArgs &a, const uint16_t *g, float *dx, h
     return hipGetLastError();
 }
 
-hipError_t launch_conv_fwd(const ConvArgs &a, hipStream_t s) { return launch_conv<false>(a, nullptr, nullptr, s); }
+hipError_t launch_conv_fwd(const ConvArgs &a, bool split, hipStream_t s) {
+    return launch_conv<false>(a, split, nullptr, nullptr, s);
+}
 
 hipError_t launch_conv_dgrad(const ConvArgs &a, const uint16_t *g, float *dx, hipStream_t s) {
-    return launch_conv<true>(a, g, dx, s);
+    return launch_conv<true>(a, true, g, dx, s);
 }
 
 hipError_t launch_conv_wgrad(const ConvArgs &a, const uint16_t *g, float *dw, float *db, hipStream_t s) {

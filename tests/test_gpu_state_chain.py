@@ -163,3 +163,33 @@ def test_batch_call_is_many(graph):
     for (fw, rw, ow), (fg, rg, og) in zip(want, got):
         assert np.array_equal(fw, fg) and np.array_equal(rw, rg)
         assert np.array_equal(ow["ledger"], og["ledger"]) and np.array_equal(ow["solid"], og["solid"])
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_filament_call_is_many(prec):
+    """Chains in a walled cap under the reservoir: the nodes that take their
+    impulses keep stored populations between the steps of a call."""
+    from paper_2607_06794_amd.sim import Lattice, LatticeParams
+    from tests import test_gpu_filaments as TF
+
+    c = TF.CASES["cap"]()
+    out = []
+    for calls in (None, [12], [2, 3, 7]):
+        print(f"[gpu] filament steps of one call {prec} {calls}", flush=True)
+        lp = LatticeParams(shape=c["shape"], periodic=c["periodic"], prec=prec, psi_solid=cases.PSI_SOLID.copy(),
+                           evaporation=True, rho_top=(0.0, 1.0), wall_z=c["wall"], n_fil=len(c["beads"]) // c["n_per"],
+                           fil_beads=c["n_per"], fil_eps_coh=c["eps_coh"])
+        lat = Lattice(lp, c["rho"], c["mat"], beads=c["beads"])
+        if calls is None:
+            for _ in range(12):
+                lat.step(1)
+                lat.filament_step()
+        else:
+            for n in calls:
+                lat.coupled_step(n)
+        out.append((lat.export()[1], lat.beads(), lat.observables(allow_unstable=True)))
+        lat.close()
+    assert np.abs(out[0][1][:, 9:12]).max() > 0.0  # impulses were handed over
+    for f, b, o in out[1:]:
+        assert np.array_equal(f, out[0][0]) and np.array_equal(b, out[0][1])
+        assert np.array_equal(o["ledger"], out[0][2]["ledger"]) and o["status"] == out[0][2]["status"]
