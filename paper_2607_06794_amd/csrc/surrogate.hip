@@ -1461,7 +1461,9 @@ int grid_for(int64_t n) {
 }  // namespace
 
 // Which kernel a forward (DG = false) or input-gradient layer runs on:
-//  * up to 32 or 64 columns on volumes of whole bricks: conv_brick;
+//  * up to 32 or 64 columns on volumes of whole bricks: conv_brick (an input
+//    gradient with fewer than 128 such work-groups goes on: 4 096 positions, 128 ->
+//    64: 35 us against @@E2@@);
 //  * where the GEMM's tiles would not fill the chip and K is long enough to be cut
 //    into parts (forward: only with the layer's scratch acc, whose presence says
 //    that the order of the sum is free): conv_small (4 096 positions, 128 -> 128:
@@ -1474,8 +1476,8 @@ int grid_for(int64_t n) {
 template <bool DG>
 static hipError_t launch_conv(const ConvArgs &a, bool split, const uint16_t *g, float *dx, hipStream_t s) {
     const int P = a.D * a.H * a.W, N = DG ? a.c1 + a.c2 : a.cout, kc = DG ? a.cout : a.c1 + a.c2;
-    if (a.H % BRY == 0 && a.W % BRX == 0) {
-        const int nxy = (a.H / BRY) * (a.W / BRX);
+    const int nxy = (a.H / BRY) * (a.W / BRX);
+    if (a.H % BRY == 0 && a.W % BRX == 0 && !(DG && N > 32 && nxy * (a.D / 2) < 128)) {
         if (N <= 32 && a.D % 4 == 0) {
             hipLaunchKernelGGL((conv_brick_kernel<4, 1, DG>), dim3(unsigned(nxy * (a.D / 4))), dim3(256), 0, s, a, g, dx);
             return hipGetLastError();
@@ -1496,15 +1498,15 @@ static hipError_t launch_conv(const ConvArgs &a, bool split, const uint16_t *g, 
     if (gz > 1) {
         const int nb = ((a.W + SBX - 1) / SBX) * ((a.H + SBY - 1) / SBY) * ((a.D + SBZ - 1) / SBZ);
         const int parts = kc % 32 == 0 && kc <= 256 ? gz : 0;
-        // four column tiles per work-group share the halo and each LDS operand;
-        // one where that leaves CUs idle
-        const bool wide = nb * ((N + 63) / 64) >= 192;
-        const dim3 grid(unsigned(nb), unsigned(wide ? (N + 63) / 64 : (N + 15) / 16));
+        // two column tiles per work-group share the halo and each LDS operand (four
+        // spill with the parts' sums); one where that leaves CUs idle
+        const bool wide = nb * ((N + 31) / 32) >= 192;
+        const dim3 grid(unsigned(nb), unsigned(wide ? (N + 31) / 32 : (N + 15) / 16));
         auto run = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(512), 0, s, a, g, dx, parts); };
         if (parts && kc > 128)
-            wide ? run(conv_small_kernel<4, DG, 256>) : run(conv_small_kernel<1, DG, 256>);
+            wide ? run(conv_small_kernel<2, DG, 256>) : run(conv_small_kernel<1, DG, 256>);
         else
-            wide ? run(conv_small_kernel<4, DG, 128>) : run(conv_small_kernel<1, DG, 128>);
+            wide ? run(conv_small_kernel<2, DG, 128>) : run(conv_small_kernel<1, DG, 128>);
         return hipGetLastError();
     }
     const dim3 grid(gx, ny);
