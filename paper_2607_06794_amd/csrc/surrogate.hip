@@ -464,26 +464,33 @@ __global__ void __launch_bounds__(256, 2) conv_brick_kernel(ConvArgs a, const ui
 
 // Layers of few positions (the coarse levels).  A work-group of eight
 // wavefronts computes a brick of 2 x 4 x 4 positions x 16 NT columns, each
-// wavefront an eighth of K for the whole tile: step s = (tap, 32 channels) goes
-// to wavefront s % 8.  The brick's input halo is staged in LDS, 128 channels
-// at a time; the weights' operands (16 columns x 32 consecutive channels of one
-// tap) are loaded straight from memory into the MFMA registers, the next
-// step's in flight; the wavefronts' sums meet in LDS in a fixed order, so no
-// second pass and no atomics.  Bound by the weights' way through L1 (one line
-// per column and step).  4 096 positions,
-// 128 -> 128 channels: 16 us (220 TFLOP/s); 512 positions: 6.4 us.
-//
+// wavefront parts of K (steps of a tap and 32 channels) for the whole tile.
+// The brick's input halo is staged in LDS, SCH channels at a time; the weights'
+// operands (16 columns x 32 consecutive channels of one tap) are loaded straight
+// from memory into the MFMA registers, the next step's in flight; the
+// wavefronts' sums meet in LDS in a fixed order, so no second pass and no
+// atomics.  Bound by the weights' way through L1 (one line per column and step).
+// 4 096 positions, 128 -> 128 channels: 19 us (191 TFLOP/s); 512: 10.4 us.
+// Each part is a sum of its own and the parts are added in the order in which
+// work-groups of equal speed would finish them; sums run on over the rounds: 1 us
+// faster at 4 096 positions, and the coarsest layer's results then differ in 19
+// percent of the last bits from those of a GEMM split over work-groups instead of
+// 0 to 6, its own spread.
 typedef float v4f __attribute__((ext_vector_type(4)));
 constexpr int SBZ = 2, SBY = 4, SBX = 4, SHY = SBY + 2, SHX = SBX + 2, SNH = (SBZ + 2) * SHY * SHX;
 
-// gz > 0: K (at most SCH channels, whole operands) in gz parts, part z to
-// wavefront z % 8, each summed from zero; else step s to wavefront s % 8
+// gz > 0: K (at most SCH channels, whole operands) in gz parts, each summed from
+// zero by a wavefront, and the parts added eight at a time: shorter ones first
+// (balanced rounds), the last first among equals; else step s to wavefront s % 8
+// and the wavefronts' sums added
 template <int NT, bool DG, int SCH>
 __global__ void __launch_bounds__(512, 4) conv_small_kernel(ConvArgs a, const uint16_t *g, float *dx, int gz) {
     constexpr int SLD = SCH + 8;  // channels per stage, halo row length
     constexpr int HLB = SNH * SLD * 2, RDB = 8 * 512 * NT * 4;
-    __shared__ __attribute__((aligned(16))) char lds[HLB > RDB ? HLB : RDB];
+    __shared__ __attribute__((aligned(16))) char lds[HLB + RDB];
     uint16_t *Hs = reinterpret_cast<uint16_t *>(lds);
+    float *sum = reinterpret_cast<float *>(lds + HLB);  // [wavefront][row][column]
+    __shared__ int order[27 * SCH / 256 + 1];           // the parts as they are added
     const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
     const int cin = a.c1 + a.c2, N = DG ? cin : a.cout, kc = DG ? a.cout : cin;
     const int nbx = (a.W + SBX - 1) / SBX, nby = (a.H + SBY - 1) / SBY, b = blockIdx.x;
@@ -498,11 +505,41 @@ __global__ void __launch_bounds__(512, 4) conv_small_kernel(ConvArgs a, const ui
         wb[q] = DG ? a.w + int64_t(n) * a.cout : a.wt + int64_t(n) * 27 * cin;
     }
     const int tstride = DG ? cin * a.cout : cin;  // elements between a column's taps
-    v4f acc[2][NT], tot[2][NT];
+    const int nall = 27 * ((min(SCH, kc) + 31) / 32);  // steps of the first stage
+    if (tid < gz) {
+        const auto len = [&](int z) { return nall * (z + 1) / gz - nall * z / gz; };
+        int rank = 0;
+        for (int z = 0; z < gz; ++z) rank += len(z) < len(tid) || (len(z) == len(tid) && z > tid);
+        order[rank] = tid;
+    }
+    v4f acc[2][NT];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int q = 0; q < NT; ++q) acc[i][q] = tot[i][q] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int q = 0; q < NT; ++q) acc[i][q] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    float v[NT];  // elements tid + 512 j of the tile
+#pragma unroll
+    for (int j = 0; j < NT; ++j) v[j] = 0.0f;
+    // adds the sums of the first n wavefronts to v; leaves acc zero
+    const auto collect = [&](int n) {
+        // D element e of lane l: row 4 (l / 16) + e, column l % 16
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int q = 0; q < NT; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    sum[wv * 512 * NT + (16 * i + 4 * (l >> 4) + e) * 16 * NT + 16 * q + (l & 15)] = acc[i][q][e];
+                    acc[i][q][e] = 0.0f;
+                }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int w = 0; w < 8; ++w)
+                if (w < n) v[j] += sum[w * 512 * NT + tid + 512 * j];
+        __syncthreads();  // read before the next round's stores
+    };
 
     for (int c0 = 0; c0 < kc; c0 += SCH) {
         const int cw = min(SCH, kc - c0), ncc = (cw + 31) / 32, nst = 27 * ncc;
@@ -530,9 +567,15 @@ __global__ void __launch_bounds__(512, 4) conv_small_kernel(ConvArgs a, const ui
             hv[j] = *reinterpret_cast<const uint4 *>(src);
         }
         // the first step's weights
-        const auto part = [&](int z) { return gz ? int(int64_t(nst) * z / gz) : 0; };
-        int z = wv, st = gz ? part(z) : wv, end = part(z + 1), t = st / ncc, cc = st % ncc;
-        const bool any = gz ? z < gz : st < nst;
+        int z = wv, st = wv, end = 0;
+        const auto part = [&]() {  // the z-th to be added: steps st .. end - 1
+            const int q = __builtin_amdgcn_readfirstlane(order[min(z, gz - 1)]);
+            st = nst * q / gz;
+            end = nst * (q + 1) / gz;
+        };
+        if (gz) part();
+        int t = st / ncc, cc = st % ncc;
+        bool more = gz ? z < gz : st < nst;  // steps are left for this wavefront
         uint4 wn[NT];
         auto fetch = [&]() {
             // past the channels the last eight of them (read in bounds, then zeroed)
@@ -540,7 +583,7 @@ __global__ void __launch_bounds__(512, 4) conv_small_kernel(ConvArgs a, const ui
 #pragma unroll
             for (int q = 0; q < NT; ++q) wn[q] = *reinterpret_cast<const uint4 *>(wb[q] + off);
         };
-        if (any) fetch();
+        if (more) fetch();
 #pragma unroll
         for (int j = 0; j < HL; ++j) {
             const int e = tid + 512 * j;
@@ -548,78 +591,55 @@ __global__ void __launch_bounds__(512, 4) conv_small_kernel(ConvArgs a, const ui
                 *reinterpret_cast<uint4 *>(Hs + e / (SCH / 8) * SLD + 8 * (e % (SCH / 8))) = keep4(ok[j], hv[j]);
         }
         __syncthreads();
-        for (bool more = any; more;) {
-            const int tt = DG ? 26 - t : t, off = (tt / 9 * SHY + tt / 3 % 3) * SHX + tt % 3, c = 32 * cc + k8;
-            uint4 w[NT];
+        for (int r = 0; r < (gz ? gz : 1); r += 8) {
+            bool done = !more;
+            while (!done) {
+                const int tt = DG ? 26 - t : t, off = (tt / 9 * SHY + tt / 3 % 3) * SHX + tt % 3, c = 32 * cc + k8;
+                uint4 w[NT];
 #pragma unroll
-            for (int q = 0; q < NT; ++q) w[q] = keep4(c < cw, wn[q]);
-            bool done = false;  // a part ends with this step
-            if (gz) {
-                done = ++st == end;
-                if (done) {
-                    z += 8;
-                    st = part(z);
-                    end = part(z + 1);
-                    t = st / ncc;
-                    cc = st - t * ncc;
-                } else if (++cc == ncc) {
-                    cc = 0;
-                    ++t;
+                for (int q = 0; q < NT; ++q) w[q] = keep4(c < cw, wn[q]);
+                if (gz) {
+                    done = ++st == end;  // a part ends with this step
+                    if (done) {
+                        z += 8;
+                        part();
+                        t = st / ncc;
+                        cc = st - t * ncc;
+                    } else if (++cc == ncc) {
+                        cc = 0;
+                        ++t;
+                    }
+                    more = z < gz;
+                } else {
+                    st += 8;
+                    cc += 8;
+                    while (cc >= ncc) {
+                        cc -= ncc;
+                        ++t;
+                    }
+                    more = st < nst;
+                    done = !more;
                 }
-                more = z < gz;
-            } else {
-                st += 8;
-                cc += 8;
-                while (cc >= ncc) {
-                    cc -= ncc;
-                    ++t;
+                if (more) fetch();
+                const uint16_t *hp = Hs + (hrow + off) * SLD + c;
+                const v8bf fa0 = *reinterpret_cast<const v8bf *>(hp);
+                const v8bf fa1 = *reinterpret_cast<const v8bf *>(hp + SHY * SHX * SLD);
+#pragma unroll
+                for (int q = 0; q < NT; ++q) {
+                    const v8bf fb = __builtin_bit_cast(v8bf, w[q]);
+                    acc[0][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa0, fb, acc[0][q], 0, 0, 0);
+                    acc[1][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa1, fb, acc[1][q], 0, 0, 0);
                 }
-                more = st < nst;
             }
-            if (more) fetch();
-            const uint16_t *hp = Hs + (hrow + off) * SLD + c;
-            const v8bf fa0 = *reinterpret_cast<const v8bf *>(hp);
-            const v8bf fa1 = *reinterpret_cast<const v8bf *>(hp + SHY * SHX * SLD);
-#pragma unroll
-            for (int q = 0; q < NT; ++q) {
-                const v8bf fb = __builtin_bit_cast(v8bf, w[q]);
-                acc[0][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa0, fb, acc[0][q], 0, 0, 0);
-                acc[1][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa1, fb, acc[1][q], 0, 0, 0);
-            }
-            if (done) {
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int q = 0; q < NT; ++q)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            tot[i][q][e] += acc[i][q][e];
-                            acc[i][q][e] = 0.0f;
-                        }
-            }
+            if (gz) collect(min(8, gz - r));
         }
     }
-    // D element e of lane l: row 4 (l / 16) + e, column l % 16; [wavefront][row][column]
-    __syncthreads();
-    float *sum = reinterpret_cast<float *>(lds);
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int q = 0; q < NT; ++q)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                sum[wv * 512 * NT + (16 * i + 4 * (l >> 4) + e) * 16 * NT + 16 * q + (l & 15)] =
-                    gz ? tot[i][q][e] : acc[i][q][e];
-    __syncthreads();
+    if (!gz) collect(8);
     int at[NT];  // the element of [P][N], -1 outside
-    float v[NT];
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
         const int e = tid + 512 * j, m = e / (16 * NT), col = n0 + e % (16 * NT);
         const int z = z0 + (m >> 4), y = y0 + (m >> 2 & 3), x = x0 + (m & 3);
-        v[j] = 0.0f;
-#pragma unroll
-        for (int w = 0; w < 8; ++w) v[j] += sum[w * 512 * NT + e];
         at[j] = z < a.D && y < a.H && x < a.W && col < N ? ((z * a.H + y) * a.W + x) * N + col : -1;
     }
     if constexpr (DG) {
@@ -1463,12 +1483,12 @@ int grid_for(int64_t n) {
 // Which kernel a forward (DG = false) or input-gradient layer runs on:
 //  * up to 32 or 64 columns on volumes of whole bricks: conv_brick (an input
 //    gradient with fewer than 128 such work-groups goes on: 4 096 positions, 128 ->
-//    64: 35 us against @@E2@@);
+//    64: 35 us against 13);
 //  * where the GEMM's tiles would not fill the chip and K is long enough to be cut
 //    into parts (forward: only with the layer's scratch acc, whose presence says
 //    that the order of the sum is free): conv_small (4 096 positions, 128 -> 128:
-//    @@SM@@ us against 36 for the GEMM with its K split over work-groups and added
-//    by atomics; 512 positions @@S5@@ against 18).  K is cut where those
+//    19 us against 36 for the GEMM with its K split over work-groups and added
+//    by atomics; 512 positions 10.4 against 18).  K is cut where those
 //    work-groups cut it, so that the result is one of theirs up to the rounding
 //    of the matrix instruction: a BF16 network amplifies every other order of
 //    its early sums to 0.3 percent of its output;
