@@ -25,6 +25,8 @@ CASES = [  # D, H, W, c1, c2, cout, up1
     (4, 8, 8, 256, 8, 32, 1),
     (4, 4, 6, 16, 24, 104, 1),
     (5, 9, 9, 40, 40, 33 * 8, 0),
+    (2, 6, 6, 160, 96, 256, 0),  # K in 27 parts, four rounds of eight wavefronts
+    (3, 18, 20, 96, 64, 160, 0),  # 16 parts, two column tiles per work-group
     (8, 16, 64, 8, 0, 32, 0),  # 8 192 positions
     (9, 16, 64, 32, 0, 64, 0),  # more, whole bricks in y and x only
     (4, 40, 56, 32, 16, 32, 0),  # whole bricks
