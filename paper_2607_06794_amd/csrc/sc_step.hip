@@ -888,13 +888,16 @@ __device__ __forceinline__ double sc_collide_nodes(const StepArgs &a, int b) {
 #pragma unroll
         for (int d = 0; d < 3; ++d) ue[d] = j[d] * ir + F[k][d] * rk;
         // Eq. 2 with tau = 1: f* = f^eq
-        const Eq<C> eq = make_eq(dr[k], rho[k], ue[0], ue[1], ue[2]);
         C deq[Q], deq_sum = C(0);
+        if constexpr (sizeof(S) == 2) {
+            eq_pairs(dr[k], rho[k], ue, deq);
+        } else {
+            const Eq<C> eq = make_eq(dr[k], rho[k], ue[0], ue[1], ue[2]);
 #pragma unroll
-        for (int i = 1; i < Q; ++i) {
-            deq[i] = eq_pop(i, eq);
-            deq_sum += deq[i];
+            for (int i = 1; i < Q; ++i) deq[i] = eq_pop(i, eq);
         }
+#pragma unroll
+        for (int i = 1; i < Q; ++i) deq_sum += deq[i];
         deq[0] = dr[k] - deq_sum;
         if constexpr (DST) {
             const C v[4] = {fluid ? dr[k] : pop_mark(C(0)), ue[0], ue[1], ue[2]};
