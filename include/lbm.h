@@ -654,6 +654,10 @@ int lb_sur_residual(const float *out, const float *xin, int64_t P, const float *
 size_t lb_sur_loss_scratch_bytes(void);
 int lb_sur_loss(const float *out, const float *xin, const float *tgt, int64_t P, const float *scale, double lam,
                 float *grad, void *scratch, double *result_host, hipStream_t stream);
+/* The four results of the last lb_sur_loss queued on `stream` with this scratch
+ * (also with a null result_host), once the stream's work so far is done.
+ * Synchronises. */
+int lb_sur_loss_result(const void *scratch, double *result_host, hipStream_t stream);
 /* Per-channel sums over P cells of mask * (y - x)^2 (channels 0..5) and of the
  * mask (xin channel 6) into result_host[7]; the scratch of lb_sur_loss.
  * Synchronises. */

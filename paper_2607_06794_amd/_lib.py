@@ -75,6 +75,7 @@ EXPORTS = (
     "lb_sur_moments",
     "lb_sur_loss_scratch_bytes",
     "lb_sur_loss",
+    "lb_sur_loss_result",
     "lb_adam",
 )
 
@@ -386,6 +387,7 @@ def load(path: str = LIB_PATH):
         "lb_fill_f32": [V, I64, ct.c_float, V],
         "lb_to_bf16": [V, I64, V, V],
         "lb_sur_loss": [V, V, V, I64, V, D_, V, V, V, V],
+        "lb_sur_loss_result": [V, V, V],
         "lb_sur_residual": [V, V, I64, V, V, V, V],
         "lb_sur_moments": [V, V, I64, V, V, V],
         "lb_adam": [V, V, V, V, V, I64, I32, D_, D_, D_, D_, V],

@@ -1451,6 +1451,15 @@ int lb_sur_residual(const float *out, const float *xin, int64_t P, const float *
 
 size_t lb_sur_loss_scratch_bytes(void) { return SUR_LOSS_SCRATCH * sizeof(double); }
 
+int lb_sur_loss_result(const void *scratch, double *result_host, hipStream_t stream) {
+    if (!scratch || !result_host) return fail(LB_EINVAL, "bad loss arguments");
+    HIP_TRY(hipMemcpyAsync(result_host, static_cast<const double *>(scratch) + SUR_LOSS_PARTS, 4 * sizeof(double),
+                           hipMemcpyDeviceToHost, stream),
+            "copy loss");
+    HIP_TRY(hipStreamSynchronize(stream), "loss sync");
+    return LB_OK;
+}
+
 int lb_sur_loss(const float *out, const float *xin, const float *tgt, int64_t P, const float *scale, double lam,
                 float *grad, void *scratch, double *result_host, hipStream_t stream) {
     if (!out || !xin || !tgt || !scratch || P < 1) return fail(LB_EINVAL, "bad loss arguments");
@@ -1458,19 +1467,15 @@ int lb_sur_loss(const float *out, const float *xin, const float *tgt, int64_t P,
     int rc = chan_scale(scale, sc);
     if (rc) return rc;
     double *part = static_cast<double *>(scratch);
-    double *res = part + 256 * 7;  // LOSS_RESULT of the Python binding
+    double *res = part + SUR_LOSS_PARTS;
     HIP_TRY(launch_loss(out, xin, tgt, P, sc, lam, part, res, grad, stream), "loss");
-    if (result_host) {
-        HIP_TRY(hipMemcpyAsync(result_host, res, 4 * sizeof(double), hipMemcpyDeviceToHost, stream), "copy loss");
-        HIP_TRY(hipStreamSynchronize(stream), "loss sync");
-    }
-    return LB_OK;
+    return result_host ? lb_sur_loss_result(scratch, result_host, stream) : LB_OK;
 }
 
 int lb_sur_moments(const float *x, const float *y, int64_t P, void *scratch, double *result_host, hipStream_t stream) {
     if (!x || !y || !scratch || !result_host || P < 1) return fail(LB_EINVAL, "bad moments arguments");
     double *part = static_cast<double *>(scratch);
-    double *res = part + 256 * 7;  // LOSS_RESULT of the Python binding
+    double *res = part + SUR_LOSS_PARTS;
     HIP_TRY(launch_moments(x, y, P, part, res, stream), "moments");
     HIP_TRY(hipMemcpyAsync(result_host, res, 7 * sizeof(double), hipMemcpyDeviceToHost, stream), "copy moments");
     HIP_TRY(hipStreamSynchronize(stream), "moments sync");

@@ -339,7 +339,7 @@ hipError_t launch_normalize(const float *x, int64_t P, const ChanScale &shift, c
                             hipStream_t s);
 hipError_t launch_residual(const float *out, const float *xin, int64_t P, const ChanScale &sc, float *pred,
                            uint16_t *predb, hipStream_t s);
-constexpr int SUR_LOSS_SCRATCH = 256 * 7 + 8;  // doubles
+constexpr int SUR_LOSS_PARTS = 256 * 7, SUR_LOSS_SCRATCH = SUR_LOSS_PARTS + 8;  // doubles: partial sums, then results
 hipError_t launch_loss(const float *out, const float *xin, const float *tgt, int64_t P, const ChanScale &sc, double lam,
                        double *part, double *res, float *grad, hipStream_t s);
 hipError_t launch_moments(const float *x, const float *y, int64_t P, double *part, double *res, hipStream_t s);

@@ -26,7 +26,6 @@ from . import _lib
 
 CH = (32, 64, 128, 128)
 CIN, COUT = 8, 8  # padded input / output channel counts (7 and 6 used)
-LOSS_RESULT = 256 * 7  # doubles of partial sums before the results in the loss scratch
 
 
 def layer_shapes(ch=CH):
@@ -241,8 +240,10 @@ class UNet:
         self.loss(xin_f32, tgt_f32, lam, grad=self._gout, sync=False)
         self.backward(self._gout)
         self.adam(lr)
-        # read once the step is queued, so that the GPU does not wait for the host
-        res = self.loss_scratch.view(self.torch.float64)[LOSS_RESULT:LOSS_RESULT + 4].tolist()
+        # read on the network's own stream, once the step is queued, so that the GPU
+        # does not wait for the host
+        res = (ct.c_double * 4)()
+        _lib.check(self.lib.lb_sur_loss_result(_p(self.loss_scratch), res, self._s()))
         return res[3], res[2]
 
 
