@@ -1297,6 +1297,15 @@ int unet_check(const lb_unet *n, const void *x) {
 
 }  // namespace
 
+static int unet_forward(const lb_conv &c, hipStream_t stream) {
+    int rc = conv_check(&c, true);
+    if (rc) return rc;
+    ConvArgs a = conv_args(&c);
+    a.ordered = true;
+    HIP_TRY(launch_conv_fwd(a, c.acc != nullptr, stream), "conv forward");
+    return LB_OK;
+}
+
 int lb_sur_forward(const lb_unet *n, const void *x, hipStream_t stream) {
     int rc = unet_check(n, x);
     if (rc) return rc;
@@ -1306,7 +1315,7 @@ int lb_sur_forward(const lb_unet *n, const void *x, hipStream_t stream) {
         for (int part = 0; part < 2; ++part) {
             const int L = unet_enc(lvl, part);
             const lb_conv c = unet_conv(n, L, h, nullptr, n->act[L], nullptr, 1);
-            if ((rc = lb_conv3d_forward(&c, stream))) return rc;
+            if ((rc = unet_forward(c, stream))) return rc;
             h = n->act[L];
         }
         if (lvl < nl - 1) {
@@ -1317,13 +1326,13 @@ int lb_sur_forward(const lb_unet *n, const void *x, hipStream_t stream) {
     for (int lvl = nl - 2; lvl >= 0; --lvl) {
         const int La = unet_dec(n, lvl, 0), Lb = unet_dec(n, lvl, 1);
         lb_conv c = unet_conv(n, La, h, n->act[unet_enc(lvl, 1)], n->act[La], nullptr, 1);
-        if ((rc = lb_conv3d_forward(&c, stream))) return rc;
+        if ((rc = unet_forward(c, stream))) return rc;
         c = unet_conv(n, Lb, n->act[La], nullptr, n->act[Lb], nullptr, 1);
-        if ((rc = lb_conv3d_forward(&c, stream))) return rc;
+        if ((rc = unet_forward(c, stream))) return rc;
         h = n->act[Lb];
     }
     const lb_conv c = unet_conv(n, 4 * nl - 2, h, nullptr, nullptr, n->out, 0);
-    return lb_conv3d_forward(&c, stream);
+    return unet_forward(c, stream);
 }
 
 // gradient of one layer from its pre-activation gradient gm (BF16): weight and
@@ -1334,13 +1343,15 @@ static int unet_layer_grad(const lb_unet *n, int L, const void *x1, const void *
     const lb_conv c = unet_conv(n, L, x1, x2, nullptr, nullptr, 0);
     int rc;
     if ((rc = lb_conv3d_backward_weights(&c, gm, n->g + n->off_w[L], n->g + n->off_b[L], stream))) return rc;
-    if (dx) return lb_conv3d_backward_data(&c, gm, dx, stream);
-    if (!mg) return LB_OK;
+    if (!dx && !mg) return LB_OK;
     if ((rc = conv_check(&c, false))) return rc;
     ConvArgs a = conv_args(&c);
-    a.my = static_cast<const uint16_t *>(x1);
-    a.mg = static_cast<uint16_t *>(mg);
-    HIP_TRY(launch_conv_dgrad(a, static_cast<const uint16_t *>(gm), nullptr, stream), "conv backward data");
+    a.ordered = true;
+    if (mg) {
+        a.my = static_cast<const uint16_t *>(x1);
+        a.mg = static_cast<uint16_t *>(mg);
+    }
+    HIP_TRY(launch_conv_dgrad(a, static_cast<const uint16_t *>(gm), dx, stream), "conv backward data");
     return LB_OK;
 }
 

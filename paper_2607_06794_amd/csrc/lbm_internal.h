@@ -307,8 +307,9 @@ struct ConvArgs {
     // input, a ReLU layer's output of c1 channels)
     const uint16_t *my;
     uint16_t *mg;
+    bool ordered;  // a layer of a network: K, where it is cut, in the parts and the order that its size alone decides
 };
-// split: the order of the sum over K is free
+// split: K may be summed in parts
 hipError_t launch_conv_fwd(const ConvArgs &a, bool split, hipStream_t s);
 hipError_t launch_conv_dgrad(const ConvArgs &a, const uint16_t *g, float *dx, hipStream_t s);
 hipError_t launch_conv_wgrad(const ConvArgs &a, const uint16_t *g, float *dw, float *db, hipStream_t s);

@@ -11,8 +11,9 @@
 //   wgrad    dw[t, c, o] += sum_p x[p + o_t, c] g[p, o]
 //            M = input channels, N = output channels of one tap, K = positions
 // The kernel is chosen by the volume and N (launch_conv): a GEMM over tiles of
-// consecutive positions, bricks of positions that share their input halo in
-// LDS, or small bricks whose K is split over the wavefronts.
+// consecutive positions, the same with K cut into parts, bricks of positions that
+// share their input halo in LDS, or small bricks whose K is split over the
+// wavefronts.
 // The decoder's inputs are read in place: channels [0, c1) from the coarser
 // level through nearest-neighbour upsampling, [c1, c1 + c2) from the skip.
 #include <math.h>
@@ -24,6 +25,7 @@
 
 #include "lbm_device.h"
 #include "lbm_internal.h"
+#include "node_access.h"
 
 namespace lbm {
 
@@ -275,6 +277,193 @@ __global__ void __launch_bounds__(256) conv_gemm_kernel(ConvArgs a, const uint16
         }
 }
 
+// The GEMM with K cut into KS parts inside a work-group, for layers whose tiles do
+// not fill the chip: tiles of T x T, four wavefronts per part with LDS buffers of
+// their own, the parts' sums met in LDS.  A stage of BK channels lies inside one
+// tap and one of the two inputs (channel counts are multiples of BK), so that an
+// address costs a few scalars and one addition; rows that a tap takes outside the
+// volume read past the buffer's end, which gives zero.  Two stages are in flight.
+// The parts are cut and added as conv_small does (shorter ones first, the last
+// first among equals): the same sums bit for bit.
+//
+// Bound by the latency of a stage (0.2 us with three parts, 0.4 for a part alone).
+// 29 295 positions, 128 -> 64 channels: 40 us (326 TFLOP/s); 93 for conv_small with
+// its two parts, 65 for a GEMM whose parts were work-groups that added with atomics.
+template <int T, int KS, bool DG>
+__global__ void __launch_bounds__(256 * KS) conv_split_kernel(ConvArgs a, const uint16_t *g, float *dx) {
+    constexpr int MB = T / 64, LPT = T / 64;  // blocks of 32 per wavefront and side, rows per thread
+    __shared__ __attribute__((aligned(16))) uint16_t lds[KS][2][2 * T * LDK];  // [part][buffer][rows of A, then of B]
+    const int part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+    const int tid = threadIdx.x & 255, wv = tid >> 6, l = tid & 63;
+    const int P = a.D * a.H * a.W, HW = a.H * a.W, cin = a.c1 + a.c2;
+    const int N = DG ? cin : a.cout, kc = DG ? a.cout : cin, nst = 27 * kc / BK;
+    const int m0 = blockIdx.x * T, n0 = blockIdx.y * T, wm = (wv >> 1) * MB * 32, wn = (wv & 1) * MB * 32;
+    const int s0 = nst * part / KS, cnt = nst * (part + 1) / KS - s0;  // this part's stages
+    // this thread's rows tid / 4 + 64 j of both tiles, channels 8 (tid % 4) .. + 7
+    const int row = tid >> 2, k8 = 8 * (tid & 3), H2 = a.H >> 1, W2 = a.W >> 1;
+    int p[LPT], px[LPT], py[LPT], pz[LPT];
+    unsigned tmask[LPT];
+    uint32_t bo[LPT];
+#pragma unroll
+    for (int j = 0; j < LPT; ++j) {
+        p[j] = m0 + row + 64 * j;
+        px[j] = p[j] % a.W;
+        py[j] = p[j] / a.W % a.H;
+        pz[j] = p[j] / HW;
+        tmask[j] = p[j] < P ? tap_mask(pz[j], py[j], px[j], a.D, a.H, a.W) : 0u;
+        // columns past the last read its weights and are not stored
+        bo[j] = uint32_t(min(n0 + row + 64 * j, N - 1) * (DG ? a.cout : 27 * cin) + k8) * 2u;
+    }
+    const auto wr = make_rsrc(DG ? a.w : a.wt, uint32_t(27 * cin) * uint32_t(a.cout) * 2u);
+    int t = s0 * BK / kc, c = s0 * BK % kc;  // tap and channel of the next stage to load
+    struct Stage {
+        uint4 a[LPT], b[LPT];
+    } in[2];
+    const auto load = [&](Stage &r) {
+        const int tt = min(t, 26);  // (past the last stage: loaded, not used)
+        const int dz = tt / 9 - 1, dy = tt / 3 % 3 - 1, dxx = tt % 3 - 1;
+        const bool skip = !DG && c >= a.c1, up = !DG && !skip && a.up1;
+        const int C = DG ? a.cout : (skip ? a.c2 : a.c1), cc = skip ? c - a.c1 : c;
+        const uint32_t bytes = uint32_t(up ? P >> 3 : P) * uint32_t(C) * 2u;
+        const auto xr = make_rsrc(DG ? g : (skip ? a.x2 : a.x1), bytes);
+        const uint32_t so = uint32_t(DG ? tt * cin * a.cout + c : tt * cin + c) * 2u;
+#pragma unroll
+        for (int j = 0; j < LPT; ++j) {
+            int q = p[j] + (DG ? -1 : 1) * (dz * HW + dy * a.W + dxx);
+            if (up) q = (((pz[j] + dz) >> 1) * H2 + ((py[j] + dy) >> 1)) * W2 + ((px[j] + dxx) >> 1);
+            const bool ok = (tmask[j] >> (DG ? 26 - tt : tt)) & 1u;
+            const auto va = __builtin_amdgcn_raw_buffer_load_b128(xr, ok ? uint32_t(q * C + cc + k8) * 2u : bytes, 0, 0);
+            const auto vb = __builtin_amdgcn_raw_buffer_load_b128(wr, bo[j], so, 0);
+            r.a[j] = make_uint4(va[0], va[1], va[2], va[3]);
+            r.b[j] = make_uint4(vb[0], vb[1], vb[2], vb[3]);
+        }
+        c += BK;
+        if (c >= kc) {
+            c = 0;
+            ++t;
+        }
+    };
+    const auto store = [&](const Stage &r, int buf) {
+#pragma unroll
+        for (int j = 0; j < LPT; ++j) {
+            *reinterpret_cast<uint4 *>(&lds[part][buf][(row + 64 * j) * LDK + k8]) = r.a[j];
+            *reinterpret_cast<uint4 *>(&lds[part][buf][(T + row + 64 * j) * LDK + k8]) = r.b[j];
+        }
+    };
+    v16f acc[MB][MB];
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < MB; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+    // stage st from buffer cur, while the next goes to LDS and the one after is loaded
+    const auto stage = [&](int st, int cur, Stage &next, Stage &after) {
+        load(after);
+        if (st < cnt) {
+#pragma unroll
+            for (int kk = 0; kk < BK; kk += 16) {
+                v8bf fa[MB], fb[MB];
+                const uint16_t *at = lds[part][cur] + (l & 31) * LDK + kk + 8 * (l >> 5);
+#pragma unroll
+                for (int i = 0; i < MB; ++i) {
+                    fa[i] = *reinterpret_cast<const v8bf *>(at + (wm + 32 * i) * LDK);
+                    fb[i] = *reinterpret_cast<const v8bf *>(at + (T + wn + 32 * i) * LDK);
+                }
+#pragma unroll
+                for (int i = 0; i < MB; ++i)
+#pragma unroll
+                    for (int j = 0; j < MB; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);  // the wait for the next stage's loads stays behind the products
+        store(next, cur ^ 1);
+        __syncthreads();
+    };
+    load(in[0]);
+    load(in[1]);
+    store(in[0], 0);
+    __syncthreads();
+    const int most = (nst + KS - 1) / KS;  // the longest part's: every wavefront passes the same barriers
+    int st = 0;
+    for (; st + 1 < most; st += 2) {
+        stage(st, 0, in[1], in[0]);
+        stage(st + 1, 1, in[0], in[1]);
+    }
+    if (st < most) stage(st, 0, in[1], in[0]);
+
+    // the parts in the order in which they are added
+    const auto len = [&](int z) { return nst * (z + 1) / KS - nst * z / KS; };
+    int order[KS];
+#pragma unroll
+    for (int q = 0; q < KS; ++q) {
+        int rank = 0;
+#pragma unroll
+        for (int z = 0; z < KS; ++z) rank += len(z) < len(q) || (len(z) == len(q) && z > q);
+#pragma unroll
+        for (int r = 0; r < KS; ++r)
+            if (rank == r) order[r] = q;
+    }
+    // first part's wavefronts: its own sums and the others', from LDS
+    float *sum = reinterpret_cast<float *>(lds);  // [part - 1][block column][element][thread]
+    static_assert((KS - 1) * MB * 4096 * 4 <= sizeof(lds), "the parts' sums fit");
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+        if (part > 0) {
+#pragma unroll
+            for (int j = 0; j < MB; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) sum[((part - 1) * MB + j) * 4096 + e * 256 + tid] = acc[i][j][e];
+        }
+        __syncthreads();
+        if (part == 0) {
+#pragma unroll
+            for (int j = 0; j < MB; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    float v = 0.0f;
+#pragma unroll
+                    for (int r = 0; r < KS; ++r)
+                        v += order[r] == 0 ? acc[i][j][e] : sum[((order[r] - 1) * MB + j) * 4096 + e * 256 + tid];
+                    acc[i][j][e] = v;
+                }
+        }
+        if (i + 1 < MB) __syncthreads();
+    }
+    if (part > 0) return;
+
+    // D element e of lane l: row 8 (e / 4) + 4 (l / 32) + e % 4, column l % 32
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < MB; ++j) {
+            const int col = n0 + wn + 32 * j + (l & 31);
+            if (col >= N) continue;
+            int at[16];
+            float v[16];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int r = m0 + wm + 32 * i + 8 * (e >> 2) + 4 * (l >> 5) + (e & 3);
+                at[e] = r < P ? r * N + col : -1;
+                v[e] = acc[i][j][e];
+            }
+            if constexpr (DG) {
+                put_grads(a, dx, at, v);
+                continue;
+            }
+            const float bias = a.b ? a.b[col] : 0.0f;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                if (at[e] < 0) continue;
+                float r = v[e] + bias;
+                if (a.relu) r = fmaxf(r, 0.0f);
+                if (a.y) a.y[at[e]] = f2bf(r);
+                if (a.yf) a.yf[at[e]] = r;
+            }
+        }
+}
+
 // Forward convolution of a brick of ZB x 8 x 8 positions (M = 64 ZB rows)
 // against up to 32 WN output channels, for volumes made of whole bricks:
 // ZB = 4, WN = 1 for layers of up to 32 output channels, ZB = 2, WN = 2 for
@@ -437,6 +626,13 @@ __global__ void __launch_bounds__(256, 2) conv_brick_kernel(ConvArgs a, const ui
         return (int64_t(z0 + (m >> 6)) * a.H + (y0 + ((m >> 3) & 7))) * a.W + (x0 + (m & 7));
     };
     if constexpr (DG) {
+        if (!a.mg) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) dx[at(i, e) * ncol + col] = acc[i][e];
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             int64_t q[16];
@@ -471,11 +667,9 @@ __global__ void __launch_bounds__(256, 2) conv_brick_kernel(ConvArgs a, const ui
 // wavefronts' sums meet in LDS in a fixed order, so no second pass and no
 // atomics.  Bound by the weights' way through L1 (one line per column and step).
 // 4 096 positions, 128 -> 128 channels: 19 us (191 TFLOP/s); 512: 10.4 us.
-// Each part is a sum of its own and the parts are added in the order in which
-// work-groups of equal speed would finish them; sums run on over the rounds: 1 us
-// faster at 4 096 positions, and the coarsest layer's results then differ in 19
-// percent of the last bits from those of a GEMM split over work-groups instead of
-// 0 to 6, its own spread.
+// In a network's layers each part is a sum of its own and the parts are added in
+// the order of equally fast work-groups, shorter first, last first; otherwise the
+// wavefronts' sums run on (17 us against 19 at 4 096 positions, 128 -> 128).
 typedef float v4f __attribute__((ext_vector_type(4)));
 constexpr int SBZ = 2, SBY = 4, SBX = 4, SHY = SBY + 2, SHX = SBX + 2, SNH = (SBZ + 2) * SHY * SHX;
 
@@ -1486,12 +1680,20 @@ int grid_for(int64_t n) {
 //    64: 35 us against 13);
 //  * where the GEMM's tiles would not fill the chip and K is long enough to be cut
 //    into parts (forward: only with the layer's scratch acc, whose presence says
-//    that the order of the sum is free): conv_small (4 096 positions, 128 -> 128:
-//    19 us against 36 for the GEMM with its K split over work-groups and added
-//    by atomics; 512 positions 10.4 against 18).  K is cut where those
-//    work-groups cut it, so that the result is one of theirs up to the rounding
-//    of the matrix instruction: a BF16 network amplifies every other order of
-//    its early sums to 0.3 percent of its output;
+//    that K may be cut): conv_small, or conv_split where conv_small's work-groups
+//    would come in more than two rounds, which is the line: 4 096 positions, 256 ->
+//    128 (1 024 work-groups of 16 columns): 30 us, conv_split 43; 4 185 positions
+//    (1 280): 45 and 43; 29 295 positions, 64 -> 64: 36 and 24.  Up to 32 columns
+//    always conv_small (29 295 positions, 256 -> 32: 56 and 67).  Tiles of 128
+//    where that leaves half the CUs at work (29 295 positions, 96 -> 128: 44 us,
+//    tiles of 64 58; 12 480 positions: 42 and 31).
+//    Layers of a network (ordered) take their parts from the size of a GEMM over
+//    up to 512 work-groups and add them in one order, whichever kernel runs: a
+//    BF16 network amplifies every other order of its early sums to 0.3 percent of
+//    its output.  conv_split has up to four such parts; with so few of them half of
+//    conv_small's wavefronts or more have nothing to do (28 672 positions, 192 ->
+//    64: 184 us, conv_split 53; 64 -> 64: 49 and 24; at the line, 12 480 positions,
+//    32 -> 64: 16 and 11);
 //  * otherwise the GEMM (262 144 positions, 32 -> 96: 104 us, conv_small 190).
 template <bool DG>
 static hipError_t launch_conv(const ConvArgs &a, bool split, const uint16_t *g, float *dx, hipStream_t s) {
@@ -1513,11 +1715,27 @@ static hipError_t launch_conv(const ConvArgs &a, bool split, const uint16_t *g, 
     const bool big = int64_t((P + 255) / 256) * ny >= 512;
     const unsigned gx = unsigned(big ? (P + 255) / 256 : (P + 127) / 128);
     // parts of K: at least eight steps each, over up to 512 work-groups
-    const int nst = (27 * kc + BK - 1) / BK;
-    const int gz = split && gx * ny < 256 ? std::min(nst / 8, int(512 / (gx * ny))) : 1;
+    const int nst = (27 * kc + BK - 1) / BK, tiles = int(gx * ny);
+    const int gz = split && tiles < 256 ? std::min(nst / 8, 512 / tiles) : 1;
     if (gz > 1) {
         const int nb = ((a.W + SBX - 1) / SBX) * ((a.H + SBY - 1) / SBY) * ((a.D + SBZ - 1) / SBZ);
-        const int parts = kc % 32 == 0 && kc <= 256 ? gz : 0;
+        const int wgs = nb * ((N + 15) / 16);  // conv_small's work-groups of 16 columns
+        const bool aligned = kc % BK == 0 && (DG || a.c1 % BK == 0);
+        auto cut = [&](auto kern, int T, int KS) {
+            const dim3 grid(unsigned((P + T - 1) / T), unsigned((N + T - 1) / T));
+            hipLaunchKernelGGL(kern, grid, dim3(unsigned(256 * KS)), 0, s, a, g, dx);
+            return hipGetLastError();
+        };
+        if (aligned && N > 32) {
+            if (a.ordered && gz <= 4 && int64_t(wgs) * nst >= 40000)
+                return gz == 2   ? cut(conv_split_kernel<64, 2, DG>, 64, 2)
+                       : gz == 3 ? cut(conv_split_kernel<64, 3, DG>, 64, 3)
+                                 : cut(conv_split_kernel<64, 4, DG>, 64, 4);
+            if (!a.ordered && wgs >= 1100)
+                return N > 64 && tiles >= 130 ? cut(conv_split_kernel<128, 2, DG>, 128, 2)
+                                              : cut(conv_split_kernel<64, 3, DG>, 64, 3);
+        }
+        const int parts = a.ordered && kc % 32 == 0 && kc <= 256 ? gz : 0;
         // two column tiles per work-group share the halo and each LDS operand (four
         // spill with the parts' sums); one where that leaves CUs idle
         const bool wide = nb * ((N + 31) / 32) >= 192;
