@@ -100,39 +100,55 @@ __device__ inline void wg_sum(double (&v)[NV], double *sh) {
 
 // r_ij^2 = (dx^2 + dy^2) + dz^2 without contraction: the edge decision is
 // taken exactly as stated
-__device__ inline double net_r2(const double *pos, int i, int j) {
-    const double dx = pos[3 * j] - pos[3 * i], dy = pos[3 * j + 1] - pos[3 * i + 1], dz = pos[3 * j + 2] - pos[3 * i + 2];
+__device__ inline double net_r2(const double *pi, const double *pj) {
+    const double dx = pj[0] - pi[0], dy = pj[1] - pi[1], dz = pj[2] - pi[2];
     return __dadd_rn(__dadd_rn(__dmul_rn(dx, dx), __dmul_rn(dy, dy)), __dmul_rn(dz, dz));
 }
 
 // Beads j != i with 0 < r_ij^2 < r_c^2, ascending j; deg may exceed NET_DEG
 // (only the first NET_DEG are stored; the host reports the excess).  One
-// wavefront per bead, 64 candidates at a time, compacted by ballots: with one
+// wavefront for PB beads, 64 candidates at a time, compacted by ballots: with one
 // thread per bead the scan was a chain of n tests on n / 256 work-groups
-// (314 us for 3 300 beads; now 12).  ROWS: the lists of the row-sorted solve,
-// as 16-bit indices (the conductances follow when the rows are laid out).
-template <bool ROWS>
+// (314 us for 3 300 beads; now 12).  PB = 1 while that leaves CUs idle; beyond
+// NET_ROWS each candidate's loads serve four beads (65 536 beads, the call with one
+// iteration: 10.6 -> 5.4 ms; the scan by threads 8.2).
+// ROWS: the lists of the row-sorted solve, as 16-bit indices (the conductances
+// follow when the rows are laid out).
+template <bool ROWS, int PB>
 __global__ void __launch_bounds__(NET_TB) net_edges_kernel(NetArgs a) {
-    const int i = blockIdx.x * (NET_TB / 64) + int(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (i >= a.n) return;  // uniform per wavefront
-    int k = 0;
+    const int i0 = (blockIdx.x * (NET_TB / 64) + int(threadIdx.x >> 6)) * PB, lane = threadIdx.x & 63;
+    if (i0 >= a.n) return;  // uniform per wavefront
+    double own[PB][3];
+    int k[PB];
+#pragma unroll
+    for (int b = 0; b < PB; ++b) {
+        k[b] = 0;
+        for (int d = 0; d < 3; ++d) own[b][d] = a.pos[3 * min(i0 + b, a.n - 1) + d];
+    }
     for (int j0 = 0; j0 < a.n; j0 += 64) {
         const int j = min(j0 + lane, a.n - 1);
-        const double r2 = net_r2(a.pos, i, j);
-        const bool hit = j0 + lane < a.n && r2 > 0.0 && r2 < a.rc2;
-        const uint64_t m = __ballot(hit);
-        const int at = k + __popcll(m & ((uint64_t(1) << lane) - 1));
-        if (hit && at < NET_DEG) {
-            if constexpr (ROWS) {
-                reinterpret_cast<uint16_t *>(a.nbr)[size_t(i) * NET_DEG + at] = uint16_t(j);
-            } else {
-                a.nbr[size_t(i) * NET_DEG + at] = j;
-                a.g[size_t(i) * NET_DEG + at] = 1.0 / sqrt(r2);
+        const double pj[3] = {a.pos[3 * j], a.pos[3 * j + 1], a.pos[3 * j + 2]};
+#pragma unroll
+        for (int b = 0; b < PB; ++b) {
+            const int i = i0 + b;
+            const double r2 = net_r2(own[b], pj);
+            const bool hit = i < a.n && j0 + lane < a.n && r2 > 0.0 && r2 < a.rc2;
+            const uint64_t m = __ballot(hit);
+            const int at = k[b] + __popcll(m & ((uint64_t(1) << lane) - 1));
+            if (hit && at < NET_DEG) {
+                if constexpr (ROWS) {
+                    reinterpret_cast<uint16_t *>(a.nbr)[size_t(i) * NET_DEG + at] = uint16_t(j);
+                } else {
+                    a.nbr[size_t(i) * NET_DEG + at] = j;
+                    a.g[size_t(i) * NET_DEG + at] = 1.0 / sqrt(r2);
+                }
             }
+            k[b] += __popcll(m);
         }
-        k += __popcll(m);
     }
-    if (lane == 0) a.deg[i] = k;
+#pragma unroll
+    for (int b = 0; b < PB; ++b)
+        if (lane == 0 && i0 + b < a.n) a.deg[i0 + b] = k[b];
 }
 
 // ---------------------------------------------------------------------------
@@ -163,7 +179,7 @@ __global__ void __launch_bounds__(NET_TB) net_rows_kernel(NetArgs a) {
     }
     if (lane == 0) a.cls[before] = i;  // the bead of each rank
     const int j = lane < di ? reinterpret_cast<const uint16_t *>(a.nbr)[size_t(i) * NET_DEG + lane] : 0;
-    a.g[size_t(lane) * a.n + before] = lane < di ? 1.0 / sqrt(net_r2(a.pos, i, j)) : 0.0;
+    a.g[size_t(lane) * a.n + before] = lane < di ? 1.0 / sqrt(net_r2(a.pos + 3 * i, a.pos + 3 * j)) : 0.0;
     reinterpret_cast<uint16_t *>(net_cols(a))[(size_t(lane >> 1) * a.n + before) * 2 + (lane & 1)] = uint16_t(8 * j);
 }
 
@@ -490,12 +506,12 @@ hipError_t launch_net_edges(const NetArgs &a, hipStream_t s) {
     if (a.n <= 0) return hipSuccess;
     const int nblk = (a.n + NET_TB / 64 - 1) / (NET_TB / 64);
     if (a.n <= NET_ROWS) {
-        hipLaunchKernelGGL(net_edges_kernel<true>, dim3(nblk), dim3(NET_TB), 0, s, a);
+        hipLaunchKernelGGL((net_edges_kernel<true, 1>), dim3(nblk), dim3(NET_TB), 0, s, a);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(net_rows_kernel, dim3(nblk), dim3(NET_TB), 0, s, a);
     } else {
-        hipLaunchKernelGGL(net_edges_kernel<false>, dim3(nblk), dim3(NET_TB), 0, s, a);
+        hipLaunchKernelGGL((net_edges_kernel<false, 4>), dim3((nblk + 3) / 4), dim3(NET_TB), 0, s, a);
     }
     return hipGetLastError();
 }
