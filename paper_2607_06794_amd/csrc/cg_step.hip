@@ -52,7 +52,11 @@ __device__ inline void pull(const CGArgs &a, const NodeNbr &nb, typename Codec<S
     }
 }
 
-// Eq. 3: rho_k = rref_k + sum_i d_i and j over opposite pairs
+// Eq. 3: rho_k over the populations d_i + w_i rref_k, and j over opposite pairs.
+// (Not rref_k + sum_i d_i: where a component is nearly absent its deviations add up
+// to -rref_k through partial sums as large, whose rounding is many times that of
+// the populations: 6e-8 against 1.4e-8 of rref_k, and a normal nearly along the
+// wall's turns that into up to 1e-3 of a population within four steps.)
 template <class C>
 __device__ inline void moments(const CGArgs &a, const C (&fv)[2][Q], C (&rho)[2], C (&j)[3]) {
 #pragma unroll
@@ -61,8 +65,8 @@ __device__ inline void moments(const CGArgs &a, const C (&fv)[2][Q], C (&rho)[2]
     for (int k = 0; k < 2; ++k) {
         C s = C(0);
 #pragma unroll
-        for (int i = 0; i < Q; ++i) s += fv[k][i];
-        rho[k] = C(a.rho_ref[k]) + s;
+        for (int i = 0; i < Q; ++i) s += fma_(wgt<C>(i), C(a.rho_ref[k]), fv[k][i]);
+        rho[k] = s;
 #pragma unroll
         for (int i = 1; i < Q; i += 2) {
             const C d = fv[k][i] - fv[k][i + 1];
