@@ -447,8 +447,9 @@ int lb_set_tiles(lb_ctx *ctx, const lb_tile *tile, hipStream_t stream);
 
 /* Time every supported tile shape for trial_steps >= 1 steps each (HIP events
  * on the stream), keep the fastest and return it in *best.  The trial steps
- * are real steps of the simulation (the state advances by n_shapes *
- * trial_steps steps).  Synchronises. */
+ * are real steps of the simulation: the state advances by 1 + trial_steps
+ * steps per shape.  With tau = 1 there is nothing to choose from: the present
+ * shape alone is timed, and stays.  Synchronises. */
 int lb_autotune(lb_ctx *ctx, int32_t trial_steps, hipStream_t stream, lb_tile *best);
 
 /*

@@ -1661,40 +1661,43 @@ int lb_autotune(lb_ctx *c, int32_t trial_steps, hipStream_t stream, lb_tile *bes
     const bool tau1 = c->p.tau[0] == 1.0 && c->p.tau[1] == 1.0;
     const int shapes[4][2] = {{4, 1}, {8, 1}, {8, 2}, {16, 2}};
     const int nz = c->p.nz;
-    std::vector<int> chunks;
-    for (int zc : {4, 8, 12, 16, 24, 32, 48, 64})
-        if (zc <= nz) chunks.push_back(zc);
-    if (chunks.empty()) chunks.push_back(nz);
+    std::vector<lb_tile> trials;
+    if (two_pass(c->p)) {
+        // every shape launches the same two passes: the present one stays
+        trials.push_back({c->tile.tile_y, c->tile.rows_per_thread, c->zchunk, 0.0});
+    } else {
+        std::vector<int> chunks;
+        for (int zc : {4, 8, 12, 16, 24, 32, 48, 64})
+            if (zc <= nz) chunks.push_back(zc);
+        if (chunks.empty()) chunks.push_back(nz);
+        for (const auto &sh : shapes)
+            for (int zc : chunks)
+                if (tile_ok(sh[0], sh[1], tau1)) trials.push_back({sh[0], sh[1], zc, 0.0});
+    }
     hipEvent_t e0, e1;
     HIP_TRY(hipEventCreate(&e0), "event");
     HIP_TRY(hipEventCreate(&e1), "event");
     lb_tile b{0, 0, 0, 1e30};
     int rc = LB_OK;
-    for (const auto &sh : shapes) {
-        if (!tile_ok(sh[0], sh[1], tau1)) continue;
-        for (int zc : chunks) {
-            lb_tile t{sh[0], sh[1], zc, 0.0};
-            if ((rc = lb_set_tiles(c, &t, stream)) != LB_OK) break;
-            if ((rc = lb_step(c, 1, stream)) != LB_OK) break;  // first launch of a shape untimed
-            (void)hipEventRecord(e0, stream);
-            if ((rc = lb_step(c, trial_steps, stream)) != LB_OK) break;
-            (void)hipEventRecord(e1, stream);
-            if (hipEventSynchronize(e1) != hipSuccess) {
-                rc = fail(LB_EHIP, "autotune sync");
-                break;
-            }
-            float ms = 0.f;
-            (void)hipEventElapsedTime(&ms, e0, e1);
-            const double us = 1e3 * ms / trial_steps;
-            if (us < b.us_per_step) b = lb_tile{sh[0], sh[1], zc, us};
+    for (const lb_tile &t : trials) {
+        if (trials.size() > 1 && (rc = lb_set_tiles(c, &t, stream)) != LB_OK) break;
+        if ((rc = lb_step(c, 1, stream)) != LB_OK) break;  // first launch of a shape untimed
+        (void)hipEventRecord(e0, stream);
+        if ((rc = lb_step(c, trial_steps, stream)) != LB_OK) break;
+        (void)hipEventRecord(e1, stream);
+        if (hipEventSynchronize(e1) != hipSuccess) {
+            rc = fail(LB_EHIP, "autotune sync");
+            break;
         }
-        if (rc != LB_OK) break;
+        float ms = 0.f;
+        (void)hipEventElapsedTime(&ms, e0, e1);
+        const double us = 1e3 * ms / trial_steps;
+        if (us < b.us_per_step) b = lb_tile{t.tile_y, t.rows_per_thread, t.zchunk, us};
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc != LB_OK) return rc;
-    rc = lb_set_tiles(c, &b, stream);
-    if (rc != LB_OK) return rc;
+    if (trials.size() > 1 && (rc = lb_set_tiles(c, &b, stream)) != LB_OK) return rc;
     *best = b;
     return LB_OK;
 }

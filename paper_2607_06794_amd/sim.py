@@ -350,7 +350,8 @@ class Lattice:
         """Pick the fastest tile shape with lb_autotune (real steps), caching by lattice class.
 
         The cache is a JSON file keyed by (gfx arch, precision, lattice shape,
-        tau = 1); a hit applies the stored shape without running trials.
+        tau = 1); a hit applies the stored shape without running trials.  With
+        tau = 1 no shape changes the step: 1 + trial_steps steps time it.
         """
         path = cache or os.path.join(
             os.environ.get("XDG_CACHE_HOME", os.path.expanduser("~/.cache")), "paper_2607_06794_amd", "tiles.json")
