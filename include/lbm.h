@@ -245,7 +245,8 @@ int lb_init(const lb_params *p, const lb_buffers *buf, const double *rho_init_ho
  * the next step.  A no-op without rods.  Asynchronous. */
 int lb_rods_step(lb_ctx *ctx, hipStream_t stream);
 /* nsteps coupled steps: lb_step(1) followed by lb_rods_step or lb_fil_step,
- * nsteps times, with the same results.  Asynchronous. */
+ * nsteps times, with the same results.  Asynchronous.  After LB_EHIP from a
+ * call of several steps the state is lost (see lb_step). */
 int lb_coupled_step(lb_ctx *ctx, int32_t nsteps, hipStream_t stream);
 
 /* Copy the rod states to out_host [n_rods][13] (layout as in lb_init).
@@ -270,7 +271,9 @@ int lb_fil_get(lb_ctx *ctx, double *out_host, hipStream_t stream);
 
 /* Advance the fluid nsteps >= 0 time steps (pull stream, boundaries, moments,
  * pseudopotential force, velocity shift, BGK collision, store; reservoir
- * ledger).  Asynchronous. */
+ * ledger).  Asynchronous.  After LB_EHIP from a call of two steps or more the
+ * state is lost: the steps within a call may pass on moments, over the
+ * populations it began with, and the context can only be destroyed. */
 int lb_step(lb_ctx *ctx, int32_t nsteps, hipStream_t stream);
 
 /* FP64 reductions of the current state into *out (host).  Synchronises.
@@ -455,9 +458,10 @@ int lb_autotune(lb_ctx *ctx, int32_t trial_steps, hipStream_t stream, lb_tile *b
 /*
  * Batches (many lattices per launch).  A batch advances n >= 1 lattices that
  * were each set up with lb_init (any sizes, parameters, rod counts and tile
- * shapes; one precision) with shared launches: one fused-step launch per
- * tile class walks a device work list of (lattice, tile) entries with a
- * parameter record per lattice, and each rod pass covers the rods of every
+ * shapes; one precision) with shared launches: one launch per tile class (two,
+ * of stream and collision, for the lattices with tau = 1) walks a device work
+ * list of (lattice, tile) entries with a parameter record per lattice, and
+ * each rod pass covers the rods of every
  * lattice.  Results are identical to stepping each lattice alone with
  * lb_step and lb_rods_step.  While a batch exists its lattices must be
  * stepped only through it (lb_batch_step fails with LB_EINVAL otherwise);
@@ -469,10 +473,11 @@ typedef struct lb_batch lb_batch;
 size_t lb_batch_workspace_bytes(lb_ctx *const *ctxs, int32_t n); /* 0 on bad input */
 /* Synchronises (uploads the work lists and records). */
 int lb_batch_create(lb_ctx *const *ctxs, int32_t n, void *workspace_dev, hipStream_t stream, lb_batch **out);
-/* nsteps steps of every lattice: the fused fluid step, then (with_rods != 0)
+/* nsteps steps of every lattice: the fluid step, then (with_rods != 0)
  * the rod update.  use_graph != 0: pairs of steps run as one HIP graph,
  * captured on first use on a stream of the batch's own and replayed on
- * `stream` (the graph holds no memset or memcpy nodes).  Asynchronous. */
+ * `stream` (the graph holds no memset or memcpy nodes).  Asynchronous.  After
+ * LB_EHIP from a call of two steps or more the lattices' state is lost. */
 int lb_batch_step(lb_batch *b, int32_t nsteps, int32_t with_rods, int32_t use_graph, hipStream_t stream);
 int lb_batch_destroy(lb_batch *b);
 
