@@ -1464,10 +1464,11 @@ size_t lb_sur_loss_scratch_bytes(void) { return SUR_LOSS_SCRATCH * sizeof(double
 
 int lb_sur_loss_result(const void *scratch, double *result_host, hipStream_t stream) {
     if (!scratch || !result_host) return fail(LB_EINVAL, "bad loss arguments");
-    HIP_TRY(hipMemcpyAsync(result_host, static_cast<const double *>(scratch) + SUR_LOSS_PARTS, 4 * sizeof(double),
-                           hipMemcpyDeviceToHost, stream),
+    // one call that copies on the stream and waits for it: a training step takes 28 us
+    // more with an asynchronous copy and a synchronisation (1 460 and 1 432)
+    HIP_TRY(hipMemcpyWithStream(result_host, static_cast<const double *>(scratch) + SUR_LOSS_PARTS, 4 * sizeof(double),
+                                hipMemcpyDeviceToHost, stream),
             "copy loss");
-    HIP_TRY(hipStreamSynchronize(stream), "loss sync");
     return LB_OK;
 }
 
