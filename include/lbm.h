@@ -139,8 +139,8 @@ typedef struct {
      * spacing; random bits from a xorshift32 stream per node and step,
      * seeded by a hash of node, step and sr_seed and advanced per population
      * array, so they depend on node, array and step only), which keeps the
-     * stored errors unbiased.  Only
-     * the fused Shan-Chen step rounds stochastically (lb_init, the rod passes
+     * stored errors unbiased.  Only the Shan-Chen step itself rounds
+     * stochastically (lb_init, the rod passes
      * and the surrogate's lift round to nearest); a batch does not take such
      * lattices (LB_ENOTSUP). */
     int32_t round_stochastic;

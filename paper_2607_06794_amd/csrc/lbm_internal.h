@@ -8,7 +8,6 @@
 
 namespace lbm {
 
-// Arguments of the fused step kernel (passed by value as kernel arguments).
 // n / d for n < 2^31 by a divisor known at the launch: a product and a shift
 // (m = floor(2^(31 + s) / d) + 1 with 2^s >= d makes the quotient exact)
 struct Divider {
@@ -24,11 +23,14 @@ struct Divider {
     }
 };
 
+// Arguments of the step kernels (passed by value).
 struct StepArgs {
     const void *fsrc;
     void *fdst;
     const uint8_t *mat;
-    double *ledger_part;  // [nty*ntx][2] running FP64 sums, one slot per xy tile
+    // [..][2] running FP64 sums: a slot per xy tile, or (two-pass step) per block
+    // of NB nodes that touches the plane below the reservoir
+    double *ledger_part;
     unsigned *status;
     int nx, ny, nz;
     int px, py, pz;
@@ -44,9 +46,13 @@ struct StepArgs {
     // interfacial evaporation sink (Eq. 8); sink = 0: off
     int sink;
     double sink_J0, sink_K, sink_h0;
-    const int32_t *h_read;  // [nz][nx*ny] liquid nodes per column and z chunk of the previous step
+    // [nz][nx*ny] liquid nodes per column and z chunk of the previous step (the
+    // two-pass step keeps whole columns, in the first plane)
+    const int32_t *h_read;
     int32_t *h_write;       // the same for this step
-    double *sink_ledger;    // [ntx*nty*nzc][2] mass moved A -> B, one running pair per work-group
+    // [..][2] mass moved A -> B, a running pair per work-group (ntx*nty*nzc, or one
+    // per block of NB nodes)
+    double *sink_ledger;
     void *rho_out;          // [2][fs] densities in compute precision (two-pass step: psi_k of every node), or null
     Divider by_nx, by_ny;
     void *jm;               // two-pass step: 5 arrays for j and the deviations between the passes
@@ -75,11 +81,12 @@ struct CGArgs {
 };
 hipError_t launch_cg_step(int prec, const CGArgs &a, hipStream_t s);
 
-// Tile shape of the fused step: TX = 64 columns x tile_y rows, each thread
-// owning rows_per_thread rows; the work-group marches zchunk planes.
+// Tile shape of the fused step: TX = 64 columns x tile_y rows, one row per thread
+// (two are accepted with tau = 1, which has no tiles); the work-group marches
+// zchunk planes.
 struct TileCfg {
     int tile_y = 8;
-    int rows_per_thread = 2;
+    int rows_per_thread = 1;
     int zchunk = 0;
 };
 

@@ -38,7 +38,7 @@
 //    kernel; the step stores zero deviations into all of them beforehand, so
 //    that waves cut by a rod store whole lines.  On lattices with rods the
 //    step also stores every node's densities (compute precision; zero on rod
-//    nodes), which the rod passes read instead of summing 19 populations per
+//    nodes here, the wall's psi after the two passes), which the rod passes read instead of summing 19 populations per
 //    surface node in the order of their lists.
 //
 // Evaporation sink (separate instantiations; FP32 storage, or FP64 with
@@ -628,7 +628,7 @@ __global__ void __launch_bounds__(64 * TY) sc_step_batch_kernel(const StepArgs *
 // step, fused -> two passes (stream + collide):
 //   FP32 256 x 128 x 64: 145 -> 120 us (5.3 TB/s, the rate of a large copy);
 //     with the densities of a rod lattice stored, 162 -> 134 us
-//   FP16, stochastic: 137 -> 82 us;  FP64: 299 us (5.1 TB/s)
+//   FP16, stochastic: 137 -> 80 us;  FP64: 299 us (5.1 TB/s)
 //   FP32 117 x 51 x 37: 61 -> 18 us;  FP64 32^3: 64 -> 10.5 us (two launches)
 // so tau = 1 always takes this form.  With tau != 1 the collision needs the
 // populations themselves, which would have to be pulled or stored once more.
@@ -960,8 +960,8 @@ __global__ void __launch_bounds__(NB) sc_stream_kernel(StepArgs a) {
 //   FP32 256 x 128 x 64: 124 -> 66 us (48 + 27 in the profiler's clocks);
 //     128 x 64 x 64: 33 -> 26; 117 x 51 x 37: 18.3 -> 17.4
 //   FP64 256 x 128 x 64: 304 -> 138 us; 128 x 64 x 64: 64 -> 43; 32^3: 14.5 -> 13
-// (128 x 64 x 32 alone is even in FP32, 18.8 -> 19.5), so every call of two steps
-// or more takes it.  Bricks of 32 x 4 x 4 are as fast on large lattices and
+// (128 x 64 x 32 alone is even in FP32, 18.8 -> 19.5).  Which calls of two steps or
+// more take it, and why the line lies there: moment_chain in lbm_api.hip.  Bricks of 32 x 4 x 4 are as fast on large lattices and
 // 8 percent slower on the ragged one; reading the neighbours' moments through L1
 // instead of LDS: 61 us for the pass, before the rest population had its array.
 constexpr int XB = 32, YB = 4, ZB = 2, BT = XB * YB * ZB;
@@ -1146,8 +1146,7 @@ __global__ void __launch_bounds__(NB) sc_collide_kernel(StepArgs a) {
         }
     }
 }
-// batches: a work list of (lattice, run of BATCH_RUN node blocks) entries
-constexpr int BATCH_RUN = 1;
+// batches: a work list of (lattice, block of NB nodes) entries
 template <class S>
 __global__ void __launch_bounds__(NB) sc_stream_batch_kernel(const StepArgs *__restrict__ all,
                                                              const int2 *__restrict__ work) {

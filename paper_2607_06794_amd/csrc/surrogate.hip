@@ -1737,7 +1737,10 @@ static hipError_t launch_conv(const ConvArgs &a, bool split, const uint16_t *g, 
         }
         const int parts = a.ordered && kc % 32 == 0 && kc <= 256 ? gz : 0;
         // two column tiles per work-group share the halo and each LDS operand (four
-        // spill with the parts' sums); one where that leaves CUs idle
+        // spill with the parts' sums); one where that leaves CUs idle.  us with one /
+        // two by work-groups of two: 128 -> 128 channels 7.6 / 10.3 with 64, 10.8 /
+        // 10.5 with 168, 11.0 / 10.9 with 256, 19.7 / 17.4 with 512; 128 -> 256 7.7 /
+        // 10.3 with 128, 19.1 / 16.6 with 512: even from 168 to 400, 192 taken
         const bool wide = nb * ((N + 31) / 32) >= 192;
         const dim3 grid(unsigned(nb), unsigned(wide ? (N + 31) / 32 : (N + 15) / 16));
         auto run = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(512), 0, s, a, g, dx, parts); };
@@ -1769,10 +1772,12 @@ hipError_t launch_conv_dgrad(const ConvArgs &a, const uint16_t *g, float *dx, hi
 hipError_t launch_conv_wgrad(const ConvArgs &a, const uint16_t *g, float *dw, float *db, hipStream_t s) {
     const int nb = ((a.W + BRX - 1) / BRX) * ((a.H + BRY - 1) / BRY) * ((a.D + 3) / 4);
     const int ncb = (a.c1 + a.c2 + 31) / 32, nob = (a.cout + 31) / 32;
-    // the bricks shared out over about WG_TARGET work-groups (two fit a CU):
-    // fewer leave CUs idle, more add their sums into dw more often (the 15
-    // layers of the 128 x 64 x 32 canvas: 413 us with 384, 417 with 512, 595
-    // with 256, 607 with 768)
+    // the bricks shared out over about WG_TARGET work-groups (two fit a CU, 512 the
+    // chip): fewer leave CUs idle, more run in a second wave and add their sums into
+    // dw more often.  us of a network's 15 layers with 256 / 384 / 448 / 512 / 640:
+    // canvas 32 x 64 x 128 450 / 413 / 407 / 424 / 556; 32 x 56 x 128 420 / 397 / 399 /
+    // 400 / 538; 40 x 72 x 136 664 / 570 / 577 / 562 / 776; 24 x 40 x 104 290 / 305 /
+    // 303 / 316 / 411; 16 x 32 x 64 178 / 196 / 196 / 201 / 215; smaller ones even
     constexpr int WG_TARGET = 448;
     const int share = std::max(1, std::min(nb, WG_TARGET / (3 * ncb * nob)));
     hipLaunchKernelGGL(conv_wgrad_kernel, dim3(unsigned(share), unsigned(3 * ncb), unsigned(nob)), dim3(256), 0, s, a, g,

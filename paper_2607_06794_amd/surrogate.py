@@ -78,7 +78,8 @@ class UNet:
         self.pb = torch.zeros(n, dtype=torch.int16, device=self.device)
         self.pt = torch.zeros(n, dtype=torch.int16, device=self.device)  # weights packed for the forward
         self.step_count = 0
-        # activations (BF16) and gradients (FP32) per level
+        # activations (BF16) per level; gradients: gA and gB take a layer's
+        # pre-activation gradient (BF16) or a pooled input's (FP32), gcat FP32
         self.P = [(D >> l) * (H >> l) * (W >> l) for l in range(nlev)]
         bf = dict(dtype=torch.int16, device=self.device)
         self.act = {}
@@ -94,8 +95,8 @@ class UNet:
         self.loss_scratch = torch.zeros(self.lib.lb_sur_loss_scratch_bytes() // 4 + 64, **f32)
         # BF16 pre-activation gradient of the layer being differentiated
         self.gm = torch.zeros(max(self.P[lvl] * co for _, _, _, co, _, lvl in self.layers), **bf)
-        # FP32 scratch for the split-K forward of the coarse levels
-        self.acc = torch.zeros(max(self.P[lvl] * co for _, _, _, co, _, lvl in self.layers if lvl >= 1), **f32)
+        # not written: the pointer lets a coarse layer's forward sum K in parts
+        self.acc = torch.zeros(4, **f32)
         # output scale per channel (the network predicts changes in these units)
         self.scale = np.ones(6, np.float32)
         # input normalisation: lattice velocities are O(1e-3 .. 1e-2) next to
