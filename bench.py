@@ -1,4 +1,4 @@
-"""Throughput of the fused Shan-Chen D3Q19 step on one MI355X.
+"""Throughput of the coupled Shan-Chen D3Q19 step on one MI355X.
 
 Workload (default): the elongated sessile cap on the 256 x 128 x 64 lattice
 (footprint 150 x 36, height 24, stripe 160 x 40, reservoir plane on top),
@@ -6,9 +6,10 @@ FP32 populations.  One step = one pass of the hot path over the lattice.
 Inputs are resident in HBM before the timed region starts.
 
 Prints ONE JSON line with the metric (MLUPS over fluid nodes), a roofline
-object for the fused step kernel (algorithmic bytes / average launch time,
-measured with HIP events on the launch stream) and the FP64 oracle timed on
-the host cores on a bounded sample of the same workload.
+object for the two kernels of a fluid step inside a call of many (the bytes
+that they cannot do without / the fluid step's time, from HIP events on the
+launch stream) and the FP64 oracle timed on the host cores on a bounded sample
+of the same workload.
 """
 from __future__ import annotations
 
@@ -26,7 +27,6 @@ import time  # noqa: E402
 import numpy as np  # noqa: E402
 
 ROOT = os.path.dirname(os.path.abspath(__file__))
-TILE_CACHE = None  # JSON file of the autotuner's choices (--tile-cache; None: the per-user default)
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0  # MI355X published HBM3E bandwidth
@@ -43,11 +43,15 @@ def algorithmic_bytes_per_lu(prec):
     return 2 * 19 * 2 * BYTES_PER_ELEM[prec]
 
 
-def density_store_bytes_per_lu(prec):
-    # lattices with rods: the step also writes both densities in compute
-    # precision (FP64 for FP64 storage, else FP32) for the rod passes -- the
-    # library's choice, outside the algorithmic bytes
-    return 2 * (8 if prec == "f64" else 4)
+def step_bytes_per_lu(prec, rho_ref=0.0):
+    # a fluid step inside a call: the stream pass and the collide pass, which
+    # pass on psi_k and j (with a storage reference also rho_k - rho_ref) in
+    # compute precision.  FP32 and FP64 steps go from moments to moments (per
+    # component rho, u and the rest population); 16-bit ones from populations
+    # to populations
+    c = 8 if prec == "f64" else 4
+    state = 10 * c if prec in ("f32", "f64") else 2 * 19 * BYTES_PER_ELEM[prec]
+    return 2 * state + 2 * (5 + (2 if rho_ref else 0)) * c
 
 
 # 16-bit storage forms: (storage, reference density) -- rho_ref = 0 stores
@@ -102,8 +106,7 @@ def rod_params(lp, length=24.0):
     return lp
 
 
-def time_step(case, prec, steps, warmup, tile, autotune, rods=None, segment=0, rho_ref=(0.0, 0.0),
-              rounding="nearest"):
+def time_step(case, prec, steps, warmup, tile, rods=None, segment=0, rho_ref=(0.0, 0.0), rounding="nearest"):
     """Time `steps` coupled steps (fluid step + rod update).
 
     With rods, the steps run in segments of at most `segment` steps, each
@@ -112,10 +115,12 @@ def time_step(case, prec, steps, warmup, tile, autotune, rods=None, segment=0, r
     stress placement) cross the liquid-vapour interface and the coupled state
     degrades after a few hundred steps, and timing a degraded state would time
     less rod work.  A segment is one call of that many steps.  Returns (ms per
-    whole step, ms per fluid step on its own, fluid nodes, observables of the
-    last segment, chosen tile, segments).  The fluid step's own duration comes
-    from a pair of HIP events around each of up to 100 single steps on a fresh
-    lattice, after the timed segments.
+    whole step inside a call, ms per fluid step in a call of its own, fluid
+    nodes, observables of the last segment, segments).  The second
+    comes from a pair of HIP events around each of up to 100 calls of one step
+    on a fresh lattice, after the timed segments: such a call goes from
+    populations to populations, while FP32 and FP64 steps inside a call pass on
+    moments.
     """
     import torch
 
@@ -123,9 +128,8 @@ def time_step(case, prec, steps, warmup, tile, autotune, rods=None, segment=0, r
     from tests import cases
 
     lp = rod_params(cases.lattice_params(case, prec, rho_ref=rho_ref, rounding=rounding, **tile))
-    chosen = dict(tile)
     seg = steps if (rods is None or segment <= 0) else min(segment, steps)
-    total_ms = fused_ms = 0.0
+    total_ms = 0.0
     done = nseg = 0
     n_fluid = 0
     obs = None
@@ -134,14 +138,6 @@ def time_step(case, prec, steps, warmup, tile, autotune, rods=None, segment=0, r
         lat = Lattice(lp, case["rho"], case["mat"], rods=rods)
         if nseg == 0:
             n_fluid = int(lat.observables()["fluid_nodes"])
-            if autotune:
-                # tile shape picked by the library's autotuner (its trial steps
-                # are ordinary fluid steps, run before the timed region)
-                t = lat.autotune(trial_steps=10, cache=TILE_CACHE)
-                chosen = {k: t[k] for k in ("tile_y", "rows_per_thread", "zchunk")}
-                lat.close()
-                lp = rod_params(cases.lattice_params(case, prec, rho_ref=rho_ref, rounding=rounding, **chosen))
-                lat = Lattice(lp, case["rho"], case["mat"], rods=rods)
             lat.coupled_step(warmup)
         n = min(seg, steps - done)
         torch.cuda.synchronize()
@@ -169,14 +165,14 @@ def time_step(case, prec, steps, warmup, tile, autotune, rods=None, segment=0, r
         b.record(stream)
         lat.rods_step()
     torch.cuda.synchronize()
-    fused_ms = sum(a.elapsed_time(b) for a, b in ev)
+    single_ms = sum(a.elapsed_time(b) for a, b in ev)
     lat.close()
-    return total_ms / steps, fused_ms / single, n_fluid, obs, chosen, nseg
+    return total_ms / steps, single_ms / single, n_fluid, obs, nseg
 
 
 def batched_form(steps, warmup, n_lattices=64):
     """Many-droplet sweep: every lattice stepped alone, one after another, against
-    the batched step (one launch per tile class and per rod pass) with and
+    the batched step (shared launches for each pass) with and
     without the HIP graph, fluid-only and coupled (with rods).  Each coupled
     variant starts from freshly initialised lattices (rods placed anywhere in
     the fluid degrade the state within a few hundred steps)."""
@@ -187,7 +183,6 @@ def batched_form(steps, warmup, n_lattices=64):
     from tests import cases
 
     specs = list(inputs.sweep_droplets(n_lattices))
-    tuned = {}
 
     def make():
         lats = []
@@ -196,17 +191,7 @@ def batched_form(steps, warmup, n_lattices=64):
                      body_force=(0.0, 0.0, 0.0))
             lp = rod_params(cases.lattice_params(c, "f32"), length=d["rod_length"])
             lp.eps_att = d["eps_att"]
-            lat = Lattice(lp, d["rho"], d["mat"], rods=d["rods"])
-            key = d["shape"]
-            if key not in tuned:
-                # tile shape per grid class from the autotuner (its trial steps
-                # are fluid steps of the first lattice of the class)
-                t = lat.autotune(trial_steps=5, cache=TILE_CACHE)
-                tuned[key] = (t["tile_y"], t["rows_per_thread"], t["zchunk"])
-                lat.close()
-                lat = Lattice(lp, d["rho"], d["mat"], rods=d["rods"])
-            lat.set_tiles(*tuned[key])
-            lats.append(lat)
+            lats.append(Lattice(lp, d["rho"], d["mat"], rods=d["rods"]))
         torch.cuda.synchronize()
         return lats
 
@@ -256,7 +241,8 @@ def batched_form(steps, warmup, n_lattices=64):
         out[key]["status"] = {v: res[v][1] for v in res}
         log(f"[bench] batched {key}: solo {res['solo'][0]:.2f} ms, batched {res['batched'][0]:.2f} ms, "
             f"graph {res['graph'][0]:.2f} ms per step")
-    out["grid_classes"] = {f"{k[2]}x{k[1]}x{k[0]}": v for k, v in tuned.items()}
+    shapes = ["{2}x{1}x{0}".format(*d["shape"]) for d in specs]
+    out["grid_classes"] = {k: shapes.count(k) for k in sorted(set(shapes))}
     return out
 
 
@@ -686,11 +672,12 @@ def copy_probe(mib, reps=5):
             "us_per_copy": ms * 1e3, "gbs_read_plus_written": 2 * n * 4 / (ms * 1e-3) / 1e9}
 
 
-def traffic_record(prec, tile, n_fluid, ms_fused, rods=False, bpl=None):
-    """Measured HBM traffic of the fused step from the committed counter
-    record (FETCH_SIZE and WRITE_SIZE per launch, each scaled by what the
-    counter reads for a plain copy of known size), or None when the record
-    does not describe this kernel source, precision, tile and lattice."""
+def traffic_record(prec, n_fluid, ms_fluid, rods=False):
+    """Measured HBM traffic of a fluid step inside a call from the committed
+    counter record (FETCH_SIZE and WRITE_SIZE per launch of its two kernels,
+    each scaled by what the counter reads for a plain copy of known size), or
+    None when the record does not describe this kernel source, precision and
+    lattice."""
     import hashlib
 
     path = os.path.join(ROOT, "profiles", "sc_step_traffic.json")
@@ -701,13 +688,13 @@ def traffic_record(prec, tile, n_fluid, ms_fused, rods=False, bpl=None):
             sha = hashlib.sha256(fh.read()).hexdigest()
     except (OSError, ValueError):
         return None
-    if rec.get("sc_step_sha256") != sha or rec.get("prec") != prec or rec.get("tile") != tile \
-            or rec.get("fluid_nodes") != n_fluid or bool(rec.get("rods", False)) != bool(rods):
+    if rec.get("sc_step_sha256") != sha or rec.get("prec") != prec or rec.get("fluid_nodes") != n_fluid \
+            or bool(rec.get("rods", False)) != bool(rods):
         return None
-    kib = 1024.0
-    b = rec["fetch_kib"] * kib * rec["fetch_scale"] + rec["write_kib"] * kib * rec["write_scale"]
-    bpl = algorithmic_bytes_per_lu(prec) if bpl is None else bpl
-    return {"bytes_per_launch": b, "gbs": b / (ms_fused * 1e-3) / 1e9, "vs_algorithmic": b / (bpl * n_fluid)}
+    b = sum(1024.0 * (k["fetch_kib"] * rec["fetch_scale"] + k["write_kib"] * rec["write_scale"])
+            for k in rec["kernels"].values())
+    return {"bytes_per_step": b, "gbs": b / (ms_fluid * 1e-3) / 1e9,
+            "vs_needed": b / (step_bytes_per_lu(prec) * n_fluid)}
 
 
 def network_form(case, reps=5, n_rods=300, seed=5000):
@@ -748,14 +735,15 @@ def network_form(case, reps=5, n_rods=300, seed=5000):
 
 
 def cg_form(steps=200, warmup=20):
-    """The paper's colour-gradient step (three passes: colour, normals, then
-    collision with the capillary force and recolouring) on the same cap under
-    a lid (the step takes no reservoir), FP32: 150 / 60 / 120 degrees on
-    stripe / surround / lid, sigma = 0.01, beta = 0.7.  Timed per step with
-    HIP events on the launch stream; bytes per fluid node: the method's
-    minimum 304 (each population read and written once) and the three-pass
-    design's 496 (populations read twice, C written once and read once,
-    normal and |grad C| written once and read once)."""
+    """The paper's colour-gradient step (four passes: stream with colour and
+    moments, ghost colours of the walls, normals, then collision with the
+    capillary force and recolouring) on the same cap under a lid (the step
+    takes no reservoir), FP32: 150 / 60 / 120 degrees on stripe / surround /
+    lid, sigma = 0.01, beta = 0.7.  Timed per step with HIP events on the
+    launch stream; bytes per fluid node: the method's minimum 304 (each
+    population read and written once) and the passes' 388 (besides, C written
+    once and read twice, rho_k and j, the normal and |grad C| written once and
+    read once)."""
     import torch
 
     from paper_2607_06794_amd import inputs
@@ -784,17 +772,18 @@ def cg_form(steps=200, warmup=20):
     o = lat.observables(allow_unstable=True)
     lat.close()
     return {"us_per_step": ms * 1e3, "mlups": n_fluid / (ms * 1e-3) / 1e6, "fluid_nodes": n_fluid,
-            "gbs_at_304": 304 * n_fluid / (ms * 1e-3) / 1e9, "gbs_at_496": 496 * n_fluid / (ms * 1e-3) / 1e9,
-            "frac_at_496": 496 * n_fluid / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, "status": int(o["status"]),
-            "note": "colour-gradient step, cap under a lid, FP32, three passes per step"}
+            "gbs_at_304": 304 * n_fluid / (ms * 1e-3) / 1e9, "gbs_at_388": 388 * n_fluid / (ms * 1e-3) / 1e9,
+            "frac_at_388": 388 * n_fluid / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, "status": int(o["status"]),
+            "note": "colour-gradient step, cap under a lid, FP32, four passes per step"}
 
 
 def filament_form(steps=100, warmup=10):
     """The paper's bead-spring filaments (Eqs. 9-12) in the same cap: as many
     of 200 requested straight chains of twelve beads (L = 24) as fit inside
-    the liquid, eps_coh = 0.004, FP32 fluid.  Timed per coupled step (fused
-    step + filament update: gather, partner lists, five substeps, spread,
-    apply) and per fused step, with HIP events on the launch stream."""
+    the liquid, eps_coh = 0.004, FP32 fluid.  Timed with HIP events on the
+    launch stream per coupled step (fluid step + filament update: gather,
+    partner lists, five substeps, spread, apply) inside a call, and, on a fresh
+    lattice, for calls of one fluid step and one filament update in turn."""
     import torch
 
     from paper_2607_06794_amd import inputs
@@ -813,22 +802,30 @@ def filament_form(steps=100, warmup=10):
     lat.coupled_step(warmup)
     torch.cuda.synchronize()
     stream = torch.cuda.current_stream()
-    ev = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for _ in range(steps)]
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     e0.record(stream)
-    for a, b in ev:
-        a.record(stream)
-        lat.step(1)
-        b.record(stream)
-        lat.filament_step()
+    lat.coupled_step(steps)
     e1.record(stream)
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1) / steps
-    mf = sum(a.elapsed_time(b) for a, b in ev) / steps
     o = lat.observables(allow_unstable=True)
     lat.close()
-    return {"filaments": nf, "beads": nf * 12, "us_per_coupled_step": ms * 1e3, "us_fused_fluid_step": mf * 1e3,
-            "us_filament_update": (ms - mf) * 1e3, "mlups": n_fluid / (ms * 1e-3) / 1e6, "status": int(o["status"]),
+    lat = Lattice(lp, case["rho"], case["mat"], beads=beads)
+    lat.coupled_step(warmup)
+    torch.cuda.synchronize()
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(2 * steps + 1)]
+    ev[0].record(stream)
+    for s in range(steps):
+        lat.step(1)
+        ev[2 * s + 1].record(stream)
+        lat.filament_step()
+        ev[2 * s + 2].record(stream)
+    torch.cuda.synchronize()
+    mf = sum(ev[2 * s].elapsed_time(ev[2 * s + 1]) for s in range(steps)) / steps
+    mu = sum(ev[2 * s + 1].elapsed_time(ev[2 * s + 2]) for s in range(steps)) / steps
+    lat.close()
+    return {"filaments": nf, "beads": nf * 12, "us_per_coupled_step": ms * 1e3, "us_single_fluid_step": mf * 1e3,
+            "us_single_filament_update": mu * 1e3, "mlups": n_fluid / (ms * 1e-3) / 1e6, "status": int(o["status"]),
             "placement": "straight chains fully inside the cap (clearance 2.2, margin 0.5), of 200 requested"}
 
 
@@ -874,12 +871,10 @@ def main():
                     help="weight of the squared relative rho_A mass error in the training loss")
     ap.add_argument("--surrogate-snapshots", type=int, default=16,
                     help="canvases per droplet (pairs: 7/8 of the droplets x (snapshots - 1))")
-    ap.add_argument("--tile-cache", default=None, help="JSON file for the autotuner's tile choices")
+    ap.add_argument("--tile-cache", default=None, help="not used: tau = 1 has no tiles")
     ap.add_argument("--unet-only", action="store_true", help="time the U-Net alone (one JSON line)")
     ap.add_argument("--copy-probe", type=int, default=0, help="MiB of a plain copy for counter calibration, then exit")
     args = ap.parse_args()
-    global TILE_CACHE
-    TILE_CACHE = args.tile_cache
     if args.gpus != 1:
         print(f"bench.py measures one GPU only (asked for --gpus {args.gpus}); the library has no multi-GPU path",
               file=sys.stderr)
@@ -911,16 +906,20 @@ def main():
     tile = dict(tile_y=args.tile_y, rows_per_thread=args.rows_per_thread, zchunk=args.zchunk)
     log(f"[bench] workload cap 256x128x64 prec={args.prec} rods={n_rods} (physical fit {n_phys}) "
         f"steps={args.steps} warmup={args.warmup}")
-    autotune = args.tile_y == 0 and args.rows_per_thread == 0 and args.zchunk == 0
-    ms, ms_fused, n_fluid, obs, chosen, nseg = time_step(case, args.prec, args.steps, args.warmup, tile, autotune,
-                                                         rods, args.segment, rho_ref=(args.rho_ref, args.rho_ref),
-                                                         rounding=args.rounding)
+    ms, ms_single, n_fluid, obs, nseg = time_step(case, args.prec, args.steps, args.warmup, tile, rods,
+                                                  args.segment, rho_ref=(args.rho_ref, args.rho_ref),
+                                                  rounding=args.rounding)
     mlups = n_fluid / (ms * 1e-3) / 1e6
-    bpl = algorithmic_bytes_per_lu(args.prec)
-    achieved = bpl * n_fluid / (ms_fused * 1e-3) / 1e9
-    dsb = density_store_bytes_per_lu(args.prec) if n_rods > 0 else 0
-    log(f"[bench] {ms * 1e3:.1f} us/step ({ms_fused * 1e3:.1f} us fused fluid step), {mlups:.0f} MLUPS, "
-        f"{achieved:.0f} GB/s algorithmic in the fused step")
+    # the fluid's share: the same lattice without rods in calls of the same length;
+    # the roofline's fluid step: in a call of 100 steps
+    call = min(args.steps, args.segment) if args.segment > 0 else args.steps
+    (ms_fluid, _, n_free, _, _), (ms_inner, _, _, _, _) = (
+        time_step(case, args.prec, n, args.warmup, tile, rho_ref=(args.rho_ref, args.rho_ref), rounding=args.rounding)
+        for n in (call, 100))
+    bpl = step_bytes_per_lu(args.prec, args.rho_ref)
+    achieved = bpl * n_free / (ms_inner * 1e-3) / 1e9
+    log(f"[bench] {ms * 1e3:.1f} us/step (fluid without rods {ms_fluid * 1e3:.1f}, fluid step in a call of its own "
+        f"{ms_single * 1e3:.1f}), {mlups:.0f} MLUPS, {achieved:.0f} GB/s in the fluid step")
 
     forms = {}
     if args.forms:
@@ -928,31 +927,33 @@ def main():
         # each 16-bit form also states its error against the oracle (10^4
         # steps of the static droplet)
         errs = storage_error_report()
-        msf, base, _, _, _, _ = time_step(case, "f32", 500, 50, tile, autotune, None)
-        forms["f32"] = {"us_per_fused_step": base * 1e3, "mlups": n_fluid / (base * 1e-3) / 1e6, "speedup_vs_f32": 1.0,
-                        "gbs_algorithmic": algorithmic_bytes_per_lu("f32") * n_fluid / (base * 1e-3) / 1e9}
+        base, base1, n_form, _, _ = time_step(case, "f32", 500, 50, tile)
+
+        def rates(msf, msk, n, prec):
+            # a step inside a call of many, and a step in a call of its own
+            # (from populations to populations: the algorithmic bytes)
+            return {"us_per_step": msf * 1e3, "us_per_single_step": msk * 1e3, "mlups": n / (msf * 1e-3) / 1e6,
+                    "speedup_vs_f32": base / msf, "speedup_vs_f32_single": base1 / msk,
+                    "gbs_algorithmic_single": algorithmic_bytes_per_lu(prec) * n / (msk * 1e-3) / 1e9}
+
+        forms["f32"] = rates(base, base1, n_form, "f32")
         for name, (prec, ref) in FORMS16.items():
-            msf, msk, _, _, _, _ = time_step(case, prec, 500, 50, tile, autotune, None, rho_ref=(ref, ref),
-                                             rounding="stochastic")
+            msf, msk, _, _, _ = time_step(case, prec, 500, 50, tile, rho_ref=(ref, ref), rounding="stochastic")
             forms[name] = {"storage": "FP16" if prec == "f16dev" else "BF16", "rho_ref": ref, "rounding": "stochastic",
                            "stores": "f_i" if ref == 0 else "f_i - w_i rho_ref (deviation from the lattice weights)",
-                           "us_per_fused_step": msk * 1e3, "mlups": n_fluid / (msk * 1e-3) / 1e6,
-                           "speedup_vs_f32": base / msk,
-                           "gbs_algorithmic": algorithmic_bytes_per_lu(prec) * n_fluid / (msk * 1e-3) / 1e9,
-                           "error_vs_oracle": errs[name]}
-            log(f"[bench] form {name}: {msk * 1e3:.1f} us, {forms[name]['mlups']:.0f} MLUPS, "
-                f"x{forms[name]['speedup_vs_f32']:.2f} vs f32")
+                           **rates(msf, msk, n_form, prec), "error_vs_oracle": errs[name]}
+            log(f"[bench] form {name}: {msf * 1e3:.1f} us, {forms[name]['mlups']:.0f} MLUPS, "
+                f"x{forms[name]['speedup_vs_f32']:.2f} vs f32 (x{forms[name]['speedup_vs_f32_single']:.2f} with one step "
+                f"per call)")
         # the paper's evaporation law (Eq. 8) in place of the reservoir plane:
         # the same cap under a lid, FP32, J0 = 1e-4, K = 0.01, h0 = the cap height
         sink_case = cases.sink_case(shape=case["shape"], footprint=spec.footprint, height=spec.height,
                                     stripe=spec.stripe, seed=spec.seed, J0=1e-4, K=0.01)
-        msf, msk, n_sink, obs_s, _, _ = time_step(sink_case, "f32", 500, 50, tile, autotune, None)
-        forms["f32sink"] = {"us_per_fused_step": msk * 1e3, "mlups": n_sink / (msk * 1e-3) / 1e6,
-                            "speedup_vs_f32": base / msk,
-                            "gbs_algorithmic": algorithmic_bytes_per_lu("f32") * n_sink / (msk * 1e-3) / 1e9,
+        msf, msk, n_sink, obs_s, _ = time_step(sink_case, "f32", 500, 50, tile)
+        forms["f32sink"] = {**rates(msf, msk, n_sink, "f32"),
                             "moved_A_to_B": float(obs_s["ledger"][0]), "status": int(obs_s["status"]),
                             "note": "interfacial sink (Eq. 8) instead of the reservoir plane, lid on top, 550 steps"}
-        log(f"[bench] form f32sink: {msk * 1e3:.1f} us, {forms['f32sink']['mlups']:.0f} MLUPS, "
+        log(f"[bench] form f32sink: {msf * 1e3:.1f} us, {forms['f32sink']['mlups']:.0f} MLUPS, "
             f"x{forms['f32sink']['speedup_vs_f32']:.2f} vs f32, moved {obs_s['ledger'][0]:.1f}")
 
     if args.forms:
@@ -961,7 +962,8 @@ def main():
         forms["f32filaments"] = filament_form()
         ff = forms["f32filaments"]
         log(f"[bench] form f32filaments: {ff['filaments']} chains, {ff['us_per_coupled_step']:.1f} us per coupled "
-            f"step ({ff['us_filament_update']:.1f} us filament update)")
+            f"step (in calls of one: fluid {ff['us_single_fluid_step']:.1f} + filaments "
+            f"{ff['us_single_filament_update']:.1f})")
 
     batched = None
     if args.batched > 0:
@@ -996,7 +998,7 @@ def main():
             cpu["network"] = {"ms_per_solve": (time.perf_counter() - t0) * 1e3, "kind": "oracle",
                               "I_tot": o["I_tot"], "edges": o["edges"]}
 
-    tr = traffic_record(args.prec, chosen, n_fluid, ms_fused, rods=n_rods > 0, bpl=bpl + dsb)
+    tr = traffic_record(args.prec, n_free, ms_inner) if args.rho_ref == 0.0 else None
     out = {
         "metric": METRIC,
         "value": mlups,
@@ -1013,7 +1015,7 @@ def main():
         "config": {
             "workload": "elongated sessile cap 256x128x64, Shan-Chen D3Q19 two-component, G=3.6, tau=1, "
                         "striped bounce-back wall, reservoir plane (rho_A=0), rigid rods L=24 R=2 eps=1e-4; "
-                        "one step = fused fluid step + rod update",
+                        "one step = fluid step + rod update",
             "lattice": [256, 128, 64],
             "fluid_nodes": n_fluid,
             "prec": args.prec,
@@ -1021,9 +1023,9 @@ def main():
             "rods_placement": "stress (requested count anywhere in the fluid)",
             "rods_physical_fit": n_phys,
             "timed_segments": nseg,
-            "tile": chosen,
-            "us_fused_fluid_step": ms_fused * 1e3,
-            "rod_time_share": max(0.0, 1.0 - ms_fused / ms),
+            "us_fluid_step": ms_fluid * 1e3,
+            "us_single_fluid_step": ms_single * 1e3,
+            "rod_time_share": max(0.0, 1.0 - ms_fluid / ms),
         },
         "forms": forms,
         "batched": batched,
@@ -1036,13 +1038,14 @@ def main():
             "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS,
             "traffic": (tr["gbs"] if tr else None),
-            "traffic_bytes_per_launch": (tr["bytes_per_launch"] if tr else None),
-            "traffic_vs_algorithmic": (tr["vs_algorithmic"] if tr else None),
-            "kernel": "sc_step_kernel",
+            "traffic_bytes_per_step": (tr["bytes_per_step"] if tr else None),
+            "traffic_vs_needed": (tr["vs_needed"] if tr else None),
+            "kernel": ("sc_stream_state_kernel + sc_collide_kernel" if args.prec in ("f32", "f64")
+                       else "sc_stream_kernel + sc_collide_kernel"),
             "bytes_per_lu": bpl,
-            "units_per_launch": n_fluid,
-            "density_store_bytes_per_lu": dsb,
-            "achieved_incl_density_store": (bpl + dsb) * n_fluid / (ms_fused * 1e-3) / 1e9,
+            "units_per_step": n_free,
+            "algorithmic_bytes_per_lu_single": algorithmic_bytes_per_lu(args.prec),
+            "achieved_single": algorithmic_bytes_per_lu(args.prec) * n_fluid / (ms_single * 1e-3) / 1e9,
         },
         "cpu_baseline": cpu,
         "status": int(obs["status"]),
