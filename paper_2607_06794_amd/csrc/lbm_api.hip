@@ -693,9 +693,13 @@ static StepArgs step_args(const lb_ctx *c, int cur) {
 // populations (it opens the other one), so that moments are even or ahead from
 // the smallest lattice on (32^3 12.8 / 11.6, 128 x 64 x 32 19.0 / 19.6), and the
 // rods' link pass reads 8 values of a node instead of up to 36 (39 / 23 us).
+constexpr int64_t CHAIN_BYTES = int64_t(64) << 20;
+static bool chain_form(const lb_params &p) {
+    return two_pass(p) && !p.sink_on && (p.prec == LB_F32 || p.prec == LB_F64);
+}
+static int64_t state_bytes(const lb_params &p) { return 2 * Q * nodes(&p) * int64_t(elem_bytes(p.prec)); }
 static bool moment_chain(const lb_params &p) {
-    if (!two_pass(p) || p.sink_on || (p.prec != LB_F32 && p.prec != LB_F64)) return false;
-    return p.n_rods > 0 || p.evap_on || 2 * Q * nodes(&p) * elem_bytes(p.prec) > (int64_t(64) << 20);
+    return chain_form(p) && (p.n_rods > 0 || p.evap_on || state_bytes(p) > CHAIN_BYTES);
 }
 // Step record of such a call: the populations in buffer src at its start, in
 // buffer dst at its end.  In between, the buffer that does not hold the
@@ -1776,12 +1780,22 @@ std::vector<int> batch_classes(lb_ctx *const *ctxs, int n, std::vector<lb_batch:
     return of;
 }
 
-// Whether the lattices' calls of several steps pass the state on as moments:
-// what each does alone (moment_chain), for all of them together.
+// Whether the lattices' calls of several steps pass the state on as moments: where
+// each does alone (moment_chain), or where they do not fit the caches together
+// (us per call of ten steps, populations / moments: FP32 16 lattices of 32^3, 80 MB,
+// 376 / 292; 32 of 64 x 48 x 32, 0.48 GB, 2 077 / 1 134, with walls 2 190 against
+// 2 155 for the one-pass step; 120 of 16^3, 75 MB, 381 / 378; FP64 16 of 32^3
+// 665 / 500).
 bool batch_chain(lb_ctx *const *ctxs, int n) {
-    for (int i = 0; i < n; ++i)
-        if (!moment_chain(ctxs[i]->p)) return false;
-    return true;
+    int64_t bytes = 0;
+    bool alone = true;
+    for (int i = 0; i < n; ++i) {
+        const lb_params &p = ctxs[i]->p;
+        if (!chain_form(p)) return false;
+        alone = alone && moment_chain(p);
+        bytes += state_bytes(p);
+    }
+    return alone || bytes > CHAIN_BYTES;
 }
 
 // work list of the stream pass from moments: the booking blocks first (long
