@@ -109,7 +109,7 @@ __device__ inline double net_r2(const double *pi, const double *pj) {
 // (only the first NET_DEG are stored; the host reports the excess).  One
 // wavefront for PB beads, 64 candidates at a time, compacted by ballots: with one
 // thread per bead the scan was a chain of n tests on n / 256 work-groups
-// (314 us for 3 300 beads; now 12).  PB = 1 while that leaves CUs idle; beyond
+// (314 us for 3 300 beads; now 18).  PB = 1 while that leaves CUs idle; beyond
 // NET_ROWS each candidate's loads serve four beads (65 536 beads, the call with one
 // iteration: 10.6 -> 5.4 ms; the scan by threads 8.2).
 // ROWS: the lists of the row-sorted solve, as 16-bit indices (the conductances
